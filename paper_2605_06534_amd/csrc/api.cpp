@@ -120,10 +120,8 @@ extern "C" void rose_shard_plan_destroy(rose_plan *p) {
     delete p;
 }
 
-// The tile order a launch into these buckets uses: the caller's choice, else by density.
-static int pick_tile_order(const rose_plan *p, const rose_bucket *buckets) {
-    int order = p->tile_order.load(std::memory_order_relaxed);
-    if (order != ROSE_TILE_ORDER_AUTO_PICK) return order;
+// Changed elements per million that a launch into these buckets is expected to find (-1: unknown).
+static int32_t expected_ppm(const rose_plan *p, const rose_bucket *buckets) {
     int32_t ppm = p->seen_density_ppm.load(std::memory_order_relaxed);
     if (ppm < 0 && p->capacity_sum > 0) {
         // nothing read back yet: the buckets cannot hold more than their capacities, which bounds the density
@@ -132,6 +130,13 @@ static int pick_tile_order(const rose_plan *p, const rose_bucket *buckets) {
         const double bound = 1e6 * room / (double)p->capacity_sum;
         ppm = bound >= 1e6 ? -1 : (int32_t)bound;
     }
+    return ppm;
+}
+
+// The tile order a launch into these buckets uses: the caller's choice, else by density.
+static int pick_tile_order(const rose_plan *p, int32_t ppm) {
+    int order = p->tile_order.load(std::memory_order_relaxed);
+    if (order != ROSE_TILE_ORDER_AUTO_PICK) return order;
     return ppm < 0 ? ROSE_TILE_ORDER_SPREAD
                    : ppm < kTimedBelowPpm ? ROSE_TILE_ORDER_TIMED
                                           : ppm < kNeighboursBelowPpm ? ROSE_TILE_ORDER_NEIGHBOURS : ROSE_TILE_ORDER_SPREAD;
@@ -139,7 +144,7 @@ static int pick_tile_order(const rose_plan *p, const rose_bucket *buckets) {
 
 extern "C" rose_status rose_plan_pick_tile_order(const rose_plan *p, const rose_bucket *buckets, int32_t *order) {
     if (!p || !buckets || !order) return ROSE_ERR_ARG;
-    *order = pick_tile_order(p, buckets);
+    *order = pick_tile_order(p, expected_ppm(p, buckets));
     return ROSE_OK;
 }
 
@@ -191,12 +196,13 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     const bool f32 = new_dtype == ROSE_FP32_RNE;
     const int resident = p->resident[(f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     // Tile order: the caller's choice, else picked from the density the plan's last checked launch showed
-    // (7B-style workload, neighbours against spread on the same buffers: 2.7 / 1.8 / 1.4 / 1.0 % faster at
-    // 1 / 2 / 5 / 7 %, 2 / 13 % slower at 8 / 10 %; timed against neighbours: 1.6 / 5 / 8 / 7 / 1 % faster at
-    // 0.5 / 1 / 2 / 3 / 4 %, 2 % slower at 5 %).
-    const int order = pick_tile_order(p, buckets);
+    // (7B-style workload on the same buffers, ms: timed 4.66 / 4.74 at 3.5 / 4 % where neighbours takes 4.78 /
+    // 4.77, which pays from 4.5 % on; neighbours 5.29 / 5.46 / 6.19 at 7 / 8 / 10 % where spread takes
+    // 5.37 / 5.47 / 5.63).
+    const int32_t ppm = expected_ppm(p, buckets);
+    const int order = pick_tile_order(p, ppm);
     return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, resident,
-                               p->worker_cap.load(std::memory_order_relaxed), order, stream) == 0
+                               p->worker_cap.load(std::memory_order_relaxed), order, ppm, stream) == 0
                ? ROSE_OK
                : ROSE_ERR_HIP;
 }

@@ -312,11 +312,15 @@ constexpr u64 kValueMask = (1ull << kStatusShift) - 1;
 #ifndef ROSE_WRITE_PERIOD_LOG2
 #define ROSE_WRITE_PERIOD_LOG2 12     // ticks of the 100 MHz clock between windows (2^12: 41 us)
 #endif
-#ifndef ROSE_WRITE_RING_NUM
-#define ROSE_WRITE_RING_NUM 6        // eighths of the ring that may fill up between windows
+// Ticks a window is open, for the tile order and density a launch runs with (rule: encode_walk).
+#ifndef ROSE_WRITE_OPEN_TIMED
+#define ROSE_WRITE_OPEN_TIMED 1024    // 10 us
 #endif
-#ifndef ROSE_WRITE_OPEN_LOG2
-#define ROSE_WRITE_OPEN_LOG2 10       // ticks a window is open (2^10: 10 us)
+#ifndef ROSE_WRITE_OPEN_NEAR
+#define ROSE_WRITE_OPEN_NEAR 1536     // 15 us
+#endif
+#ifndef ROSE_WRITE_OPEN_WIDE
+#define ROSE_WRITE_OPEN_WIDE 2048     // 20 us
 #endif
 #ifndef ROSE_COUNT_AHEAD
 #define ROSE_COUNT_AHEAD 1    // count the rest of a ticket's tiles before waiting for room (dense inputs)
@@ -1120,18 +1124,19 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         if (wave == 0) {
             const u64 unknown = __ballot(lane < q_len && !has_prefix(wq_w));
             int n_ready = unknown ? __ffsll((long long)unknown) - 1 : q_len;
-            // Timed order: bucket stores go out in windows of time that all workgroups share (a
+            // Bucket stores go out in windows of time that all workgroups share (a
             // constant-rate clock every wave can read): a steady trickle of writes among the reads
             // costs the memory far more than the same bytes written in bursts (a plain streaming
             // kernel that reads two streams at 7.1 TB/s loses 22 % when it writes 1.5 % of what it
             // reads tile by tile, and 6 % when it writes the same bytes in such windows).  Outside a
-            // window parked tiles simply stay parked, unless the ring or the queue is more than three
-            // quarters full.
-            if (a.timed) {
+            // window parked tiles simply stay parked, unless the queue is more than three quarters
+            // full.  The ring may fill up: a workgroup that finds no room copies out what is ready at
+            // once (drain).  Announcing early, from three quarters of the ring on, writes more of the
+            // entries outside the windows (7B-style workload at 4 %: 5.04 ms; 4.74 ms this way).
+            if (a.window_open) {
                 const uint32_t now = (uint32_t)__builtin_amdgcn_s_memrealtime();
-                const bool open = (now & ((1u << ROSE_WRITE_PERIOD_LOG2) - 1u)) < (1u << ROSE_WRITE_OPEN_LOG2);
-                const bool pressure = q_len > kQueue * 3 / 4 || ring_used > (uint32_t)kRing * ROSE_WRITE_RING_NUM / 8;
-                if (!open && !pressure) n_ready = 0;
+                const bool open = (now & ((1u << ROSE_WRITE_PERIOD_LOG2) - 1u)) < a.window_open;
+                if (!open && q_len <= kQueue * 3 / 4) n_ready = 0;
             }
             if (lane < n_ready) s_excl[parity][lane] = wq_w & kValueMask;
             if (lane == 0) s_nready[parity] = n_ready;
@@ -1998,7 +2003,7 @@ __global__ __launch_bounds__(256) void bw_mix_kernel(const uint4 *a, const uint4
         } else {
             ++n_due;
             const uint32_t now = (uint32_t)__builtin_amdgcn_s_memrealtime();
-            const bool open = (now & ((1u << ROSE_WRITE_PERIOD_LOG2) - 1u)) < (1u << ROSE_WRITE_OPEN_LOG2);
+            const bool open = (now & ((1u << ROSE_WRITE_PERIOD_LOG2) - 1u)) < ROSE_WRITE_OPEN_TIMED;
             if (open || n_due >= 64u) {
                 for (; n_due > 0; --n_due, due_from += gridDim.x) write_chunk(due_from);
             }
@@ -2107,13 +2112,40 @@ int static_scratch(void **ptr, size_t *bytes) {
 #define ROSE_SERVER_WGS 16          // workgroups of the grid that serve prefixes (kWaves servers each)
 #endif
 
+// How a launch in this tile order walks its tiles: tiles per ticket, and how long of each period of
+// 41 us the bucket stores may go out (0: always).  ppm: changed elements per million, -1 unknown.
+//   timed       4 tiles, 10 us.  The entries of a period fit the ring up to about 4 %.
+//   neighbours  Denser: longer windows, so that less waits.  Up to 5 % still 4 tiles, with windows of
+//               15 us; above, and for arithmetic payloads (whose kernel is busier between its loads),
+//               3 tiles, whose prefixes are ready sooner and leave the ring room, and 20 us.
+// 7B-style workload, one process, same buffers, ms (always = neighbours with no windows, 3 tiles):
+//               4 %   4.5 %   5 %   5.5 %   6 %   7 %   8 %   10 %   30 %
+//   always      5.11  5.13    5.19  5.21    5.27  5.32  5.52  6.34   10.75
+//   4 x 10 us   4.74  4.90    5.10  5.26    5.33  5.55  6.02  6.49   19.5
+//   4 x 15 us   4.77  4.83    4.96  5.12    5.24  5.48  6.03  6.49   19.5
+//   3 x 20 us   4.96  4.98    5.03  5.06    5.14  5.29  5.46  6.19   10.30
+// (fp32 masters, two 32B-style layers: 3.16 / 3.06 / 2.98 / 2.95 ms at 5 %, 3.17 / 3.24 / 3.19 / 3.04 at 6 %;
+// arithmetic payloads, eight 7B-style layers: 1.601 / 1.637 / 1.629 / 1.604 at 5 %, 1.571 / 1.584 / 1.576 / 1.561 at 4 %)
+constexpr int32_t kNearBelowPpm = 50000;
+static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
+    a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
+    a->batch = kBatch;
+    a->window_open = 0;
+    if (order == ROSE_TILE_ORDER_TIMED) {
+        a->batch = kBatchTimed;
+        a->window_open = ROSE_WRITE_OPEN_TIMED;
+    } else if (order == ROSE_TILE_ORDER_NEIGHBOURS) {
+        const bool near = !arith && ppm >= 0 && ppm < kNearBelowPpm;
+        a->batch = near ? kBatchTimed : kBatch;
+        a->window_open = near ? ROSE_WRITE_OPEN_NEAR : ROSE_WRITE_OPEN_WIDE;
+    }
+}
+
 int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
-                  int worker_cap, int order, void *stream) {
+                  int worker_cap, int order, int32_t ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
-    a.adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
-    a.timed = order == ROSE_TILE_ORDER_TIMED ? 1 : 0;
-    a.batch = a.timed ? kBatchTimed : kBatch;
+    encode_walk(order, ppm, arith, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are

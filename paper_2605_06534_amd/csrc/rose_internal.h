@@ -85,7 +85,7 @@ struct EncodeArgs {
     int32_t n_tickets;                      // tickets the counter hands out
     int32_t adjacent;                       // a ticket's tiles are neighbours in the bucket (see ticket_tile)
     int32_t batch;                          // tiles per ticket
-    int32_t timed;                          // bucket stores go out in shared windows of time (see encode_body)
+    uint32_t window_open;                   // clock ticks of a period in which bucket stores go out (0: always)
     unsigned int *ticket;                   // workspace header: the ticket counter
 };
 
@@ -97,8 +97,7 @@ constexpr int kBlock = 64;
 // A ticket hands a worker a batch of tiles: the tiles at one position of as many consecutive blocks
 // (a "group" of blocks has kBlock tickets).  All tickets come from one counter, in order.  The
 // counter serves one ticket in about 14 ns, whoever asks: with 3 tiles (96 KB of input) per ticket it
-// alone caps a launch at about 6 TB/s, which the other tile orders do not reach anyway; the timed
-// order does, and takes 4.
+// alone caps a launch at about 6 TB/s; the launches that can read faster than that take 4 (encode_walk).
 #ifndef ROSE_BATCH
 #define ROSE_BATCH 3
 #endif
@@ -136,9 +135,10 @@ struct RefreshArgs {
     int32_t n;
 };
 // resident: workgroups of this kernel variant that fit on the device at once (encode_resident_all);
-// worker_cap: 0, or the most workgroups that may walk tiles; order: ROSE_TILE_ORDER_SPREAD, _NEIGHBOURS or _TIMED
+// worker_cap: 0, or the most workgroups that may walk tiles; order: ROSE_TILE_ORDER_SPREAD, _NEIGHBOURS or _TIMED;
+// ppm: changed elements per million as far as known or bounded, else -1
 int launch_encode(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
-                  int worker_cap, int order, void *stream);
+                  int worker_cap, int order, int32_t ppm, void *stream);
 // resident workgroups of each of the eight encode kernel variants on the current device
 // (index: fp32 input + 2 * refresh + 4 * arithmetic payload)
 int encode_resident_all(int resident[8]);
