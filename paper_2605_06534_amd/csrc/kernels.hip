@@ -136,9 +136,13 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
 #define ROSE_NT_STORES 1
 #endif
 // 128-bit load / store through the global address space (pointers fetched from a table would
-// otherwise be treated as generic and use the slower flat instructions)
+// otherwise be treated as generic and use the slower flat instructions).  The address needs no more
+// than the alignment of a 16-bit element: the compiler emits the same instruction, and the memory
+// pipeline cuts what crosses a line.  Two streams read in 16 KB tiles: 6.6 TB/s at aligned addresses,
+// 6.5 with one stream 2 or 4 bytes off, 5.6 - 6.2 with both off.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef __attribute__((address_space(1))) u32x4_any global_u32x4;
 __device__ __forceinline__ uint4 gload16(const void *p) {
     u32x4 v = *reinterpret_cast<const global_u32x4 *>(reinterpret_cast<uintptr_t>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
@@ -248,8 +252,8 @@ __device__ __forceinline__ void load_tile_fast(const void *base, const Piece &pc
     for (int j = 0; j < kIters; ++j) out[j] = raw_to_bf16(r, j);
 }
 
-// General path (ragged last tile of a piece, shapes or pointers that are not multiples of 16
-// bytes): one vector, element by element; patterns past the end of the piece read as zero.
+// General path (last vector of a piece, very short runs, odd addresses): one vector, element by element;
+// patterns past the end of the piece read as zero.
 template <int SRC_F32>
 __device__ __forceinline__ uint4 load_vec_general(const void *base, const Piece &pc, uint32_t k) {
     // deliberately one element at a time in a rolled loop: this path is rare and must stay small
@@ -270,6 +274,27 @@ __device__ __forceinline__ uint4 load_vec_general(const void *base, const Piece 
         w3 |= (q == 3) ? v : 0u;
     }
     return make_uint4(w0, w1, w2, w3);
+}
+
+// Vectors that straddle the end of a run (kPieceSplit: runs of at least 8 elements that are no multiple
+// of 8).  Element i < left of the vector at k lies left from the end of its run, the others at the start
+// of the next run.  A 128-bit load at src_index(k) holds the former in place, and one at
+// split_tail_at(k) the latter in place; both stay between the vector's first and last element.
+__device__ __forceinline__ uint32_t split_left(const Piece &pc, uint32_t k, uint32_t *q) {
+    *q = __umulhi(k, pc.magic) >> pc.shift;
+    return (*q + 1) * (uint32_t)pc.run - k;              // elements of k's run from k on: below 8 if it straddles
+}
+__device__ __forceinline__ int64_t split_tail_at(const Piece &pc, uint32_t q, uint32_t left) {
+    return pc.src_off + (int64_t)(q + 1) * pc.stride - left;
+}
+// elements 0 .. left-1 of a, the others of b
+__device__ __forceinline__ uint4 split_merge(uint4 a, uint4 b, uint32_t left) {
+    auto part = [&](uint32_t x, uint32_t y, int32_t d) {  // d: how many of the dword's two elements x gives
+        const uint32_t m = d >= 2 ? 0xFFFFFFFFu : d == 1 ? 0xFFFFu : 0u;
+        return (x & m) | (y & ~m);
+    };
+    const int32_t l = (int32_t)left;
+    return make_uint4(part(a.x, b.x, l), part(a.y, b.y, l - 2), part(a.z, b.z, l - 4), part(a.w, b.w, l - 6));
 }
 
 __device__ __forceinline__ uint4 xor4(uint4 a, uint4 b) { return make_uint4(a.x ^ b.x, a.y ^ b.y, a.z ^ b.z, a.w ^ b.w); }
@@ -517,7 +542,7 @@ struct TileCtx {
     const void *new_base;
     uint32_t k_tile;
     uint32_t limit;     // see load_raw
-    uint32_t vec;       // 128-bit loads are legal for this tile
+    uint32_t vec;       // bit 0: 128-bit loads are legal for this tile; bit 2: its vectors may straddle runs
     int32_t piece;      // index of pc in the piece table
 };
 
@@ -529,9 +554,11 @@ __device__ __forceinline__ TileCtx tile_ctx(const EncodeArgs &a, int32_t tile) {
     c.new_base = reinterpret_cast<const void *>(cload64(a.new_ptrs + c.pc.tensor));
     c.k_tile = (uint32_t)(tile - c.pc.first_tile) * (uint32_t)kTile;
     c.limit = (c.k_tile + (uint32_t)kTile <= (uint32_t)c.pc.len) ? 0xFFFFFFFFu : (uint32_t)c.pc.len;
-    // uniform choice: aligned piece and aligned tensors -> 128-bit loads
-    c.vec = ((c.pc.flags & kPieceVec) && ((((uintptr_t)c.old_base) | ((uintptr_t)c.new_base)) & 15u) == 0 &&
-             c.k_tile + (uint32_t)kVec <= (uint32_t)c.pc.len) ? 1u : 0u;
+    // uniform choice: 128-bit loads at whatever element they start, as long as runs hold a whole vector (a
+    // decoder whose tensors start at odd elements and whose rows are 765 elements a shard, 131 M weights:
+    // 526 us with one element per load for such tiles, 151 us this way)
+    c.vec = ((c.pc.flags & kPieceLoad16) && ((((uintptr_t)c.old_base) | ((uintptr_t)c.new_base)) & 1u) == 0 &&
+             c.k_tile + (uint32_t)kVec <= (uint32_t)c.pc.len) ? ((c.pc.flags & kPieceSplit) ? 5u : 1u) : 0u;
     return c;
 }
 
@@ -544,7 +571,7 @@ struct TileMeta {
     int32_t shard;
     int32_t seg;        // tensor whose segment starts with this tile, else -1
     uint32_t limit;     // see load_raw
-    uint32_t vec;       // bit 0: 128-bit loads are legal; bit 1: piece of a replicated tensor
+    uint32_t vec;       // bit 0: 128-bit loads are legal; bit 1: piece of a replicated tensor; bit 2: see TileCtx
     uint32_t k_tile;
 };
 __device__ __forceinline__ TileMeta tile_meta(const TileCtx &c, int32_t tile) {
@@ -695,6 +722,18 @@ __device__ __forceinline__ int walk_step(const EncodeArgs &a, Walk &w, int32_t *
         w.ticket = w.next_ticket;
         w.have_next = false;
         w.j = -1;
+    }
+}
+
+// eight new patterns from element e on, any alignment
+template <int NEW_F32>
+__device__ __forceinline__ uint4 load_new_vec(const void *base, int64_t e) {
+    if constexpr (NEW_F32) {
+        const uint32_t *p32 = static_cast<const uint32_t *>(base) + e;
+        const uint4 lo = gload16(p32), hi = gload16(p32 + 4);
+        return make_uint4(pack_rne(lo.x, lo.y), pack_rne(lo.z, lo.w), pack_rne(hi.x, hi.y), pack_rne(hi.z, hi.w));
+    } else {
+        return gload16(static_cast<const uint16_t *>(base) + e);
     }
 }
 
@@ -939,14 +978,19 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 const int64_t e = src_index(c.pc, k, true);
                 const uint4 o = gload16(c.old_base + e);
                 uint4 n;
-                if constexpr (NEW_F32) {
-                    const uint32_t *p32 = static_cast<const uint32_t *>(c.new_base) + e;
-                    const uint4 lo = gload16(p32), hi = gload16(p32 + 4);
-                    n = make_uint4(pack_rne(lo.x, lo.y), pack_rne(lo.z, lo.w), pack_rne(hi.x, hi.y), pack_rne(hi.z, hi.w));
-                } else {
-                    n = gload16(static_cast<const uint16_t *>(c.new_base) + e);
+                n = load_new_vec<NEW_F32>(c.new_base, e);
+                uint32_t m = nz16_mask(xor4(o, n));
+                if (c.vec & 4u) {                      // the part of the vector that lies in the next run
+                    uint32_t q;
+                    const uint32_t left = split_left(c.pc, k, &q);
+                    if (left < (uint32_t)kVec) {
+                        const int64_t e2 = split_tail_at(c.pc, q, left);
+                        const uint32_t keep = (1u << left) - 1u;
+                        m = (m & keep) |
+                            (nz16_mask(xor4(gload16(c.old_base + e2), load_new_vec<NEW_F32>(c.new_base, e2))) & ~keep);
+                    }
                 }
-                cnt += __popc(nz16_mask(xor4(o, n)));
+                cnt += __popc(m);
             }
         } else {
 #pragma unroll 1
@@ -1053,6 +1097,45 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 for (int j = 0; j < kIters; ++j)
                     if (k_wave + (uint32_t)(j * 64 + lane) * kVec + kVec > cur.limit) mask[j] = 0;
             }
+            // Runs that are no multiple of 8 elements: the vectors that straddle the end of a run hold
+            // their first elements only; the rest is loaded now.  A lane takes its first such vector,
+            // whichever of its four that is, then its second: with runs of 512 elements or more hardly
+            // any lane has two, and the tile waits for one round of loads.
+            if (cur.vec & 4u) {
+                const TileCtx c = tile_ctx(a, __builtin_amdgcn_readfirstlane(tile));
+                uint32_t todo = 0;
+#pragma unroll
+                for (int j = 0; j < kIters; ++j) {
+                    const uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
+                    uint32_t q;
+                    if (split_left(c.pc, k, &q) < (uint32_t)kVec && k + kVec <= cur.limit) todo |= 1u << j;
+                }
+#pragma unroll 1
+                while (todo) {
+                    const uint32_t js = __ffs(todo) - 1;
+                    todo &= todo - 1;
+                    uint32_t q;
+                    const uint32_t left = split_left(c.pc, k_wave + (js * 64 + (uint32_t)lane) * kVec, &q);
+                    const int64_t e = split_tail_at(c.pc, q, left);
+                    const uint4 o = gload16(c.old_base + e);
+                    const uint4 n = load_new_vec<NEW_F32>(c.new_base, e);
+                    const uint32_t keep = (1u << left) - 1u, m = nz16_mask(xor4(o, n)) & ~keep;
+                    uint32_t esc8 = 0;
+                    uint4 pay = n;
+                    if constexpr (ARITH) pay = arith_vec(o, n, &esc8);
+#pragma unroll
+                    for (int jj = 0; jj < kIters; ++jj) {
+                        if ((uint32_t)jj == js) {
+                            mask[jj] = (mask[jj] & keep) | m;
+                            nv[jj] = split_merge(nv[jj], n, left);
+                            if constexpr (ARITH) {
+                                pv[jj] = split_merge(pv[jj], pay, left);
+                                esc_all = (esc_all & ~((0xFFu & ~keep) << (8 * jj))) | ((esc8 & ~keep) << (8 * jj));
+                            }
+                        }
+                    }
+                }
+            }
             // a piece whose length is not a multiple of 8: the one vector that straddles its end
             if (cur.limit != 0xFFFFFFFFu && (cur.limit & (kVec - 1))) {
                 const uint32_t ks = cur.limit & ~(uint32_t)(kVec - 1);
@@ -1079,7 +1162,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 }
             }
         } else {
-            // shapes or pointers that are not multiples of 16 bytes.  Kept as a rolled loop (one
+            // runs of fewer than 8 elements, pieces of fewer than 8, odd addresses.  Kept as a rolled loop (one
             // vector in flight) so that this rare path does not set the kernel's register budget;
             // the selects put the result into static slots
             const TileCtx c = tile_ctx(a, __builtin_amdgcn_readfirstlane(tile));
@@ -1348,7 +1431,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 for (int j = 0; j < kIters; ++j) {
                     if (mask[j] || whole) {
                         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
-                        if ((cur.vec & 1u) && (c.limit == 0xFFFFFFFFu || k + kVec <= c.limit)) {
+                        bool one = (cur.vec & 1u) && (c.limit == 0xFFFFFFFFu || k + kVec <= c.limit);
+                        if (cur.vec & 4u) {
+                            uint32_t q;
+                            one = one && split_left(c.pc, k, &q) >= (uint32_t)kVec;
+                        }
+                        if (one) {
 #if ROSE_REFRESH_NT
                             {
                                 u32x4 w = {nv[j].x, nv[j].y, nv[j].z, nv[j].w};

@@ -123,8 +123,14 @@ static void segment_pieces(const rose_tensor_desc &t, int32_t ti, int32_t d, int
         bool vec = (src_off % rose::kVec == 0) && (local_base % rose::kVec == 0) &&
                    (!strided || run % rose::kVec == 0) && (!src_strided || src_stride % rose::kVec == 0) &&
                    (!dst_strided || lstride % rose::kVec == 0);
-        if (strided && vec && !rose::magic_ok((uint32_t)run, p.magic, p.shift, (uint32_t)len)) vec = false;
+        bool load16 = !src_strided || run >= rose::kVec;
+        if (strided && (vec || load16) && !rose::magic_ok((uint32_t)run, p.magic, p.shift, (uint32_t)len)) {
+            vec = false;
+            load16 = load16 && !src_strided;
+        }
         if (vec) p.flags |= rose::kPieceVec;
+        if (load16) p.flags |= rose::kPieceLoad16;
+        if (load16 && src_strided && run % rose::kVec) p.flags |= rose::kPieceSplit;
         out.push_back(p);
     };
     // rows (or columns) [lo, hi) that both the sender's block and the destination's block hold

@@ -31,6 +31,9 @@ enum : int32_t {
     kPieceVec = 2,      // offsets and run lengths are multiples of kVec: 128-bit loads are legal
     kPieceStrided = 4,  // runs of `run` elements every `stride` source elements
     kPieceReplicated = 16, // piece of a replicated tensor: several destinations read the same source
+    kPieceLoad16 = 32,  // a vector of kVec elements is one 128-bit load of the source, at any alignment: the source is
+                        // contiguous or its runs are at least kVec long (then two, see kPieceSplit)
+    kPieceSplit = 64,   // with kPieceLoad16: source runs that are no multiple of kVec, a vector may straddle two
     kPieceDstStrided = 8 // runs of `run` elements every `lstride` LOCAL indices (the sender's slice
                         // covers only part of each row of the destination shard)
 };
