@@ -201,8 +201,10 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     // 5.37 / 5.47 / 5.63).
     const int32_t ppm = expected_ppm(p, buckets);
     const int order = pick_tile_order(p, ppm);
+    const bool order_free = p->tile_order.load(std::memory_order_relaxed) == ROSE_TILE_ORDER_AUTO_PICK;
     return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, resident,
-                               p->worker_cap.load(std::memory_order_relaxed), order, ppm, stream) == 0
+                               p->worker_cap.load(std::memory_order_relaxed), order, order_free, ppm,
+                               stream) == 0
                ? ROSE_OK
                : ROSE_ERR_HIP;
 }

@@ -630,6 +630,53 @@ __device__ __forceinline__ void load_raw_pair(const TileCtx &c, uint32_t t_off, 
     }
 }
 
+// eight new patterns from element e on, any alignment
+template <int NEW_F32>
+__device__ __forceinline__ uint4 load_new_vec(const void *base, int64_t e) {
+    if constexpr (NEW_F32) {
+        const uint32_t *p32 = static_cast<const uint32_t *>(base) + e;
+        const uint4 lo = gload16(p32), hi = gload16(p32 + 4);
+        return make_uint4(pack_rne(lo.x, lo.y), pack_rne(lo.z, lo.w), pack_rne(hi.x, hi.y), pack_rne(hi.z, hi.w));
+    } else {
+        return gload16(static_cast<const uint16_t *>(base) + e);
+    }
+}
+
+// A tile's patterns, old and new, whatever its shape and alignment: the 128-bit loads of load_raw_pair, then
+// what they cannot give (vectors that reach past the piece, straddle two runs, or have no 128-bit load).
+// Elements past the end of the piece read as zero on both sides.  For kernels that do not keep a tile's loads
+// in flight across other work (the ticket kernel has its own form of this).
+template <int NEW_F32>
+__device__ __forceinline__ void load_tile_pair(const TileCtx &c, uint32_t t_off, uint4 (&o)[kIters], uint4 (&n)[kIters]) {
+    RawTile<0> ro;
+    RawTile<NEW_F32> rn;
+    if (c.vec & 1u) {
+        load_raw_pair<NEW_F32>(c, t_off, ro, rn);
+#pragma unroll
+        for (int j = 0; j < kIters; ++j) {
+            o[j] = ro.v[j];
+            n[j] = raw_to_bf16(rn, j);
+        }
+        if (c.limit == 0xFFFFFFFFu && !(c.vec & 4u)) return;
+    }
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) {
+        const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
+        if (!(c.vec & 1u) || k + kVec > (uint32_t)c.pc.len) {
+            o[j] = load_vec_general<0>(c.old_base, c.pc, k);
+            n[j] = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
+        } else if (c.vec & 4u) {
+            uint32_t q;
+            const uint32_t left = split_left(c.pc, k, &q);
+            if (left < (uint32_t)kVec) {
+                const int64_t e = split_tail_at(c.pc, q, left);
+                o[j] = split_merge(o[j], gload16(c.old_base + e), left);
+                n[j] = split_merge(n[j], load_new_vec<NEW_F32>(c.new_base, e), left);
+            }
+        }
+    }
+}
+
 // The j-th tile of a ticket, or -1 if there is none.  A ticket stands for a.batch tiles (kBatch below; the
 // launcher picks it).  A group of kBatch consecutive blocks has
 // kBatch * kBlock tile positions ("slots", block after block) and kBlock tickets.  Two orders:
@@ -725,16 +772,24 @@ __device__ __forceinline__ int walk_step(const EncodeArgs &a, Walk &w, int32_t *
     }
 }
 
-// eight new patterns from element e on, any alignment
-template <int NEW_F32>
-__device__ __forceinline__ uint4 load_new_vec(const void *base, int64_t e) {
-    if constexpr (NEW_F32) {
-        const uint32_t *p32 = static_cast<const uint32_t *>(base) + e;
-        const uint4 lo = gload16(p32), hi = gload16(p32 + 4);
-        return make_uint4(pack_rne(lo.x, lo.y), pack_rne(lo.z, lo.w), pack_rne(hi.x, hi.y), pack_rne(hi.z, hi.w));
-    } else {
-        return gload16(static_cast<const uint16_t *>(base) + e);
+// Exclusive rank of each of this lane's vectors inside the wave's span; returns the wave's total.  The
+// per-vector counts (<= 8, wave totals <= 512) are scanned two at a time in 16-bit fields.
+__device__ __forceinline__ uint32_t vector_ranks(const uint32_t (&mask)[kIters], uint32_t (&rank)[kIters]) {
+    uint32_t wave_total = 0;
+#pragma unroll
+    for (int j = 0; j < kIters; j += 2) {
+        const uint32_t c0 = __popc(mask[j]);
+        const uint32_t c1 = (j + 1 < kIters) ? __popc(mask[j + 1]) : 0u;
+        const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        rank[j] = wave_total + (inc & 0xFFFFu) - c0;
+        wave_total += tot & 0xFFFFu;
+        if (j + 1 < kIters) {
+            rank[j + 1] = wave_total + (inc >> 16) - c1;
+            wave_total += tot >> 16;
+        }
     }
+    return wave_total;
 }
 
 template <int NEW_F32, int REFRESH, int ARITH>
@@ -1243,23 +1298,9 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         loaded = next_state == kWalkTile;
         if (loaded) nxt = start_tile(next);
 
-        // ---- (e) exclusive rank of each of this lane's vectors inside the wave's span: the
-        // per-vector counts (<= 8, wave totals <= 512) are scanned two at a time in 16-bit fields
+        // ---- (e) ranks of the entries ----
         uint32_t rank[kIters];
-        uint32_t wave_total = 0;
-#pragma unroll
-        for (int j = 0; j < kIters; j += 2) {
-            const uint32_t c0 = __popc(mask[j]);
-            const uint32_t c1 = (j + 1 < kIters) ? __popc(mask[j + 1]) : 0u;
-            const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
-            const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-            rank[j] = wave_total + (inc & 0xFFFFu) - c0;
-            wave_total += tot & 0xFFFFu;
-            if (j + 1 < kIters) {
-                rank[j + 1] = wave_total + (inc >> 16) - c1;
-                wave_total += tot >> 16;
-            }
-        }
+        const uint32_t wave_total = vector_ranks(mask, rank);
         if (lane == 0) s_wave_total[parity][wave] = wave_total;
         __syncthreads();
         if (accept_now) walk_accept(a, walk, (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket[parity]));
@@ -1536,6 +1577,126 @@ ROSE_ENCODE_KERNEL(1, 1, 0, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 0, 1, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 #undef ROSE_ENCODE_KERNEL
+
+// ---------------------------------------------------------------------------------------------
+// encode in two launches, for updates of few tiles (launch_encode says how few): the first counts every
+// tile's changes, the second adds up the counts in front of its tile, reads the tile again and writes its
+// entries.  Nothing waits for another workgroup, so there is nothing to reset, no ticket, no serving wave
+// and no drain at the end; the price, reading everything twice, is small while the second reading comes
+// from the caches.  What bounds the ticket kernel on such updates is its counter (14 ns per ticket and one
+// last request per workgroup) and the way from a count to its prefix (4096 x 4096, p = 1 %: 39.8 us a call,
+// this way 24.8; a whole update of a decoder of 11 M weights, TP4, with its checks and applies: 215 and 182 us).
+// ---------------------------------------------------------------------------------------------
+template <int NEW_F32>
+__global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uint32_t *counts) {
+    __shared__ uint32_t s_cnt[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const TileCtx c = tile_ctx(a, (int32_t)blockIdx.x);
+    uint4 o[kIters], n[kIters];
+    load_tile_pair<NEW_F32>(c, (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec, o, n);
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) {
+        cnt += __popc(nz16_mask(xor4(o[j], n[j])));
+    }
+    const uint32_t wave_cnt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(cnt), 63);
+    if (lane == 0) s_cnt[wave] = wave_cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int w = 0; w < kWaves; ++w) total += s_cnt[w];
+        counts[blockIdx.x] = total;
+    }
+}
+
+template <int NEW_F32, int REFRESH, int ARITH>
+__global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, const uint32_t *counts) {
+    __shared__ uint32_t s_entry[kTile];      // an entry as in encode_body's ring
+    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t tile = (int32_t)blockIdx.x;
+    const TileCtx c = tile_ctx(a, tile);
+    const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
+    const int32_t chain_begin = a.chain_first[c.pc.shard], chain_end = a.chain_first[c.pc.shard + 1];
+    uint4 o[kIters], n[kIters];
+    load_tile_pair<NEW_F32>(c, t_off, o, n);
+    // entries of the chain's earlier tiles (below 2^31 together: a destination's local index is 31 bits)
+    uint32_t before = 0;
+    for (int32_t t = chain_begin + (int32_t)threadIdx.x; t < tile; t += kThreads) before += counts[t];
+    before = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(before), 63);
+
+    uint32_t mask[kIters], rank[kIters];
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
+    const uint32_t wave_total = vector_ranks(mask, rank);
+    if (lane == 0) {
+        s_before[wave] = before;
+        s_cnt[wave] = wave_total;
+    }
+    __syncthreads();
+    uint32_t wave_excl = 0, total = 0;
+    u64 excl = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w < wave) wave_excl += s_cnt[w];
+        total += s_cnt[w];
+        excl += s_before[w];
+    }
+    const BucketDev b = a.bucket[c.pc.shard];
+    if (threadIdx.x == 0) {
+        if ((c.pc.flags & kPieceFirst) && tile == c.pc.first_tile) b.seg_off[c.pc.tensor] = (int64_t)excl;
+        if (tile == chain_end - 1) b.seg_off[a.n_tensors] = (int64_t)(excl + total);
+    }
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) {
+        uint4 pay = n[j];
+        uint32_t esc8 = 0;
+        if constexpr (ARITH) pay = arith_vec(o[j], n[j], &esc8);
+        uint32_t m = mask[j], slot = wave_excl + rank[j];
+        while (m) {
+            const uint32_t e = __ffs(m) - 1;
+            m &= m - 1;
+            s_entry[slot++] = ((t_off + (uint32_t)(j * 64) * kVec + e) << 16) | pick16(pay, e) | ((esc8 >> e) << 31);
+        }
+    }
+    if constexpr (REFRESH) {                 // as in encode_body
+        if (!(c.pc.flags & kPieceReplicated)) {
+            uint16_t *ob = const_cast<uint16_t *>(c.old_base);
+#pragma unroll
+            for (int j = 0; j < kIters; ++j) {
+                const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
+                uint32_t q, m = mask[j];
+                if (!m) continue;
+                if ((c.vec & 1u) && k + kVec <= (uint32_t)c.pc.len &&
+                    !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
+                    gstore16(ob + src_index(c.pc, k, true), n[j]);
+                } else {
+                    while (m) {
+                        const uint32_t e = __ffs(m) - 1;
+                        m &= m - 1;
+                        ob[src_index(c.pc, k + e, false)] = (uint16_t)pick16(n[j], e);
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const bool dst_strided = (c.pc.flags & kPieceDstStrided) != 0;
+    const uint32_t phase = (uint32_t)excl & 31u;         // lined up with the bucket's lines, see copy_out
+    for (uint32_t kk = threadIdx.x; kk < total + phase; kk += kThreads) {
+        const uint32_t k = kk - phase;
+        const u64 pos = excl + k;
+        if (kk >= phase && pos < (u64)b.capacity) {
+            const uint32_t entry = s_entry[k];
+            uint32_t local = c.k_tile + ((entry >> 16) & (uint32_t)(kTile - 1));
+            uint32_t q = 0;
+            if (dst_strided) q = c.pc.run == 1 ? local : (__umulhi(local, c.pc.magic) >> c.pc.shift);
+            local = (uint32_t)c.pc.local_base + q * (uint32_t)c.pc.lstride + (local - q * (uint32_t)c.pc.run);
+            b.idx[pos] = (int32_t)(local | (ARITH ? entry & 0x80000000u : 0u));
+            b.val[pos] = (uint16_t)entry;
+        }
+    }
+}
 
 // Replicated tensors after an encode with refresh: old <- bf16(new), whole tensors (they are small).
 __global__ __launch_bounds__(256) void refresh_replicated_kernel(const int32_t *list, const int64_t *numel, int32_t n,
@@ -2153,6 +2314,15 @@ static EncodeKernel encode_variant(int new_is_f32, int refresh, int arith) {
     return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
 }
 
+typedef void (*CountKernel)(EncodeArgs, uint32_t *);
+typedef void (*EmitKernel)(EncodeArgs, const uint32_t *);
+static EmitKernel emit_variant(int new_is_f32, int refresh, int arith) {
+    static const EmitKernel table[8] = {emit_tiles_kernel<0, 0, 0>, emit_tiles_kernel<1, 0, 0>, emit_tiles_kernel<0, 1, 0>,
+                                        emit_tiles_kernel<1, 1, 0>, emit_tiles_kernel<0, 0, 1>, emit_tiles_kernel<1, 0, 1>,
+                                        emit_tiles_kernel<0, 1, 1>, emit_tiles_kernel<1, 1, 1>};
+    return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+}
+
 // Number of workgroups of each encode kernel variant that fit on the current device at once.
 int encode_resident_all(int resident[8]) {
     int dev = 0, cus = 0;
@@ -2229,10 +2399,34 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
     }
 }
 
+// Updates that go in two launches (count_tiles_kernel, emit_tiles_kernel) instead of tickets: those that read
+// at most this much.  One matrix of 4096 columns, p = 1 %, us per call back to back, two launches / tickets:
+//   32 MiB 15.6 / 31.7   64 MiB 23.5 / 39.6   96 MiB 34.7 / 46.7   128 MiB 46.0 / 54.6   192 MiB 70.0 / 64.4
+// fp32 masters, p = 2 %: 96 MiB 37.7 / 43.9, 144 MiB 56.6 / 54.7, 192 MiB 76.6 / 64.5; with 8 shards, whose chains
+// are shorter, the lines cross at 192 MiB.  (Handing the second launch the tiles last read first: no gain.)
+#ifndef ROSE_TWO_LAUNCH_BYTES
+#define ROSE_TWO_LAUNCH_BYTES (128 << 20)
+#endif
+static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, hipStream_t st) {
+    if (refresh && refresh->n > 0)
+        hipLaunchKernelGGL(refresh_replicated_kernel, dim3(8, refresh->n > 1024 ? 1024 : refresh->n), dim3(256), 0, st,
+                           refresh->list, refresh->numel, refresh->n, const_cast<void *const *>(a.old_ptrs), a.new_ptrs,
+                           new_is_f32);
+}
+
 int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
-                  int worker_cap, int order, int32_t ppm, void *stream) {
+                  int worker_cap, int order, bool order_free, int32_t ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
+    if (order_free && worker_cap == 0 && (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4) <= ROSE_TWO_LAUNCH_BYTES) {
+        uint32_t *counts = reinterpret_cast<uint32_t *>(a.tile_desc);
+        const CountKernel count = new_is_f32 ? count_tiles_kernel<1> : count_tiles_kernel<0>;
+        hipLaunchKernelGGL(count, dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
+        hipLaunchKernelGGL(emit_variant(new_is_f32, refresh ? 1 : 0, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a,
+                           counts);
+        launch_refresh_replicated(a, new_is_f32, refresh, st);
+        return (int)hipGetLastError();
+    }
     encode_walk(order, ppm, arith, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
@@ -2263,12 +2457,7 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
     hipLaunchKernelGGL(reset_kernel, dim3(reset_blocks), dim3(256), 0, st, reinterpret_cast<u64 *>(a.abort_flag), n_words);
     const dim3 grid(workers + server_wgs), block(kThreads);
     hipLaunchKernelGGL(encode_variant(new_is_f32, refresh ? 1 : 0, arith), grid, block, 0, st, a);
-    if (refresh) {
-        if (refresh->n > 0)
-            hipLaunchKernelGGL(refresh_replicated_kernel, dim3(8, refresh->n > 1024 ? 1024 : refresh->n), dim3(256), 0, st,
-                               refresh->list, refresh->numel, refresh->n, const_cast<void *const *>(a.old_ptrs),
-                               a.new_ptrs, new_is_f32);
-    }
+    launch_refresh_replicated(a, new_is_f32, refresh, st);
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64), 0, st, a);
     return (int)hipGetLastError();
 }

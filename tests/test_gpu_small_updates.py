@@ -1,0 +1,55 @@
+"""Small updates go in two launches instead of tickets: same buckets, refresh and payloads, from empty
+tensors up to the largest update of that kind and the smallest one beyond.  Expected values come from
+the oracle, bit for bit."""
+import pytest
+
+import paper_2605_06534_amd as R
+from gpu_harness import full_parity
+from test_gpu_arith import check_arith
+from test_gpu_parity import T, bern_case
+from test_gpu_refresh import check_refresh
+from test_gpu_unaligned import packed_case, shapes
+
+pytestmark = pytest.mark.gpu
+
+TILE = 8192
+
+
+@pytest.mark.parametrize("p", [0.0, 0.03, 1.0])
+@pytest.mark.parametrize("numel", [1, 7, 8, 9, TILE - 1, TILE, TILE + 1, 3 * TILE + 17])
+def test_flat_sizes(numel, p):
+    print("case: small flat numel=%d p=%g" % (numel, p), flush=True)
+    ts = [T(1, numel, R.REPLICATED), T(0, 16, R.SPLIT_ROWS), T(2, numel, R.SPLIT_ROWS)]
+    full_parity(bern_case(ts, 2, p, seed=numel))
+    check_arith(bern_case(ts, 2, p, seed=numel + 1))
+    check_refresh(bern_case(ts, 2, p, seed=numel + 2))
+
+
+@pytest.mark.parametrize("run", [7, 9, 513, 765])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_packed(run, fp32):
+    print("case: small packed run=%d fp32=%s" % (run, fp32), flush=True)
+    for tp, first_old, first_new, p in [(2, 1, 3, 0.05), (3, 7, 0, 0.9)]:
+        ts = shapes(run, tp)
+        full_parity(packed_case(ts, tp, p, run, first_old, first_new, fp32))
+        check_arith(packed_case(ts, tp, p, run + 1, first_old, first_new, fp32))
+        check_refresh(packed_case(ts, tp, p, run + 2, first_old, first_new, fp32))
+
+
+@pytest.mark.parametrize("tiles", [4096, 4097])
+def test_both_sides_of_the_line(tiles):
+    print("case: small tiles=%d" % tiles, flush=True)
+    full_parity(bern_case([T(1, tiles * TILE, R.REPLICATED)], 1, 0.01, seed=tiles), check_dense=False)
+
+
+def test_overflow_is_reported_and_bounded():
+    print("case: small overflow", flush=True)
+    c = bern_case([T(64, 512, R.SPLIT_ROWS), T(1, 3000, R.REPLICATED)], 2, 0.25, seed=2, capacity=1000)
+    for b in c.buckets:
+        b.idx.fill_(-7)
+    c.encode()
+    for d, b in enumerate(c.buckets):
+        with pytest.raises(R.RoseError) as e:
+            R.bucket_check(c.plan, b)
+        assert e.value.required > 1000
+        assert (b.idx[1000:] == -7).all()
