@@ -1716,31 +1716,40 @@ __global__ __launch_bounds__(256) void refresh_replicated_kernel(const int32_t *
 // apply (App. F S2D): every entry's value goes to its local index of the receiver's copy.
 //
 // Scattered 2-byte stores reach memory as byte-masked partial writes of the lines they touch,
-// which the memory side turns into slow read-modify-writes (measured: about 3 TB/s of line
-// traffic).  So the kernel does the read-modify-write itself, one 64-byte line at a time, with
-// 128-bit accesses marked non-temporal (a line is touched once per launch; with the hints this
-// path was never slower than direct stores between 1 % and 10 % density, without them it lost
-// below 3 %): a wave takes 64 consecutive entries (ascending local index inside a segment,
+// which the memory side turns into read-modify-writes of its own.  Between about 1 and 8 % of
+// the elements the kernel does better to do the read-modify-write itself, one 64-byte line at a time,
+// with 128-bit accesses marked non-temporal (a line is touched once per launch; 7B-style workload at 5 %,
+// one shard: 1.22 ms, with direct stores 1.37): a wave takes 64 consecutive entries (ascending local index inside a segment,
 // so the entries of a line are neighbours), finds the distinct lines they touch, loads those lines
 // into LDS, patches the entries in, and stores the lines back whole.
 //
 // A line's entries may straddle two waves' chunks (a line holds at most 32 entries, a chunk 64):
 // the line belongs to the wave that holds its FIRST entry; that wave also applies the entries of
-// its last line that lie in the next chunk, and the next wave skips them.  Entries whose own
-// 16-byte part of the line is not entirely inside the tensor (the last few elements of a tensor
-// whose size is not a multiple of 8) and entries of tensors that are not 16-byte aligned are stored
-// directly; the line path never touches those bytes.
+// its last line that lie in the next chunk, and the next wave skips them.  This division holds whether
+// a chunk's entries then go by whole lines or by direct stores.  Lines are lines of the ADDRESS, whatever
+// element a tensor starts at.  Entries whose own 16-byte part of the line is not entirely inside the tensor
+// (the first and last few elements of a tensor that starts or ends between multiples of 16 bytes; the part
+// may hold elements of its neighbour in a packed buffer) are stored directly; the line path never touches
+// those bytes.
+//
+// What bounds it between 1 and 8 %: the memory's rate for this pattern (reads come in 128-byte units, writes
+// in 64: 5.9 TB/s of them at 5 %), and below it the time a chunk's rounds of loads take, so registers and
+// waits matter: the line loads stand under no condition, which would make the compiler wait for one before
+// the next (1.50 against 1.38 ms at 8 %), and the kernel keeps to 64 registers (a version that spilled a few
+// took 1.45 ms at 5 % instead of 1.17).
 // ---------------------------------------------------------------------------------------------
-#ifndef ROSE_APPLY_NT
-#define ROSE_APPLY_NT 14     // non-temporal hints: 1 entry loads, 2 line loads, 4 line stores, 8 direct stores
-                             // (measured best on the 7B workload at 1 - 10 % density)
-#endif
-#ifndef ROSE_APPLY_BLOCKS
-#define ROSE_APPLY_BLOCKS (256 * 512)           // most workgroups an apply launch uses (7B workload, four shards, one
-                                                // chunk per wave: 2.40 / 3.64 / 4.92 ms at 1 / 2 / 5 % with 256 * 128,
-                                                // 2.36 / 3.48 / 4.51 ms with 256 * 512 or more)
-#endif
-constexpr int kApplyThreads = 256;
+// Workgroups of 8 waves (of 4: the same within 3 %).  How a launch is laid out is chosen by what the bucket can
+// hold against the elements of the shard; how its chunks are written, by what they hold.
+//   below 1/28   apply_kernel<1>, 4 waves per SIMD: where the touched lines lie apart the memory does better with
+//                fewer of them in flight (7B-style workload, one shard, against 8 waves: 0.79 and 0.84 ms at 2 %,
+//                0.67 and 0.71 at 1.5 %, 0.55 and 0.56 at 1 %; from 3 % on it loses)
+//   up to 1/7    apply_kernel<0>, 8 waves per SIMD, a wave per chunk while the grid allows it (at 5 %: 1.17 ms,
+//                1.21 with a quarter of the workgroups)
+//   above        at most kApplyBlocks workgroups: a bucket sized for every element costs the idle ones (four
+//                times as many: 80 us more)
+// A bucket that turns out to hold 1/7 of the shard goes by direct stores throughout (apply_direct).
+constexpr int kApplyThreads = 512;
+constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 28, kApplyDenseDiv = 7;
 constexpr int kApplyWaves = kApplyThreads / 64;
 #ifndef ROSE_APPLY_LINE
 #define ROSE_APPLY_LINE 64                      // bytes moved around an entry: 64 or 32 (32 halves the bytes at low
@@ -1752,6 +1761,8 @@ constexpr int kLineElems = ROSE_APPLY_LINE / 2; // line of 16-bit elements
 constexpr int kLineShift = ROSE_APPLY_LINE == 128 ? 6 : ROSE_APPLY_LINE == 64 ? 5 : 4;
 constexpr int kLineParts = kLineElems / 8;      // 16-byte parts of a line
 constexpr int kLinesPerRound = 64 / kLineParts; // lines a wave moves with one load per lane
+constexpr int kLineRounds = 64 / kLinesPerRound;     // rounds of one load per lane that move up to 64 lines
+constexpr int kDirectPerLine = 3, kLoneDen = 10;     // direct stores, see apply_chunk
 static_assert(ROSE_APPLY_LINE == 128 || ROSE_APPLY_LINE == 64 || ROSE_APPLY_LINE == 32, "line size");
 
 
@@ -1761,9 +1772,19 @@ __device__ __forceinline__ void lds_wave_fence() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// Largest t in [0, n) with seg_off[t] <= e, for a wave-uniform e < seg_off[n]: a 64-ary search,
-// one parallel probe per round (two rounds up to 4096 tensors).
+// Segment of entry e (wave-uniform, e < seg_off[n]): the largest t in [0, n) with seg_off[t] <= e.  Up to 256
+// segments all ends are read at once and counted; more of them take a 64-ary search, one parallel probe per
+// round (two rounds up to 4096).
 __device__ __forceinline__ int32_t wave_find_segment(const int64_t *seg_off, int32_t n, int64_t e, int lane) {
+    if (n <= 256) {
+        int64_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = j * 64 + lane < n ? seg_off[j * 64 + lane] : INT64_MAX;
+        int32_t cnt = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cnt += __popcll(__ballot(v[j] <= e));
+        return cnt > 0 ? cnt - 1 : 0;
+    }
     int32_t lo = 0, hi = n;
     while (hi - lo > 1) {
         const int32_t step = (hi - lo + 63) >> 6;
@@ -1783,201 +1804,177 @@ __device__ __forceinline__ uint16_t apply_value(uint32_t cur, uint32_t val, bool
     return (uint16_t)pack_bf16_pair(__uint_as_float(cur << 16) + __uint_as_float(val << 16), 0.0f);
 }
 
-// arith != 0: the bucket holds arithmetic payloads (bit 31 of an index marks an entry that carries
-// the new pattern instead)
-//
-// The entries are cut into RUNS of chunks of 64, dealt round robin to the grid's waves, so that at any
-// time the waves work inside one band of the bucket that moves forward.  How long a run should be
-// depends on the density (measured on the 7B-style workload, 4 shards: runs of 1 / 8 chunks take
-// 2.36 / 2.58 ms at 1 %, 4.51 / 5.56 ms at 5 %, 7.30 / 6.0 ms at 10 %): where nearly every line of the
-// destination is touched, long runs make a wave stream through a contiguous piece of it; where the
-// touched lines lie apart, one chunk per wave and as many workgroups as there are chunks do best.  The
-// kernel picks the run length from the density it sees (entries against the elements of the shard).
-// Inside a run what a chunk needs from its neighbours is at hand: the next chunk's entries are
-// requested one chunk ahead (they are also the look-ahead for a line that straddles the two chunks),
-// the previous chunk's last index stays in a register, and the segment the wave is in (tensor, ends,
-// destination pointer, size) is uniform state that moves forward and is fetched with scalar loads.
-// All of a chunk's line loads are issued before the first is taken in.
-#ifndef ROSE_APPLY_RUN
-#define ROSE_APPLY_RUN 8        // chunks per run in the dense regime
-#endif
-#ifndef ROSE_APPLY_DENSE_DIV
-#define ROSE_APPLY_DENSE_DIV 13 // dense regime: at least one entry per this many elements of the shard
-#endif
-#ifndef ROSE_APPLY_DENSE_BLOCKS
-#define ROSE_APPLY_DENSE_BLOCKS (256 * 128)     // workgroups that take part in the dense regime
-#endif
-constexpr int kLineRounds = 64 / kLinesPerRound;     // rounds of one load per lane that move up to 64 lines
-// shard_elems: elements of the destination shard's tensors together (for the density estimate; objects,
-// which hold a part of a stream, pass a value that keeps them out of the dense regime)
-__device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
-                                           void *const *dst_ptrs, int arith, int64_t shard_elems) {
-    __shared__ uint4 s_line[kApplyWaves][64][kLineParts];   // wave, line slot, 16-byte part
-    __shared__ u64 s_addr[kApplyWaves][64];             // address of the line
-    __shared__ int32_t s_parts[kApplyWaves][64];        // 16-byte parts of the line inside the tensor
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int64_t total = b.seg_off[n_tensors];
-    if (total > b.capacity) total = b.capacity;
-    if (total <= 0) return;
-    const bool dense = total >= shard_elems / ROSE_APPLY_DENSE_DIV;
-    uint32_t n_wgs = gridDim.x;
-    if (dense && n_wgs > (uint32_t)ROSE_APPLY_DENSE_BLOCKS) n_wgs = ROSE_APPLY_DENSE_BLOCKS;
-    const uint32_t wg = blockIdx.x;
-    if (wg >= n_wgs) return;
-    const int64_t n_waves = (int64_t)n_wgs * kApplyWaves;
-    const int64_t run = dense ? (int64_t)ROSE_APPLY_RUN * 64 : 64;
+// A segment of the bucket and the tensor it belongs to: all uniform, fetched with scalar loads.
+struct Segment {
+    int32_t t, numel;
+    int64_t start, end;
+    uint16_t *dst;
+};
+__device__ __forceinline__ Segment load_segment(const BucketDev &b, const int32_t *local_numel, void *const *dst_ptrs,
+                                                int32_t t) {
+    Segment s;
+    s.t = t;
+    s.start = (int64_t)cload64(b.seg_off + t);
+    s.end = (int64_t)cload64(b.seg_off + t + 1);
+    s.dst = reinterpret_cast<uint16_t *>(cload64(dst_ptrs + t));
+    s.numel = (int32_t)cload32(local_numel + t);
+    return s;
+}
+// the segment that holds entry e, from s or one before it on (ends: e < total <= seg_off[n_tensors])
+__device__ __forceinline__ void next_segment(const BucketDev &b, const int32_t *local_numel, void *const *dst_ptrs,
+                                             int64_t e, Segment &s) {
+    while (e >= s.end) s = load_segment(b, local_numel, dst_ptrs, s.t + 1);
+}
+
+// Dense buckets: every entry is one 2-byte store, nothing else.  Where most lines take many entries the
+// memory merges the stores, and the work per entry is what binds the line path (7B-style workload, one
+// shard: 3.27 against 1.90 ms at 30 %, 4.95 against 2.25 at 50 %, 1.85 against 1.63 at 15 %).  Two chunks per
+// wave: one does better where the grid has a wave for each, four never.
+constexpr int kDirectChunks = 2;
+__device__ __forceinline__ void apply_direct(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
+                                             void *const *dst_ptrs, int arith, int64_t total, int64_t wbase, int lane) {
     const int32_t idx_mask = arith ? 0x7FFFFFFF : -1;
-    int32_t t_u = 0, t_have = -1, numel_u = 0;          // uniform: segment of the chunk's first entry, and the
-    int64_t seg_start_u = 0, seg_end_u = 0;             // tensor whose pointer and size are loaded
-    uint16_t *dst_u = nullptr;
-
-    for (int64_t rbase = ((int64_t)wg * kApplyWaves + wave) * run; rbase < total; rbase += n_waves * run) {
-        int64_t wbase = rbase;
-        const int64_t wend = rbase + run < total ? rbase + run : total;
-        if (wbase >= seg_end_u) {                       // (empty segments are stepped over by the search)
-            t_u = __builtin_amdgcn_readfirstlane(wave_find_segment(b.seg_off, n_tensors, wbase, lane));
-            seg_start_u = (int64_t)cload64(b.seg_off + t_u);
-            seg_end_u = (int64_t)cload64(b.seg_off + t_u + 1);
+    int32_t idx[kDirectChunks];
+    uint32_t val[kDirectChunks];
+#pragma unroll
+    for (int u = 0; u < kDirectChunks; ++u) {
+        const int64_t e = wbase + u * 64 + lane;
+        idx[u] = 0;
+        val[u] = 0;
+        if (e < total) {
+            idx[u] = b.idx[e];
+            val[u] = b.val[e];
         }
-        // the run's first chunk, and the last index before the run
-        int32_t cur_idx_raw = 0, prev_last = 0;
-        uint32_t cur_val = 0;
-        if (wbase + lane < total) {
-#if ROSE_APPLY_NT & 1
-            cur_idx_raw = __builtin_nontemporal_load(b.idx + wbase + lane);
-            cur_val = __builtin_nontemporal_load(b.val + wbase + lane);
-#else
-            cur_idx_raw = b.idx[wbase + lane];
-            cur_val = b.val[wbase + lane];
-#endif
+    }
+    Segment s = load_segment(b, local_numel, dst_ptrs,
+                             __builtin_amdgcn_readfirstlane(wave_find_segment(b.seg_off, n_tensors, wbase, lane)));
+    const int64_t wend = wbase + kDirectChunks * 64 < total ? wbase + kDirectChunks * 64 : total;
+    for (int64_t pos = wbase; pos < wend; pos = s.end) {
+        next_segment(b, local_numel, dst_ptrs, pos, s);
+#pragma unroll
+        for (int u = 0; u < kDirectChunks; ++u) {
+            const int64_t e = wbase + u * 64 + lane;
+            const uint32_t i = (uint32_t)(idx[u] & idx_mask);
+            if (e >= pos && e < s.end && e < wend && i < (uint32_t)s.numel) {   // an index outside the tensor is dropped
+                const bool add = arith && idx[u] >= 0;
+                const uint16_t v = apply_value(add ? s.dst[i] : 0u, val[u], add);
+                __builtin_nontemporal_store(v, s.dst + i);
+            }
         }
-        if (wbase > 0) prev_last = b.idx[wbase - 1] & idx_mask;
+    }
+}
 
-        for (;;) {
-            const int64_t e = wbase + lane, e2 = e + 64;
-            const bool valid = e < total;
-            // the next chunk's entries: requested now, needed as look-ahead below and as the entries
-            // of the next round (the run's last chunk only looks into them)
-            int32_t nxt_idx_raw = 0;
-            uint32_t nxt_val = 0;
-            if (e2 < total && (lane < kLineElems || wbase + 64 < wend)) {     // whole only if the run goes on
-#if ROSE_APPLY_NT & 1
-                nxt_idx_raw = __builtin_nontemporal_load(b.idx + e2);
-                nxt_val = __builtin_nontemporal_load(b.val + e2);
-#else
-                nxt_idx_raw = b.idx[e2];
-                nxt_val = b.val[e2];
-#endif
-            }
-            const int32_t idx_raw = cur_idx_raw;
-            const uint32_t val = cur_val;
-            const bool look = lane < kLineElems && e2 < total;
-            const int32_t idx2_raw = look ? nxt_idx_raw : 0;
-            const uint32_t val2 = look ? nxt_val : 0u;
-            const int32_t idx = idx_raw & idx_mask, idx2 = idx2_raw & idx_mask;
-            const bool add = arith && idx_raw >= 0, add2 = arith && idx2_raw >= 0;
+// One chunk of 64 entries.  What it needs comes in three rounds of loads: the entries, the entries behind
+// them and the segment ends; the segment's tensor, by scalar loads; the lines.  All that concerns a segment
+// is uniform: a chunk that holds entries of several takes them one segment after the other.
+//   LONE    also lines that take one entry each go by direct stores
+// A chunk's owned entries go by direct 2-byte stores where they are crowded, three or more to a line (from
+// 8 % on the line path's work per entry binds it: 7B-style workload, one shard, 1.32 against 1.29 ms at 8 %, 2.21
+// against 1.72 at 20 %), and with LONE where hardly two share a line (0.1 %: 78 against 85 us).
+template <int LONE>
+__device__ __forceinline__ void apply_chunk(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
+                                            void *const *dst_ptrs, int arith, int64_t total, int64_t wbase, int lane,
+                                            uint4 (*s_line)[kLineParts], uint32_t *s_no) {
+    const int32_t idx_mask = arith ? 0x7FFFFFFF : -1;
+    const int64_t e = wbase + lane, e2 = e + 64;
+    const int n = total - wbase < 64 ? (int)(total - wbase) : 64;      // entries of the chunk
+    const bool look = lane < kLineElems && e2 < total;
+    int32_t idx_raw = 0, idx2_raw = 0;
+    uint32_t val = 0, val2 = 0;
+    if (lane < n) {
+        idx_raw = b.idx[e];
+        val = b.val[e];
+    }
+    if (look) {
+        idx2_raw = b.idx[e2];
+        val2 = b.val[e2];
+    }
+    const uint32_t prev_idx = wbase > 0 ? cload32(b.idx + wbase - 1) & (uint32_t)idx_mask : 0u;
+    Segment s = load_segment(b, local_numel, dst_ptrs,
+                             __builtin_amdgcn_readfirstlane(wave_find_segment(b.seg_off, n_tensors, wbase, lane)));
+    const uint32_t idx = (uint32_t)(idx_raw & idx_mask), idx2 = (uint32_t)(idx2_raw & idx_mask);
+    const bool add = arith && idx_raw >= 0, add2 = arith && idx2_raw >= 0;
+    const int part = lane % kLineParts;
+    uint16_t *lines16 = reinterpret_cast<uint16_t *>(s_line);
 
-            // tensor of the chunk's first entry, then of each lane's entry
-            while (wbase >= seg_end_u) {                // ends: wbase < total <= seg_off[n_tensors]
-                ++t_u;
-                seg_start_u = seg_end_u;
-                seg_end_u = (int64_t)cload64(b.seg_off + t_u + 1);
-            }
-            int32_t t = t_u;
-            int64_t seg_end = seg_end_u;
-            uint16_t *dst;
-            int32_t numel;
-            const int64_t chunk_last = wbase + 63 < total ? wbase + 63 : total - 1;
-            if (chunk_last < seg_end_u) {               // the whole chunk lies in one segment: all uniform
-                if (t_have != t_u) {
-                    dst_u = reinterpret_cast<uint16_t *>(cload64(dst_ptrs + t_u));
-                    numel_u = (int32_t)cload32(local_numel + t_u);
-                    t_have = t_u;
-                }
-                dst = valid ? dst_u : nullptr;
-                numel = valid ? numel_u : 0;
-            } else {
-                while (valid && e >= seg_end) {
-                    ++t;
-                    seg_end = b.seg_off[t + 1];
-                }
-                dst = valid ? static_cast<uint16_t *>(dst_ptrs[t]) : nullptr;
-                numel = valid ? local_numel[t] : 0;
-            }
-            // may this entry go through the line path?  (depends on the entry alone)
-            const bool ok = valid && (((uintptr_t)dst) & 15u) == 0 && idx >= 0 && (idx | 7) < numel;
-            const u64 key = valid ? (((u64)(uint32_t)t << 32) | (uint32_t)(idx >> kLineShift)) : ~0ull;
-
-            // same line as the entry before?  lane 0 looks at the last entry of the previous chunk
-            u64 prev_key = __shfl_up(key, 1, 64);
-            if (lane == 0)
-                prev_key = wbase > seg_start_u ? (((u64)(uint32_t)t << 32) | (uint32_t)(prev_last >> kLineShift)) : ~0ull - 1;
-            const bool same = valid && key == prev_key;
-            // leading lanes that continue the previous chunk's last line were applied with that chunk
-            const u64 not_same = __ballot(!same);
-            const int first_own = not_same ? __ffsll((long long)not_same) - 1 : 64;
-            const bool owned = ok && lane >= first_own;
-            const bool direct = valid && !ok && idx >= 0 && idx < numel;   // an index outside the tensor is dropped
-
-            // entries of the next chunk that still lie in this chunk's last line
-            const u64 key63 = __shfl(key, 63, 64);
-            const bool own63 = __shfl((int)owned, 63, 64) != 0;
-            const int64_t seg_end63 = __shfl(seg_end, 63, 64);
-            const int32_t numel63 = __shfl(numel, 63, 64);
-            const bool ext = own63 && look && e2 < seg_end63 &&
-                             ((key63 & ~0xffffffffull) | (uint32_t)(idx2 >> kLineShift)) == key63 && idx2 >= 0 &&
-                             (idx2 | 7) < numel63;
-
-            // distinct lines of the owned entries
-            const bool prev_owned = __shfl_up((int)owned, 1, 64) != 0 && lane > 0;
-            const bool head = owned && (!prev_owned || !same);
-            const u64 heads = __ballot(head);
-            const int n_lines = __popcll(heads);
-            const int slot = __popcll(heads & ((2ull << lane) - 1)) - 1;      // line slot of an owned lane
-            if (head) {
-                const int32_t line_first = (idx >> kLineShift) << kLineShift;
-                s_addr[wave][slot] = (u64)(uintptr_t)(dst + line_first);
-                int32_t parts = (numel - line_first) >> 3;
-                s_parts[wave][slot] = parts > kLineParts ? kLineParts : parts;
-            }
+    for (int lo = 0; lo < n;) {                         // the segments that the chunk's entries belong to
+        next_segment(b, local_numel, dst_ptrs, wbase + lo, s);
+        const int hi = s.end - wbase < n ? (int)(s.end - wbase) : n;
+        // lines are lines of the address: the tensor starts `mis` elements behind the start of one.  (An
+        // address that is not a multiple of 2 has no elements in lines: nothing is ok.)
+        const uint64_t base = reinterpret_cast<uint64_t>(s.dst);
+        const uint64_t line0 = base & ~(uint64_t)(ROSE_APPLY_LINE - 1);
+        const uint32_t mis = (uint32_t)(base >> 1) & (uint32_t)(kLineElems - 1);
+        const uint32_t numel = (base & 1u) ? 0u : (uint32_t)s.numel, lim = numel + mis;     // below 2^31 + 32
+        constexpr uint32_t kNoLine = 0xFFFFFFFFu;
+        // line of an entry that may go through the line path (depends on the entry alone): its 16-byte part
+        // lies inside the tensor
+        auto line_of = [&](uint32_t i) -> uint32_t {
+            const uint32_t p = i + mis;
+            return (i < numel && (p & ~7u) >= mis && (p | 7u) < lim) ? p >> kLineShift : kNoLine;
+        };
+        const bool in = lane >= lo && lane < hi;
+        const uint32_t line = in ? line_of(idx) : kNoLine;
+        // same line as the entry before?  lane 0 looks at the last entry of the previous chunk
+        const uint32_t before0 = lo == 0 && wbase > s.start ? line_of(prev_idx) : kNoLine;
+        const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)before0, (int)line, 0x138, 0xf, 0xf, false);  // wave_shr:1
+        const u64 ok_m = __ballot(line != kNoLine);
+        const u64 same_m = __ballot(line == before) & ok_m;
+        // leading lanes that continue the previous chunk's last line were applied with that chunk
+        const u64 owned_m = ok_m & ~(same_m & ~(same_m + 1));
+        const bool owned = (owned_m >> lane) & 1u;
+        const bool loose = in && line == kNoLine && idx < (uint32_t)s.numel;   // an index outside the tensor is dropped
+        // entries of the next chunk that still lie in this chunk's last line
+        const uint32_t line63 = (uint32_t)__builtin_amdgcn_readlane((int)line, 63);
+        const bool ext = (owned_m >> 63) && look && e2 < s.end && line_of(idx2) == line63;
+        // distinct lines of the owned entries
+        const u64 heads = owned_m & ~(same_m & (owned_m << 1));
+        const int n_lines = __popcll(heads);
+        uint16_t *const dst = s.dst;
+        auto store_one = [&](uint32_t i, uint32_t v, bool plus) {
+            __builtin_nontemporal_store(apply_value(plus ? dst[i] : 0u, v, plus), dst + i);
+        };
+        const int n_owned = __popcll(owned_m);
+        // (one comparison, both factors are negative or neither is: a second branch costs the kernel 20
+        // registers and with them its occupancy)
+        const int crowded = n_owned - kDirectPerLine * n_lines, not_lone = LONE ? kLoneDen * n_owned - (kLoneDen + 1) * n_lines : 1;
+        if (crowded * not_lone >= 0) {
+            if (owned || loose) store_one(idx, val, add);
+            if (ext) store_one(idx2, val2, add2);
+        } else {
+            const bool head = (heads >> lane) & 1u;
+            const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u)) - (head ? 0 : 1);
+            if (head) s_no[slot] = line;
             lds_wave_fence();
-
-            // load the lines: kLineParts lanes per line, kLinesPerRound lines per round; every
-            // round's load is issued before the first one is put into LDS
-            const int part = lane % kLineParts;
+            // Load the lines: kLineParts lanes per line, kLinesPerRound lines per round, every round's load
+            // before the first is put into LDS.  Nothing here is under a condition, so that the compiler
+            // need not wait between the rounds: a lane without a line, or whose part lies outside the
+            // tensor, loads the part of the first owned entry, into a place that nothing reads.
+            const uint32_t some = ((uint32_t)__builtin_amdgcn_readlane((int)idx, __ffsll((long long)heads) - 1) + mis) >> 3;
             uint4 lv[kLineRounds];
-            u64 la[kLineRounds];
+            uint32_t at[kLineRounds];                   // 16-byte part, counted from the first line
             bool on[kLineRounds];
 #pragma unroll
-            for (int r = 0; r < kLineRounds; ++r) {
-                const int sl = r * kLinesPerRound + lane / kLineParts;
-                on[r] = sl < n_lines && part < s_parts[wave][sl];
-                la[r] = on[r] ? s_addr[wave][sl] + (u64)(part * 16) : 0;
-            }
+            for (int r = 0; r < kLineRounds; ++r) at[r] = s_no[r * kLinesPerRound + lane / kLineParts];
 #pragma unroll
             for (int r = 0; r < kLineRounds; ++r) {
-                lv[r] = make_uint4(0, 0, 0, 0);
-                if (on[r]) {
-#if ROSE_APPLY_NT & 2
-                    lv[r] = gload16_stream(reinterpret_cast<const void *>((uintptr_t)la[r]));
-#else
-                    lv[r] = gload16(reinterpret_cast<const void *>((uintptr_t)la[r]));
-#endif
-                }
+                at[r] = at[r] * kLineParts + (uint32_t)part;
+                on[r] = (r * kLinesPerRound + lane / kLineParts < n_lines) & (at[r] * 8u >= mis) & (at[r] * 8u + 8u <= lim);
+                at[r] = on[r] ? at[r] : some;
+                lv[r] = gload16_stream(reinterpret_cast<const void *>(line0 + (uint64_t)at[r] * 16u));
             }
 #pragma unroll
-            for (int r = 0; r < kLineRounds; ++r)
-                if (on[r]) s_line[wave][r * kLinesPerRound + lane / kLineParts][part] = lv[r];
+            for (int r = 0; r < kLineRounds; ++r) s_line[r * kLinesPerRound + lane / kLineParts][part] = lv[r];
             lds_wave_fence();
 
             // patch
-            uint16_t *lines16 = reinterpret_cast<uint16_t *>(&s_line[wave][0][0]);
             if (owned) {
-                uint16_t *q = lines16 + slot * kLineElems + (idx & (kLineElems - 1));
+                uint16_t *q = lines16 + slot * kLineElems + ((idx + mis) & (uint32_t)(kLineElems - 1));
                 *q = apply_value(*q, val, add);
             }
             if (ext) {
-                uint16_t *q = lines16 + (n_lines - 1) * kLineElems + (idx2 & (kLineElems - 1));
+                uint16_t *q = lines16 + (n_lines - 1) * kLineElems + ((idx2 + mis) & (uint32_t)(kLineElems - 1));
                 *q = apply_value(*q, val2, add2);
             }
             lds_wave_fence();
@@ -1986,38 +1983,41 @@ __device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors
 #pragma unroll
             for (int r = 0; r < kLineRounds; ++r) {
                 if (on[r]) {
-                    const uint4 v4 = s_line[wave][r * kLinesPerRound + lane / kLineParts][part];
-#if ROSE_APPLY_NT & 4
+                    const uint4 v4 = s_line[r * kLinesPerRound + lane / kLineParts][part];
                     u32x4 w = {v4.x, v4.y, v4.z, v4.w};
-                    __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>((uintptr_t)la[r]));
-#else
-                    gstore16(reinterpret_cast<void *>((uintptr_t)la[r]), v4);
-#endif
+                    __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(line0 + (uint64_t)at[r] * 16u));
                 }
             }
-            if (direct) {
-                const uint16_t v = apply_value(add ? dst[idx] : 0u, val, add);
-#if ROSE_APPLY_NT & 8
-                __builtin_nontemporal_store(v, dst + idx);
-#else
-                dst[idx] = v;
-#endif
-            }
-            lds_wave_fence();                           // the LDS slots are reused by the next chunk
-
-            wbase += 64;
-            if (wbase >= wend) break;
-            prev_last = __builtin_amdgcn_readlane(idx, 63); // the chunk was full: another one follows
-            cur_idx_raw = nxt_idx_raw;
-            cur_val = nxt_val;
+            if (loose) store_one(idx, val, add);
+            lds_wave_fence();                           // the LDS slots are reused
         }
+        lo = hi;
     }
 }
 
-__global__ __launch_bounds__(kApplyThreads) void apply_kernel(BucketDev b, int32_t n_tensors,
+template <int SPARSE>
+__device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
+                                           void *const *dst_ptrs, int arith, int64_t dense_from) {
+    __shared__ uint4 s_line[kApplyWaves][64][kLineParts];   // wave, line slot, 16-byte part
+    __shared__ uint32_t s_no[kApplyWaves][64];              // line numbers
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t total = b.seg_off[n_tensors];
+    if (total > b.capacity) total = b.capacity;
+    const int64_t first = (int64_t)blockIdx.x * kApplyWaves + wave, n_waves = (int64_t)gridDim.x * kApplyWaves;
+    if (!SPARSE && total >= dense_from) {
+        for (int64_t wbase = first * kDirectChunks * 64; wbase < total; wbase += n_waves * kDirectChunks * 64)
+            apply_direct(b, n_tensors, local_numel, dst_ptrs, arith, total, wbase, lane);
+    } else {
+        for (int64_t wbase = first * 64; wbase < total; wbase += n_waves * 64)
+            apply_chunk<SPARSE>(b, n_tensors, local_numel, dst_ptrs, arith, total, wbase, lane, s_line[wave], s_no[wave]);
+    }
+}
+
+template <int SPARSE>
+__global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(SPARSE ? 4 : 8, SPARSE ? 4 : 8))) void apply_kernel(BucketDev b, int32_t n_tensors,
                                                               const int32_t *local_numel, void *const *dst_ptrs, int arith,
-                                                              int64_t shard_elems) {
-    apply_body(b, n_tensors, local_numel, dst_ptrs, arith, shard_elems);
+                                                              int64_t dense_from) {
+    apply_body<SPARSE>(b, n_tensors, local_numel, dst_ptrs, arith, dense_from);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2143,7 +2143,7 @@ __global__ __launch_bounds__(kApplyThreads) void apply_object_kernel(const char 
     if (*verdict == ticket) return;                                    // the validation pass found it out of order
     const BucketDev b = object_arrays(obj, n_tensors, n);
     if (b.seg_off[0] != 0 || b.seg_off[n_tensors] != n) return;
-    apply_body(b, n_tensors, local_numel + (size_t)(h[2] / (uint32_t)tp) * n_tensors, dst_ptrs, (int)h[8], INT64_MAX);
+    apply_body<0>(b, n_tensors, local_numel + (size_t)(h[2] / (uint32_t)tp) * n_tensors, dst_ptrs, (int)h[8], INT64_MAX);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2465,10 +2465,11 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
 int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel, void *const *dst_ptrs,
                  int arith, int64_t shard_elems, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int64_t chunks = (b.capacity + kApplyThreads - 1) / kApplyThreads;
-    int blocks = chunks < 1 ? 1 : (chunks > ROSE_APPLY_BLOCKS ? ROSE_APPLY_BLOCKS : (int)chunks);
-    hipLaunchKernelGGL(apply_kernel, dim3(blocks), dim3(kApplyThreads), 0, st, b, n_tensors, local_numel, dst_ptrs, arith,
-                       shard_elems);
+    const int64_t want = (b.capacity + kApplyThreads - 1) / kApplyThreads;
+    const int most = b.capacity < shard_elems / kApplyDenseDiv ? 4 * kApplyBlocks : kApplyBlocks;
+    const int blocks = want < 1 ? 1 : (want > most ? most : (int)want);
+    hipLaunchKernelGGL(b.capacity < shard_elems / kApplySparseDiv ? apply_kernel<1> : apply_kernel<0>, dim3(blocks),
+                       dim3(kApplyThreads), 0, st, b, n_tensors, local_numel, dst_ptrs, arith, shard_elems / kApplyDenseDiv);
     return (int)hipGetLastError();
 }
 
@@ -2486,8 +2487,9 @@ int launch_apply_object(const void *object, size_t object_bytes, int32_t n_tenso
                         unsigned long long ticket, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     int64_t chunks = ((int64_t)(object_bytes / 6) + kApplyThreads - 1) / kApplyThreads;
-    int blocks = chunks < 1 ? 1 : (chunks > ROSE_APPLY_BLOCKS ? ROSE_APPLY_BLOCKS : (int)chunks);
-    const int vblocks = blocks > 4096 ? 4096 : blocks;
+    int blocks = chunks < 1 ? 1 : (chunks > kApplyBlocks ? kApplyBlocks : (int)chunks);
+    const int64_t vwant = ((int64_t)(object_bytes / 6) + 255) / 256;
+    const int vblocks = vwant < 1 ? 1 : (vwant > 4096 ? 4096 : (int)vwant);
     hipLaunchKernelGGL(object_clear_kernel, dim3(1), dim3(1), 0, st, verdict);
     hipLaunchKernelGGL(object_validate_kernel, dim3(vblocks), dim3(256), 0, st, static_cast<const char *>(object),
                        object_bytes, n_tensors, n_buckets, verdict, ticket);
