@@ -205,51 +205,16 @@ __device__ __forceinline__ uint32_t dst_index(const Piece &pc, uint32_t k, bool 
 // Tile loaders.  A lane's vector j holds the eight 16-bit patterns at piece-relative local indices
 // k .. k+7 with k = k_wave + (j * 64 + lane) * 8.
 //
-// load_raw / load_tile_fast (used by the dense copy): the whole tile lies inside the piece and
-// every vector is 16-byte aligned, so all loads are 128-bit loads issued back to back.  Loading
-// (raw registers) is split from conversion (fp32 -> bf16) so that a tile's loads can be issued long
-// before its data is needed; the encode kernel has its own loader for that (load_raw_pair).
+// Loading (raw registers) is split from conversion (fp32 -> bf16) so that a tile's loads can be issued long
+// before its data is needed.
 template <int SRC_F32> struct RawTile;
 template <> struct RawTile<0> { uint4 v[kIters]; };
 template <> struct RawTile<1> { uint4 lo[kIters], hi[kIters]; };
 
-// `limit` is the piece length for a tile that reaches past the end of its piece (vectors that do
-// not fit entirely read as zero) and 0xFFFFFFFF for a full tile.
-__device__ __forceinline__ void load_raw(const void *base, const Piece &pc, uint32_t k_wave, int lane,
-                                         uint32_t limit, RawTile<0> &r) {
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) {
-        const uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
-        r.v[j] = make_uint4(0, 0, 0, 0);
-        if (k + kVec <= limit) r.v[j] = gload16(static_cast<const uint16_t *>(base) + src_index(pc, k, true));
-    }
-}
-__device__ __forceinline__ void load_raw(const void *base, const Piece &pc, uint32_t k_wave, int lane,
-                                         uint32_t limit, RawTile<1> &r) {
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) {
-        const uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
-        r.lo[j] = r.hi[j] = make_uint4(0, 0, 0, 0);
-        if (k + kVec <= limit) {
-            const uint32_t *p = static_cast<const uint32_t *>(base) + src_index(pc, k, true);
-            r.lo[j] = gload16(p);
-            r.hi[j] = gload16(p + 4);
-        }
-    }
-}
 __device__ __forceinline__ uint4 raw_to_bf16(const RawTile<0> &r, int j) { return r.v[j]; }
 __device__ __forceinline__ uint4 raw_to_bf16(const RawTile<1> &r, int j) {
     return make_uint4(pack_rne(r.lo[j].x, r.lo[j].y), pack_rne(r.lo[j].z, r.lo[j].w),
                       pack_rne(r.hi[j].x, r.hi[j].y), pack_rne(r.hi[j].z, r.hi[j].w));
-}
-
-template <int SRC_F32>
-__device__ __forceinline__ void load_tile_fast(const void *base, const Piece &pc, uint32_t k_wave, int lane,
-                                               uint4 (&out)[kIters]) {
-    RawTile<SRC_F32> r;
-    load_raw(base, pc, k_wave, lane, 0xFFFFFFFFu, r);
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) out[j] = raw_to_bf16(r, j);
 }
 
 // General path (last vector of a piece, very short runs, odd addresses): one vector, element by element;
@@ -541,7 +506,7 @@ struct TileCtx {
     const uint16_t *old_base;
     const void *new_base;
     uint32_t k_tile;
-    uint32_t limit;     // see load_raw
+    uint32_t limit;     // the piece's length for a tile that reaches past its end, 0xFFFFFFFF for a full tile
     uint32_t vec;       // bit 0: 128-bit loads are legal for this tile; bit 2: its vectors may straddle runs
     int32_t piece;      // index of pc in the piece table
 };
@@ -570,7 +535,7 @@ struct TileMeta {
     int32_t piece;      // -1, or the piece whose table entry maps element numbers to local indices
     int32_t shard;
     int32_t seg;        // tensor whose segment starts with this tile, else -1
-    uint32_t limit;     // see load_raw
+    uint32_t limit;     // see TileCtx
     uint32_t vec;       // bit 0: 128-bit loads are legal; bit 1: piece of a replicated tensor; bit 2: see TileCtx
     uint32_t k_tile;
 };
@@ -2147,7 +2112,13 @@ __global__ __launch_bounds__(kApplyThreads) void apply_object_kernel(const char 
 }
 
 // ---------------------------------------------------------------------------------------------
-// dense copy of one shard: the same tiles as encode, moved instead of compared.
+// dense copy of one shard: the same tiles as encode, moved instead of compared.  One tile per workgroup, all
+// of its loads in flight together, loads and stores non-temporal: what a plain copy does best with (2 GiB:
+// 5.0 - 5.4 TB/s from a grid of 2048 or 8192 workgroups, 5.9 from one workgroup per tile, 6.1 with both hints).
+// Loads take any alignment at little cost, stores do not (5.7 TB/s), so a tile's vectors are lined up with
+// the DESTINATION: they begin `head` elements into the piece, which the first tile copies one by one.
+// (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements, TP2: 4130 -> 1421 us; rows of
+// 765 elements a shard, 131 M weights: 248 -> 89 us.)
 // ---------------------------------------------------------------------------------------------
 template <int NEW_F32>
 __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
@@ -2156,25 +2127,58 @@ __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const void *new_base = reinterpret_cast<const void *>(cload64(a.new_ptrs + pc.tensor));
     uint16_t *dst = reinterpret_cast<uint16_t *>(cload64(a.dst_ptrs + pc.tensor));
+    const uint32_t len = (uint32_t)pc.len;
     const uint32_t k_tile = (uint32_t)(tile - pc.first_tile) * (uint32_t)kTile;
-    const uint32_t k_wave = k_tile + (uint32_t)wave * kWaveSpan;
-    const bool fast = (pc.flags & kPieceVec) && k_tile + (uint32_t)kTile <= (uint32_t)pc.len &&
-                      ((((uintptr_t)new_base) | ((uintptr_t)dst)) & 15u) == 0;
-    if (fast) {
-        uint4 nv[kIters];
-        load_tile_fast<NEW_F32>(new_base, pc, k_wave, lane, nv);
-#pragma unroll
-        for (int j = 0; j < kIters; ++j)
-            gstore16(dst + dst_index(pc, k_wave + (uint32_t)(j * 64 + lane) * kVec, true), nv[j]);
-    } else {
+    const bool dst_strided = (pc.flags & kPieceDstStrided) != 0;
+    const uint32_t head = dst_strided ? 0u : (0u - ((uint32_t)((uintptr_t)dst >> 1) + (uint32_t)pc.local_base)) & 7u;
+    const uint32_t k0 = k_tile + head, k_lane = k0 + (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
+    auto copy_one = [&](uint32_t k) {
+        const int64_t s = src_index(pc, k, false);
+        dst[dst_index(pc, k, false)] = NEW_F32 ? (uint16_t)rne_bf16(static_cast<const uint32_t *>(new_base)[s])
+                                               : static_cast<const uint16_t *>(new_base)[s];
+    };
+    if (k_tile == 0 && threadIdx.x < head && threadIdx.x < len) copy_one(threadIdx.x);
+    const bool vec = (pc.flags & kPieceLoad16) && ((((uintptr_t)new_base) | ((uintptr_t)dst)) & 1u) == 0 &&
+                     k0 + (uint32_t)kVec <= len && (!dst_strided || pc.run >= kVec);
+    if (!vec) {
 #pragma unroll 1
-        for (int j = 0; j < kIters; ++j) {
-            uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
-            uint4 n = load_vec_general<NEW_F32>(new_base, pc, k);
+        for (int j = 0; j < kIters; ++j)
+            for (uint32_t i = 0; i < (uint32_t)kVec; ++i) {
+                const uint32_t k = k_lane + (uint32_t)(j * 64) * kVec + i;
+                if (k < len) copy_one(k);
+            }
+        return;
+    }
+    // may a vector straddle the end of a run, on either side?
+    const bool src_split = (pc.flags & kPieceStrided) && (((uint32_t)pc.run | head) & 7u);
+    const bool dst_split = dst_strided && ((uint32_t)pc.run & 7u);
+    RawTile<NEW_F32> r;
 #pragma unroll
-            for (uint32_t i = 0; i < (uint32_t)kVec; ++i)
-                if (k + i < (uint32_t)pc.len) dst[dst_index(pc, k + i, false)] = (uint16_t)pick16(n, i);
+    for (int j = 0; j < kIters; ++j) {                  // unconditional, see load_raw_pair
+        uint32_t k = k_lane + (uint32_t)(j * 64) * kVec;
+        if (k + kVec > len) k = k0;
+        const int64_t e = src_index(pc, k, true);
+        if constexpr (NEW_F32) {
+            r.lo[j] = gload16_stream(static_cast<const uint32_t *>(new_base) + e);
+            r.hi[j] = gload16_stream(static_cast<const uint32_t *>(new_base) + e + 4);
+        } else {
+            r.v[j] = gload16_stream(static_cast<const uint16_t *>(new_base) + e);
         }
+    }
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) {
+        const uint32_t k = k_lane + (uint32_t)(j * 64) * kVec;
+        uint32_t left = kVec, q = 0;
+        if (src_split || dst_split) left = split_left(pc, k, &q);
+        if (k + kVec > len || (dst_split && left < (uint32_t)kVec)) {
+            for (uint32_t i = 0; i < (uint32_t)kVec; ++i)
+                if (k + i < len) copy_one(k + i);
+            continue;
+        }
+        uint4 v = raw_to_bf16(r, j);
+        if (src_split && left < (uint32_t)kVec) v = split_merge(v, load_new_vec<NEW_F32>(new_base, split_tail_at(pc, q, left)), left);
+        u32x4 w = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(dst + dst_index(pc, k, true))));
     }
 }
 

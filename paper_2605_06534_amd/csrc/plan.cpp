@@ -120,15 +120,7 @@ static void segment_pieces(const rose_tensor_desc &t, int32_t ti, int32_t d, int
         if (src_strided) p.flags |= rose::kPieceStrided;
         if (dst_strided) p.flags |= rose::kPieceDstStrided;
         if (strided && run >= 2) rose::make_magic((uint32_t)run, &p.magic, &p.shift);
-        bool vec = (src_off % rose::kVec == 0) && (local_base % rose::kVec == 0) &&
-                   (!strided || run % rose::kVec == 0) && (!src_strided || src_stride % rose::kVec == 0) &&
-                   (!dst_strided || lstride % rose::kVec == 0);
-        bool load16 = !src_strided || run >= rose::kVec;
-        if (strided && (vec || load16) && !rose::magic_ok((uint32_t)run, p.magic, p.shift, (uint32_t)len)) {
-            vec = false;
-            load16 = load16 && !src_strided;
-        }
-        if (vec) p.flags |= rose::kPieceVec;
+        const bool load16 = !src_strided || (run >= rose::kVec && rose::magic_ok((uint32_t)run, p.magic, p.shift, (uint32_t)len));
         if (load16) p.flags |= rose::kPieceLoad16;
         if (load16 && src_strided && run % rose::kVec) p.flags |= rose::kPieceSplit;
         out.push_back(p);

@@ -28,7 +28,6 @@ constexpr int kTile = kThreads * kVec * kIters;    // elements per tile
 
 enum : int32_t {
     kPieceFirst = 1,    // first piece of its (tensor, shard) segment
-    kPieceVec = 2,      // offsets and run lengths are multiples of kVec: 128-bit loads are legal
     kPieceStrided = 4,  // runs of `run` elements every `stride` source elements
     kPieceReplicated = 16, // piece of a replicated tensor: several destinations read the same source
     kPieceLoad16 = 32,  // a vector of kVec elements is one 128-bit load of the source, at any alignment: the source is
