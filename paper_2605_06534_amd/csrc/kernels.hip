@@ -119,19 +119,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
     return x;
 }
 
+// the OR of x over each group of four lanes
+__device__ __forceinline__ uint32_t or_of_four(uint32_t x) {
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);     // quad_perm 1,0,3,2
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);     // quad_perm 2,3,0,1
+    return x;
+}
+
 // Cache policy of the encode kernel's streams (measured on the 7B workload: both hints together
 // take 0.27 ms off 5.65 ms; either alone gains nothing): the two tensors are read once and the
 // bucket entries are written once, so both are marked non-temporal.
 #ifndef ROSE_NT_LOADS
 #define ROSE_NT_LOADS 1
 #endif
-#ifndef ROSE_REFRESH_NT
-#define ROSE_REFRESH_NT 1
-#endif
-#ifndef ROSE_REFRESH_WHOLE
-#define ROSE_REFRESH_WHOLE 160         // entries per tile above which refresh rewrites the whole tile
-                                       // (7B workload: 7.7 ms at 1 %, 8.0 ms at 5 %; 10.7 ms at 5 % without)
-#endif
+constexpr int kRefreshWide = 200;      // entries per tile up to which a refresh writes 128-byte lines, see encode_body
 #ifndef ROSE_NT_STORES
 #define ROSE_NT_STORES 1
 #endif
@@ -1430,12 +1431,18 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             if (!skip && !(cur.vec & 2u)) {
                 const TileCtx c = tile_ctx(a, __builtin_amdgcn_readfirstlane(tile));
                 uint16_t *ob = const_cast<uint16_t *>(c.old_base);
-                // a tile with many changes is written whole: full lines cost the memory less than
-                // many partial ones
-                const bool whole = (cur.vec & 1u) && c.limit == 0xFFFFFFFFu && tile_total > (uint32_t)ROSE_REFRESH_WHOLE;
+                // Whole 64-byte lines (four lanes' vectors), or 128-byte ones where changes are few, go back if
+                // anything in them has changed: the memory takes whole lines far better than parts of
+                // them, and better than the whole tile at any density (twelve 8B-style layers, single
+                // vectors up to 160 entries a tile and whole tiles above / 64-byte / 128-byte lines: 3.91 / 3.44 / 3.35
+                // ms at 1 %, 4.21 / 3.75 / 3.70 at 2 %, 4.15 / 4.07 / 4.10 at 5 %, 4.47 / 4.47 / 4.47 at 12 %).
+                const bool wide = tile_total <= (uint32_t)kRefreshWide;
 #pragma unroll
                 for (int j = 0; j < kIters; ++j) {
-                    if (mask[j] || whole) {
+                    uint32_t line = or_of_four(mask[j]);
+                    const uint32_t pair = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)line, 0x141, 0xf, 0xf, true);  // row_half_mirror
+                    if (wide) line |= pair;
+                    if (line) {
                         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
                         bool one = (cur.vec & 1u) && (c.limit == 0xFFFFFFFFu || k + kVec <= c.limit);
                         if (cur.vec & 4u) {
@@ -1443,14 +1450,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                             one = one && split_left(c.pc, k, &q) >= (uint32_t)kVec;
                         }
                         if (one) {
-#if ROSE_REFRESH_NT
-                            {
-                                u32x4 w = {nv[j].x, nv[j].y, nv[j].z, nv[j].w};
-                                __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(ob + src_index(c.pc, k, true))));
-                            }
-#else
-                            gstore16(ob + src_index(c.pc, k, true), nv[j]);     // unchanged elements keep their bits
-#endif
+                            u32x4 w = {nv[j].x, nv[j].y, nv[j].z, nv[j].w};     // unchanged elements keep their bits
+                            __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(ob + src_index(c.pc, k, true))));
                         } else {
                             uint32_t m = mask[j];
                             while (m) {
@@ -1631,7 +1632,7 @@ __global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, cons
             for (int j = 0; j < kIters; ++j) {
                 const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
                 uint32_t q, m = mask[j];
-                if (!m) continue;
+                if (!or_of_four(m)) continue;       // whole 64-byte lines
                 if ((c.vec & 1u) && k + kVec <= (uint32_t)c.pc.len &&
                     !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
                     gstore16(ob + src_index(c.pc, k, true), n[j]);
