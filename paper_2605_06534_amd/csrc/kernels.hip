@@ -158,6 +158,10 @@ __device__ __forceinline__ uint4 gload16_stream(const void *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+__device__ __forceinline__ void gstore16_stream(void *p, uint4 v) {
+    u32x4 w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(p)));
+}
 __device__ __forceinline__ void gstore16(void *p, uint4 v) {
     u32x4 w = {v.x, v.y, v.z, v.w};
     *reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(p)) = w;
@@ -1998,6 +2002,7 @@ __host__ __device__ inline size_t object_size(int32_t n_tensors, int64_t n) {
     return object_idx_off(n_tensors) + up16(4 * (size_t)n) + up16(2 * (size_t)n);
 }
 
+constexpr int kPackTile = 4096;         // entries a workgroup moves or checks at a time
 __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, int32_t n_tensors, int64_t first,
                                                    int64_t n, int32_t payload, char *obj) {
     int64_t total = b.seg_off[n_tensors];
@@ -2032,9 +2037,28 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
     if (!ok) return;
     int32_t *idx = reinterpret_cast<int32_t *>(obj + a_off);
     uint16_t *val = reinterpret_cast<uint16_t *>(obj + b_off);
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        idx[e] = b.idx[first + e];
-        val[e] = b.val[first + e];
+    // 128-bit accesses, read and written once: the object's arrays are aligned, the bucket's range starts at any
+    // entry.  A workgroup's loads are all in flight together.  (84 M entries in eight objects: 234 us with an
+    // entry per lane, 192 us this way.)
+    const int32_t *from_idx = b.idx + first;
+    const uint16_t *from_val = b.val + first;
+    for (int64_t e0 = (int64_t)blockIdx.x * kPackTile; e0 < n; e0 += (int64_t)gridDim.x * kPackTile) {
+        if (e0 + kPackTile <= n) {
+            uint4 vi[4], vv[2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) vi[j] = gload16_stream(from_idx + e0 + (j * 256 + threadIdx.x) * 4);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) vv[j] = gload16_stream(from_val + e0 + (j * 256 + threadIdx.x) * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) gstore16_stream(idx + e0 + (j * 256 + threadIdx.x) * 4, vi[j]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) gstore16_stream(val + e0 + (j * 256 + threadIdx.x) * 8, vv[j]);
+        } else {
+            for (int64_t e = e0 + threadIdx.x; e < n; e += 256) {
+                idx[e] = from_idx[e];
+                val[e] = from_val[e];
+            }
+        }
     }
 }
 
@@ -2083,15 +2107,40 @@ __global__ __launch_bounds__(256) void object_validate_kernel(const char *obj, s
         bad |= lo < 0 || hi < lo || hi > n;
     }
     const int32_t m = h[8] ? 0x7FFFFFFF : -1;
-    for (int64_t e = gid + 1; e < n; e += stride) {
-        if ((b.idx[e] & m) <= (b.idx[e - 1] & m)) {
-            // allowed only if some segment starts at e: smallest t with seg_off[t] >= e
-            int32_t lo = 0, hi = n_tensors;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (b.seg_off[mid] < e) lo = mid + 1; else hi = mid;
+    // Four neighbours per 128-bit load (the array is padded to whole ones), the one before them from the lane
+    // below; four loads in flight per lane.  (Eight objects of 84 M entries checked and applied: 1376 us with two
+    // 4-byte loads an entry, 1318 us this way.)
+    for (int64_t e0 = (int64_t)blockIdx.x * kPackTile; e0 < n; e0 += (int64_t)gridDim.x * kPackTile) {
+        uint4 v[4];
+        int32_t first[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t e = e0 + (j * 256 + threadIdx.x) * 4;
+            v[j] = make_uint4(0, 0, 0, 0);
+            first[j] = -1;
+            if (e < n) {
+                v[j] = gload16(b.idx + e);
+                if ((threadIdx.x & 63) == 0 && e > 0) first[j] = b.idx[e - 1] & m;
             }
-            bad |= b.seg_off[lo] != e;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t e = e0 + (j * 256 + threadIdx.x) * 4;
+            const int32_t x[4] = {(int32_t)v[j].x & m, (int32_t)v[j].y & m, (int32_t)v[j].z & m, (int32_t)v[j].w & m};
+            int32_t before = __builtin_amdgcn_update_dpp(first[j], x[3], 0x138, 0xf, 0xf, false);    // wave_shr:1
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (e + i > 0 && e + i < n && x[i] <= before) {
+                    // allowed only if some segment starts at e + i: smallest t with seg_off[t] >= e + i
+                    int32_t lo = 0, hi = n_tensors;
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi) >> 1;
+                        if (b.seg_off[mid] < e + i) lo = mid + 1; else hi = mid;
+                    }
+                    bad |= b.seg_off[lo] != e + i;
+                }
+                before = x[i];
+            }
         }
     }
     if (bad) *verdict = ticket;
@@ -2481,8 +2530,8 @@ int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_num
 int launch_pack(const BucketDev &b, int32_t shard, int32_t n_tensors, int64_t first, int64_t n, int32_t payload,
                 void *object, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int64_t want = (n + 1023) / 1024;
-    int blocks = want < 1 ? 1 : (want > 256 * 16 ? 256 * 16 : (int)want);
+    int64_t want = (n + kPackTile - 1) / kPackTile;
+    int blocks = want < 1 ? 1 : (want > (1 << 20) ? 1 << 20 : (int)want);
     hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, st, b, shard, n_tensors, first, n, payload, static_cast<char *>(object));
     return (int)hipGetLastError();
 }
@@ -2493,7 +2542,7 @@ int launch_apply_object(const void *object, size_t object_bytes, int32_t n_tenso
     hipStream_t st = static_cast<hipStream_t>(stream);
     int64_t chunks = ((int64_t)(object_bytes / 6) + kApplyThreads - 1) / kApplyThreads;
     int blocks = chunks < 1 ? 1 : (chunks > kApplyBlocks ? kApplyBlocks : (int)chunks);
-    const int64_t vwant = ((int64_t)(object_bytes / 6) + 255) / 256;
+    const int64_t vwant = ((int64_t)(object_bytes / 6) + kPackTile - 1) / kPackTile;
     const int vblocks = vwant < 1 ? 1 : (vwant > 4096 ? 4096 : (int)vwant);
     hipLaunchKernelGGL(object_clear_kernel, dim3(1), dim3(1), 0, st, verdict);
     hipLaunchKernelGGL(object_validate_kernel, dim3(vblocks), dim3(256), 0, st, static_cast<const char *>(object),

@@ -193,3 +193,53 @@ def test_objects_of_the_7b_workload_at_64_mb():
     torch.cuda.synchronize()
     for x, y, w in zip(a, b, want):
         assert torch.equal(x.view(torch.int16), w.view(torch.int16)) and torch.equal(y.view(torch.int16), w.view(torch.int16))
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 7, 8, 4095, 4096, 4097, 3 * 4096 + 5])
+@pytest.mark.parametrize("first", [0, 1, 2, 7])
+def test_pack_at_any_entry_and_order_checked_at_every_entry(n, first):
+    """Ranges that start and end anywhere; a pair of entries out of order is found wherever it stands."""
+    print("case: pack n=%d first=%d" % (n, first), flush=True)
+    sizes = [20000, 3, 50000]
+    plan = R.shard_plan([dict(rows=1, cols=s, rule=R.REPLICATED) for s in sizes], 1)
+    plan.upload()
+    rng = np.random.default_rng(n * 10 + first)
+    seg, idx = [0], []
+    for s, k in zip(sizes, ((n + first) // 2, min(2, n + first - (n + first) // 2), 0)):
+        idx.append(np.sort(rng.choice(s, size=k, replace=False)))
+        seg.append(seg[-1] + k)
+    rest = n + first - seg[-2]
+    idx[2] = np.sort(rng.choice(sizes[2], size=rest, replace=False))
+    seg[3] = seg[2] + rest
+    b = R.Bucket(n + first, 3)
+    idx = np.concatenate(idx).astype(np.int32)
+    val = rng.integers(0, 1 << 16, size=n + first, dtype=np.uint16)
+    b.idx[:n + first] = torch.from_numpy(idx).cuda()
+    b.val[:n + first] = torch.from_numpy(val.view(np.int16)).cuda()
+    b.seg_off.copy_(torch.tensor(seg, dtype=torch.int64))
+    obj = torch.full((R.object_bytes(plan, n),), 0xEE, dtype=torch.uint8, device="cuda")
+    R.bucket_pack(plan, 0, b, first, n, obj)
+    torch.cuda.synchronize()
+    want = oracle.pack_object({"idx": idx, "val": val, "seg_off": np.array(seg, dtype=np.int64)}, 0, first, n)
+    assert np.array_equal(obj.cpu().numpy(), want)
+    a_off = (64 + 8 * 4 + 15) // 16 * 16
+    swaps = [e for e in sorted({1, 2, 3, 4, 5, 8, 255, 256, 257, 1023, 1024, 1025, 4095, 4096, 4097, n - 1}) if 0 < e < n]
+    for e in swaps:
+        if first + e in seg[1:3]:
+            continue
+        bad = obj.clone()
+        w = bad[a_off:a_off + 4 * n].view(torch.int32)
+        w[e] = w[e - 1]                                  # not strictly ascending
+        dst = [torch.zeros(s, dtype=torch.int16, device="cuda") for s in sizes]
+        R.object_apply(plan, bad, R.ptr_table(dst))
+        torch.cuda.synchronize()
+        assert not any(x.any() for x in dst), (n, first, e)
+    dst = [torch.zeros(s, dtype=torch.int16, device="cuda") for s in sizes]
+    R.object_apply(plan, obj, R.ptr_table(dst))
+    torch.cuda.synchronize()
+    ref = [np.zeros(s, dtype=np.uint16) for s in sizes]
+    for t in range(3):
+        lo, hi = max(seg[t], first), max(seg[t + 1], first)
+        ref[t][idx[lo:hi]] = val[lo:hi]
+    for g, r in zip(dst, ref):
+        assert np.array_equal(g.cpu().numpy().view(np.uint16), r)
