@@ -2113,6 +2113,7 @@ __global__ __launch_bounds__(256) void object_validate_kernel(const char *obj, s
     for (int64_t e0 = (int64_t)blockIdx.x * kPackTile; e0 < n; e0 += (int64_t)gridDim.x * kPackTile) {
         uint4 v[4];
         int32_t first[4];
+        uint32_t falls = 0;                             // bit 4 j + i: entry i of load j does not exceed the one before
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int64_t e = e0 + (j * 256 + threadIdx.x) * 4;
@@ -2130,17 +2131,22 @@ __global__ __launch_bounds__(256) void object_validate_kernel(const char *obj, s
             int32_t before = __builtin_amdgcn_update_dpp(first[j], x[3], 0x138, 0xf, 0xf, false);    // wave_shr:1
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (e + i > 0 && e + i < n && x[i] <= before) {
-                    // allowed only if some segment starts at e + i: smallest t with seg_off[t] >= e + i
-                    int32_t lo = 0, hi = n_tensors;
-                    while (lo < hi) {
-                        const int32_t mid = (lo + hi) >> 1;
-                        if (b.seg_off[mid] < e + i) lo = mid + 1; else hi = mid;
-                    }
-                    bad |= b.seg_off[lo] != e + i;
-                }
+                if (e + i > 0 && e + i < n && x[i] <= before) falls |= 1u << (4 * j + i);
                 before = x[i];
             }
+        }
+        // allowed only where some segment starts: smallest t with seg_off[t] >= that entry.  (All lanes search at
+        // the same time, whichever of their entries it is: with short segments most waves hold several.)
+        while (falls) {
+            const int at = __ffs(falls) - 1;
+            falls &= falls - 1;
+            const int64_t e = e0 + ((at >> 2) * 256 + threadIdx.x) * 4 + (at & 3);
+            int32_t lo = 0, hi = n_tensors;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (b.seg_off[mid] < e) lo = mid + 1; else hi = mid;
+            }
+            bad |= b.seg_off[lo] != e;
         }
     }
     if (bad) *verdict = ticket;
