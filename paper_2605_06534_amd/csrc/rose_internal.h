@@ -207,6 +207,7 @@ struct rose_plan {
     mutable int32_t n_repl = 0;
     mutable unsigned long long *d_verdict = nullptr;   // [kVerdictSlots]
     mutable int resident[8] = {0};             // see encode_resident_all
+    mutable bool uses_mail = false;            // holds a share of the pinned words of bucket checks (api.cpp)
     mutable void *static_ws = nullptr;         // the library's built-in scratch on `device`
     mutable size_t static_ws_bytes = 0;
 };

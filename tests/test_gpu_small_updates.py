@@ -53,3 +53,31 @@ def test_overflow_is_reported_and_bounded():
             R.bucket_check(c.plan, b)
         assert e.value.required > 1000
         assert (b.idx[1000:] == -7).all()
+
+
+def test_checks_from_many_threads():
+    """More bucket checks at a time than a plan has pinned words, each on a stream of its own."""
+    import threading
+    import torch
+    print("case: threaded checks", flush=True)
+    ts = [T(1, 4096, R.REPLICATED)]
+    plan = R.shard_plan(ts, 1)
+    plan.upload()
+    buckets = [R.Bucket(4096, 1) for _ in range(96)]
+    for i, b in enumerate(buckets):
+        b.seg_off.copy_(torch.tensor([0, i + 1], dtype=torch.int64))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                if R.bucket_check(plan, buckets[i]) != i + 1:
+                    wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(96)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
