@@ -81,3 +81,33 @@ def test_checks_from_many_threads():
     for t in threads:
         t.join()
     assert not wrong
+
+
+def test_two_launches_in_a_graph():
+    """The counting and the writing launch captured once and replayed on changed inputs, with eager work between."""
+    import torch
+    from oracle import oracle
+    from gpu_harness import assert_buckets_equal, bits
+    from workloads import models
+    print("case: small update in a graph", flush=True)
+    c = bern_case(models.decoder(2, 320, 8, 8, 40, 1376, 2048, fused=True), 2, 0.05, seed=91)
+    c.encode()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            R.delta_encode(c.plan, c.old_tab, c.new_tab, c.new_dtype, c.buckets, c.ws)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        for n in c.new:
+            n.copy_(torch.roll(n, rep))
+        for b in c.buckets:
+            b.idx.fill_(-7)
+            b.seg_off.fill_(-1)
+        c.ws.fill_(-1)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        want = oracle.encode_model([dict(t, old=bits(o), new=bits(n)) for t, o, n in zip(c.tensors, c.old, c.new)], c.tp)
+        for d in range(c.tp):
+            assert_buckets_equal(c.host_bucket(d), want[d], "replay %d shard %d" % (rep, d))
