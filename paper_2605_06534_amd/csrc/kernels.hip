@@ -1715,8 +1715,10 @@ __global__ __launch_bounds__(256) void refresh_replicated_kernel(const int32_t *
 //                0.67 and 0.71 at 1.5 %, 0.55 and 0.56 at 1 %; from 3 % on it loses)
 //   up to 1/7    apply_kernel<0>, 8 waves per SIMD, a wave per chunk while the grid allows it (at 5 %: 1.17 ms,
 //                1.21 with a quarter of the workgroups)
-//   above        at most kApplyBlocks workgroups: a bucket sized for every element costs the idle ones (four
-//                times as many: 80 us more)
+//   above        8 waves per SIMD
+// Only between 1/28 and 1/7 more than kApplyBlocks workgroups are launched: the waves that find no chunk cost (a
+// bucket with room for every element: 80 us for four times as many; a 32B-style shard set whose buckets hold
+// twice what came: 10.2 instead of 9.5 ms for its eight applies).
 // A bucket that turns out to hold 1/7 of the shard goes by direct stores throughout (apply_direct).
 constexpr int kApplyThreads = 512;
 constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 28, kApplyDenseDiv = 7;
@@ -1742,17 +1744,17 @@ __device__ __forceinline__ void lds_wave_fence() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// Segment of entry e (wave-uniform, e < seg_off[n]): the largest t in [0, n) with seg_off[t] <= e.  Up to 256
+// Segment of entry e (wave-uniform, e < seg_off[n]): the largest t in [0, n) with seg_off[t] <= e.  Up to 512
 // segments all ends are read at once and counted; more of them take a 64-ary search, one parallel probe per
 // round (two rounds up to 4096).
 __device__ __forceinline__ int32_t wave_find_segment(const int64_t *seg_off, int32_t n, int64_t e, int lane) {
-    if (n <= 256) {
-        int64_t v[4];
+    if (n <= 512) {
+        int64_t v[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = j * 64 + lane < n ? seg_off[j * 64 + lane] : INT64_MAX;
+        for (int j = 0; j < 8; ++j) v[j] = j * 64 + lane < n ? seg_off[j * 64 + lane] : INT64_MAX;
         int32_t cnt = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) cnt += __popcll(__ballot(v[j] <= e));
+        for (int j = 0; j < 8; ++j) cnt += __popcll(__ballot(v[j] <= e));
         return cnt > 0 ? cnt - 1 : 0;
     }
     int32_t lo = 0, hi = n;
@@ -2526,9 +2528,10 @@ int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_num
                  int arith, int64_t shard_elems, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t want = (b.capacity + kApplyThreads - 1) / kApplyThreads;
-    const int most = b.capacity < shard_elems / kApplyDenseDiv ? 4 * kApplyBlocks : kApplyBlocks;
+    const bool sparse = b.capacity < shard_elems / kApplySparseDiv, dense = b.capacity >= shard_elems / kApplyDenseDiv;
+    const int most = sparse || dense ? kApplyBlocks : 4 * kApplyBlocks;
     const int blocks = want < 1 ? 1 : (want > most ? most : (int)want);
-    hipLaunchKernelGGL(b.capacity < shard_elems / kApplySparseDiv ? apply_kernel<1> : apply_kernel<0>, dim3(blocks),
+    hipLaunchKernelGGL(sparse ? apply_kernel<1> : apply_kernel<0>, dim3(blocks),
                        dim3(kApplyThreads), 0, st, b, n_tensors, local_numel, dst_ptrs, arith, shard_elems / kApplyDenseDiv);
     return (int)hipGetLastError();
 }

@@ -20,7 +20,7 @@ SIZES = [1, 2, 7, 8, 9, 31, 32, 33, 3, 5, 300001, 64, 1, 40000, 65537, 15, 1, 1,
 @pytest.mark.parametrize("many", [False, True])
 def test_packed_shard(p, first, payload, many):
     print("case: packed apply p=%g first=%d %s many=%s" % (p, first, payload, many), flush=True)
-    sizes = SIZES + [3] * 300 + [100003] if many else SIZES      # more than 256 segments: the other search
+    sizes = SIZES + [3] * 600 + [100003] if many else SIZES      # more than 512 segments: the other search
     rng = np.random.default_rng(int(p * 1000) + first)
     plan = R.shard_plan([T(1, n, R.REPLICATED) for n in sizes], 1)
     plan.upload()
