@@ -1577,6 +1577,8 @@ __global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uin
         for (int w = 0; w < kWaves; ++w) total += s_cnt[w];
         counts[blockIdx.x] = total;
     }
+    // the header's words are this call's, whatever the workspace held: no wait gave up, no ticket was counted ahead
+    if (blockIdx.x == 0 && threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
 }
 
 template <int NEW_F32, int REFRESH, int ARITH>

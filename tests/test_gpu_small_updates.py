@@ -111,3 +111,14 @@ def test_two_launches_in_a_graph():
         want = oracle.encode_model([dict(t, old=bits(o), new=bits(n)) for t, o, n in zip(c.tensors, c.old, c.new)], c.tp)
         for d in range(c.tp):
             assert_buckets_equal(c.host_bucket(d), want[d], "replay %d shard %d" % (rep, d))
+
+
+def test_diagnostic_words_are_this_launch_s():
+    """Words 2 and 3 of the workspace count what happened in the launch (here: no tickets, nothing to count),
+    not what the workspace held before."""
+    import torch
+    print("case: diagnostic words", flush=True)
+    c = bern_case([T(64, 512, R.SPLIT_ROWS), T(1, 3000, R.REPLICATED)], 2, 0.1, seed=3)
+    c.ws.fill_(-1)
+    c.encode()
+    assert c.ws.view(torch.int32)[2:4].tolist() == [0, 0]
