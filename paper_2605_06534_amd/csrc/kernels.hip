@@ -1838,9 +1838,82 @@ __device__ __forceinline__ void apply_direct(const BucketDev &b, int32_t n_tenso
     }
 }
 
+// Line of an entry that may go through the line path (depends on the entry alone): its 16-byte part lies inside
+// the tensor.  Lines are lines of the address: the tensor starts `mis` elements behind the start of one.  (An
+// address that is not a multiple of 2 has no elements in lines: no entry has one.)
+constexpr uint32_t kNoLine = 0xFFFFFFFFu;
+struct Lines {
+    uint32_t mis, numel, lim;                           // lim: elements from the first line's start to the tensor's end
+    __device__ __forceinline__ Lines(const uint16_t *dst, int32_t tensor_numel) {
+        const uint64_t base = reinterpret_cast<uint64_t>(dst);
+        mis = (uint32_t)(base >> 1) & (uint32_t)(kLineElems - 1);
+        numel = (base & 1u) ? 0u : (uint32_t)tensor_numel;
+        lim = numel + mis;                              // below 2^31 + 32
+    }
+    __device__ __forceinline__ uint32_t of(uint32_t i) const {
+        const uint32_t p = i + mis;
+        return (i < numel && (p & ~7u) >= mis && (p | 7u) < lim) ? p >> kLineShift : kNoLine;
+    }
+};
+
+// What a chunk holds in a lane: its entry, and (lanes below kLineElems) the entry 64 further on, the next chunk's.
+struct ChunkEntry {
+    uint32_t idx, val, idx2, val2, prev_idx;            // prev_idx: index of the entry before the chunk
+    bool add, add2, look;                               // look: the entry of the next chunk exists
+};
+
+// A chunk that holds entries of several segments (s: the first one's): every lane finds its own segment, and the
+// entries the chunk owns go by direct stores.  The ends of the next 64 segments are read by one lane each and
+// searched by moves between lanes; only behind those a lane searches the table.  (Segment after segment, with a
+// round of dependent loads for each, an apply into 2000 tensors of 40 elements at 5 % took 32.5 us; this way 3.9.)
+__device__ __forceinline__ void apply_mixed(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
+                                            void *const *dst_ptrs, const Segment &s, const ChunkEntry &c, int64_t wbase,
+                                            int n, int lane) {
+    const int32_t at = s.t + 1 + lane;
+    const int64_t away = (at < n_tensors ? b.seg_off[at] : INT64_MAX) - wbase;
+    const int32_t end = away < 64 ? (int32_t)away : 64;
+    int32_t k = 0;                                      // ends at or before this lane's entry
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1)
+        if (__shfl(end, k + step - 1, 64) <= lane) k += step;
+    int32_t t = s.t + k;
+    if (k == 63 && t + 1 < n_tensors && b.seg_off[t + 1] <= wbase + lane) {      // (rare: 64 segments or more)
+        int32_t hi = n_tensors;
+        while (hi - t > 1) {
+            const int32_t mid = (t + hi) >> 1;
+            if (b.seg_off[mid] <= wbase + lane) t = mid; else hi = mid;
+        }
+    }
+    uint16_t *const dst = static_cast<uint16_t *>(dst_ptrs[t]);
+    const int32_t numel = local_numel[t];
+    const Lines lines(dst, numel);
+    const uint32_t line = lane < n ? lines.of(c.idx) : kNoLine;
+    // leading lanes that continue the previous chunk's last line were applied with that chunk
+    uint32_t before = (uint32_t)__shfl_up((int)line, 1, 64);
+    int32_t t_before = __shfl_up(t, 1, 64);
+    if (lane == 0) {
+        before = wbase > s.start ? lines.of(c.prev_idx) : kNoLine;
+        t_before = t;
+    }
+    const u64 same_m = __ballot(line != kNoLine && line == before && t == t_before);
+    const u64 lead = same_m & ~(same_m + 1);
+    auto store_one = [](uint16_t *d, uint32_t i, uint32_t v, bool plus) {
+        __builtin_nontemporal_store(apply_value(plus ? d[i] : 0u, v, plus), d + i);
+    };
+    if (lane < n && !((lead >> lane) & 1u) && c.idx < (uint32_t)numel) store_one(dst, c.idx, c.val, c.add);
+    // entries of the next chunk that still lie in this chunk's last line
+    const uint32_t line63 = (uint32_t)__builtin_amdgcn_readlane((int)line, 63);
+    if (line63 != kNoLine) {
+        const Segment last = load_segment(b, local_numel, dst_ptrs, __builtin_amdgcn_readlane(t, 63));
+        const Lines last_lines(last.dst, last.numel);
+        if (c.look && wbase + 64 + lane < last.end && last_lines.of(c.idx2) == line63)
+            store_one(last.dst, c.idx2, c.val2, c.add2);
+    }
+}
+
 // One chunk of 64 entries.  What it needs comes in three rounds of loads: the entries, the entries behind
-// them and the segment ends; the segment's tensor, by scalar loads; the lines.  All that concerns a segment
-// is uniform: a chunk that holds entries of several takes them one segment after the other.
+// them and the segment ends; the segment's tensor, by scalar loads; the lines.  All that concerns the segment
+// is uniform; a chunk with entries of several goes another way (apply_mixed).
 //   LONE    also lines that take one entry each go by direct stores
 // A chunk's owned entries go by direct 2-byte stores where they are crowded, three or more to a line (from
 // 8 % on the line path's work per entry binds it: 7B-style workload, one shard, 1.32 against 1.29 ms at 8 %, 2.21
@@ -1852,120 +1925,111 @@ __device__ __forceinline__ void apply_chunk(const BucketDev &b, int32_t n_tensor
     const int32_t idx_mask = arith ? 0x7FFFFFFF : -1;
     const int64_t e = wbase + lane, e2 = e + 64;
     const int n = total - wbase < 64 ? (int)(total - wbase) : 64;      // entries of the chunk
-    const bool look = lane < kLineElems && e2 < total;
+    ChunkEntry c;
+    c.look = lane < kLineElems && e2 < total;
     int32_t idx_raw = 0, idx2_raw = 0;
-    uint32_t val = 0, val2 = 0;
+    c.val = c.val2 = 0;
     if (lane < n) {
         idx_raw = b.idx[e];
-        val = b.val[e];
+        c.val = b.val[e];
     }
-    if (look) {
+    if (c.look) {
         idx2_raw = b.idx[e2];
-        val2 = b.val[e2];
+        c.val2 = b.val[e2];
     }
-    const uint32_t prev_idx = wbase > 0 ? cload32(b.idx + wbase - 1) & (uint32_t)idx_mask : 0u;
-    Segment s = load_segment(b, local_numel, dst_ptrs,
-                             __builtin_amdgcn_readfirstlane(wave_find_segment(b.seg_off, n_tensors, wbase, lane)));
-    const uint32_t idx = (uint32_t)(idx_raw & idx_mask), idx2 = (uint32_t)(idx2_raw & idx_mask);
-    const bool add = arith && idx_raw >= 0, add2 = arith && idx2_raw >= 0;
+    c.prev_idx = cload32(b.idx + (wbase > 0 ? wbase - 1 : 0)) & (uint32_t)idx_mask;      // (unused in the first chunk)
+    const Segment s = load_segment(b, local_numel, dst_ptrs,
+                                   __builtin_amdgcn_readfirstlane(wave_find_segment(b.seg_off, n_tensors, wbase, lane)));
+    c.idx = (uint32_t)(idx_raw & idx_mask);
+    c.idx2 = (uint32_t)(idx2_raw & idx_mask);
+    c.add = arith && idx_raw >= 0;
+    c.add2 = arith && idx2_raw >= 0;
+    asm volatile("" :: "s"(s.dst), "s"(s.numel));       // the segment's loads go out together, in front of the branch
+    if (s.end - wbase < n) {
+        apply_mixed(b, n_tensors, local_numel, dst_ptrs, s, c, wbase, n, lane);
+        return;
+    }
     const int part = lane % kLineParts;
     uint16_t *lines16 = reinterpret_cast<uint16_t *>(s_line);
-
-    for (int lo = 0; lo < n;) {                         // the segments that the chunk's entries belong to
-        next_segment(b, local_numel, dst_ptrs, wbase + lo, s);
-        const int hi = s.end - wbase < n ? (int)(s.end - wbase) : n;
-        // lines are lines of the address: the tensor starts `mis` elements behind the start of one.  (An
-        // address that is not a multiple of 2 has no elements in lines: nothing is ok.)
-        const uint64_t base = reinterpret_cast<uint64_t>(s.dst);
-        const uint64_t line0 = base & ~(uint64_t)(ROSE_APPLY_LINE - 1);
-        const uint32_t mis = (uint32_t)(base >> 1) & (uint32_t)(kLineElems - 1);
-        const uint32_t numel = (base & 1u) ? 0u : (uint32_t)s.numel, lim = numel + mis;     // below 2^31 + 32
-        constexpr uint32_t kNoLine = 0xFFFFFFFFu;
-        // line of an entry that may go through the line path (depends on the entry alone): its 16-byte part
-        // lies inside the tensor
-        auto line_of = [&](uint32_t i) -> uint32_t {
-            const uint32_t p = i + mis;
-            return (i < numel && (p & ~7u) >= mis && (p | 7u) < lim) ? p >> kLineShift : kNoLine;
-        };
-        const bool in = lane >= lo && lane < hi;
-        const uint32_t line = in ? line_of(idx) : kNoLine;
-        // same line as the entry before?  lane 0 looks at the last entry of the previous chunk
-        const uint32_t before0 = lo == 0 && wbase > s.start ? line_of(prev_idx) : kNoLine;
-        const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)before0, (int)line, 0x138, 0xf, 0xf, false);  // wave_shr:1
-        const u64 ok_m = __ballot(line != kNoLine);
-        const u64 same_m = __ballot(line == before) & ok_m;
-        // leading lanes that continue the previous chunk's last line were applied with that chunk
-        const u64 owned_m = ok_m & ~(same_m & ~(same_m + 1));
-        const bool owned = (owned_m >> lane) & 1u;
-        const bool loose = in && line == kNoLine && idx < (uint32_t)s.numel;   // an index outside the tensor is dropped
-        // entries of the next chunk that still lie in this chunk's last line
-        const uint32_t line63 = (uint32_t)__builtin_amdgcn_readlane((int)line, 63);
-        const bool ext = (owned_m >> 63) && look && e2 < s.end && line_of(idx2) == line63;
-        // distinct lines of the owned entries
-        const u64 heads = owned_m & ~(same_m & (owned_m << 1));
-        const int n_lines = __popcll(heads);
-        uint16_t *const dst = s.dst;
-        auto store_one = [&](uint32_t i, uint32_t v, bool plus) {
-            __builtin_nontemporal_store(apply_value(plus ? dst[i] : 0u, v, plus), dst + i);
-        };
-        const int n_owned = __popcll(owned_m);
-        // (one comparison, both factors are negative or neither is: a second branch costs the kernel 20
-        // registers and with them its occupancy)
-        const int crowded = n_owned - kDirectPerLine * n_lines, not_lone = LONE ? kLoneDen * n_owned - (kLoneDen + 1) * n_lines : 1;
-        if (crowded * not_lone >= 0) {
-            if (owned || loose) store_one(idx, val, add);
-            if (ext) store_one(idx2, val2, add2);
-        } else {
-            const bool head = (heads >> lane) & 1u;
-            const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u)) - (head ? 0 : 1);
-            if (head) s_no[slot] = line;
-            lds_wave_fence();
-            // Load the lines: kLineParts lanes per line, kLinesPerRound lines per round, every round's load
-            // before the first is put into LDS.  Nothing here is under a condition, so that the compiler
-            // need not wait between the rounds: a lane without a line, or whose part lies outside the
-            // tensor, loads the part of the first owned entry, into a place that nothing reads.
-            const uint32_t some = ((uint32_t)__builtin_amdgcn_readlane((int)idx, __ffsll((long long)heads) - 1) + mis) >> 3;
-            uint4 lv[kLineRounds];
-            uint32_t at[kLineRounds];                   // 16-byte part, counted from the first line
-            bool on[kLineRounds];
+    const Lines lines(s.dst, s.numel);
+    const uint64_t line0 = reinterpret_cast<uint64_t>(s.dst) & ~(uint64_t)(ROSE_APPLY_LINE - 1);
+    const bool in = lane < n;
+    const uint32_t line = in ? lines.of(c.idx) : kNoLine;
+    // same line as the entry before?  lane 0 looks at the last entry of the previous chunk
+    const uint32_t before0 = wbase > s.start ? lines.of(c.prev_idx) : kNoLine;
+    const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)before0, (int)line, 0x138, 0xf, 0xf, false);  // wave_shr:1
+    const u64 ok_m = __ballot(line != kNoLine);
+    const u64 same_m = __ballot(line == before) & ok_m;
+    // leading lanes that continue the previous chunk's last line were applied with that chunk
+    const u64 owned_m = ok_m & ~(same_m & ~(same_m + 1));
+    const bool owned = (owned_m >> lane) & 1u;
+    const bool loose = in && line == kNoLine && c.idx < (uint32_t)s.numel;   // an index outside the tensor is dropped
+    // entries of the next chunk that still lie in this chunk's last line
+    const uint32_t line63 = (uint32_t)__builtin_amdgcn_readlane((int)line, 63);
+    const bool ext = (owned_m >> 63) && c.look && e2 < s.end && lines.of(c.idx2) == line63;
+    // distinct lines of the owned entries
+    const u64 heads = owned_m & ~(same_m & (owned_m << 1));
+    const int n_lines = __popcll(heads);
+    uint16_t *const dst = s.dst;
+    auto store_one = [&](uint32_t i, uint32_t v, bool plus) {
+        __builtin_nontemporal_store(apply_value(plus ? dst[i] : 0u, v, plus), dst + i);
+    };
+    const int n_owned = __popcll(owned_m);
+    // (one comparison, both factors are negative or neither is: a second branch costs the kernel 20
+    // registers and with them its occupancy)
+    const int crowded = n_owned - kDirectPerLine * n_lines, not_lone = LONE ? kLoneDen * n_owned - (kLoneDen + 1) * n_lines : 1;
+    if (crowded * not_lone >= 0) {
+        if (owned || loose) store_one(c.idx, c.val, c.add);
+        if (ext) store_one(c.idx2, c.val2, c.add2);
+    } else {
+        const bool head = (heads >> lane) & 1u;
+        const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u)) - (head ? 0 : 1);
+        if (head) s_no[slot] = line;
+        lds_wave_fence();
+        // Load the lines: kLineParts lanes per line, kLinesPerRound lines per round, every round's load
+        // before the first is put into LDS.  Nothing here is under a condition, so that the compiler
+        // need not wait between the rounds: a lane without a line, or whose part lies outside the
+        // tensor, loads the part of the first owned entry, into a place that nothing reads.
+        const uint32_t some = ((uint32_t)__builtin_amdgcn_readlane((int)c.idx, __ffsll((long long)heads) - 1) + lines.mis) >> 3;
+        uint4 lv[kLineRounds];
+        uint32_t at[kLineRounds];                   // 16-byte part, counted from the first line
+        bool on[kLineRounds];
 #pragma unroll
-            for (int r = 0; r < kLineRounds; ++r) at[r] = s_no[r * kLinesPerRound + lane / kLineParts];
+        for (int r = 0; r < kLineRounds; ++r) at[r] = s_no[r * kLinesPerRound + lane / kLineParts];
 #pragma unroll
-            for (int r = 0; r < kLineRounds; ++r) {
-                at[r] = at[r] * kLineParts + (uint32_t)part;
-                on[r] = (r * kLinesPerRound + lane / kLineParts < n_lines) & (at[r] * 8u >= mis) & (at[r] * 8u + 8u <= lim);
-                at[r] = on[r] ? at[r] : some;
-                lv[r] = gload16_stream(reinterpret_cast<const void *>(line0 + (uint64_t)at[r] * 16u));
-            }
-#pragma unroll
-            for (int r = 0; r < kLineRounds; ++r) s_line[r * kLinesPerRound + lane / kLineParts][part] = lv[r];
-            lds_wave_fence();
-
-            // patch
-            if (owned) {
-                uint16_t *q = lines16 + slot * kLineElems + ((idx + mis) & (uint32_t)(kLineElems - 1));
-                *q = apply_value(*q, val, add);
-            }
-            if (ext) {
-                uint16_t *q = lines16 + (n_lines - 1) * kLineElems + ((idx2 + mis) & (uint32_t)(kLineElems - 1));
-                *q = apply_value(*q, val2, add2);
-            }
-            lds_wave_fence();
-
-            // store the lines back whole
-#pragma unroll
-            for (int r = 0; r < kLineRounds; ++r) {
-                if (on[r]) {
-                    const uint4 v4 = s_line[r * kLinesPerRound + lane / kLineParts][part];
-                    u32x4 w = {v4.x, v4.y, v4.z, v4.w};
-                    __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(line0 + (uint64_t)at[r] * 16u));
-                }
-            }
-            if (loose) store_one(idx, val, add);
-            lds_wave_fence();                           // the LDS slots are reused
+        for (int r = 0; r < kLineRounds; ++r) {
+            at[r] = at[r] * kLineParts + (uint32_t)part;
+            on[r] = (r * kLinesPerRound + lane / kLineParts < n_lines) & (at[r] * 8u >= lines.mis) & (at[r] * 8u + 8u <= lines.lim);
+            at[r] = on[r] ? at[r] : some;
+            lv[r] = gload16_stream(reinterpret_cast<const void *>(line0 + (uint64_t)at[r] * 16u));
         }
-        lo = hi;
+#pragma unroll
+        for (int r = 0; r < kLineRounds; ++r) s_line[r * kLinesPerRound + lane / kLineParts][part] = lv[r];
+        lds_wave_fence();
+
+        // patch
+        if (owned) {
+            uint16_t *q = lines16 + slot * kLineElems + ((c.idx + lines.mis) & (uint32_t)(kLineElems - 1));
+            *q = apply_value(*q, c.val, c.add);
+        }
+        if (ext) {
+            uint16_t *q = lines16 + (n_lines - 1) * kLineElems + ((c.idx2 + lines.mis) & (uint32_t)(kLineElems - 1));
+            *q = apply_value(*q, c.val2, c.add2);
+        }
+        lds_wave_fence();
+
+        // store the lines back whole
+#pragma unroll
+        for (int r = 0; r < kLineRounds; ++r) {
+            if (on[r]) {
+                const uint4 v4 = s_line[r * kLinesPerRound + lane / kLineParts][part];
+                u32x4 w = {v4.x, v4.y, v4.z, v4.w};
+                __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(line0 + (uint64_t)at[r] * 16u));
+            }
+        }
+        if (loose) store_one(c.idx, c.val, c.add);
+        lds_wave_fence();                           // the LDS slots are reused
     }
 }
 
