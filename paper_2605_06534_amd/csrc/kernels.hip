@@ -1710,21 +1710,23 @@ __global__ __launch_bounds__(256) void refresh_replicated_kernel(const int32_t *
 // the next (1.50 against 1.38 ms at 8 %), and the kernel keeps to 64 registers (a version that spilled a few
 // took 1.45 ms at 5 % instead of 1.17).
 // ---------------------------------------------------------------------------------------------
-// Workgroups of 8 waves (of 4: the same within 3 %).  How a launch is laid out is chosen by what the bucket can
-// hold against the elements of the shard; how its chunks are written, by what they hold.
-//   below 1/28   apply_kernel<1>, 4 waves per SIMD: where the touched lines lie apart the memory does better with
+// How a launch is laid out is chosen by what the bucket can hold, by itself and against the elements of the shard;
+// how its chunks are written, by what they hold.
+//   Workgroups of 8 waves, and of 4 up to 8192 chunks, which do not fill the device: 328 workgroups of 8 leave some
+//   CUs with twice the work of the others (4096 x 4096, one shard, 1 %: 8.1 us with 8, 6.9 with 4; 0.5 %: 5.5 and 4.6).
+//   below 1/24   apply_kernel<1>, 4 waves per SIMD: where the touched lines lie apart the memory does better with
 //                fewer of them in flight (7B-style workload, one shard, against 8 waves: 0.79 and 0.84 ms at 2 %,
-//                0.67 and 0.71 at 1.5 %, 0.55 and 0.56 at 1 %; from 3 % on it loses)
-//   up to 1/7    apply_kernel<0>, 8 waves per SIMD, a wave per chunk while the grid allows it (at 5 %: 1.17 ms,
-//                1.21 with a quarter of the workgroups)
-//   above        8 waves per SIMD
-// Only between 1/28 and 1/7 more than kApplyBlocks workgroups are launched: the waves that find no chunk cost (a
-// bucket with room for every element: 80 us for four times as many; a 32B-style shard set whose buckets hold
-// twice what came: 10.2 instead of 9.5 ms for its eight applies).
+//                0.67 and 0.71 at 1.5 %, 0.55 and 0.56 at 1 %; buckets of a 67 M shard with room for 3.75 %: 36.3 and
+//                38.2 us; with room for 4.4 % it loses 5 %).  Not up to 8192 chunks: fewer waves are in flight anyway,
+//                and lone entries do better by lines (67 M elements, 0.1 %: 4.2 us, 5.3 with it).
+//   up to 1/3    apply_kernel<0>, 8 waves per SIMD, and twice kApplyBlocks workgroups: a wave that takes a second
+//                chunk waits for the stores of its first, but a wave that finds none costs too (one shard with 1x /
+//                2x / 4x: 1.21 / 1.16 / 1.16 ms at 5 %, 1.62 / 1.53 / 1.40 at 12 %; at 0.2 % with room for 10 %:
+//                178 / 203 / 259 us)
+//   above        kApplyBlocks workgroups
 // A bucket that turns out to hold 1/7 of the shard goes by direct stores throughout (apply_direct).
-constexpr int kApplyThreads = 512;
-constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 28, kApplyDenseDiv = 7;
-constexpr int kApplyWaves = kApplyThreads / 64;
+constexpr int kApplyWaves = 8, kApplySmallWaves = 4, kApplySmallChunks = 8192;
+constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 24, kApplyDenseDiv = 7, kApplyRoomyDiv = 3;
 #ifndef ROSE_APPLY_LINE
 #define ROSE_APPLY_LINE 64                      // bytes moved around an entry: 64 or 32 (32 halves the bytes at low
                                                 // density and is slower all the same: 7B workload 3.61 instead of
@@ -2033,15 +2035,15 @@ __device__ __forceinline__ void apply_chunk(const BucketDev &b, int32_t n_tensor
     }
 }
 
-template <int SPARSE>
+template <int SPARSE, int WAVES>
 __device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel,
                                            void *const *dst_ptrs, int arith, int64_t dense_from) {
-    __shared__ uint4 s_line[kApplyWaves][64][kLineParts];   // wave, line slot, 16-byte part
-    __shared__ uint32_t s_no[kApplyWaves][64];              // line numbers
+    __shared__ uint4 s_line[WAVES][64][kLineParts];         // wave, line slot, 16-byte part
+    __shared__ uint32_t s_no[WAVES][64];                    // line numbers
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t total = b.seg_off[n_tensors];
     if (total > b.capacity) total = b.capacity;
-    const int64_t first = (int64_t)blockIdx.x * kApplyWaves + wave, n_waves = (int64_t)gridDim.x * kApplyWaves;
+    const int64_t first = (int64_t)blockIdx.x * WAVES + wave, n_waves = (int64_t)gridDim.x * WAVES;
     if (!SPARSE && total >= dense_from) {
         for (int64_t wbase = first * kDirectChunks * 64; wbase < total; wbase += n_waves * kDirectChunks * 64)
             apply_direct(b, n_tensors, local_numel, dst_ptrs, arith, total, wbase, lane);
@@ -2051,11 +2053,11 @@ __device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors
     }
 }
 
-template <int SPARSE>
-__global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(SPARSE ? 4 : 8, SPARSE ? 4 : 8))) void apply_kernel(BucketDev b, int32_t n_tensors,
-                                                              const int32_t *local_numel, void *const *dst_ptrs, int arith,
-                                                              int64_t dense_from) {
-    apply_body<SPARSE>(b, n_tensors, local_numel, dst_ptrs, arith, dense_from);
+template <int SPARSE, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(SPARSE ? 4 : 8, SPARSE ? 4 : 8)))
+void apply_kernel(BucketDev b, int32_t n_tensors, const int32_t *local_numel, void *const *dst_ptrs, int arith,
+                  int64_t dense_from) {
+    apply_body<SPARSE, WAVES>(b, n_tensors, local_numel, dst_ptrs, arith, dense_from);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2220,10 +2222,11 @@ __global__ __launch_bounds__(256) void object_validate_kernel(const char *obj, s
     if (bad) *verdict = ticket;
 }
 
-__global__ __launch_bounds__(kApplyThreads) void apply_object_kernel(const char *obj, size_t object_bytes, int32_t n_tensors,
-                                                                     int32_t n_buckets, int32_t tp,
-                                                                     const int32_t *local_numel, void *const *dst_ptrs,
-                                                                     const u64 *verdict, u64 ticket) {
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void apply_object_kernel(const char *obj, size_t object_bytes, int32_t n_tensors,
+                                                                  int32_t n_buckets, int32_t tp,
+                                                                  const int32_t *local_numel, void *const *dst_ptrs,
+                                                                  const u64 *verdict, u64 ticket) {
     uint32_t h[9];
     for (int i = 0; i < 9; ++i) h[i] = reinterpret_cast<const uint32_t *>(obj)[i];
     int64_t n;
@@ -2232,7 +2235,7 @@ __global__ __launch_bounds__(kApplyThreads) void apply_object_kernel(const char 
     if (*verdict == ticket) return;                                    // the validation pass found it out of order
     const BucketDev b = object_arrays(obj, n_tensors, n);
     if (b.seg_off[0] != 0 || b.seg_off[n_tensors] != n) return;
-    apply_body<0>(b, n_tensors, local_numel + (size_t)(h[2] / (uint32_t)tp) * n_tensors, dst_ptrs, (int)h[8], INT64_MAX);
+    apply_body<0, WAVES>(b, n_tensors, local_numel + (size_t)(h[2] / (uint32_t)tp) * n_tensors, dst_ptrs, (int)h[8], INT64_MAX);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2590,15 +2593,20 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
     return (int)hipGetLastError();
 }
 
+typedef void (*ApplyKernel)(BucketDev, int32_t, const int32_t *, void *const *, int, int64_t);
 int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel, void *const *dst_ptrs,
                  int arith, int64_t shard_elems, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int64_t want = (b.capacity + kApplyThreads - 1) / kApplyThreads;
-    const bool sparse = b.capacity < shard_elems / kApplySparseDiv, dense = b.capacity >= shard_elems / kApplyDenseDiv;
-    const int most = sparse || dense ? kApplyBlocks : 4 * kApplyBlocks;
+    const bool small = b.capacity <= (int64_t)kApplySmallChunks * 64;
+    const bool sparse = !small && b.capacity < shard_elems / kApplySparseDiv;
+    const ApplyKernel kernel = small ? apply_kernel<0, kApplySmallWaves>
+                                     : sparse ? apply_kernel<1, kApplyWaves> : apply_kernel<0, kApplyWaves>;
+    const int per_wg = (small ? kApplySmallWaves : kApplyWaves) * 64;
+    const int64_t want = (b.capacity + per_wg - 1) / per_wg;
+    const int most = sparse || b.capacity >= shard_elems / kApplyRoomyDiv ? kApplyBlocks : 2 * kApplyBlocks;
     const int blocks = want < 1 ? 1 : (want > most ? most : (int)want);
-    hipLaunchKernelGGL(sparse ? apply_kernel<1> : apply_kernel<0>, dim3(blocks),
-                       dim3(kApplyThreads), 0, st, b, n_tensors, local_numel, dst_ptrs, arith, shard_elems / kApplyDenseDiv);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(per_wg), 0, st, b, n_tensors, local_numel, dst_ptrs, arith,
+                       shard_elems / kApplyDenseDiv);
     return (int)hipGetLastError();
 }
 
@@ -2615,14 +2623,17 @@ int launch_apply_object(const void *object, size_t object_bytes, int32_t n_tenso
                         const int32_t *local_numel, void *const *dst_ptrs, unsigned long long *verdict,
                         unsigned long long ticket, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int64_t chunks = ((int64_t)(object_bytes / 6) + kApplyThreads - 1) / kApplyThreads;
-    int blocks = chunks < 1 ? 1 : (chunks > kApplyBlocks ? kApplyBlocks : (int)chunks);
+    const bool small = object_bytes / 6 <= (size_t)kApplySmallChunks * 64;
+    const int per_wg = (small ? kApplySmallWaves : kApplyWaves) * 64;
+    const int64_t want = ((int64_t)(object_bytes / 6) + per_wg - 1) / per_wg;
+    const int blocks = want < 1 ? 1 : (want > kApplyBlocks ? kApplyBlocks : (int)want);
+    const auto apply = small ? apply_object_kernel<kApplySmallWaves> : apply_object_kernel<kApplyWaves>;
     const int64_t vwant = ((int64_t)(object_bytes / 6) + kPackTile - 1) / kPackTile;
     const int vblocks = vwant < 1 ? 1 : (vwant > 4096 ? 4096 : (int)vwant);
     hipLaunchKernelGGL(object_clear_kernel, dim3(1), dim3(1), 0, st, verdict);
     hipLaunchKernelGGL(object_validate_kernel, dim3(vblocks), dim3(256), 0, st, static_cast<const char *>(object),
                        object_bytes, n_tensors, n_buckets, verdict, ticket);
-    hipLaunchKernelGGL(apply_object_kernel, dim3(blocks), dim3(kApplyThreads), 0, st, static_cast<const char *>(object),
+    hipLaunchKernelGGL(apply, dim3(blocks), dim3(per_wg), 0, st, static_cast<const char *>(object),
                        object_bytes, n_tensors, n_buckets, tp, local_numel, dst_ptrs, verdict, ticket);
     return (int)hipGetLastError();
 }
