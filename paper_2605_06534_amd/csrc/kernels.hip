@@ -632,7 +632,9 @@ __device__ __forceinline__ void load_tile_pair(const TileCtx &c, uint32_t t_off,
 #pragma unroll
     for (int j = 0; j < kIters; ++j) {
         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
-        if (!(c.vec & 1u) || k + kVec > (uint32_t)c.pc.len) {
+        if (k >= (uint32_t)c.pc.len) {                  // (at once: a tile of a small tensor holds hardly anything else)
+            o[j] = n[j] = make_uint4(0, 0, 0, 0);
+        } else if (!(c.vec & 1u) || k + kVec > (uint32_t)c.pc.len) {
             o[j] = load_vec_general<0>(c.old_base, c.pc, k);
             n[j] = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
         } else if (c.vec & 4u) {

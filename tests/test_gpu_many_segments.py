@@ -7,7 +7,11 @@ import pytest
 import torch
 
 import paper_2605_06534_amd as R
+from gpu_harness import full_parity
+from test_gpu_arith import check_arith
 from test_gpu_parity import T
+from test_gpu_refresh import check_refresh
+from test_gpu_unaligned import packed_case
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +66,16 @@ def test_many_segments(name, p, payload):
         R.object_apply(plan, obj, tab)
     torch.cuda.synchronize()
     assert np.array_equal(dst.cpu().numpy().view(np.uint16), want), "objects"
+
+
+@pytest.mark.parametrize("run", [1, 5, 8, 40, 700])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_many_small_tensors_encoded(run, fp32):
+    """Tiles of which a few vectors hold anything: contiguous tensors and column blocks, 0 to 700 elements."""
+    print("case: many small tensors run=%d fp32=%s" % (run, fp32), flush=True)
+    ts = []
+    for i in range(40):
+        ts += [T(1, run + i % 9, R.REPLICATED), T(1 + i % 3, 2 * run, R.SPLIT_COLS), T(0, 16, R.SPLIT_ROWS), T(2, 9 * run, R.SPLIT_ROWS)]
+    full_parity(packed_case(ts, 2, 0.4, run, 1, 3, fp32))
+    check_arith(packed_case(ts, 2, 0.4, run + 1, 1, 3, fp32))
+    check_refresh(packed_case(ts, 2, 0.4, run + 2, 1, 3, fp32))
