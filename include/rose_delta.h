@@ -190,7 +190,7 @@ rose_status rose_plan_set_worker_cap(rose_plan *plan, int32_t workers);
  * about 4 %.  (The neighbours order holds entries back too, for longer windows.)  ROSE_TILE_ORDER_AUTO_PICK (the default): the library picks, from the density of the
  * plan's previous launch as far as rose_bucket_check has read it back (until then from the share of
  * the shards that the buckets passed in could hold at most).
- * (With AUTO_PICK and no worker cap, an update that reads at most 128 MiB goes without tickets, in no
+ * (With AUTO_PICK and no worker cap, an update that reads at most 80 MiB goes without tickets, in no
  * order at all.)
  * May be called at any time from any thread; a launch uses the value it finds.
  */

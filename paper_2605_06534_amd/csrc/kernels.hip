@@ -1590,7 +1590,7 @@ __global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, cons
     const int32_t chain_begin = a.chain_first[c.pc.shard], chain_end = a.chain_first[c.pc.shard + 1];
     uint4 o[kIters], n[kIters];
     load_tile_pair<NEW_F32>(c, t_off, o, n);
-    // entries of the chain's earlier tiles (below 2^31 together: a destination's local index is 31 bits)
+    // entries of the chain's earlier tiles (as many as all tiles have elements at most, see kTwoLaunchBytes)
     uint32_t before = 0;
     for (int32_t t = chain_begin + (int32_t)threadIdx.x; t < tile; t += kThreads) before += counts[t];
     before = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(before), 63);
@@ -2541,13 +2541,19 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
 }
 
 // Updates that go in two launches (count_tiles_kernel, emit_tiles_kernel) instead of tickets: those that read
-// at most this much.  One matrix of 4096 columns, p = 1 %, us per call back to back, two launches / tickets:
-//   32 MiB 15.6 / 31.7   64 MiB 23.5 / 39.6   96 MiB 34.7 / 46.7   128 MiB 46.0 / 54.6   192 MiB 70.0 / 64.4
-// fp32 masters, p = 2 %: 96 MiB 37.7 / 43.9, 144 MiB 56.6 / 54.7, 192 MiB 76.6 / 64.5; with 8 shards, whose chains
-// are shorter, the lines cross at 192 MiB.  (Handing the second launch the tiles last read first: no gain.)
-#ifndef ROSE_TWO_LAUNCH_BYTES
-#define ROSE_TWO_LAUNCH_BYTES (128 << 20)
-#endif
+// at most this much.  The line lies where they win whether the inputs are in the caches or have to come from
+// memory (256 MB written elsewhere before each call), at any density, payload, refresh or not.  One matrix of 4096
+// columns, us per call, two launches / tickets:
+//                               32 MiB        64 MiB        96 MiB        128 MiB
+//   bf16, 1 %, cached           12.2 / 33.7   22.6 / 40.0   34.1 / 47.9   45.6 / 52.5
+//   bf16, 1 %, from memory      17.1 / 32.3   27.9 / 40.5   39.9 / 48.0   51.3 / 52.7
+//   bf16, 30 %, from memory     24.7 / 37.0   41.6 / 47.9   58.4 / 55.7   75.3 / 70.4
+//   fp32, 5 %, from memory      20.9 / 29.9   33.6 / 40.5   43.9 / 45.0   56.7 / 51.1
+//   refresh, bf16, 5 %, memory  19.8 / 34.9   35.4 / 45.9   51.1 / 54.6
+//   refresh, fp32, 10 %, memory 23.0 / 33.6   39.4 / 45.4   52.6 / 50.5
+// At 88 MiB the first cases turn (bf16 30 % 54.4 / 54.1, eight shards of fp32 at 10 % 48.6 / 46.4).
+constexpr int64_t kTwoLaunchBytes = (int64_t)80 << 20;
+static_assert(kTwoLaunchBytes / 4 < (int64_t)1 << 31, "emit_tiles_kernel adds up entries in 32 bits");
 static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, hipStream_t st) {
     if (refresh && refresh->n > 0)
         hipLaunchKernelGGL(refresh_replicated_kernel, dim3(8, refresh->n > 1024 ? 1024 : refresh->n), dim3(256), 0, st,
@@ -2559,7 +2565,7 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
                   int worker_cap, int order, bool order_free, int32_t ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
-    if (order_free && worker_cap == 0 && (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4) <= ROSE_TWO_LAUNCH_BYTES) {
+    if (order_free && worker_cap == 0 && (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4) <= kTwoLaunchBytes) {
         uint32_t *counts = reinterpret_cast<uint32_t *>(a.tile_desc);
         const CountKernel count = new_is_f32 ? count_tiles_kernel<1> : count_tiles_kernel<0>;
         hipLaunchKernelGGL(count, dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);

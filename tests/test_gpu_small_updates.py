@@ -36,10 +36,16 @@ def test_packed(run, fp32):
         check_refresh(packed_case(ts, tp, p, run + 2, first_old, first_new, fp32))
 
 
-@pytest.mark.parametrize("tiles", [4096, 4097])
+@pytest.mark.parametrize("tiles", [2560, 2561, 4096, 4097])
 def test_both_sides_of_the_line(tiles):
     print("case: small tiles=%d" % tiles, flush=True)
     full_parity(bern_case([T(1, tiles * TILE, R.REPLICATED)], 1, 0.01, seed=tiles), check_dense=False)
+
+
+@pytest.mark.parametrize("tiles", [2560, 2561])
+def test_refresh_on_both_sides_of_the_line(tiles):
+    print("case: small refresh tiles=%d" % tiles, flush=True)
+    check_refresh(bern_case([T(tiles, TILE, R.SPLIT_ROWS)], 1, 0.02, seed=tiles))
 
 
 def test_overflow_is_reported_and_bounded():
