@@ -2072,7 +2072,8 @@ __host__ __device__ inline size_t object_size(int32_t n_tensors, int64_t n) {
     return object_idx_off(n_tensors) + up16(4 * (size_t)n) + up16(2 * (size_t)n);
 }
 
-constexpr int kPackTile = 4096;         // entries a workgroup moves at a time
+// LOADS: 128-bit loads of indices a lane has in flight (1024 entries of a workgroup each)
+template <int LOADS>
 __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, int32_t n_tensors, int64_t first,
                                                    int64_t n, int32_t payload, char *obj) {
     int64_t total = b.seg_off[n_tensors];
@@ -2108,26 +2109,50 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
     int32_t *idx = reinterpret_cast<int32_t *>(obj + a_off);
     uint16_t *val = reinterpret_cast<uint16_t *>(obj + b_off);
     // 128-bit accesses, read and written once: the object's arrays are aligned, the bucket's range starts at any
-    // entry.  A workgroup's loads are all in flight together.  (84 M entries in eight objects: 234 us with an
-    // entry per lane, 192 us this way.)
+    // entry.  A workgroup's loads are all in flight together.  (84 M entries in eight objects: 234 us with an entry
+    // per lane, 192 us this way.)
+    constexpr int kTileEntries = LOADS * 1024, kValLoads = LOADS > 1 ? LOADS / 2 : 1, kValLanes = LOADS > 1 ? 256 : 128;
     const int32_t *from_idx = b.idx + first;
     const uint16_t *from_val = b.val + first;
-    for (int64_t e0 = (int64_t)blockIdx.x * kPackTile; e0 < n; e0 += (int64_t)gridDim.x * kPackTile) {
-        if (e0 + kPackTile <= n) {
-            uint4 vi[4], vv[2];
+    for (int64_t e0 = (int64_t)blockIdx.x * kTileEntries; e0 < n; e0 += (int64_t)gridDim.x * kTileEntries) {
+        uint4 vi[LOADS], vv[kValLoads];
+        if (e0 + kTileEntries <= n) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) vi[j] = gload16_stream(from_idx + e0 + (j * 256 + threadIdx.x) * 4);
+            for (int j = 0; j < LOADS; ++j) vi[j] = gload16_stream(from_idx + e0 + (j * 256 + threadIdx.x) * 4);
+            if (threadIdx.x < kValLanes) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) vv[j] = gload16_stream(from_val + e0 + (j * 256 + threadIdx.x) * 8);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gstore16_stream(idx + e0 + (j * 256 + threadIdx.x) * 4, vi[j]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) gstore16_stream(val + e0 + (j * 256 + threadIdx.x) * 8, vv[j]);
-        } else {
-            for (int64_t e = e0 + threadIdx.x; e < n; e += 256) {
-                idx[e] = from_idx[e];
-                val[e] = from_val[e];
+                for (int j = 0; j < kValLoads; ++j) vv[j] = gload16_stream(from_val + e0 + (j * 256 + threadIdx.x) * 8);
             }
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j) gstore16_stream(idx + e0 + (j * 256 + threadIdx.x) * 4, vi[j]);
+            if (threadIdx.x < kValLanes) {
+#pragma unroll
+                for (int j = 0; j < kValLoads; ++j) gstore16_stream(val + e0 + (j * 256 + threadIdx.x) * 8, vv[j]);
+            }
+        } else {                                        // the last tile: whole vectors, then the few entries behind them
+            const int64_t left = n - e0, i_end = left & ~(int64_t)3, v_end = left & ~(int64_t)7;
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j) {
+                const int64_t e = (j * 256 + threadIdx.x) * 4;
+                if (e < i_end) vi[j] = gload16_stream(from_idx + e0 + e);
+            }
+#pragma unroll
+            for (int j = 0; j < kValLoads; ++j) {
+                const int64_t e = (j * 256 + threadIdx.x) * 8;
+                if (e < v_end) vv[j] = gload16_stream(from_val + e0 + e);
+            }
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j) {
+                const int64_t e = (j * 256 + threadIdx.x) * 4;
+                if (e < i_end) gstore16_stream(idx + e0 + e, vi[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < kValLoads; ++j) {
+                const int64_t e = (j * 256 + threadIdx.x) * 8;
+                if (e < v_end) gstore16_stream(val + e0 + e, vv[j]);
+            }
+            if (threadIdx.x < left - i_end) idx[e0 + i_end + threadIdx.x] = from_idx[e0 + i_end + threadIdx.x];
+            if (threadIdx.x < left - v_end) val[e0 + v_end + threadIdx.x] = from_val[e0 + v_end + threadIdx.x];
         }
     }
 }
@@ -2633,17 +2658,22 @@ int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_num
     return (int)hipGetLastError();
 }
 
+// Entries up to which objects are packed and checked by workgroups of 1024 entries, one load a lane: 2048 of them.
+// (Checked and applied, small objects: 0.9 us less than with 4096 entries a workgroup.  Packed, us, an entry per
+// lane / 4096 / 1024: 168 k entries 2.9 / 4.1 / 3.0, from memory 5.0 / 9.0 / 3.8; 840 k 3.7 / 4.0 / 3.9, from memory
+// 8.6 / 7.3 / 4.5.)
+constexpr int64_t kFewEntries = 1 << 21;
 int launch_pack(const BucketDev &b, int32_t shard, int32_t n_tensors, int64_t first, int64_t n, int32_t payload,
                 void *object, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int64_t want = (n + kPackTile - 1) / kPackTile;
-    int blocks = want < 1 ? 1 : (want > (1 << 20) ? 1 << 20 : (int)want);
-    hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, st, b, shard, n_tensors, first, n, payload, static_cast<char *>(object));
+    const bool few = n <= kFewEntries;
+    const int64_t tile = few ? 1024 : 4096, want = (n + tile - 1) / tile;
+    const int blocks = want < 1 ? 1 : (want > (1 << 20) ? 1 << 20 : (int)want);
+    const auto pack = few ? pack_kernel<1> : pack_kernel<4>;
+    hipLaunchKernelGGL(pack, dim3(blocks), dim3(256), 0, st, b, shard, n_tensors, first, n, payload, static_cast<char *>(object));
     return (int)hipGetLastError();
 }
 
-constexpr int kCheckFew = 1 << 21;      // entries up to which an object is checked with one load a lane: 2048 workgroups
-// (small objects, checked and applied: 0.9 us less than with four)
 int launch_apply_object(const void *object, size_t object_bytes, int32_t n_tensors, int32_t n_buckets, int32_t tp,
                         const int32_t *local_numel, void *const *dst_ptrs, unsigned long long *verdict,
                         unsigned long long ticket, void *stream) {
@@ -2654,7 +2684,7 @@ int launch_apply_object(const void *object, size_t object_bytes, int32_t n_tenso
     const int blocks = want < 1 ? 1 : (want > kApplyBlocks ? kApplyBlocks : (int)want);
     const auto apply = small ? apply_object_kernel<kApplySmallWaves> : apply_object_kernel<kApplyWaves>;
     // one load a lane until that fills the device, then four
-    const bool few = object_bytes / 6 <= (size_t)kCheckFew;
+    const bool few = object_bytes / 6 <= (size_t)kFewEntries;
     const int64_t vtile = few ? 1024 : 4096, vwant = ((int64_t)(object_bytes / 6) + vtile - 1) / vtile;
     const int vblocks = vwant < 1 ? 1 : (vwant > 4096 ? 4096 : (int)vwant);
     const auto check = few ? object_validate_kernel<1> : object_validate_kernel<4>;

@@ -74,3 +74,24 @@ def test_segment_table_out_of_order():
         assert applied(plan, obj, sizes) == 0, (t, v)
         table[t] = keep
     assert applied(plan, obj, sizes) == int(seg[-1])
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 7, 8, 9, 1023, 1024, 1025, 2047, 4097, (1 << 21) - 1, (1 << 21) + 1, (1 << 21) + 4099])
+@pytest.mark.parametrize("first", [0, 1, 6])
+def test_packed_ranges(n, first):
+    """The object's arrays are the bucket's range, at the edges of a lane's, a workgroup's and a launch's share."""
+    print("case: pack n=%d first=%d" % (n, first), flush=True)
+    total = n + first + 2
+    plan = R.shard_plan([T(1, total, R.REPLICATED)], 1)
+    b = R.Bucket(total, 1)
+    b.idx[:total] = torch.arange(total, dtype=torch.int32, device="cuda")
+    b.val[:total] = torch.randint(-30000, 30000, (total,), device="cuda", dtype=torch.int16)
+    b.seg_off.copy_(torch.tensor([0, total], dtype=torch.int64))
+    size = R.object_bytes(plan, n)
+    store = torch.full((size + 64,), 0xEE, dtype=torch.uint8, device="cuda")
+    R.bucket_pack(plan, 0, b, first, n, store[:size])
+    torch.cuda.synchronize()
+    a, v = 80, 80 + (4 * n + 15) // 16 * 16
+    assert torch.equal(store[a:a + 4 * n].view(torch.int32), b.idx[first:first + n])
+    assert torch.equal(store[v:v + 2 * n].view(torch.int16), b.val[first:first + n])
+    assert not store[a + 4 * n:v].any() and not store[v + 2 * n:size].any() and (store[size:] == 0xEE).all()
