@@ -182,7 +182,7 @@ rose_status rose_plan_set_worker_cap(rose_plan *plan, int32_t workers);
  * The order in which the encode kernel's workgroups take tiles (it changes speed only: the buckets
  * are the same bytes either way).  ROSE_TILE_ORDER_SPREAD: a workgroup takes tiles that lie 64 tiles
  * apart, so that the prefix sums across workgroups are ready soonest; best above about 7.5 % of changed
- * elements.  ROSE_TILE_ORDER_NEIGHBOURS: it takes three or four neighbouring tiles and writes their entries
+ * elements.  ROSE_TILE_ORDER_NEIGHBOURS: it takes three neighbouring tiles and writes their entries
  * as one run, which shares fewer 64-byte lines of the bucket with other workgroups; best between
  * about 4 and 7.5 %.  ROSE_TILE_ORDER_TIMED: four neighbouring tiles, and the entries are held in the
  * workgroup until a window of time that all workgroups share (they read one clock), so that the

@@ -2546,9 +2546,9 @@ int static_scratch(void **ptr, size_t *bytes) {
 // How a launch in this tile order walks its tiles: tiles per ticket, and how long of each period of
 // 41 us the bucket stores may go out (0: always).  ppm: changed elements per million, -1 unknown.
 //   timed       4 tiles, 10 us.  The entries of a period fit the ring up to about 4 %.
-//   neighbours  Denser: longer windows, so that less waits.  Up to 5 % still 4 tiles, with windows of
-//               15 us; above, and for arithmetic payloads (whose kernel is busier between its loads),
-//               3 tiles, whose prefixes are ready sooner and leave the ring room, and 20 us.
+//   neighbours  Denser: 3 tiles, whose prefixes are ready sooner and leave the ring room, and longer windows, so
+//               that less waits: up to 5 % 15 us; above, and for arithmetic payloads (whose kernel is busier
+//               between its loads), 20 us.
 // 7B-style workload, one process, same buffers, ms (always = neighbours with no windows, 3 tiles):
 //               4 %   4.5 %   5 %   5.5 %   6 %   7 %   8 %   10 %   30 %
 //   always      5.11  5.13    5.19  5.21    5.27  5.32  5.52  6.34   10.75
@@ -2557,6 +2557,9 @@ int static_scratch(void **ptr, size_t *bytes) {
 //   3 x 20 us   4.96  4.98    5.03  5.06    5.14  5.29  5.46  6.19   10.30
 // (fp32 masters, two 32B-style layers: 3.16 / 3.06 / 2.98 / 2.95 ms at 5 %, 3.17 / 3.24 / 3.19 / 3.04 at 6 %;
 // arithmetic payloads, eight 7B-style layers: 1.601 / 1.637 / 1.629 / 1.604 at 5 %, 1.571 / 1.584 / 1.576 / 1.561 at 4 %)
+// Four tiles would gain up to 3 % between 4 and 5 %, but the density is the last launch's, and where more comes they
+// lose far more: seen 4.5 %, 20 / 30 % came: 8.9 / 19.4 ms with 4 x 15 us, 7.8 / 10.0 with 3 x 15; fp32 masters, 15 %
+// came: 19.4 and 11.1 (always: 7.8 / 10.3 and 11.8).
 constexpr int32_t kNearBelowPpm = 50000;
 static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
     a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
@@ -2567,7 +2570,6 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
         a->window_open = ROSE_WRITE_OPEN_TIMED;
     } else if (order == ROSE_TILE_ORDER_NEIGHBOURS) {
         const bool near = !arith && ppm >= 0 && ppm < kNearBelowPpm;
-        a->batch = near ? kBatchTimed : kBatch;
         a->window_open = near ? ROSE_WRITE_OPEN_NEAR : ROSE_WRITE_OPEN_WIDE;
     }
 }

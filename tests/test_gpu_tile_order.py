@@ -8,6 +8,7 @@ import paper_2605_06534_amd as R
 from paper_2605_06534_amd import binding
 from workloads import models
 from gpu_harness import full_parity
+from test_gpu_arith import check_arith
 from test_gpu_parity import bern_case
 
 pytestmark = pytest.mark.gpu
@@ -27,3 +28,29 @@ def test_order_follows_the_density_read_back(p, want):
     assert c.plan.pick_tile_order(caps) == want
     full_parity(c)                                                             # the launch in the picked order
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("p,want", [(0.02, binding.TILE_ORDER_TIMED), (0.045, binding.TILE_ORDER_NEIGHBOURS),
+                                    (0.06, binding.TILE_ORDER_NEIGHBOURS), (0.12, binding.TILE_ORDER_SPREAD)])
+@pytest.mark.parametrize("arith", [False, True])
+def test_launches_in_the_order_picked(p, want, arith):
+    """An update too large for two launches: one launch before any density is known, one in the order picked from
+    the density read back, one after a wrong guess (a tenth of the density).  The workspace's ticket counter
+    (word 1024) shows that tickets were taken."""
+    print("case: launch in the picked order p=%g arith=%s" % (p, arith), flush=True)
+    ts = models.decoder(2, 1024, 16, 16, 64, 2816, 4096, fused=True)
+    c = bern_case(ts, 4, p, seed=9)
+    for what in ("unknown", "known", "guessed too low"):
+        c.ws.fill_(0)
+        for b in c.buckets:
+            b.idx.fill_(-7)
+        if what == "guessed too low":
+            few = R.Bucket(8, len(ts))
+            few.capacity = 1 << 40
+            few.seg_off[-1] = int(0.1 * p * c.plan.bucket_capacity(0))
+            R.bucket_check(c.plan, few)
+            assert c.plan.pick_tile_order([b.capacity for b in c.buckets]) == binding.TILE_ORDER_TIMED
+        elif what == "known":
+            assert c.plan.pick_tile_order([b.capacity for b in c.buckets]) == want
+        check_arith(c) if arith else full_parity(c, check_dense=False)
+        assert int(c.ws.view(torch.int32)[1024]) > 0, what
