@@ -1,9 +1,12 @@
 """Small updates go in two launches instead of tickets: same buckets, refresh and payloads, from empty
 tensors up to the largest update of that kind and the smallest one beyond.  Expected values come from
 the oracle, bit for bit."""
+import numpy as np
 import pytest
+import torch
 
 import paper_2605_06534_amd as R
+from oracle import oracle
 from gpu_harness import full_parity
 from test_gpu_arith import check_arith
 from test_gpu_parity import T, bern_case
@@ -51,20 +54,24 @@ def test_refresh_on_both_sides_of_the_line(tiles):
 def test_overflow_is_reported_and_bounded():
     print("case: small overflow", flush=True)
     c = bern_case([T(64, 512, R.SPLIT_ROWS), T(1, 3000, R.REPLICATED)], 2, 0.25, seed=2, capacity=1000)
-    for b in c.buckets:
-        b.idx.fill_(-7)
+    want = oracle.encode_model(c.records(), 2)
+    for b in c.buckets:                                 # room behind the capacity to watch
+        b.idx = torch.full((1064,), -7, dtype=torch.int32, device="cuda")
+        b.val = torch.full((1064,), -7, dtype=torch.int16, device="cuda")
     c.encode()
     for d, b in enumerate(c.buckets):
         with pytest.raises(R.RoseError) as e:
             R.bucket_check(c.plan, b)
-        assert e.value.required > 1000
-        assert (b.idx[1000:] == -7).all()
+        assert e.value.required == want[d]["seg_off"][-1] > 1000
+        assert np.array_equal(b.seg_off.cpu().numpy(), want[d]["seg_off"])
+        assert np.array_equal(b.idx[:1000].cpu().numpy(), want[d]["idx"][:1000])
+        assert np.array_equal(b.val[:1000].cpu().numpy().view(np.uint16), want[d]["val"][:1000])
+        assert (b.idx[1000:] == -7).all() and (b.val[1000:] == -7).all()
 
 
 def test_checks_from_many_threads():
     """More bucket checks at a time than a plan has pinned words, each on a stream of its own."""
     import threading
-    import torch
     print("case: threaded checks", flush=True)
     ts = [T(1, 4096, R.REPLICATED)]
     plan = R.shard_plan(ts, 1)
@@ -73,26 +80,27 @@ def test_checks_from_many_threads():
     for i, b in enumerate(buckets):
         b.seg_off.copy_(torch.tensor([0, i + 1], dtype=torch.int64))
     torch.cuda.synchronize()
-    wrong = []
+    wrong, right = [], [0] * 96
 
     def work(i):
-        with torch.cuda.stream(torch.cuda.Stream()):
-            for _ in range(20):
-                if R.bucket_check(plan, buckets[i]) != i + 1:
-                    wrong.append(i)
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(20):
+                    if R.bucket_check(plan, buckets[i]) == i + 1:
+                        right[i] += 1
+        except Exception as e:                          # would only end the thread
+            wrong.append((i, e))
 
     threads = [threading.Thread(target=work, args=(i,)) for i in range(96)]
     for t in threads:
         t.start()
     for t in threads:
         t.join()
-    assert not wrong
+    assert not wrong and right == [20] * 96
 
 
 def test_two_launches_in_a_graph():
     """The counting and the writing launch captured once and replayed on changed inputs, with eager work between."""
-    import torch
-    from oracle import oracle
     from gpu_harness import assert_buckets_equal, bits
     from workloads import models
     print("case: small update in a graph", flush=True)
@@ -122,7 +130,6 @@ def test_two_launches_in_a_graph():
 def test_diagnostic_words_are_this_launch_s():
     """Words 2 and 3 of the workspace count what happened in the launch (here: no tickets, nothing to count),
     not what the workspace held before."""
-    import torch
     print("case: diagnostic words", flush=True)
     c = bern_case([T(64, 512, R.SPLIT_ROWS), T(1, 3000, R.REPLICATED)], 2, 0.1, seed=3)
     c.ws.fill_(-1)
