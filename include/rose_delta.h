@@ -24,7 +24,9 @@
  *   - Errors that the host can see are returned before anything is queued.
  *     No exception crosses this boundary.  The library keeps no state outside plan
  *     handles, except the built-in scratch array of rose_delta_encode_static (one
- *     per device, see there).
+ *     per device, see there) and, while a plan is resident on a device, 512 bytes of
+ *     pinned host memory that rose_bucket_check reads totals back into (shared by all
+ *     plans and threads, freed with the last resident plan).
  *   - Weights are 16-bit patterns (bf16).  "Changed" means the two patterns
  *     differ; an entry carries the new pattern and applying it overwrites.
  *   - Entry coordinates are int32 flat indices local to the destination shard's
@@ -187,9 +189,10 @@ rose_status rose_plan_set_worker_cap(rose_plan *plan, int32_t workers);
  * about 4 and 7.5 %.  ROSE_TILE_ORDER_TIMED: four neighbouring tiles, and the entries are held in the
  * workgroup until a window of time that all workgroups share (they read one clock), so that the
  * memory sees the bucket writes in bursts instead of a steady trickle among the reads; best below
- * about 4 %.  (The neighbours order holds entries back too, for longer windows.)  ROSE_TILE_ORDER_AUTO_PICK (the default): the library picks, from the density of the
- * plan's previous launch as far as rose_bucket_check has read it back (until then from the share of
- * the shards that the buckets passed in could hold at most).
+ * about 4 %.  (The neighbours order holds entries back too, for longer windows.)
+ * ROSE_TILE_ORDER_AUTO_PICK (the default): the library picks, from the density of the plan's previous
+ * launch as far as rose_bucket_check has read it back (until then from the share of the shards that the
+ * buckets passed in could hold at most).
  * (With AUTO_PICK and no worker cap, an update that reads at most 80 MiB goes without tickets, in no
  * order at all.)
  * May be called at any time from any thread; a launch uses the value it finds.
@@ -201,7 +204,8 @@ rose_status rose_plan_set_worker_cap(rose_plan *plan, int32_t workers);
 rose_status rose_plan_set_tile_order(rose_plan *plan, int32_t order);
 /*
  * The order an encode launch into `buckets` (HOST array of rose_plan_n_buckets structs; only the
- * capacities are read) would use at this moment: the order set, or the library's pick.  Host only.
+ * capacities are read) would use at this moment if it takes tickets: the order set, or the library's pick
+ * (see there for small updates, which take none).  Host only.
  * ROSE_ERR_ARG for null pointers.
  */
 rose_status rose_plan_pick_tile_order(const rose_plan *plan, const rose_bucket *buckets, int32_t *order);
@@ -239,8 +243,9 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * previous and the new weights that writes all tp buckets.
  *   old_ptrs, new_ptrs  DEVICE arrays of n_tensors device pointers to the full tensors
  *                       (row-major; bf16, or fp32 for new when new_dtype = ROSE_FP32_RNE).
- *                       Tensors aligned to 16 bytes take the 128-bit load path; others still
- *                       work, more slowly.  Both are only read.
+ *                       Tensors may start at any element (128-bit loads at any alignment); at odd
+ *                       byte addresses, and where rows hold fewer than 8 elements of a shard, they are
+ *                       read element by element, which is slow.  Both are only read.
  *   buckets             HOST array of rose_plan_n_buckets bucket structs (tp of them; tp * pp_dst for a
  *                       pipeline plan); their device arrays are written.
  *   workspace           DEVICE scratch of at least rose_plan_workspace_bytes, 256-byte aligned;
@@ -249,6 +254,8 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * Returns ROSE_ERR_ARG / ROSE_ERR_ALIGN / ROSE_ERR_HIP without queuing anything.  A bucket
  * that is too small is not an error of this call: see rose_bucket_check.
  *
+ * An update that reads at most 80 MiB goes in two launches that wait for nothing (unless a tile order or a
+ * worker cap is set); what follows is about the others.
  * The kernel's workgroups wait on each other's tile counts.  The wait is bounded: if a count does
  * not arrive within a few seconds the launch is marked as failed, every workgroup still exits,
  * seg_off[n_tensors] of every bucket is set to -1, rose_bucket_check returns ROSE_ERR_HIP and
@@ -263,7 +270,7 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * rose_plan_set_worker_cap limits the workgroups that walk tiles.  After a launch the 32-bit words 2
  * and 3 of the workspace hold diagnostic counts (how often a workgroup received two tickets of one group of blocks in a row;
  * how often it counted a ticket's remaining tiles ahead of a wait, which happens where more than
- * about a third of the elements change).
+ * about a third of the elements change; both are 0 after an update in two launches).
  */
 rose_status rose_delta_encode(const rose_plan *plan, const void *const *old_ptrs,
                               const void *const *new_ptrs, int32_t new_dtype,
@@ -275,7 +282,9 @@ rose_status rose_delta_encode(const rose_plan *plan, const void *const *old_ptrs
  * current for the next step): the same buckets as rose_delta_encode, and afterwards every old
  * tensor the sender holds equals the new one as bf16 (for fp32 input: its round-to-nearest-even
  * cast), so that the same old tensors serve the next step while the new ones may be overwritten by
- * the trainer.  Only the 16-byte vectors that contain a change are written (whole replicated
+ * the trainer.  Groups of up to 64 consecutive elements (in the order of a destination's local indices)
+ * are written back whole where anything in them has changed, unchanged elements with the value they have;
+ * nothing else may write the old tensors while the call runs.  (Whole replicated
  * tensors, which are small, are copied by a second kernel once every destination has read them;
  * that includes the replicated tensors a sender holds without sending them, so their old and new
  * pointers must be valid here although rose_delta_encode never reads them).

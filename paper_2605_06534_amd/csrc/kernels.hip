@@ -1553,8 +1553,8 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 // encode in two launches, for updates of few tiles (launch_encode says how few): the first counts every
 // tile's changes, the second adds up the counts in front of its tile, reads the tile again and writes its
 // entries.  Nothing waits for another workgroup, so there is nothing to reset, no ticket, no serving wave
-// and no drain at the end; the price, reading everything twice, is small while the second reading comes
-// from the caches.  What bounds the ticket kernel on such updates is its counter (14 ns per ticket and one
+// and no drain at the end; the price is that everything is read twice (the counters see both readings in full at
+// the memory side of the L2s, 67 MB each for 4096 x 4096).  What bounds the ticket kernel on such updates is its counter (14 ns per ticket and one
 // last request per workgroup) and the way from a count to its prefix (4096 x 4096, p = 1 %: 39.8 us a call,
 // this way 24.8; a whole update of a decoder of 11 M weights, TP4, with its checks and applies: 215 and 182 us).
 // ---------------------------------------------------------------------------------------------
@@ -2579,7 +2579,7 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
 
 // Updates that go in two launches (count_tiles_kernel, emit_tiles_kernel) instead of tickets: those that read
 // at most this much.  The line lies where they win whether the inputs are in the caches or have to come from
-// memory (256 MB written elsewhere before each call), at any density, payload, refresh or not.  One matrix of 4096
+// memory (512 MB written elsewhere before each call), at any density, payload, refresh or not.  One matrix of 4096
 // columns, us per call, two launches / tickets:
 //                               32 MiB        64 MiB        96 MiB        128 MiB
 //   bf16, 1 %, cached           12.2 / 33.7   22.6 / 40.0   34.1 / 47.9   45.6 / 52.5
