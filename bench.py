@@ -172,7 +172,7 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
     if staged or args.tp_src > 1:
         n_elems = sum(olds[t].numel() for t in range(len(tensors)) if held[t])
     old_tab, new_tab = R.ptr_table(olds), R.ptr_table(news)
-    ws = R.workspace(plan)
+    ws = R.workspace(plan).zero_()
     frac = 0.03 if p is None else min(1.0, 1.3 * p + 0.002)    # the clustered recipe changes about 1.6 %
     buckets = [R.Bucket(int(plan.bucket_capacity(d) * frac) + 4096, len(tensors)) for d in range(n_b)]
     shards, shard_tabs = [], []
@@ -209,6 +209,9 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
     torch.cuda.synchronize()
     nnz = [R.bucket_check(plan, buckets[d]) for d in range(n_b)]   # raises if a bucket overflowed
     nnz_total = sum(nnz)
+    # Small updates go in two launches instead of tickets; the library's ticket counter (the workspace's 32-bit word
+    # 1024, which only a launch that takes tickets writes) says which way these went.
+    by_tickets = int(ws.view(torch.int32)[1024]) != 0
 
     if arith:
         # an arithmetic bucket may be applied once only: start the receivers from W_{t-1} again and
@@ -287,7 +290,7 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
         "nnz": nnz_total, "new_dtype": "fp32->bf16 RNE" if new_dtype == R.FP32_RNE else "bf16",
         "in_bytes_per_elem": in_bytes_per_elem, "ms_per_step": ms_per_step, "t_enc": t_enc, "t_app": t_app,
         "t_copy": t_copy, "scanned": scanned, "enc_bytes": enc_bytes, "app_bytes": app_bytes,
-        "app_line_bytes": app_line_bytes, "tiles": plan.n_tiles(),
+        "app_line_bytes": app_line_bytes, "tiles": plan.n_tiles(), "by_tickets": by_tickets,
         "enc_frac": enc_bytes / 1e9 / (t_enc / 1e3) / HBM_PEAK_GBS,
         "both_frac": (enc_bytes + app_bytes) / 1e9 / ((t_enc + t_app) / 1e3) / HBM_PEAK_GBS,
         "app_line_frac": app_line_bytes / 1e9 / (t_app / 1e3) / HBM_PEAK_GBS if t_app > 0 else None,
@@ -423,13 +426,18 @@ def main():
         crossover["%dGbps" % gbps] = {"sparse_s": round((m["t_enc"] + m["t_app"]) / 1e3 + 6 * m["nnz"] / bps, 4),
                                       "dense_s": round(m["t_copy"] / 1e3 + 2 * m["n_elems"] / bps, 4)}
 
-    kernel = "encode_kernel<%d, 0, %d>" % (1 if recipe == "clustered_f32" else 0, 1 if args.payload == "arith" else 0)
+    f32, arith = 1 if recipe == "clustered_f32" else 0, 1 if args.payload == "arith" else 0
+    kernels = ["encode_kernel<%d, 0, %d>" % (f32, arith)] if m["by_tickets"] else \
+        ["count_tiles_kernel<%d>" % f32, "emit_tiles_kernel<%d, 0, %d>" % (f32, arith)]
+    kernel = " + ".join(kernels)
     traffic, traffic_src = None, {"note": "non-default run: no committed profile applies"}
     if args.traffic_bytes is not None:
         traffic, traffic_src = args.traffic_bytes, {"note": "--traffic-bytes"}
     elif args.layers is None and args.tp_src == 1 and args.seed == 0 and args.tp is None \
             and args.pp_src == 1 and args.pp_dst == 1:
-        traffic, traffic_src = profile_traffic(args.workload, p, kernel.replace(" ", ""))
+        found = [profile_traffic(args.workload, p, k.replace(" ", "")) for k in kernels]
+        traffic = sum(t for t, _ in found) if all(t is not None for t, _ in found) else None
+        traffic_src = next((s for t, s in found if t is None), found[0][1])
     value = m["scanned"] / 1e9 / (m["ms_per_step"] / 1e3)
     out = {
         "metric": "weight-delta encode+apply GB/s (bf16 scanned)",
