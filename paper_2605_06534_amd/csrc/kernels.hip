@@ -163,6 +163,14 @@ __device__ __forceinline__ void gstore16_stream(void *p, uint4 v) {
     __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(p)));
 }
 
+// Single elements the same way.  (Flat accesses may come back out of turn: where one can be on its way, the compiler
+// waits for everything instead of for the load it needs.)
+typedef __attribute__((address_space(1))) uint16_t global_u16;
+typedef __attribute__((address_space(1))) uint32_t global_u32;
+__device__ __forceinline__ uint32_t gload_u16(const void *p) { return *reinterpret_cast<const global_u16 *>(reinterpret_cast<uintptr_t>(p)); }
+__device__ __forceinline__ uint32_t gload_u32(const void *p) { return *reinterpret_cast<const global_u32 *>(reinterpret_cast<uintptr_t>(p)); }
+__device__ __forceinline__ void gstore_u16(void *p, uint32_t v) { *reinterpret_cast<global_u16 *>(reinterpret_cast<uintptr_t>(p)) = (uint16_t)v; }
+
 // Uniform (per-workgroup) table reads through the constant address space, so that they become
 // scalar loads served by the scalar cache instead of vector loads.  Only used for what the launch itself does not
 // write: the plan's piece / tile tables, the caller's pointer tables, and in apply a bucket's indices and
@@ -2285,6 +2293,7 @@ __global__ __launch_bounds__(WAVES * 64) void apply_object_kernel(const char *ob
 // (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements, TP2: 4130 -> 1421 us; rows of
 // 765 elements a shard, 131 M weights: 248 -> 89 us.)
 // ---------------------------------------------------------------------------------------------
+constexpr int kCopyAtOnce = 2048;       // workgroups (of 256 threads, 8 waves per SIMD)
 template <int NEW_F32>
 __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const int32_t tile = a.tile_begin + (int32_t)blockIdx.x;
@@ -2299,8 +2308,8 @@ __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const uint32_t k0 = k_tile + head, k_lane = k0 + (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
     auto copy_one = [&](uint32_t k) {
         const int64_t s = src_index(pc, k, false);
-        dst[dst_index(pc, k, false)] = NEW_F32 ? (uint16_t)rne_bf16(static_cast<const uint32_t *>(new_base)[s])
-                                               : static_cast<const uint16_t *>(new_base)[s];
+        gstore_u16(dst + dst_index(pc, k, false), NEW_F32 ? rne_bf16(gload_u32(static_cast<const uint32_t *>(new_base) + s))
+                                                          : gload_u16(static_cast<const uint16_t *>(new_base) + s));
     };
     if (k_tile == 0 && threadIdx.x < head && threadIdx.x < len) copy_one(threadIdx.x);
     const bool vec = (pc.flags & kPieceLoad16) && ((((uintptr_t)new_base) | ((uintptr_t)dst)) & 1u) == 0 &&
@@ -2331,8 +2340,12 @@ __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
         }
     }
     // The ordinary tile by itself: among the rare cases its stores lie lines of code apart, and a launch that does
-    // not last long pays for each (one matrix of 1 M elements: 3.4 us, 3.7 that way; fp32 masters 3.9 and 4.3).
+    // not last long pays for each (one matrix of 1 M elements: 3.4 us, 3.7 that way; fp32 masters 3.8 and 4.3).
     if (!src_split && !dst_split && k0 + (uint32_t)kTile <= len) {
+        // A bf16 launch whose workgroups are all resident reads first and writes then (four shards of 8192 x 4096:
+        // 24.0 us, 27.9 with each store as soon as its load is there; with the input in memory 28.6 and 33.8); longer
+        // ones do better without (1 GiB in four shards: 330 us, 337 with the wait), fp32 masters too.
+        if (!NEW_F32 && gridDim.x <= (unsigned)kCopyAtOnce) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int j = 0; j < kIters; ++j)
             gstore16_stream(dst + dst_index(pc, k_lane + (uint32_t)(j * 64) * kVec, true), raw_to_bf16(r, j));
