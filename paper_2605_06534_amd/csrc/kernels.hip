@@ -1562,7 +1562,8 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 // tile's changes, the second adds up the counts in front of its tile, reads the tile again and writes its
 // entries.  Nothing waits for another workgroup, so there is nothing to reset, no ticket, no serving wave
 // and no drain at the end; the price is that everything is read twice (the counters see both readings in full at
-// the memory side of the L2s, 67 MB each for 4096 x 4096).  What bounds the ticket kernel on such updates is its counter (14 ns per ticket and one
+// the memory side of the L2s, 67 MB each for 4096 x 4096).  What bounds the ticket kernel on such updates is its
+// counter (14 ns per ticket and one
 // last request per workgroup) and the way from a count to its prefix (4096 x 4096, p = 1 %: 39.8 us a call,
 // this way 24.8; a whole update of a decoder of 11 M weights, TP4, with its checks and applies: 215 and 182 us).
 // ---------------------------------------------------------------------------------------------
@@ -1730,14 +1731,17 @@ __global__ __launch_bounds__(256) void refresh_replicated_kernel(const int32_t *
 //                0.67 and 0.71 at 1.5 %, 0.55 and 0.56 at 1 %; buckets of a 67 M shard with room for 3.75 %: 36.3 and
 //                38.2 us; with room for 4.4 % it loses 5 %).  Not up to 8192 chunks: fewer waves are in flight anyway,
 //                and lone entries do better by lines (67 M elements, 0.1 %: 4.2 us, 5.3 with it).
+//   below 1/20   apply_kernel<0>, 5 waves per SIMD in workgroups of 4 (against 8 in workgroups of 8, with room for
+//                4.75 %: 1.045 and 1.078 ms, 67 M elements 38.5 and 40.5 us; with room for 5.6 % 134 - 268 M elements
+//                lose 8 %)
 //   up to 1/3    apply_kernel<0>, 8 waves per SIMD, and twice kApplyBlocks workgroups: a wave that takes a second
 //                chunk waits for the stores of its first, but a wave that finds none costs too (one shard with 1x /
 //                2x / 4x: 1.21 / 1.16 / 1.16 ms at 5 %, 1.62 / 1.53 / 1.40 at 12 %; at 0.2 % with room for 10 %:
 //                178 / 203 / 259 us)
-//   above        kApplyBlocks workgroups
+//   above        kApplyBlocks workgroups (of 8 waves)
 // A bucket that turns out to hold 1/7 of the shard goes by direct stores throughout (apply_direct).
 constexpr int kApplyWaves = 8, kApplySmallWaves = 4, kApplySmallChunks = 8192;
-constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 24, kApplyDenseDiv = 7, kApplyRoomyDiv = 3;
+constexpr int kApplyBlocks = 256 * 256, kApplySparseDiv = 24, kApplyMiddleDiv = 20, kApplyDenseDiv = 7, kApplyRoomyDiv = 3;
 #ifndef ROSE_APPLY_LINE
 #define ROSE_APPLY_LINE 64                      // bytes moved around an entry: 64 or 32 (32 halves the bytes at low
                                                 // density and is slower all the same: 7B workload 3.61 instead of
@@ -2064,8 +2068,9 @@ __device__ __forceinline__ void apply_body(const BucketDev &b, int32_t n_tensors
     }
 }
 
-template <int SPARSE, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(SPARSE ? 4 : 8, SPARSE ? 4 : 8)))
+// PER_SIMD: waves per SIMD that the kernel is held to
+template <int SPARSE, int WAVES, int PER_SIMD>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD)))
 void apply_kernel(BucketDev b, int32_t n_tensors, const int32_t *local_numel, void *const *dst_ptrs, int arith,
                   int64_t dense_from) {
     apply_body<SPARSE, WAVES>(b, n_tensors, local_numel, dst_ptrs, arith, dense_from);
@@ -2665,11 +2670,13 @@ int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_num
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool small = b.capacity <= (int64_t)kApplySmallChunks * 64;
     const bool sparse = !small && b.capacity < shard_elems / kApplySparseDiv;
-    const ApplyKernel kernel = small ? apply_kernel<0, kApplySmallWaves>
-                                     : sparse ? apply_kernel<1, kApplyWaves> : apply_kernel<0, kApplyWaves>;
-    const int per_wg = (small ? kApplySmallWaves : kApplyWaves) * 64;
+    const bool middle = !small && !sparse && b.capacity < shard_elems / kApplyMiddleDiv;
+    const ApplyKernel kernel = small ? apply_kernel<0, kApplySmallWaves, 8>
+                             : sparse ? apply_kernel<1, kApplyWaves, 4>
+                             : middle ? apply_kernel<0, kApplySmallWaves, 5> : apply_kernel<0, kApplyWaves, 8>;
+    const int waves = small || middle ? kApplySmallWaves : kApplyWaves, per_wg = waves * 64;
     const int64_t want = (b.capacity + per_wg - 1) / per_wg;
-    const int most = sparse || b.capacity >= shard_elems / kApplyRoomyDiv ? kApplyBlocks : 2 * kApplyBlocks;
+    const int most = (sparse || b.capacity >= shard_elems / kApplyRoomyDiv ? kApplyBlocks : 2 * kApplyBlocks) * (kApplyWaves / waves);
     const int blocks = want < 1 ? 1 : (want > most ? most : (int)want);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(per_wg), 0, st, b, n_tensors, local_numel, dst_ptrs, arith,
                        shard_elems / kApplyDenseDiv);

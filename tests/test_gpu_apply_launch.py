@@ -1,5 +1,5 @@
 """Apply on both sides of the lines its launch is chosen by: small workgroups or large (8192 chunks of 64
-entries), sparse or not (room for a 24th of the shard), twice the workgroups or not (a third of it).  Bucket and
+entries), sparse or not (room for a 24th of the shard), five waves a SIMD or eight (a 20th), twice the workgroups or not (a third of it).  Bucket and
 object, compared bit for bit with plain assignment."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ SMALL = 8192 * 64
 
 
 @pytest.mark.parametrize("capacity", [1, 255, 257, SMALL - 1, SMALL, SMALL + 1, SMALL + 511])
-@pytest.mark.parametrize("times", [1, 3, 4, 25])
+@pytest.mark.parametrize("times", [1, 3, 4, 22, 25])
 @pytest.mark.parametrize("fill", [0.2, 1.0])
 def test_lines_of_the_launch(capacity, times, fill):
     print("case: apply launch capacity=%d shard=%d x fill=%g" % (capacity, times, fill), flush=True)
