@@ -209,9 +209,9 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
     torch.cuda.synchronize()
     nnz = [R.bucket_check(plan, buckets[d]) for d in range(n_b)]   # raises if a bucket overflowed
     nnz_total = sum(nnz)
-    # Small updates go in two launches instead of tickets; the library's ticket counter (the workspace's 32-bit word
-    # 1024, which only a launch that takes tickets writes) says which way these went.
-    by_tickets = int(ws.view(torch.int32)[1024]) != 0
+    # Updates that are not large go in two launches instead of tickets; the workspace's 32-bit word 4 (the tiles of such
+    # an update, 0 after one by tickets) says which way these went.
+    by_tickets = int(ws.view(torch.int32)[4]) == 0
 
     if arith:
         # an arithmetic bucket may be applied once only: start the receivers from W_{t-1} again and
@@ -428,7 +428,7 @@ def main():
 
     f32, arith = 1 if recipe == "clustered_f32" else 0, 1 if args.payload == "arith" else 0
     kernels = ["encode_kernel<%d, 0, %d>" % (f32, arith)] if m["by_tickets"] else \
-        ["count_tiles_kernel<%d>" % f32, "emit_tiles_kernel<%d, 0, %d>" % (f32, arith)]
+        ["stage_tiles_kernel<%d, 0, %d>" % (f32, arith), "emit_staged_kernel<%d, 0, %d>" % (f32, arith)]
     kernel = " + ".join(kernels)
     traffic, traffic_src = None, {"note": "non-default run: no committed profile applies"}
     if args.traffic_bytes is not None:

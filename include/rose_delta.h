@@ -193,8 +193,8 @@ rose_status rose_plan_set_worker_cap(rose_plan *plan, int32_t workers);
  * ROSE_TILE_ORDER_AUTO_PICK (the default): the library picks, from the density of the plan's previous
  * launch as far as rose_bucket_check has read it back (until then from the share of the shards that the
  * buckets passed in could hold at most).
- * (With AUTO_PICK and no worker cap, an update that reads at most 80 MiB goes without tickets, in no
- * order at all.)
+ * (With AUTO_PICK and no worker cap, an update that is not large goes without tickets, in no order at
+ * all: see rose_delta_encode.)
  * May be called at any time from any thread; a launch uses the value it finds.
  */
 #define ROSE_TILE_ORDER_AUTO_PICK 0
@@ -233,7 +233,9 @@ rose_status rose_plan_map_index(const rose_plan *plan, int32_t t, int64_t g, int
                                 int32_t *n_dest, int32_t *local);
 /* worst-case number of entries this sender produces for bucket d (every element changed) */
 rose_status rose_plan_bucket_capacity(const rose_plan *plan, int32_t d, int64_t *max_entries);
-/* bytes of device scratch that rose_delta_encode needs (256-byte aligned buffer) */
+/* bytes of device scratch for rose_delta_encode (256-byte aligned buffer).  For plans of up to 65536 tiles this
+ * includes room to park entries in (at most 8064 bytes a tile, and 48 MiB together), which lets updates that are not
+ * large go without tickets. */
 rose_status rose_plan_workspace_bytes(const rose_plan *plan, size_t *bytes);
 /* number of tiles the encode kernel walks (for reporting) */
 rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
@@ -254,8 +256,10 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * Returns ROSE_ERR_ARG / ROSE_ERR_ALIGN / ROSE_ERR_HIP without queuing anything.  A bucket
  * that is too small is not an error of this call: see rose_bucket_check.
  *
- * An update that reads at most 80 MiB goes in two launches that wait for nothing (unless a tile order or a
- * worker cap is set); what follows is about the others.
+ * Unless a tile order or a worker cap is set, an update that reads at most 80 MiB goes in two launches that wait
+ * for nothing, and so does a larger one (300 MiB at 12 % up to 1.2 GiB at 1 % of changed elements; half as much again
+ * with arithmetic payloads or refresh) once the density is known (rose_bucket_check has read a total back, or the
+ * buckets bound it), as far as the workspace has room for the entries.  What follows is about the others.
  * The kernel's workgroups wait on each other's tile counts.  The wait is bounded: if a count does
  * not arrive within a few seconds the launch is marked as failed, every workgroup still exits,
  * seg_off[n_tensors] of every bucket is set to -1, rose_bucket_check returns ROSE_ERR_HIP and
@@ -270,7 +274,8 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * rose_plan_set_worker_cap limits the workgroups that walk tiles.  After a launch the 32-bit words 2
  * and 3 of the workspace hold diagnostic counts (how often a workgroup received two tickets of one group of blocks in a row;
  * how often it counted a ticket's remaining tiles ahead of a wait, which happens where more than
- * about a third of the elements change; both are 0 after an update in two launches).
+ * about a third of the elements change; both are 0 after an update in two launches).  Word 4 is the number of tiles
+ * of an update in two launches, and 0 after one by tickets.
  */
 rose_status rose_delta_encode(const rose_plan *plan, const void *const *old_ptrs,
                               const void *const *new_ptrs, int32_t new_dtype,

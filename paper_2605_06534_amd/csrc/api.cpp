@@ -205,8 +205,7 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     const bool built_in = workspace == nullptr && workspace_bytes == (size_t)-1;
     if (!p || !old_ptrs || !new_ptrs || !buckets || (!workspace && !built_in)) return ROSE_ERR_ARG;
     if (new_dtype != ROSE_BF16 && new_dtype != ROSE_FP32_RNE) return ROSE_ERR_ARG;
-    size_t need = 0;
-    rose_plan_workspace_bytes(p, &need);
+    const size_t need = rose::workspace_need(p);
     if (!aligned(old_ptrs, 8) || !aligned(new_ptrs, 8)) return ROSE_ERR_ALIGN;
     rose::EncodeArgs a;
     std::memset(&a, 0, sizeof a);
@@ -242,6 +241,12 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     a.block_desc = a.tile_desc + a.n_tiles;
     a.tp = p->n_buckets;
     a.n_tensors = p->n_tensors;
+    const size_t slots_at = (need + 255) / 256 * 256;
+    if (a.n_tiles > 0 && a.n_tiles <= rose::kStageMostTiles && workspace_bytes > slots_at) {
+        const size_t room = (workspace_bytes - slots_at) / sizeof(uint32_t) / (size_t)a.n_tiles / 32 * 32;   // whole lines
+        a.slots = reinterpret_cast<uint32_t *>(ws + slots_at);
+        a.slot_size = (int32_t)(room < (size_t)rose::kStageSlot ? room : (size_t)rose::kStageSlot);
+    }
     rose::RefreshArgs r{p->d_repl_list, p->d_repl_numel, p->n_repl};
     const bool f32 = new_dtype == ROSE_FP32_RNE;
     const int resident = p->resident[(f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];

@@ -1558,126 +1558,330 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 #undef ROSE_ENCODE_KERNEL
 
 // ---------------------------------------------------------------------------------------------
-// encode in two launches, for updates of few tiles (launch_encode says how few): the first counts every
-// tile's changes, the second adds up the counts in front of its tile, reads the tile again and writes its
-// entries.  Nothing waits for another workgroup, so there is nothing to reset, no ticket, no serving wave
-// and no drain at the end; the price is that everything is read twice (the counters see both readings in full at
-// the memory side of the L2s, 67 MB each for 4096 x 4096).  What bounds the ticket kernel on such updates is its
-// counter (14 ns per ticket and one
-// last request per workgroup) and the way from a count to its prefix (4096 x 4096, p = 1 %: 39.8 us a call,
-// this way 24.8; a whole update of a decoder of 11 M weights, TP4, with its checks and applies: 215 and 182 us).
+// encode in two launches, without tickets (launch_encode says when).  Nothing waits for another workgroup, so there
+// is nothing to reset, no ticket, no serving wave and no drain at the end.  The first launch reads every tile, one
+// workgroup a tile, and counts its changes; the second adds up the counts in front of its tiles and writes the
+// entries.  Two forms:
+//   staged    the first launch parks a tile's compacted entries in the tile's slot of the workspace, the second copies
+//             them to the bucket.  A tile that holds more than its slot does parks nothing and is read again.
+//   read again   no slots: the second launch reads every tile a second time.
 // ---------------------------------------------------------------------------------------------
-template <int NEW_F32>
-__global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uint32_t *counts) {
-    __shared__ uint32_t s_cnt[kWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const TileCtx c = tile_ctx(a, (int32_t)blockIdx.x);
-    uint4 o[kIters], n[kIters];
-    load_tile_pair<NEW_F32>(c, (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec, o, n);
-    uint32_t cnt = 0;
+constexpr int kGroupMost = 16;           // tiles a workgroup of the second launch copies out at most
+
+// Refresh: the lines of the tile in which anything changed, from registers.  Whole 64-byte lines, non-temporal (16 M
+// weights at 5 %, inputs from memory: 48.9 us with ordinary stores, 35.4 this way; with the inputs in the caches the same).
+__device__ __forceinline__ void refresh_tile(const TileCtx &c, uint32_t t_off, uint32_t total, const uint32_t (&mask)[kIters],
+                                             const uint4 (&n)[kIters]) {
+    uint16_t *ob = const_cast<uint16_t *>(c.old_base);
+    const bool wide = total <= (uint32_t)kRefreshWide;
 #pragma unroll
     for (int j = 0; j < kIters; ++j) {
-        cnt += __popc(nz16_mask(xor4(o[j], n[j])));
+        const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
+        uint32_t q, m = mask[j], line = or_of_four(m);
+        const uint32_t pair = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)line, 0x141, 0xf, 0xf, true);      // row_half_mirror
+        if (wide) line |= pair;
+        if (!line) continue;
+        if ((c.vec & 1u) && k + kVec <= (uint32_t)c.pc.len && !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
+            gstore16_stream(ob + src_index(c.pc, k, true), n[j]);
+        } else {
+            while (m) {
+                const uint32_t e = __ffs(m) - 1;
+                m &= m - 1;
+                ob[src_index(c.pc, k + e, false)] = (uint16_t)pick16(n[j], e);
+            }
+        }
     }
-    const uint32_t wave_cnt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(cnt), 63);
-    if (lane == 0) s_cnt[wave] = wave_cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t total = 0;
-        for (int w = 0; w < kWaves; ++w) total += s_cnt[w];
-        counts[blockIdx.x] = total;
+}
+
+// The changed elements of a vector go to consecutive places in LDS: offset in the tile << 16 | new pattern, and for
+// arithmetic payloads the old pattern beside it.
+template <int ARITH>
+__device__ __forceinline__ void park_vector(uint32_t in_tile, uint32_t m, uint4 o, uint4 n, uint32_t at, uint32_t *s_entry,
+                                            uint16_t *s_was) {
+    while (m) {
+        const uint32_t e = __ffs(m) - 1;
+        m &= m - 1;
+        s_entry[at] = ((in_tile + e) << 16) | pick16(n, e);
+        if constexpr (ARITH) s_was[at] = (uint16_t)pick16(o, e);
+        ++at;
     }
-    // the header's words are this call's, whatever the workspace held: no wait gave up, no ticket was counted ahead
-    if (blockIdx.x == 0 && threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
+}
+// Entry k as it is written: an arithmetic payload is formed here, of the compacted entries only (the ticket kernel, which
+// has no registers for old and new patterns side by side, forms it of every element: 320 instructions more a wave and tile).
+template <int ARITH>
+__device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, const uint16_t *s_was) {
+    const uint32_t entry = s_entry[k];
+    if constexpr (!ARITH) return entry;
+    uint32_t esc;
+    const uint32_t pay = arith_pair(s_was[k], entry & 0xFFFFu, &esc);
+    return (entry & 0x7FFF0000u) | (pay & 0xFFFFu) | ((esc & 1u) << 31);
 }
 
 template <int NEW_F32, int REFRESH, int ARITH>
-__global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, const uint32_t *counts) {
-    __shared__ uint32_t s_entry[kTile];      // an entry as in encode_body's ring
-    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+__global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uint16_t *counts, uint32_t *slots, int32_t slot_size,
+                                                               int32_t stream) {
+    __shared__ uint32_t s_entry[kStageSlot];
+    __shared__ uint16_t s_was[ARITH ? kStageSlot : 1];
+    __shared__ uint32_t s_cnt[kWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int32_t tile = (int32_t)blockIdx.x;
     const TileCtx c = tile_ctx(a, tile);
     const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
-    const int32_t chain_begin = a.chain_first[c.pc.shard], chain_end = a.chain_first[c.pc.shard + 1];
     uint4 o[kIters], n[kIters];
     load_tile_pair<NEW_F32>(c, t_off, o, n);
-    // entries of the chain's earlier tiles (as many as all tiles have elements at most, see kTwoLaunchBytes)
-    uint32_t before = 0;
-    for (int32_t t = chain_begin + (int32_t)threadIdx.x; t < tile; t += kThreads) before += counts[t];
-    before = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(before), 63);
+    uint32_t mask[kIters], rank[kIters];
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
+    const uint32_t wave_total = vector_ranks(mask, rank);
+    if (lane == 0) s_cnt[wave] = wave_total;
+    __syncthreads();
+    uint32_t wave_excl = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w < wave) wave_excl += s_cnt[w];
+        total += s_cnt[w];
+    }
+    if (threadIdx.x == 0) counts[tile] = (uint16_t)total;
+    if (tile == 0) {
+        // the header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one
+        if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
+        if (threadIdx.x == kWsTilesWord) a.abort_flag[kWsTilesWord] = (uint32_t)a.n_tiles;
+        if (threadIdx.x == kWsTilesWord + 1) *a.ticket = (uint32_t)a.n_tiles;      // handed out by the grid
+    }
+    total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+    if (total == 0 || total > (uint32_t)slot_size) return;
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec, mask[j], o[j], n[j], wave_excl + rank[j], s_entry, s_was);
+    if constexpr (REFRESH) {
+        if (!(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total, mask, n);
+    }
+    __syncthreads();
+    uint32_t *slot = slots + (size_t)tile * (uint32_t)slot_size;
+    for (uint32_t k = threadIdx.x; k < total; k += kThreads) {
+        const uint32_t entry = parked<ARITH>(k, s_entry, s_was);
+        if (stream) __builtin_nontemporal_store(entry, slot + k);
+        else slot[k] = entry;
+    }
+}
 
+// What the second launch needs of a tile besides its count.
+struct EmitTile {
+    uint32_t start;     // entries of the workgroup's earlier tiles
+    uint32_t base;      // local index of the tile's first element; with a piece, the element's number inside it
+    int32_t piece;      // -1, or the piece whose table entry maps element numbers to local indices
+};
+
+// local index of the element at number `k` of a piece whose local indices come in strided runs (runs of one element
+// have no magic divisor: the quotient is the number itself)
+__device__ __forceinline__ uint32_t strided_local(const Piece *p, uint32_t k) {
+    const uint32_t run = (uint32_t)p->run;
+    const uint32_t q = run == 1u ? k : (__umulhi(k, p->magic) >> p->shift);
+    return (uint32_t)p->local_base + q * (uint32_t)p->lstride + (k - q * run);
+}
+
+// A tile read (again), compacted in LDS a PART-th of its waves at a time, written.  `before` is called while the loads
+// are on their way and returns the wave's share of the entries in front of the tile, besides the `excl` that are known;
+// with SEGMENTS the tile's segment ends are written too.
+template <int NEW_F32, int REFRESH, int ARITH, int PARTS, bool SEGMENTS, typename BEFORE>
+__device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64 excl, BEFORE before, uint32_t *s_entry,
+                                          uint16_t *s_was, uint32_t *s_before, uint32_t *s_cnt) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const TileCtx c = tile_ctx(a, tile);
+    const BucketDev b = a.bucket[c.pc.shard];
+    const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
+    uint4 o[kIters], n[kIters];
+    load_tile_pair<NEW_F32>(c, t_off, o, n);
+    const uint32_t share = before(c);
     uint32_t mask[kIters], rank[kIters];
 #pragma unroll
     for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
     const uint32_t wave_total = vector_ranks(mask, rank);
     if (lane == 0) {
-        s_before[wave] = before;
+        s_before[wave] = share;
         s_cnt[wave] = wave_total;
     }
     __syncthreads();
-    uint32_t wave_excl = 0, total = 0;
-    u64 excl = 0;
+    uint32_t total = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        if (w < wave) wave_excl += s_cnt[w];
-        total += s_cnt[w];
         excl += s_before[w];
+        total += s_cnt[w];
     }
-    const BucketDev b = a.bucket[c.pc.shard];
-    if (threadIdx.x == 0) {
+    if (SEGMENTS && threadIdx.x == 0) {
         if ((c.pc.flags & kPieceFirst) && tile == c.pc.first_tile) b.seg_off[c.pc.tensor] = (int64_t)excl;
-        if (tile == chain_end - 1) b.seg_off[a.n_tensors] = (int64_t)(excl + total);
+        if (tile == a.chain_first[c.pc.shard + 1] - 1) b.seg_off[a.n_tensors] = (int64_t)(excl + total);
     }
+    const bool dst_strided = (c.pc.flags & kPieceDstStrided) != 0;
+#pragma unroll 1
+    for (int part = 0; part < kWaves; part += kWaves / PARTS) {
+        if (part) __syncthreads();                             // the part before has been written
+        uint32_t at0 = 0, here = 0;
 #pragma unroll
-    for (int j = 0; j < kIters; ++j) {
-        uint4 pay = n[j];
-        uint32_t esc8 = 0;
-        if constexpr (ARITH) pay = arith_vec(o[j], n[j], &esc8);
-        uint32_t m = mask[j], slot = wave_excl + rank[j];
-        while (m) {
-            const uint32_t e = __ffs(m) - 1;
-            m &= m - 1;
-            s_entry[slot++] = ((t_off + (uint32_t)(j * 64) * kVec + e) << 16) | pick16(pay, e) | ((esc8 >> e) << 31);
+        for (int w = 0; w < kWaves / PARTS; ++w) {
+            if (part + w < wave) at0 += s_cnt[part + w];
+            here += s_cnt[part + w];
         }
-    }
-    if constexpr (REFRESH) {                 // as in encode_body
-        if (!(c.pc.flags & kPieceReplicated)) {
-            uint16_t *ob = const_cast<uint16_t *>(c.old_base);
+        if (wave >= part && wave < part + kWaves / PARTS) {
 #pragma unroll
-            for (int j = 0; j < kIters; ++j) {
-                const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
-                uint32_t q, m = mask[j];
-                if (!or_of_four(m)) continue;       // whole 64-byte lines
-                if ((c.vec & 1u) && k + kVec <= (uint32_t)c.pc.len &&
-                    !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
-                    // (non-temporal, as in encode_body: with the inputs in the caches the same, else 5 % of 16 M weights
-                    // 48.9 -> 35.4 us, the ticket kernel 45.9)
-                    gstore16_stream(ob + src_index(c.pc, k, true), n[j]);
-                } else {
-                    while (m) {
-                        const uint32_t e = __ffs(m) - 1;
-                        m &= m - 1;
-                        ob[src_index(c.pc, k + e, false)] = (uint16_t)pick16(n[j], e);
-                    }
-                }
+            for (int j = 0; j < kIters; ++j) park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec, mask[j], o[j], n[j], at0 + rank[j], s_entry, s_was);
+        }
+        if constexpr (REFRESH) {
+            if (part == 0 && !(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total, mask, n);
+        }
+        __syncthreads();
+        const uint32_t phase = (uint32_t)excl & 31u;           // lined up with the bucket's lines, see copy_out
+        for (uint32_t kk = threadIdx.x; kk < here + phase; kk += kThreads) {
+            const uint32_t k = kk - phase;
+            const u64 pos = excl + k;
+            if (kk >= phase && pos < (u64)b.capacity) {
+                const uint32_t entry = parked<ARITH>(k, s_entry, s_was);
+                uint32_t local = c.k_tile + ((entry >> 16) & (uint32_t)(kTile - 1));
+                local = dst_strided ? strided_local(a.pieces + c.piece, local) : (uint32_t)c.pc.local_base + local;
+                b.idx[pos] = (int32_t)(local | (ARITH ? entry & 0x80000000u : 0u));
+                b.val[pos] = (uint16_t)entry;
             }
         }
+        excl += here;
+    }
+}
+
+// This thread's share of the counts of tiles begin .. end - 1, added up over the wave.
+__device__ __forceinline__ uint32_t wave_share_of_counts(const uint16_t *counts, int32_t begin, int32_t end) {
+    const uint16_t *p = counts + begin;
+    const uint32_t m = (uint32_t)(end - begin), whole = m / 8;
+    uint32_t sum = 0;
+    for (uint32_t i = threadIdx.x; i < whole; i += kThreads) {
+        const uint4 v = gload16(p + i * 8);
+        sum += (v.x & 0xFFFFu) + (v.x >> 16) + (v.y & 0xFFFFu) + (v.y >> 16) + (v.z & 0xFFFFu) + (v.z >> 16) + (v.w & 0xFFFFu) +
+               (v.w >> 16);
+    }
+    if (threadIdx.x < m % 8) sum += gload_u16(p + whole * 8 + threadIdx.x);
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(sum), 63);
+}
+
+// Second launch, every tile read again: one workgroup a tile.
+template <int NEW_F32, int REFRESH, int ARITH>
+__global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, const uint16_t *counts) {
+    constexpr int PARTS = ARITH ? 2 : 1;
+    __shared__ uint32_t s_entry[kTile / PARTS];
+    __shared__ uint16_t s_was[ARITH ? kTile / PARTS : 1];
+    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+    const int32_t tile = (int32_t)blockIdx.x;
+    emit_read<NEW_F32, REFRESH, ARITH, PARTS, true>(
+        a, tile, 0, [&](const TileCtx &c) { return wave_share_of_counts(counts, a.chain_first[c.pc.shard], tile); }, s_entry,
+        s_was, s_before, s_cnt);
+}
+
+// Second launch, staged: a workgroup copies out 2^group_log2 neighbouring tiles of one chain.
+template <int NEW_F32, int REFRESH, int ARITH>
+__global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, const uint16_t *counts, const uint32_t *slots,
+                                                              int32_t slot_size, int32_t group_log2) {
+    __shared__ uint32_t s_entry[kTile / 2];
+    __shared__ uint16_t s_was[ARITH ? kTile / 2 : 1];
+    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+    __shared__ EmitTile s_tile[kGroupMost + 1];
+    __shared__ uint32_t s_over;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t group = 1 << group_log2;
+    const int32_t first = (int32_t)blockIdx.x << group_log2, blk = first / kBlock;
+    int32_t shard = 0;
+    while (blk >= a.block_first[shard + 1]) ++shard;
+    const int32_t chain_begin = a.chain_first[shard], chain_end = a.chain_first[shard + 1];
+    const int32_t t0 = chain_begin + first - a.block_first[shard] * kBlock;
+    if (t0 >= chain_end) return;
+    const int32_t n = chain_end - t0 < group ? chain_end - t0 : group;
+    const BucketDev b = a.bucket[shard];
+
+    // lane i of wave 0: tile t0 + i
+    const bool mine = wave == 0 && lane < n;
+    int32_t my_piece = 0;
+    uint32_t count = 0, start = 0, early = 0;
+    if (mine) {
+        my_piece = a.tile_piece[t0 + lane];
+        count = gload_u16(counts + t0 + lane);
+    }
+    // a single tile's first entries need not wait for their count
+    const uint32_t *from = slots + (size_t)t0 * (uint32_t)slot_size;
+    if (group == 1 && (uint32_t)slot_size >= (uint32_t)kThreads) early = gload_u32(from + threadIdx.x);
+    // entries of the chain's earlier tiles (as many as all tiles have elements at most: they fit 32 bits, see kStageMostTiles)
+    const uint32_t before = wave_share_of_counts(counts, chain_begin, t0);
+    if (lane == 0) s_before[wave] = before;
+    int32_t seg = -1;                                          // tensor whose segment starts with the tile
+    if (wave == 0) {
+        EmitTile t = {0, 0, -1};
+        if (mine) {
+            const Piece *pc = a.pieces + my_piece;
+            const uint32_t k_tile = (uint32_t)(t0 + lane - pc->first_tile) * (uint32_t)kTile;
+            t.piece = (pc->flags & kPieceDstStrided) ? my_piece : -1;
+            t.base = k_tile + (t.piece < 0 ? (uint32_t)pc->local_base : 0u);
+            if ((pc->flags & kPieceFirst) && t0 + lane == pc->first_tile) seg = pc->tensor;
+        }
+        const uint32_t incl = wave_incl_scan(count);
+        start = incl - count;
+        t.start = start;
+        if (lane <= group) s_tile[lane] = t;
+        const u64 over = __ballot(count > (uint32_t)slot_size);
+        if (lane == 0) s_over = over != 0;
     }
     __syncthreads();
-    const bool dst_strided = (c.pc.flags & kPieceDstStrided) != 0;
-    const uint32_t phase = (uint32_t)excl & 31u;         // lined up with the bucket's lines, see copy_out
-    for (uint32_t kk = threadIdx.x; kk < total + phase; kk += kThreads) {
-        const uint32_t k = kk - phase;
-        const u64 pos = excl + k;
-        if (kk >= phase && pos < (u64)b.capacity) {
-            const uint32_t entry = s_entry[k];
-            uint32_t local = c.k_tile + ((entry >> 16) & (uint32_t)(kTile - 1));
-            uint32_t q = 0;
-            if (dst_strided) q = c.pc.run == 1 ? local : (__umulhi(local, c.pc.magic) >> c.pc.shift);
-            local = (uint32_t)c.pc.local_base + q * (uint32_t)c.pc.lstride + (local - q * (uint32_t)c.pc.run);
-            b.idx[pos] = (int32_t)(local | (ARITH ? entry & 0x80000000u : 0u));
-            b.val[pos] = (uint16_t)entry;
+    u64 excl = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) excl += s_before[w];
+    if (mine) {
+        if (seg >= 0) b.seg_off[seg] = (int64_t)(excl + start);
+        if (t0 + lane == chain_end - 1) b.seg_off[a.n_tensors] = (int64_t)(excl + start + count);
+    }
+
+    auto write = [&](u64 pos, uint32_t entry, uint32_t base, int32_t piece) {
+        if (pos >= (u64)b.capacity) return;
+        uint32_t local = base + ((entry >> 16) & (uint32_t)(kTile - 1));
+        if (piece >= 0) local = strided_local(a.pieces + piece, local);
+        __builtin_nontemporal_store((int32_t)(local | (ARITH ? entry & 0x80000000u : 0u)), b.idx + pos);
+        __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
+    };
+    // entries begin .. end - 1 of the workgroup's, from their slots; lined up with the bucket's lines, see copy_out
+    constexpr int U = 4;                                       // loads a thread has in flight
+    auto copy = [&](uint32_t begin, uint32_t end) {
+        const uint32_t phase = (uint32_t)(excl + begin) & 31u;
+        for (uint32_t kk = threadIdx.x; kk < end - begin + phase; kk += kThreads * U) {
+            uint32_t x[U], base[U];
+            int32_t piece[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t r = kk + (uint32_t)(u * kThreads) - phase;      // (wraps below phase)
+                const uint32_t k = r < end - begin ? begin + r : begin;
+                uint32_t s = 0;
+                for (int32_t h = group >> 1; h >= 1; h >>= 1) s += s_tile[s + (uint32_t)h].start <= k ? (uint32_t)h : 0u;
+                const EmitTile t = s_tile[s];
+                base[u] = t.base;
+                piece[u] = t.piece;
+                x[u] = gload_u32(from + (size_t)s * (uint32_t)slot_size + (k - t.start));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t r = kk + (uint32_t)(u * kThreads) - phase;
+                if (r < end - begin) write(excl + begin + r, x[u], base[u], piece[u]);
+            }
+        }
+    };
+    if (!s_over) {
+        uint32_t all = s_tile[group].start, done = 0;
+        if (group == 1 && (uint32_t)slot_size >= (uint32_t)kThreads) {
+            done = all < (uint32_t)kThreads ? all : (uint32_t)kThreads;
+            if (threadIdx.x < done) write(excl + threadIdx.x, early, s_tile[0].base, s_tile[0].piece);
+        }
+        if (all > done) copy(done, all);
+        return;
+    }
+    for (int32_t i = 0; i < n; ++i) {
+        const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tile[i].start);
+        const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tile[i + 1].start);
+        if (end - begin > (uint32_t)slot_size) {
+            __syncthreads();                                   // s_before and the tile before's s_entry have been read
+            emit_read<NEW_F32, REFRESH, ARITH, 2, false>(a, t0 + i, excl + begin, [](const TileCtx &) { return 0u; }, s_entry,
+                                                         s_was, s_before, s_cnt);
+        } else if (end > begin) {
+            copy(begin, end);
         }
     }
 }
@@ -2508,8 +2712,21 @@ static EncodeKernel encode_variant(int new_is_f32, int refresh, int arith) {
     return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
 }
 
-typedef void (*CountKernel)(EncodeArgs, uint32_t *);
-typedef void (*EmitKernel)(EncodeArgs, const uint32_t *);
+typedef void (*StageKernel)(EncodeArgs, uint16_t *, uint32_t *, int32_t, int32_t);
+typedef void (*EmitKernel)(EncodeArgs, const uint16_t *);
+typedef void (*EmitStagedKernel)(EncodeArgs, const uint16_t *, const uint32_t *, int32_t, int32_t);
+static StageKernel stage_variant(int new_is_f32, int refresh, int arith) {
+    static const StageKernel table[8] = {stage_tiles_kernel<0, 0, 0>, stage_tiles_kernel<1, 0, 0>, stage_tiles_kernel<0, 1, 0>,
+                                         stage_tiles_kernel<1, 1, 0>, stage_tiles_kernel<0, 0, 1>, stage_tiles_kernel<1, 0, 1>,
+                                         stage_tiles_kernel<0, 1, 1>, stage_tiles_kernel<1, 1, 1>};
+    return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+}
+static EmitStagedKernel emit_staged_variant(int new_is_f32, int refresh, int arith) {
+    static const EmitStagedKernel table[8] = {emit_staged_kernel<0, 0, 0>, emit_staged_kernel<1, 0, 0>, emit_staged_kernel<0, 1, 0>,
+                                              emit_staged_kernel<1, 1, 0>, emit_staged_kernel<0, 0, 1>, emit_staged_kernel<1, 0, 1>,
+                                              emit_staged_kernel<0, 1, 1>, emit_staged_kernel<1, 1, 1>};
+    return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+}
 static EmitKernel emit_variant(int new_is_f32, int refresh, int arith) {
     static const EmitKernel table[8] = {emit_tiles_kernel<0, 0, 0>, emit_tiles_kernel<1, 0, 0>, emit_tiles_kernel<0, 1, 0>,
                                         emit_tiles_kernel<1, 1, 0>, emit_tiles_kernel<0, 0, 1>, emit_tiles_kernel<1, 0, 1>,
@@ -2595,20 +2812,61 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
     }
 }
 
-// Updates that go in two launches (count_tiles_kernel, emit_tiles_kernel) instead of tickets: those that read
-// at most this much.  The line lies where they win whether the inputs are in the caches or have to come from
-// memory (512 MB written elsewhere before each call), at any density, payload, refresh or not.  One matrix of 4096
-// columns, us per call, two launches / tickets:
-//                               32 MiB        64 MiB        96 MiB        128 MiB
-//   bf16, 1 %, cached           12.2 / 33.7   22.6 / 40.0   34.1 / 47.9   45.6 / 52.5
-//   bf16, 1 %, from memory      17.1 / 32.3   27.9 / 40.5   39.9 / 48.0   51.3 / 52.7
-//   bf16, 30 %, from memory     24.7 / 37.0   41.6 / 47.9   58.4 / 55.7   75.3 / 70.4
-//   fp32, 5 %, from memory      20.9 / 29.9   33.6 / 40.5   43.9 / 45.0   56.7 / 51.1
-//   refresh, bf16, 5 %, memory  19.8 / 34.9   35.4 / 45.9   51.1 / 54.6
-//   refresh, fp32, 10 %, memory 23.0 / 33.6   39.4 / 45.4   52.6 / 50.5
-// At 88 MiB the first cases turn (bf16 30 % 54.4 / 54.1, eight shards of fp32 at 10 % 48.6 / 46.4).
-constexpr int64_t kTwoLaunchBytes = (int64_t)80 << 20;
-static_assert(kTwoLaunchBytes / 4 < (int64_t)1 << 31, "emit_tiles_kernel adds up entries in 32 bits");
+// Updates that go in two launches instead of by tickets, and how.  What bounds the ticket kernel on updates that are not
+// large is its counter (14 ns a ticket, two requests a workgroup), the way from a count to its prefix and the launches around
+// it, about 40 us; the staged form pays for writing and reading every entry once more instead.  One matrix of 4096 columns,
+// us per call, inputs (and the slots) in the caches / 512 MB written elsewhere before each call:
+//                  read again     staged        tickets (with nothing read twice)
+//   bf16  10 MiB   6.7 / 10.6     7.0 / 10.3    33                             1 %
+//         16 MiB   7.9 / 12.2     7.4 / 11.3    33                             1 %
+//         64 MiB   21.9 / 28.2    14.3 / 18.9   40 / 41                        1 %
+//         64 MiB   26.0 / 34.5    18.9 / 26.7   42 / 43                        10 %
+//         64 MiB   33.1 / 41.9    38.6 / 46.3   48 / 48                        30 % (past the slots: read again)
+//        192 MiB                  37 / 41       65 / 65                        1 %
+//        450 MiB                  84 / 91       113 / 112                      1 %
+//        450 MiB                  104 / 120     123 / 123                      5 %
+//        600 MiB                  134 / 157     154 / 150                      5 %
+//       1200 MiB                  222 / 243     246 / 242                      1 %
+//   fp32  600 MiB                 131 / 140     150 / 149                      3 %
+//   arithmetic, bf16 1000 MiB     229 / 259     258 / 259                      5 %
+//               bf16 2000 MiB     365 / 399     430 / 432                      1 %
+//   refresh,    bf16 1000 MiB     277 / 314     322 / 319                      5 %
+// So: read again below 12 MiB, where the second reading comes out of the caches at once, and where the slots do not hold
+// the tiles; staged up to kStagedMib of the density, half as much again for arithmetic payloads and refresh; by tickets
+// above.  Without a density (no bucket checked yet, buckets with room for everything) 80 MiB are the line for all.
+// Slots have to hold twice what is expected of a tile (densities differ between the rows of a model), below 80 MiB 1.25
+// times.  group: a workgroup of the second launch takes more tiles the more there are and the less they hold (1 % / 5 %,
+// 1, 2, 4, 8, 16 tiles: 64 MiB 15.0 14.4 14.8 15.0 16.6 / 16.7 17.4 18.7 21.6 27.5; 512 MiB 114 103 98 96 96 / 130 120 112 114
+// 114).  stream: slots written non-temporal from 192 MiB on (512 MiB, 1 %: 95.7 / 102.4 without, 95.8 / 100.1 with; 1 GiB
+// 188.6 / 207.9 and 186.5 / 191.4; 64 MiB 14.9 / 19.4 and 15.3 / 19.8).
+enum : int { kTickets = 0, kStaged = 1, kReadAgain = 2 };
+struct TwoLaunches {
+    int form, group_log2, stream;
+};
+constexpr int64_t kReadAgainMib = 12, kUnknownMib = 80, kStreamMib = 192;
+constexpr struct {
+    int32_t below_ppm;
+    int64_t mib;
+} kStagedMib[] = {{12000, 1200}, {32000, 700}, {55000, 480}, {85000, 400}, {125000, 300}};
+static_assert((kUnknownMib << 20) / 4 < (int64_t)1 << 31 && kStageMostTiles * kTile < (int64_t)1 << 31,
+              "the second launch adds up entries in 32 bits");
+static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh, int arith, int32_t ppm) {
+    const int64_t bytes = (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4), mib = (bytes + (1 << 20) - 1) >> 20;
+    const int64_t expected = ppm < 0 ? 0 : (int64_t)ppm * kTile / 1000000;
+    TwoLaunches t = {kTickets, 0, mib >= kStreamMib};
+    if (mib <= kUnknownMib) {
+        t.form = mib <= kReadAgainMib || a.slot_size < kThreads || expected * 5 / 4 + 64 > a.slot_size ? kReadAgain : kStaged;
+    } else if (ppm >= 0 && expected * 2 + 64 <= a.slot_size) {
+        for (const auto &line : kStagedMib)
+            if (ppm < line.below_ppm) {
+                if (mib <= (refresh || arith ? line.mib * 3 / 2 : line.mib)) t.form = kStaged;
+                break;
+            }
+    }
+    const int g = (mib >= 32) + (mib >= 96) + (mib >= 192) + (mib >= 384) - (ppm > 30000) - (ppm > 80000);
+    t.group_log2 = g > 0 ? g : 0;
+    return t;
+}
 static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, hipStream_t st) {
     if (refresh && refresh->n > 0)
         hipLaunchKernelGGL(refresh_replicated_kernel, dim3(8, refresh->n > 1024 ? 1024 : refresh->n), dim3(256), 0, st,
@@ -2620,14 +2878,22 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
                   int worker_cap, int order, bool order_free, int32_t ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
-    if (order_free && worker_cap == 0 && (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4) <= kTwoLaunchBytes) {
-        uint32_t *counts = reinterpret_cast<uint32_t *>(a.tile_desc);
-        const CountKernel count = new_is_f32 ? count_tiles_kernel<1> : count_tiles_kernel<0>;
-        hipLaunchKernelGGL(count, dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
-        hipLaunchKernelGGL(emit_variant(new_is_f32, refresh ? 1 : 0, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a,
-                           counts);
-        launch_refresh_replicated(a, new_is_f32, refresh, st);
-        return (int)hipGetLastError();
+    if (order_free && worker_cap == 0) {
+        const int r = refresh ? 1 : 0;
+        const TwoLaunches two = two_launches(a, new_is_f32, r, arith, ppm);
+        if (two.form != kTickets) {
+            uint16_t *counts = reinterpret_cast<uint16_t *>(a.tile_desc);
+            const int32_t slot = two.form == kStaged ? a.slot_size : 0;
+            hipLaunchKernelGGL(stage_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts, a.slots,
+                               slot, two.stream);
+            if (two.form == kStaged)
+                hipLaunchKernelGGL(emit_staged_variant(new_is_f32, r, arith), dim3(a.n_blocks * (kBlock >> two.group_log2)),
+                                   dim3(kThreads), 0, st, a, counts, a.slots, slot, two.group_log2);
+            else
+                hipLaunchKernelGGL(emit_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
+            launch_refresh_replicated(a, new_is_f32, refresh, st);
+            return (int)hipGetLastError();
+        }
     }
     encode_walk(order, ppm, arith, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;

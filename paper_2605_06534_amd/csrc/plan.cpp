@@ -354,11 +354,19 @@ extern "C" rose_status rose_plan_n_tiles(const rose_plan *p, int64_t *n_tiles) {
     return ROSE_OK;
 }
 
+size_t rose::workspace_need(const rose_plan *p) {
+    // header + one 64-bit descriptor per tile + one per block of tiles
+    return kWsHeaderBytes + (p->tile_piece.size() + (size_t)p->block_first[p->n_buckets]) * sizeof(unsigned long long);
+}
+
 extern "C" rose_status rose_plan_workspace_bytes(const rose_plan *p, size_t *bytes) {
     if (!p || !bytes) return ROSE_ERR_ARG;
-    // header + one 64-bit descriptor per tile + one per block of tiles
-    *bytes = rose::kWsHeaderBytes +
-             (p->tile_piece.size() + (size_t)p->block_first[p->n_buckets]) * sizeof(unsigned long long);
+    *bytes = rose::workspace_need(p);
+    const size_t tiles = p->tile_piece.size();
+    if (tiles > 0 && tiles <= (size_t)rose::kStageMostTiles) {
+        const size_t all = (*bytes + 255) / 256 * 256 + tiles * rose::kStageSlot * sizeof(uint32_t);
+        *bytes = all < rose::kStageMostBytes ? all : rose::kStageMostBytes;
+    }
     return ROSE_OK;
 }
 

@@ -89,6 +89,8 @@ struct EncodeArgs {
     int32_t batch;                          // tiles per ticket
     uint32_t window_open;                   // clock ticks of a period in which bucket stores go out (0: always)
     unsigned int *ticket;                   // workspace header: the ticket counter
+    uint32_t *slots;                        // one slot of slot_size entries per tile (see stage_tiles_kernel)
+    int32_t slot_size;                      // 0: the workspace has no room for slots
 };
 
 // Tiles of one chain are grouped in blocks of kBlock; a serving wave gathers a block's counts
@@ -111,8 +113,14 @@ constexpr int kBatch = ROSE_BATCH, kBatchTimed = ROSE_BATCH_TIMED;
 constexpr size_t kWsAbortOff = 0;
 constexpr int kWsCarefulWord = 2;      // 32-bit word 2 of the header counts same-group ticket pairs (diagnostic)
 constexpr int kWsAheadWord = 3;        // 32-bit word 3: how often tiles were counted ahead of a wait (diagnostic)
+constexpr int kWsTilesWord = 4;        // 32-bit word 4: tiles of a launch without tickets, else 0
 constexpr size_t kWsTicketOff = 4096;
 constexpr size_t kWsHeaderBytes = 8192;
+// Behind them (at a multiple of 256 bytes): room for compacted entries, a slot per tile, of the plans that may be encoded
+// without tickets.  A call asks for the part in front only and uses what room there is.
+constexpr int64_t kStageMostTiles = 65536;               // 2 GiB read in bf16
+constexpr size_t kStageMostBytes = ROSE_STATIC_SCRATCH_BYTES;   // all of it together, so that the built-in scratch holds it
+constexpr int kStageSlot = 2016;                         // entries of a slot at most: 24 % of a tile, 8 KB of LDS a workgroup
 
 struct CopyArgs {
     const Piece *pieces;
@@ -211,3 +219,7 @@ struct rose_plan {
     mutable void *static_ws = nullptr;         // the library's built-in scratch on `device`
     mutable size_t static_ws_bytes = 0;
 };
+
+namespace rose {
+size_t workspace_need(const rose_plan *p);     // bytes of scratch that an encode cannot do without
+}
