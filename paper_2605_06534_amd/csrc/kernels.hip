@@ -1566,14 +1566,22 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 //             them to the bucket.  A tile that holds more than its slot does parks nothing and is read again.
 //   read again   no slots: the second launch reads every tile a second time.
 // ---------------------------------------------------------------------------------------------
+// The header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one, and all tiles
+// were handed out (by the grid).
+__device__ __forceinline__ void write_header(const EncodeArgs &a) {
+    if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
+    if (threadIdx.x == kWsTilesWord) a.abort_flag[kWsTilesWord] = (uint32_t)a.n_tiles;
+    if (threadIdx.x == kWsTilesWord + 1) *a.ticket = (uint32_t)a.n_tiles;
+}
+
 constexpr int kGroupMost = 16;           // tiles a workgroup of the second launch copies out at most
 
-// Refresh: the lines of the tile in which anything changed, from registers.  Whole 64-byte lines, non-temporal (16 M
+// Refresh: the lines of the tile in which anything changed, from registers.  Whole 64-byte lines, or 128-byte ones where
+// changes are few (see encode_body), non-temporal (16 M
 // weights at 5 %, inputs from memory: 48.9 us with ordinary stores, 35.4 this way; with the inputs in the caches the same).
-__device__ __forceinline__ void refresh_tile(const TileCtx &c, uint32_t t_off, uint32_t total, const uint32_t (&mask)[kIters],
+__device__ __forceinline__ void refresh_tile(const TileCtx &c, uint32_t t_off, bool wide, const uint32_t (&mask)[kIters],
                                              const uint4 (&n)[kIters]) {
     uint16_t *ob = const_cast<uint16_t *>(c.old_base);
-    const bool wide = total <= (uint32_t)kRefreshWide;
 #pragma unroll
     for (int j = 0; j < kIters; ++j) {
         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
@@ -1642,18 +1650,13 @@ __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uin
         total += s_cnt[w];
     }
     if (threadIdx.x == 0) counts[tile] = (uint16_t)total;
-    if (tile == 0) {
-        // the header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one
-        if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
-        if (threadIdx.x == kWsTilesWord) a.abort_flag[kWsTilesWord] = (uint32_t)a.n_tiles;
-        if (threadIdx.x == kWsTilesWord + 1) *a.ticket = (uint32_t)a.n_tiles;      // handed out by the grid
-    }
+    if (tile == 0) write_header(a);
     total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
     if (total == 0 || total > (uint32_t)slot_size) return;
 #pragma unroll
     for (int j = 0; j < kIters; ++j) park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec, mask[j], o[j], n[j], wave_excl + rank[j], s_entry, s_was);
     if constexpr (REFRESH) {
-        if (!(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total, mask, n);
+        if (!(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total <= (uint32_t)kRefreshWide, mask, n);
     }
     __syncthreads();
     uint32_t *slot = slots + (size_t)tile * (uint32_t)slot_size;
@@ -1662,6 +1665,28 @@ __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uin
         if (stream) __builtin_nontemporal_store(entry, slot + k);
         else slot[k] = entry;
     }
+}
+
+// First launch, nothing parked.
+template <int NEW_F32>
+__global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uint16_t *counts) {
+    __shared__ uint32_t s_cnt[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const TileCtx c = tile_ctx(a, (int32_t)blockIdx.x);
+    uint4 o[kIters], n[kIters];
+    load_tile_pair<NEW_F32>(c, (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec, o, n);
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) cnt += __popc(nz16_mask(xor4(o[j], n[j])));
+    const uint32_t wave_cnt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(cnt), 63);
+    if (lane == 0) s_cnt[wave] = wave_cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int w = 0; w < kWaves; ++w) total += s_cnt[w];
+        counts[blockIdx.x] = (uint16_t)total;
+    }
+    if (blockIdx.x == 0) write_header(a);
 }
 
 // What the second launch needs of a tile besides its count.
@@ -1673,10 +1698,10 @@ struct EmitTile {
 
 // local index of the element at number `k` of a piece whose local indices come in strided runs (runs of one element
 // have no magic divisor: the quotient is the number itself)
-__device__ __forceinline__ uint32_t strided_local(const Piece *p, uint32_t k) {
-    const uint32_t run = (uint32_t)p->run;
-    const uint32_t q = run == 1u ? k : (__umulhi(k, p->magic) >> p->shift);
-    return (uint32_t)p->local_base + q * (uint32_t)p->lstride + (k - q * run);
+__device__ __forceinline__ uint32_t strided_local(const Piece &p, uint32_t k) {
+    const uint32_t run = (uint32_t)p.run;
+    const uint32_t q = run == 1u ? k : (__umulhi(k, p.magic) >> p.shift);
+    return (uint32_t)p.local_base + q * (uint32_t)p.lstride + (k - q * run);
 }
 
 // A tile read (again), compacted in LDS a PART-th of its waves at a time, written.  `before` is called while the loads
@@ -1687,7 +1712,6 @@ __device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64
                                           uint16_t *s_was, uint32_t *s_before, uint32_t *s_cnt) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const TileCtx c = tile_ctx(a, tile);
-    const BucketDev b = a.bucket[c.pc.shard];
     const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
     uint4 o[kIters], n[kIters];
     load_tile_pair<NEW_F32>(c, t_off, o, n);
@@ -1707,6 +1731,7 @@ __device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64
         excl += s_before[w];
         total += s_cnt[w];
     }
+    const BucketDev b = a.bucket[c.pc.shard];
     if (SEGMENTS && threadIdx.x == 0) {
         if ((c.pc.flags & kPieceFirst) && tile == c.pc.first_tile) b.seg_off[c.pc.tensor] = (int64_t)excl;
         if (tile == a.chain_first[c.pc.shard + 1] - 1) b.seg_off[a.n_tensors] = (int64_t)(excl + total);
@@ -1721,12 +1746,25 @@ __device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64
             if (part + w < wave) at0 += s_cnt[part + w];
             here += s_cnt[part + w];
         }
-        if (wave >= part && wave < part + kWaves / PARTS) {
+        if (PARTS == 1 || (wave >= part && wave < part + kWaves / PARTS)) {
 #pragma unroll
-            for (int j = 0; j < kIters; ++j) park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec, mask[j], o[j], n[j], at0 + rank[j], s_entry, s_was);
+            for (int j = 0; j < kIters; ++j) {
+                const uint32_t in_tile = t_off + (uint32_t)(j * 64) * kVec;
+                if constexpr (ARITH && PARTS == 1) {           // payloads of all elements: fewer steps one behind the other
+                    uint32_t esc8, m = mask[j], at = at0 + rank[j];
+                    const uint4 pay = arith_vec(o[j], n[j], &esc8);
+                    while (m) {
+                        const uint32_t e = __ffs(m) - 1;
+                        m &= m - 1;
+                        s_entry[at++] = ((in_tile + e) << 16) | pick16(pay, e) | ((esc8 >> e) << 31);
+                    }
+                } else {
+                    park_vector<ARITH>(in_tile, mask[j], o[j], n[j], at0 + rank[j], s_entry, s_was);
+                }
+            }
         }
         if constexpr (REFRESH) {
-            if (part == 0 && !(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total, mask, n);
+            if ((PARTS == 1 || part == 0) && !(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, false, mask, n);
         }
         __syncthreads();
         const uint32_t phase = (uint32_t)excl & 31u;           // lined up with the bucket's lines, see copy_out
@@ -1734,9 +1772,11 @@ __device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64
             const uint32_t k = kk - phase;
             const u64 pos = excl + k;
             if (kk >= phase && pos < (u64)b.capacity) {
-                const uint32_t entry = parked<ARITH>(k, s_entry, s_was);
+                const uint32_t entry = parked<(ARITH && PARTS > 1)>(k, s_entry, s_was);
                 uint32_t local = c.k_tile + ((entry >> 16) & (uint32_t)(kTile - 1));
-                local = dst_strided ? strided_local(a.pieces + c.piece, local) : (uint32_t)c.pc.local_base + local;
+                uint32_t q = 0;                                // (a piece with contiguous local indices: run 0 of a strided one)
+                if (dst_strided) q = c.pc.run == 1 ? local : (__umulhi(local, c.pc.magic) >> c.pc.shift);
+                local = (uint32_t)c.pc.local_base + q * (uint32_t)c.pc.lstride + (local - q * (uint32_t)c.pc.run);
                 b.idx[pos] = (int32_t)(local | (ARITH ? entry & 0x80000000u : 0u));
                 b.val[pos] = (uint16_t)entry;
             }
@@ -1762,14 +1802,12 @@ __device__ __forceinline__ uint32_t wave_share_of_counts(const uint16_t *counts,
 // Second launch, every tile read again: one workgroup a tile.
 template <int NEW_F32, int REFRESH, int ARITH>
 __global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, const uint16_t *counts) {
-    constexpr int PARTS = ARITH ? 2 : 1;
-    __shared__ uint32_t s_entry[kTile / PARTS];
-    __shared__ uint16_t s_was[ARITH ? kTile / PARTS : 1];
+    __shared__ uint32_t s_entry[kTile];
     __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
     const int32_t tile = (int32_t)blockIdx.x;
-    emit_read<NEW_F32, REFRESH, ARITH, PARTS, true>(
+    emit_read<NEW_F32, REFRESH, ARITH, 1, true>(
         a, tile, 0, [&](const TileCtx &c) { return wave_share_of_counts(counts, a.chain_first[c.pc.shard], tile); }, s_entry,
-        s_was, s_before, s_cnt);
+        nullptr, s_before, s_cnt);
 }
 
 // Second launch, staged: a workgroup copies out 2^group_log2 neighbouring tiles of one chain.
@@ -1835,7 +1873,7 @@ __global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, con
     auto write = [&](u64 pos, uint32_t entry, uint32_t base, int32_t piece) {
         if (pos >= (u64)b.capacity) return;
         uint32_t local = base + ((entry >> 16) & (uint32_t)(kTile - 1));
-        if (piece >= 0) local = strided_local(a.pieces + piece, local);
+        if (piece >= 0) local = strided_local(a.pieces[piece], local);
         __builtin_nontemporal_store((int32_t)(local | (ARITH ? entry & 0x80000000u : 0u)), b.idx + pos);
         __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
     };
@@ -2712,6 +2750,7 @@ static EncodeKernel encode_variant(int new_is_f32, int refresh, int arith) {
     return table[(new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
 }
 
+typedef void (*CountKernel)(EncodeArgs, uint16_t *);
 typedef void (*StageKernel)(EncodeArgs, uint16_t *, uint32_t *, int32_t, int32_t);
 typedef void (*EmitKernel)(EncodeArgs, const uint16_t *);
 typedef void (*EmitStagedKernel)(EncodeArgs, const uint16_t *, const uint32_t *, int32_t, int32_t);
@@ -2847,7 +2886,7 @@ constexpr int64_t kReadAgainMib = 12, kUnknownMib = 80, kStreamMib = 192;
 constexpr struct {
     int32_t below_ppm;
     int64_t mib;
-} kStagedMib[] = {{12000, 1200}, {32000, 700}, {55000, 480}, {85000, 400}, {125000, 300}};
+} kStagedMib[] = {{12000, 1200}, {22000, 850}, {32000, 700}, {55000, 480}, {85000, 400}, {125000, 300}};
 static_assert((kUnknownMib << 20) / 4 < (int64_t)1 << 31 && kStageMostTiles * kTile < (int64_t)1 << 31,
               "the second launch adds up entries in 32 bits");
 static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh, int arith, int32_t ppm) {
@@ -2883,14 +2922,16 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
         const TwoLaunches two = two_launches(a, new_is_f32, r, arith, ppm);
         if (two.form != kTickets) {
             uint16_t *counts = reinterpret_cast<uint16_t *>(a.tile_desc);
-            const int32_t slot = two.form == kStaged ? a.slot_size : 0;
-            hipLaunchKernelGGL(stage_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts, a.slots,
-                               slot, two.stream);
-            if (two.form == kStaged)
+            if (two.form == kStaged) {
+                hipLaunchKernelGGL(stage_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts, a.slots,
+                                   a.slot_size, two.stream);
                 hipLaunchKernelGGL(emit_staged_variant(new_is_f32, r, arith), dim3(a.n_blocks * (kBlock >> two.group_log2)),
-                                   dim3(kThreads), 0, st, a, counts, a.slots, slot, two.group_log2);
-            else
+                                   dim3(kThreads), 0, st, a, counts, a.slots, a.slot_size, two.group_log2);
+            } else {
+                const CountKernel count = new_is_f32 ? count_tiles_kernel<1> : count_tiles_kernel<0>;
+                hipLaunchKernelGGL(count, dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
                 hipLaunchKernelGGL(emit_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
+            }
             launch_refresh_replicated(a, new_is_f32, refresh, st);
             return (int)hipGetLastError();
         }

@@ -152,3 +152,13 @@ def test_lines(mib, seen, staged):
     R.delta_encode(plan, tab, tab, R.BF16, [b], ws)
     assert R.bucket_check(plan, b) == 0
     assert int(ws.view(torch.int32)[4]) == (plan.n_tiles() if staged else 0)
+
+
+@pytest.mark.parametrize("what", ["arith", "refresh"])
+@pytest.mark.parametrize("run,tp,p", [(765, 3, 0.02), (7, 2, 0.5), (8, 1, 1.0)])
+def test_read_again(run, tp, p, what):
+    """Below the smallest staged update: every tile is read twice, payloads are formed of all elements."""
+    print("case: read again run=%d tp=%d p=%g %s" % (run, tp, p, what), flush=True)
+    c = make(6, tp, run, p, run + 1)
+    CHECKS[what](c)
+    assert tiles_without_tickets(c) == c.plan.n_tiles()
