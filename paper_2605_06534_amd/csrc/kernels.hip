@@ -26,8 +26,14 @@ __device__ __forceinline__ uint32_t rne_bf16(uint32_t u) {
     return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? ((u >> 16) | 0x0040u) : r;
 }
 
+// Two at a time with the conversion instruction: the same patterns as rne_bf16 for every one of the 2^32 inputs in
+// either half, NaNs and subnormals included.  (In integer steps this was 190 of the 780 vector instructions that the fp32
+// ticket kernel spends on a tile and wave: two 32B-style layers, 1.6 %: 2.69 ms, 2.64 this way; with arithmetic payloads
+// 2.98 and 2.79; 2 M weights 8.2 and 7.4 us.)
 __device__ __forceinline__ uint32_t pack_rne(uint32_t lo, uint32_t hi) {
-    return (rne_bf16(lo) & 0xFFFFu) | (rne_bf16(hi) << 16);
+    uint32_t r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(__uint_as_float(lo)), "v"(__uint_as_float(hi)));
+    return r;
 }
 
 // 8-bit mask of the 16-bit lanes of x that are non-zero (bit e = element e, little endian).
