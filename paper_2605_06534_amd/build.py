@@ -51,7 +51,7 @@ def check_reserved_vgpr(extra=()):
     if set(bodies) != {(f, r, a) for f in (0, 1) for r in (0, 1) for a in (0, 1)}:
         raise RuntimeError("not all eight encode kernels were found in the assembly: %s" % sorted(bodies))
     for (f32, refresh, arith), body in sorted(bodies.items()):
-        reg = 255 if (f32 and refresh and arith) else 167 if (f32 or (refresh and arith)) else 127
+        reg = 255 if (f32 and refresh and arith) else 167 if (f32 or arith) else 127
         budget, uses, what = reg + 1, 0, "encode_kernel<%d, %d, %d>" % (f32, refresh, arith)
         for line in body:
             code = line.split(";")[0]

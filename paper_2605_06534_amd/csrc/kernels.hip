@@ -98,6 +98,14 @@ __device__ __forceinline__ uint32_t arith_pair(uint32_t o, uint32_t n, uint32_t 
     const uint32_t take_new = b * 0xFFFFu;              // 0xFFFF in the halves that escape
     return (n & take_new) | (d & ~take_new);
 }
+// the same for one element (patterns in the low halves)
+__device__ __forceinline__ uint32_t arith_one(uint32_t o, uint32_t n, bool *escapes) {
+    const float was = __uint_as_float(o << 16);
+    const uint32_t d = pack_bf16_pair(__uint_as_float(n << 16) - was, 0.0f);
+    const uint32_t back = pack_bf16_pair(was + __uint_as_float(d << 16), 0.0f);
+    *escapes = back != n || (d & 0x7FFFu) > 0x7F80u;
+    return *escapes ? n : d;
+}
 // the same for a vector of eight; esc8 bit e = element e escapes
 __device__ __forceinline__ uint4 arith_vec(uint4 o, uint4 n, uint32_t *esc8) {
     uint32_t b0, b1, b2, b3;
@@ -507,6 +515,7 @@ __device__ __forceinline__ void serve_blocks(const EncodeArgs &a, int32_t server
 #endif
 constexpr int kRing = ROSE_RING;        // entries parked per workgroup (power of two)
 constexpr int kQueue = ROSE_QUEUE;      // tiles parked per workgroup (<= 64)
+static_assert(kRing >= kTile, "a tile's entries fit the ring, however many they are");
 static_assert((kRing & (kRing - 1)) == 0 && (kQueue & (kQueue - 1)) == 0 && kQueue <= 64,
               "ring and queue sizes must be powers of two, the queue at most a wave");
 
@@ -775,12 +784,22 @@ __device__ __forceinline__ uint32_t vector_ranks(const uint32_t (&mask)[kIters],
     return wave_total;
 }
 
+// Entry k as it is written: an arithmetic payload is formed here, of the compacted entries only.
+template <int ARITH>
+__device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, const uint16_t *s_was) {
+    const uint32_t entry = s_entry[k];
+    if constexpr (!ARITH) return entry;
+    bool escapes;
+    const uint32_t payload = arith_one(s_was[k], entry & 0xFFFFu, &escapes);
+    return (entry & 0x7FFF0000u) | payload | (escapes ? 0x80000000u : 0u);
+}
+
 template <int NEW_F32, int REFRESH, int ARITH>
 __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     // register class, see ticket_request
-    constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || (REFRESH && ARITH)) ? 1 : 0;
-    __shared__ uint32_t s_ring[kRing];      // an entry: offset inside its tile (13 bits) << 16 | value;
-                                            // bit 31: the entry escapes (arithmetic payload only)
+    constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
+    __shared__ uint32_t s_ring[kRing];      // an entry: offset inside its tile (13 bits) << 16 | new pattern
+    __shared__ uint16_t s_was[ARITH ? kRing : 1];    // arithmetic payload: the old patterns, from which it is formed
     __shared__ uint32_t s_wave_total[2][kWaves];
     __shared__ u64 s_excl[2][kQueue];       // prefixes of the tiles an iteration copies out, oldest first
     __shared__ u64 s_excl_sync[kQueue];     // the same for a blocking drain
@@ -795,7 +814,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     __shared__ int32_t s_ok, s_ready;
     __shared__ int32_t s_ticket[2], s_ticket_sync;
     __shared__ uint32_t s_count_only[kWaves];
-    __shared__ u64 s_direct_excl;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if ((int32_t)blockIdx.x < a.n_server_wgs) {
@@ -905,7 +923,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 const uint32_t k = kk - phase;         // (wraps below phase: caught by the first test)
                 const u64 pos = excl + k;
                 if (kk >= phase && pos < (u64)b.capacity) {
-                    const uint32_t entry = s_ring[(off + k) & (kRing - 1)];
+                    const uint32_t entry = parked<ARITH>((off + k) & (kRing - 1), s_ring, s_was);
                     const uint32_t base = k < c1 ? b0 : k < c2 ? b1 : k < c3 ? b2 : b3;
                     uint32_t local = base + (ARITH ? (entry >> 16) & (uint32_t)(kTile - 1) : entry >> 16);
                     if (piece >= 0) {                  // base is the tile's first element number here
@@ -1103,8 +1121,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         // ---- (a) change masks ----
         const uint32_t k_wave = cur.k_tile + (uint32_t)wave * kWaveSpan;
         uint4 nv[kIters];                              // the new patterns
-        uint4 pv[ARITH ? kIters : 1];                  // arithmetic payloads (difference, or new where it escapes)
-        uint32_t esc_all = 0;                          // bit 8 j + e: element e of vector j escapes
+        uint4 ov[ARITH ? kIters : 1];                  // the old ones
         uint32_t mask[kIters];
         // Always taken from the load registers, also for a tile that has no 128-bit loads (its
         // result is replaced below): this way every path consumes what was loaded, and the
@@ -1113,11 +1130,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         for (int j = 0; j < kIters; ++j) {
             nv[j] = raw_to_bf16(raw_new, j);
             mask[j] = nz16_mask(xor4(raw_old.v[j], nv[j]));
-            if constexpr (ARITH) {
-                uint32_t esc8;
-                pv[j] = arith_vec(raw_old.v[j], nv[j], &esc8);
-                esc_all |= esc8 << (8 * j);
-            }
+            if constexpr (ARITH) ov[j] = raw_old.v[j];
         }
         // pin the above here: the load registers are dead from this point on, whatever the
         // scheduler would prefer
@@ -1126,8 +1139,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             asm volatile("" : "+v"(mask[j]), "+v"(nv[j].x), "+v"(nv[j].y), "+v"(nv[j].z), "+v"(nv[j].w));
         if constexpr (ARITH) {
 #pragma unroll
-            for (int j = 0; j < kIters; ++j) asm volatile("" : "+v"(pv[j].x), "+v"(pv[j].y), "+v"(pv[j].z), "+v"(pv[j].w));
-            asm volatile("" : "+v"(esc_all));
+            for (int j = 0; j < kIters; ++j) asm volatile("" : "+v"(ov[j].x), "+v"(ov[j].y), "+v"(ov[j].z), "+v"(ov[j].w));
         }
         // (the rare cases are marked as such: laid out in line they cost the fp32 kernels 2 % of an update of 67 M
         // elements)
@@ -1143,12 +1155,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             // any lane has two, and the tile waits for one round of loads.
             if (__builtin_expect((cur.vec & 4u) != 0, 0)) {
                 const TileCtx c = tile_ctx(a, __builtin_amdgcn_readfirstlane(tile));
-                uint32_t todo = 0;
+                uint32_t todo = 0, masks = 0;          // (the four masks in one register: this loop needs many)
 #pragma unroll
                 for (int j = 0; j < kIters; ++j) {
                     const uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
                     uint32_t q;
                     if (split_left(c.pc, k, &q) < (uint32_t)kVec && k + kVec <= cur.limit) todo |= 1u << j;
+                    masks |= mask[j] << (8 * j);
                 }
 #pragma unroll 1
                 while (todo) {
@@ -1159,22 +1172,18 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                     const int64_t e = split_tail_at(c.pc, q, left);
                     const uint4 o = gload16(c.old_base + e);
                     const uint4 n = load_new_vec<NEW_F32>(c.new_base, e);
-                    const uint32_t keep = (1u << left) - 1u, m = nz16_mask(xor4(o, n)) & ~keep;
-                    uint32_t esc8 = 0;
-                    uint4 pay = n;
-                    if constexpr (ARITH) pay = arith_vec(o, n, &esc8);
+                    const uint32_t tail = 0xFFu & ~((1u << left) - 1u);
+                    masks = (masks & ~(tail << (8 * js))) | ((nz16_mask(xor4(o, n)) & tail) << (8 * js));
 #pragma unroll
                     for (int jj = 0; jj < kIters; ++jj) {
-                        if ((uint32_t)jj == js) {
-                            mask[jj] = (mask[jj] & keep) | m;
-                            nv[jj] = split_merge(nv[jj], n, left);
-                            if constexpr (ARITH) {
-                                pv[jj] = split_merge(pv[jj], pay, left);
-                                esc_all = (esc_all & ~((0xFFu & ~keep) << (8 * jj))) | ((esc8 & ~keep) << (8 * jj));
-                            }
-                        }
+                        // (a vector that is not meant keeps all its elements: no branch, hence no second set of registers)
+                        const uint32_t l = (uint32_t)jj == js ? left : (uint32_t)kVec;
+                        nv[jj] = split_merge(nv[jj], n, l);
+                        if constexpr (ARITH) ov[jj] = split_merge(ov[jj], o, l);
                     }
                 }
+#pragma unroll
+                for (int j = 0; j < kIters; ++j) mask[j] = (masks >> (8 * j)) & 0xFFu;
             }
             // a piece whose length is not a multiple of 8: the one vector that straddles its end
             if (__builtin_expect(cur.limit != 0xFFFFFFFFu && (cur.limit & (kVec - 1)), 0)) {
@@ -1185,18 +1194,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                     uint4 o = load_vec_general<0>(c.old_base, c.pc, ks);
                     uint4 n = load_vec_general<NEW_F32>(c.new_base, c.pc, ks);
                     uint32_t m = nz16_mask(xor4(o, n));
-                    uint32_t esc8 = 0;
-                    uint4 pay = n;
-                    if constexpr (ARITH) pay = arith_vec(o, n, &esc8);
 #pragma unroll
                     for (int jj = 0; jj < kIters; ++jj) {
                         if ((uint32_t)jj == js) {
                             nv[jj] = n;
                             mask[jj] = m;
-                            if constexpr (ARITH) {
-                                pv[jj] = pay;
-                                esc_all = (esc_all & ~(0xFFu << (8 * jj))) | (esc8 << (8 * jj));
-                            }
+                            if constexpr (ARITH) ov[jj] = o;
                         }
                     }
                 }
@@ -1212,18 +1215,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 uint4 o = load_vec_general<0>(c.old_base, c.pc, k);
                 uint4 n = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
                 uint32_t m = nz16_mask(xor4(o, n));
-                uint32_t esc8 = 0;
-                uint4 pay = n;
-                if constexpr (ARITH) pay = arith_vec(o, n, &esc8);
 #pragma unroll
                 for (int jj = 0; jj < kIters; ++jj) {
                     if (jj == j) {
                         nv[jj] = n;
                         mask[jj] = m;
-                        if constexpr (ARITH) {
-                            pv[jj] = pay;
-                            esc_all = (esc_all & ~(0xFFu << (8 * jj))) | (esc8 << (8 * jj));
-                        }
+                        if constexpr (ARITH) ov[jj] = o;
                     }
                 }
             }
@@ -1306,8 +1303,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 
         // Room to park?  Making room may wait, and nothing may wait while a ticket is on its way
         // (it could be of the current ticket's group): take it in first.
-        const bool big = tile_total > (uint32_t)kRing;
-        if (ticket_out && !walk.careful && (big || q_len == kQueue || ring_used + tile_total > (uint32_t)kRing))
+        if (ticket_out && !walk.careful && (q_len == kQueue || ring_used + tile_total > (uint32_t)kRing))
             settle_ticket();
         // A same-group ticket has just been accepted: nothing may wait now.  This tile is not
         // parked; it is walked again after the count-only pass at the end of the iteration.
@@ -1321,7 +1317,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         bool dense = false;
 #if ROSE_COUNT_AHEAD
         // the next tile is of the same ticket: not all of the ticket is counted
-        const bool mid_ticket = !walk.careful && !cur_redo && !walk.redo && !big && next_state == kWalkTile &&
+        const bool mid_ticket = !walk.careful && !cur_redo && !walk.redo && next_state == kWalkTile &&
                                 walk.ticket == ticket_before;
         if (a.adjacent) {
             // A ticket's tiles are neighbours, so its uncounted tiles may lie in the very block whose
@@ -1336,17 +1332,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         }
 #endif
         const bool skip = walk.careful || dense;
-        if (skip) {
-        } else if (big) {
-            if (q_len > 0) drain(kDrainAll);
-        } else {
+        if (!skip) {
             while (q_len == kQueue || ring_used + tile_total > (uint32_t)kRing) drain(kDrainOldest);
         }
 
         const int32_t chain_last = a.chain_first[cur.shard + 1] - 1;
         const int32_t seg = cur.seg;
-        if (skip) {
-        } else if (!big) {
+        if (!skip) {
             // park the entries: ring slot = ring_head + rank inside the tile
             const uint32_t base = ring_head + wave_excl;
 #pragma unroll
@@ -1357,11 +1349,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 while (m && !(ROSE_DIAG & 8)) {
                     const uint32_t e = __ffs(m) - 1;
                     m &= m - 1;
-                    if constexpr (ARITH)
-                        s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(pv[j], e) & 0xFFFFu) |
-                                                     ((esc_all >> (8 * j + e)) << 31);
-                    else
-                        s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu);
+                    s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu);
+                    if constexpr (ARITH) s_was[slot & (kRing - 1)] = (uint16_t)pick16(ov[j], e);
                     ++slot;
                 }
             }
@@ -1382,65 +1371,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             ++q_len;
             ring_used += tile_total;
             ring_head = (ring_head + tile_total) & (kRing - 1);
-        } else {
-            // more entries than the ring holds: wait for the prefix now, write from registers
-            if (wave == 0) {
-                bool ok = true;
-                u64 excl = 0;
-#if !(ROSE_DIAG & 1)
-                unsigned int spins = 0;
-                for (;;) {
-                    u64 v = desc_load(a.tile_desc + tile);
-                    if ((v >> kStatusShift) == kStatusPrefix) {
-                        excl = v & kValueMask;
-                        break;
-                    }
-                    if (!keep_waiting(a.abort_flag, spins, lane)) {
-                        ok = false;
-                        break;
-                    }
-                }
-#endif
-                if (lane == 0) {
-                    s_direct_excl = excl;
-                    s_ok = ok ? 1 : 0;
-                }
-            }
-            __syncthreads();
-            const u64 tile_excl = s_direct_excl;
-            const BucketDev b = a.bucket[cur.shard];
-            const Piece big_pc = load_piece(a.pieces + (cur.piece >= 0 ? cur.piece : 0));
-            if (s_ok && !(ROSE_DIAG & 2)) {
-                if (threadIdx.x == 0) {
-                    if (seg >= 0) b.seg_off[seg] = (int64_t)tile_excl;
-                    if (tile == chain_last) b.seg_off[a.n_tensors] = (int64_t)(tile_excl + tile_total);
-                }
-                const u64 wave_base = tile_excl + wave_excl;
-#pragma unroll
-                for (int j = 0; j < kIters; ++j) {
-                    uint32_t m = mask[j];
-                    u64 pos = wave_base + rank[j];
-                    // cur.out_base + offset is the local index, or (strided local indices) the
-                    // element number that the piece maps to one
-                    const uint32_t local0 = cur.out_base + t_off + (uint32_t)(j * 64) * kVec;
-                    while (m) {
-                        const uint32_t e = __ffs(m) - 1;
-                        m &= m - 1;
-                        if (pos < (u64)b.capacity) {
-                            uint32_t local = cur.piece >= 0 ? dst_index(big_pc, local0 + e, false) : local0 + e;
-                            if constexpr (ARITH) {
-                                local |= (esc_all >> (8 * j + e)) << 31;
-                                b.val[pos] = (uint16_t)pick16(pv[j], e);
-                            } else {
-                                b.val[pos] = (uint16_t)pick16(nv[j], e);
-                            }
-                            b.idx[pos] = (int32_t)local;
-                        }
-                        ++pos;
-                    }
-                }
-            }
-            __syncthreads();                           // s_direct_excl / s_ok are reused
         }
 
         // Sender refresh (W_{t-1} <- W_t for what this tile covers): only now that the tile is known
@@ -1542,9 +1472,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 }
 
 // The instantiations get their own register budgets: 4 waves per SIMD (128 VGPRs) fit the bf16
-// kernels without spills; the fp32-master kernels hold twice the raw data, and the kernel that both
-// refreshes and forms arithmetic payloads keeps new values and payloads side by side: those get 3
-// (the one that does all three at once: 2).
+// kernels without spills; the fp32-master kernels hold twice the raw data, and those that form arithmetic
+// payloads keep old and new patterns side by side (and half as much LDS again): those get 3
+// (the one that does all three at once: 2).  Arithmetic payloads are formed of the compacted entries: formed of every
+// element, as this kernel did with 4 waves, they are 400 instructions a wave and tile for some 30 that are needed (eight
+// 7B-style layers, TP4, 1 / 5 / 10 %: 1428 / 1603 / 1822 us, this way 1311 / 1516 / 1733; with refresh 2 % 2050 and
+// 1996; two 32B-style layers of fp32 masters, 1.6 / 5 %: 2772 / 3059 and 2645 / 2972, with refresh 3939 and 3688).
 // REFRESH = 1 also writes the new bf16 values over the old ones; ARITH = 1 emits arithmetic payloads.
 template <int NEW_F32, int REFRESH, int ARITH> __global__ void encode_kernel(EncodeArgs a);
 #define ROSE_ENCODE_KERNEL(F32, REFRESH, ARITH, WAVES, VGPRS)                                                         \
@@ -1555,7 +1488,7 @@ template <int NEW_F32, int REFRESH, int ARITH> __global__ void encode_kernel(Enc
     }
 ROSE_ENCODE_KERNEL(0, 0, 0, 4, kNumVgpr0)
 ROSE_ENCODE_KERNEL(0, 1, 0, 4, kNumVgpr0)
-ROSE_ENCODE_KERNEL(0, 0, 1, 4, kNumVgpr0)
+ROSE_ENCODE_KERNEL(0, 0, 1, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(0, 1, 1, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 0, 0, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 1, 0, 3, kNumVgpr1)
@@ -1620,17 +1553,6 @@ __device__ __forceinline__ void park_vector(uint32_t in_tile, uint32_t m, uint4 
         ++at;
     }
 }
-// Entry k as it is written: an arithmetic payload is formed here, of the compacted entries only (the ticket kernel, which
-// has no registers for old and new patterns side by side, forms it of every element: 320 instructions more a wave and tile).
-template <int ARITH>
-__device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, const uint16_t *s_was) {
-    const uint32_t entry = s_entry[k];
-    if constexpr (!ARITH) return entry;
-    uint32_t esc;
-    const uint32_t pay = arith_pair(s_was[k], entry & 0xFFFFu, &esc);
-    return (entry & 0x7FFF0000u) | (pay & 0xFFFFu) | ((esc & 1u) << 31);
-}
-
 template <int NEW_F32, int REFRESH, int ARITH>
 __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uint16_t *counts, uint32_t *slots, int32_t slot_size,
                                                                int32_t stream) {
@@ -2830,8 +2752,7 @@ int static_scratch(void **ptr, size_t *bytes) {
 // 41 us the bucket stores may go out (0: always).  ppm: changed elements per million, -1 unknown.
 //   timed       4 tiles, 10 us.  The entries of a period fit the ring up to about 4 %.
 //   neighbours  Denser: 3 tiles, whose prefixes are ready sooner and leave the ring room, and longer windows, so
-//               that less waits: up to 5 % 15 us; above, and for arithmetic payloads (whose kernel is busier
-//               between its loads), 20 us.
+//               that less waits: up to 5 % 15 us, above 20 us.
 // 7B-style workload, one process, same buffers, ms (always = neighbours with no windows, 3 tiles):
 //               4 %   4.5 %   5 %   5.5 %   6 %   7 %   8 %   10 %   30 %
 //   always      5.11  5.13    5.19  5.21    5.27  5.32  5.52  6.34   10.75
@@ -2839,12 +2760,13 @@ int static_scratch(void **ptr, size_t *bytes) {
 //   4 x 15 us   4.77  4.83    4.96  5.12    5.24  5.48  6.03  6.49   19.5
 //   3 x 20 us   4.96  4.98    5.03  5.06    5.14  5.29  5.46  6.19   10.30
 // (fp32 masters, two 32B-style layers: 3.16 / 3.06 / 2.98 / 2.95 ms at 5 %, 3.17 / 3.24 / 3.19 / 3.04 at 6 %;
-// arithmetic payloads, eight 7B-style layers: 1.601 / 1.637 / 1.629 / 1.604 at 5 %, 1.571 / 1.584 / 1.576 / 1.561 at 4 %)
+// arithmetic payloads, 15 / 20 us: eight 7B-style layers 1.477 / 1.491 ms at 4.5 %, 1.489 / 1.515 at 4.8 %, fp32 masters
+// 2.83 / 2.89 at 4.5 %)
 // Four tiles would gain up to 3 % between 4 and 5 %, but the density is the last launch's, and where more comes they
 // lose far more: seen 4.5 %, 20 / 30 % came: 8.9 / 19.4 ms with 4 x 15 us, 7.8 / 10.0 with 3 x 15; fp32 masters, 15 %
 // came: 19.4 and 11.1 (always: 7.8 / 10.3 and 11.8).
 constexpr int32_t kNearBelowPpm = 50000;
-static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
+static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
     a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
     a->batch = kBatch;
     a->window_open = 0;
@@ -2852,7 +2774,7 @@ static void encode_walk(int order, int32_t ppm, int arith, EncodeArgs *a) {
         a->batch = kBatchTimed;
         a->window_open = ROSE_WRITE_OPEN_TIMED;
     } else if (order == ROSE_TILE_ORDER_NEIGHBOURS) {
-        const bool near = !arith && ppm >= 0 && ppm < kNearBelowPpm;
+        const bool near = ppm >= 0 && ppm < kNearBelowPpm;
         a->window_open = near ? ROSE_WRITE_OPEN_NEAR : ROSE_WRITE_OPEN_WIDE;
     }
 }
@@ -2942,7 +2864,7 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
             return (int)hipGetLastError();
         }
     }
-    encode_walk(order, ppm, arith, &a);
+    encode_walk(order, ppm, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are
