@@ -154,7 +154,7 @@ constexpr int kRefreshWide = 200;      // entries per tile up to which a refresh
 // otherwise be treated as generic and use the slower flat instructions).  The address needs no more
 // than the alignment of a 16-bit element: the compiler emits the same instruction, and the memory
 // pipeline cuts what crosses a line.  Two streams read in 16 KB tiles: 6.6 TB/s at aligned addresses,
-// 6.5 with one stream 2 or 4 bytes off, 5.6 - 6.2 with both off.
+// 6.5 with one stream 2 or 4 bytes off, 5.6 - 6.2 with both off (see tile_ctx).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 typedef __attribute__((address_space(1))) u32x4_any global_u32x4;
@@ -530,8 +530,10 @@ struct TileCtx {
     Piece pc;
     const uint16_t *old_base;
     const void *new_base;
-    uint32_t k_tile;
-    uint32_t limit;     // the piece's length for a tile that reaches past its end, 0xFFFFFFFF for a full tile
+    uint32_t k_tile;    // the tile's elements are k_tile .. k_tile + kTile - 1, as far as the piece has them (the first
+                        // tile of a piece that is shifted begins up to kShiftElems - 1 below 0)
+    uint32_t shift;     // elements by which the piece's tiles are shifted
+    uint32_t limit;     // the piece's length for a tile that reaches past either end, 0xFFFFFFFF for a full tile
     uint32_t vec;       // bit 0: 128-bit loads are legal for this tile; bit 2: its vectors may straddle runs
     int32_t piece;      // index of pc in the piece table
 };
@@ -542,13 +544,22 @@ __device__ __forceinline__ TileCtx tile_ctx(const EncodeArgs &a, int32_t tile) {
     c.pc = load_piece(a.pieces + c.piece);
     c.old_base = reinterpret_cast<const uint16_t *>(cload64(a.old_ptrs + c.pc.tensor));
     c.new_base = reinterpret_cast<const void *>(cload64(a.new_ptrs + c.pc.tensor));
-    c.k_tile = (uint32_t)(tile - c.pc.first_tile) * (uint32_t)kTile;
-    c.limit = (c.k_tile + (uint32_t)kTile <= (uint32_t)c.pc.len) ? 0xFFFFFFFFu : (uint32_t)c.pc.len;
     // uniform choice: 128-bit loads at whatever element they start, as long as runs hold a whole vector (a
     // decoder whose tensors start at odd elements and whose rows are 765 elements a shard, 131 M weights:
     // 526 us with one element per load for such tiles, 151 us this way)
     c.vec = ((c.pc.flags & kPieceLoad16) && ((((uintptr_t)c.old_base) | ((uintptr_t)c.new_base)) & 1u) == 0 &&
-             c.k_tile + (uint32_t)kVec <= (uint32_t)c.pc.len) ? ((c.pc.flags & kPieceSplit) ? 5u : 1u) : 0u;
+             c.pc.len >= kVec) ? ((c.pc.flags & kPieceSplit) ? 5u : 1u) : 0u;
+    // Tensors that lie one right behind the other begin anywhere.  128-bit loads at any alignment are legal, but a wave's
+    // load then touches a 128-byte line more than it fills, and a refresh writes parts of lines.  So the tiles of a piece
+    // of several tiles are moved down to the old tensor's lines (the new one's too, where both are laid out alike), if
+    // all its rows begin equally far from a line (kPieceShift); rows in runs then have vectors that straddle two.  Packed,
+    // eight 7B-style layers, 2 %: 1695 -> 1310 us (at lines 1275), with refresh 2653 -> 2025, fp32 masters 2101 -> 2030; all 32
+    // layers at 5 % 6392 -> 5158; 131 M weights in rows of 765 elements a shard 121 -> 100; 64 MiB 19.9 -> 15.7.
+    c.shift = (c.vec && (c.pc.flags & kPieceShift))
+                  ? (uint32_t)((reinterpret_cast<uintptr_t>(c.old_base) >> 1) + (uintptr_t)c.pc.src_off) & (uint32_t)(kShiftElems - 1) : 0u;
+    if ((c.pc.flags & kPieceStrided) && (c.shift & (uint32_t)(kVec - 1))) c.vec |= 4u;
+    c.k_tile = (uint32_t)(tile - c.pc.first_tile) * (uint32_t)kTile - c.shift;
+    c.limit = ((int32_t)c.k_tile >= 0 && c.k_tile + (uint32_t)kTile <= (uint32_t)c.pc.len) ? 0xFFFFFFFFu : (uint32_t)c.pc.len;
     return c;
 }
 
@@ -577,6 +588,33 @@ __device__ __forceinline__ TileMeta tile_meta(const TileCtx &c, int32_t tile) {
     return m;
 }
 
+// A lane's vector j is to hold the eight elements from k on.  One that reaches past an end of the piece is loaded
+// from its first or last eight elements instead, `moved` elements away, and put in place afterwards: no vector is loaded
+// element by element, none from outside the piece.
+__device__ __forceinline__ int32_t vector_moved(uint32_t limit, uint32_t k) {
+    const int32_t at = (int32_t)k, top = (int32_t)limit - kVec;
+    return (at < 0 ? 0 : at > top ? top : at) - at;
+}
+__device__ __forceinline__ uint4 in_place(uint4 v, int32_t moved) {
+    u64 lo = (u64)v.y << 32 | v.x, hi = (u64)v.w << 32 | v.z;
+    const int32_t s = (moved < 0 ? -moved : moved) * 16, r = s & 63;
+    if (moved >= 0) {
+        if (s >= 64) { hi = lo; lo = 0; }
+        if (r) hi = hi << r | lo >> (64 - r);
+        lo <<= r;
+    } else {
+        if (s >= 64) { lo = hi; hi = 0; }
+        if (r) lo = lo >> r | hi << (64 - r);
+        hi >>= r;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+// the same for the mask of its elements that differ; those that are not its own go
+__device__ __forceinline__ uint32_t in_place(uint32_t mask, int32_t moved) {
+    const int32_t s = moved < 0 ? -moved : moved;
+    return s >= kVec ? 0u : moved >= 0 ? (mask << s) & 0xFFu : mask >> s;
+}
+
 // Issue a tile's 128-bit loads of the old and the new tensor: both use the same element offsets,
 // which are worked out once.  t_off = wave * kWaveSpan + lane * kVec.
 template <int NEW_F32>
@@ -598,12 +636,9 @@ __device__ __forceinline__ void load_raw_at(const uint16_t *o, const void *n, OF
     }
 }
 // All of a tile's loads are issued unconditionally (no zeroing, no predication: nothing but the
-// loads themselves ever writes the load registers).  A vector that does not fit entirely inside
-// the piece is loaded from the tile's first vector instead, which tile_ctx guarantees to exist
-// for a tile with vec set; the caller discards such vectors.
+// loads themselves ever writes the load registers); see vector_moved for the ends of the piece.
 template <int NEW_F32>
 __device__ __forceinline__ void load_raw_pair(const TileCtx &c, uint32_t t_off, RawTile<0> &ro, RawTile<NEW_F32> &rn) {
-    const bool full = c.limit == 0xFFFFFFFFu;
     // One instruction sequence for both kinds of piece: a contiguous piece is walked as a strided
     // one whose row number is always 0 (magic 0).
     const bool strided = (c.pc.flags & kPieceStrided) != 0;
@@ -613,7 +648,7 @@ __device__ __forceinline__ void load_raw_pair(const TileCtx &c, uint32_t t_off, 
 #pragma unroll
     for (int j = 0; j < kIters; ++j) {
         uint32_t k = c.k_tile + t_off + (uint32_t)j * 64 * kVec;
-        if (!full && k + kVec > c.limit) k = c.k_tile;
+        k += (uint32_t)vector_moved((uint32_t)c.pc.len, k);
         const uint32_t q = __umulhi(k, magic) >> shift;
         const int64_t e = c.pc.src_off + (int64_t)q * stride + (k - q * run);
         load_raw_at<NEW_F32>(c.old_base, c.new_base, e, j, ro, rn);
@@ -632,10 +667,9 @@ __device__ __forceinline__ uint4 load_new_vec(const void *base, int64_t e) {
     }
 }
 
-// A tile's patterns, old and new, whatever its shape and alignment: the 128-bit loads of load_raw_pair, then
-// what they cannot give (vectors that reach past the piece, straddle two runs, or have no 128-bit load).
-// Elements past the end of the piece read as zero on both sides.  For kernels that do not keep a tile's loads
-// in flight across other work (the ticket kernel has its own form of this).
+// A tile's patterns, old and new, whatever its shape and alignment: the 128-bit loads of load_raw_pair, then the tails of
+// vectors that straddle two runs, or everything element by element.  For kernels that do not keep a tile's loads in flight
+// across other work (the ticket kernel has its own form of this).
 template <int NEW_F32>
 __device__ __forceinline__ void load_tile_pair(const TileCtx &c, uint32_t t_off, uint4 (&o)[kIters], uint4 (&n)[kIters]) {
     RawTile<0> ro;
@@ -647,23 +681,42 @@ __device__ __forceinline__ void load_tile_pair(const TileCtx &c, uint32_t t_off,
             o[j] = ro.v[j];
             n[j] = raw_to_bf16(rn, j);
         }
-        if (c.limit == 0xFFFFFFFFu && !(c.vec & 4u)) return;
+        if (!(c.vec & 4u)) return;
     }
 #pragma unroll
     for (int j = 0; j < kIters; ++j) {
         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
-        if (k >= (uint32_t)c.pc.len) {                  // (at once: a tile of a small tensor holds hardly anything else)
-            o[j] = n[j] = make_uint4(0, 0, 0, 0);
-        } else if (!(c.vec & 1u) || k + kVec > (uint32_t)c.pc.len) {
-            o[j] = load_vec_general<0>(c.old_base, c.pc, k);
-            n[j] = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
-        } else if (c.vec & 4u) {
+        if (!(c.vec & 1u)) {
+            if (k >= (uint32_t)c.pc.len) {              // (at once: a tile of a small tensor holds hardly anything else)
+                o[j] = n[j] = make_uint4(0, 0, 0, 0);
+            } else {
+                o[j] = load_vec_general<0>(c.old_base, c.pc, k);
+                n[j] = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
+            }
+        } else if (!vector_moved((uint32_t)c.pc.len, k)) {
             uint32_t q;
             const uint32_t left = split_left(c.pc, k, &q);
             if (left < (uint32_t)kVec) {
                 const int64_t e = split_tail_at(c.pc, q, left);
                 o[j] = split_merge(o[j], gload16(c.old_base + e), left);
                 n[j] = split_merge(n[j], load_new_vec<NEW_F32>(c.new_base, e), left);
+            }
+        }
+    }
+}
+// The masks of the elements of such a tile that differ; vectors at an end of the piece are put in place.
+__device__ __forceinline__ void tile_masks(const TileCtx &c, uint32_t t_off, uint4 (&o)[kIters], uint4 (&n)[kIters],
+                                           uint32_t (&mask)[kIters]) {
+#pragma unroll
+    for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
+    if ((c.vec & 1u) && c.limit != 0xFFFFFFFFu) {
+#pragma unroll
+        for (int j = 0; j < kIters; ++j) {
+            const int32_t moved = vector_moved(c.limit, c.k_tile + t_off + (uint32_t)(j * 64) * kVec);
+            mask[j] = in_place(mask[j], moved);
+            if (moved && mask[j]) {
+                o[j] = in_place(o[j], moved);
+                n[j] = in_place(n[j], moved);
             }
         }
     }
@@ -1144,10 +1197,16 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         // (the rare cases are marked as such: laid out in line they cost the fp32 kernels 2 % of an update of 67 M
         // elements)
         if (__builtin_expect((cur.vec & 1u) != 0, 1)) {
-            if (__builtin_expect(cur.limit != 0xFFFFFFFFu, 0)) {   // vectors past the end of the piece hold nothing
+            if (__builtin_expect(cur.limit != 0xFFFFFFFFu, 0)) {
 #pragma unroll
-                for (int j = 0; j < kIters; ++j)
-                    if (k_wave + (uint32_t)(j * 64 + lane) * kVec + kVec > cur.limit) mask[j] = 0;
+                for (int j = 0; j < kIters; ++j) {
+                    const int32_t moved = vector_moved(cur.limit, k_wave + (uint32_t)(j * 64 + lane) * kVec);
+                    mask[j] = in_place(mask[j], moved);
+                    if (moved && mask[j]) {
+                        nv[j] = in_place(nv[j], moved);
+                        if constexpr (ARITH) ov[j] = in_place(ov[j], moved);
+                    }
+                }
             }
             // Runs that are no multiple of 8 elements: the vectors that straddle the end of a run hold
             // their first elements only; the rest is loaded now.  A lane takes its first such vector,
@@ -1160,7 +1219,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 for (int j = 0; j < kIters; ++j) {
                     const uint32_t k = k_wave + (uint32_t)(j * 64 + lane) * kVec;
                     uint32_t q;
-                    if (split_left(c.pc, k, &q) < (uint32_t)kVec && k + kVec <= cur.limit) todo |= 1u << j;
+                    if (!vector_moved((uint32_t)c.pc.len, k) && split_left(c.pc, k, &q) < (uint32_t)kVec) todo |= 1u << j;
                     masks |= mask[j] << (8 * j);
                 }
 #pragma unroll 1
@@ -1184,25 +1243,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 }
 #pragma unroll
                 for (int j = 0; j < kIters; ++j) mask[j] = (masks >> (8 * j)) & 0xFFu;
-            }
-            // a piece whose length is not a multiple of 8: the one vector that straddles its end
-            if (__builtin_expect(cur.limit != 0xFFFFFFFFu && (cur.limit & (kVec - 1)), 0)) {
-                const uint32_t ks = cur.limit & ~(uint32_t)(kVec - 1);
-                const TileCtx c = tile_ctx(a, __builtin_amdgcn_readfirstlane(tile));
-                if (ks >= k_wave && ks < k_wave + (uint32_t)kWaveSpan && ((ks - k_wave) / kVec) % 64 == (uint32_t)lane) {
-                    const uint32_t js = (ks - k_wave) / (64 * kVec);
-                    uint4 o = load_vec_general<0>(c.old_base, c.pc, ks);
-                    uint4 n = load_vec_general<NEW_F32>(c.new_base, c.pc, ks);
-                    uint32_t m = nz16_mask(xor4(o, n));
-#pragma unroll
-                    for (int jj = 0; jj < kIters; ++jj) {
-                        if ((uint32_t)jj == js) {
-                            nv[jj] = n;
-                            mask[jj] = m;
-                            if constexpr (ARITH) ov[jj] = o;
-                        }
-                    }
-                }
             }
         } else {
             // runs of fewer than 8 elements, pieces of fewer than 8, odd addresses.  Kept as a rolled loop (one
@@ -1393,7 +1433,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                     if (wide) line |= pair;
                     if (line) {
                         const uint32_t k = c.k_tile + t_off + (uint32_t)(j * 64) * kVec;
-                        bool one = (cur.vec & 1u) && (c.limit == 0xFFFFFFFFu || k + kVec <= c.limit);
+                        bool one = (cur.vec & 1u) && (c.limit == 0xFFFFFFFFu || !vector_moved(c.limit, k));
                         if (cur.vec & 4u) {
                             uint32_t q;
                             one = one && split_left(c.pc, k, &q) >= (uint32_t)kVec;
@@ -1528,7 +1568,7 @@ __device__ __forceinline__ void refresh_tile(const TileCtx &c, uint32_t t_off, b
         const uint32_t pair = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)line, 0x141, 0xf, 0xf, true);      // row_half_mirror
         if (wide) line |= pair;
         if (!line) continue;
-        if ((c.vec & 1u) && k + kVec <= (uint32_t)c.pc.len && !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
+        if ((c.vec & 1u) && !vector_moved((uint32_t)c.pc.len, k) && !((c.vec & 4u) && split_left(c.pc, k, &q) < (uint32_t)kVec)) {
             gstore16_stream(ob + src_index(c.pc, k, true), n[j]);
         } else {
             while (m) {
@@ -1564,10 +1604,9 @@ __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uin
     const TileCtx c = tile_ctx(a, tile);
     const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
     uint4 o[kIters], n[kIters];
-    load_tile_pair<NEW_F32>(c, t_off, o, n);
     uint32_t mask[kIters], rank[kIters];
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
+    load_tile_pair<NEW_F32>(c, t_off, o, n);
+    tile_masks(c, t_off, o, n, mask);
     const uint32_t wave_total = vector_ranks(mask, rank);
     if (lane == 0) s_cnt[wave] = wave_total;
     __syncthreads();
@@ -1582,7 +1621,9 @@ __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uin
     total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
     if (total == 0 || total > (uint32_t)slot_size) return;
 #pragma unroll
-    for (int j = 0; j < kIters; ++j) park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec, mask[j], o[j], n[j], wave_excl + rank[j], s_entry, s_was);
+    for (int j = 0; j < kIters; ++j)                           // (offsets from where an unshifted tile would begin)
+        park_vector<ARITH>(t_off + (uint32_t)(j * 64) * kVec - c.shift, mask[j], o[j], n[j],
+                           wave_excl + rank[j], s_entry, s_was);
     if constexpr (REFRESH) {
         if (!(c.pc.flags & kPieceReplicated)) refresh_tile(c, t_off, total <= (uint32_t)kRefreshWide, mask, n);
     }
@@ -1601,11 +1642,14 @@ __global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uin
     __shared__ uint32_t s_cnt[kWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const TileCtx c = tile_ctx(a, (int32_t)blockIdx.x);
+    const uint32_t t_off = (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
     uint4 o[kIters], n[kIters];
-    load_tile_pair<NEW_F32>(c, (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec, o, n);
+    uint32_t mask[kIters];
+    load_tile_pair<NEW_F32>(c, t_off, o, n);
+    tile_masks(c, t_off, o, n, mask);
     uint32_t cnt = 0;
 #pragma unroll
-    for (int j = 0; j < kIters; ++j) cnt += __popc(nz16_mask(xor4(o[j], n[j])));
+    for (int j = 0; j < kIters; ++j) cnt += __popc(mask[j]);
     const uint32_t wave_cnt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(cnt), 63);
     if (lane == 0) s_cnt[wave] = wave_cnt;
     __syncthreads();
@@ -1645,8 +1689,7 @@ __device__ __forceinline__ void emit_read(const EncodeArgs &a, int32_t tile, u64
     load_tile_pair<NEW_F32>(c, t_off, o, n);
     const uint32_t share = before(c);
     uint32_t mask[kIters], rank[kIters];
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) mask[j] = nz16_mask(xor4(o[j], n[j]));
+    tile_masks(c, t_off, o, n, mask);
     const uint32_t wave_total = vector_ranks(mask, rank);
     if (lane == 0) {
         s_before[wave] = share;
@@ -1800,7 +1843,7 @@ __global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, con
 
     auto write = [&](u64 pos, uint32_t entry, uint32_t base, int32_t piece) {
         if (pos >= (u64)b.capacity) return;
-        uint32_t local = base + ((entry >> 16) & (uint32_t)(kTile - 1));
+        uint32_t local = base + (uint32_t)((int32_t)(entry << 1) >> 17);       // (negative in the first tile of a shifted piece)
         if (piece >= 0) local = strided_local(a.pieces[piece], local);
         __builtin_nontemporal_store((int32_t)(local | (ARITH ? entry & 0x80000000u : 0u)), b.idx + pos);
         __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
@@ -2468,7 +2511,7 @@ __global__ __launch_bounds__(WAVES * 64) void apply_object_kernel(const char *ob
 // (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements, TP2: 4130 -> 1421 us; rows of
 // 765 elements a shard, 131 M weights: 248 -> 89 us.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCopyAtOnce = 2048;       // workgroups (of 256 threads, 8 waves per SIMD)
+constexpr int kCopyAtOnce = 2112;       // workgroups (2048 of 256 threads, 8 waves per SIMD; a few find nothing to copy)
 template <int NEW_F32>
 __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const int32_t tile = a.tile_begin + (int32_t)blockIdx.x;
@@ -2818,7 +2861,7 @@ constexpr struct {
 static_assert((kUnknownMib << 20) / 4 < (int64_t)1 << 31 && kStageMostTiles * kTile < (int64_t)1 << 31,
               "the second launch adds up entries in 32 bits");
 static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh, int arith, int32_t ppm) {
-    const int64_t bytes = (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4), mib = (bytes + (1 << 20) - 1) >> 20;
+    const int64_t bytes = (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4), mib = (bytes + (1 << 19)) >> 20;
     const int64_t expected = ppm < 0 ? 0 : (int64_t)ppm * kTile / 1000000;
     TwoLaunches t = {kTickets, 0, mib >= kStreamMib};
     if (mib <= kUnknownMib) {

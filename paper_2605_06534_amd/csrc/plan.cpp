@@ -247,7 +247,14 @@ extern "C" rose_status rose_shard_plan_create_pp(const rose_tensor_desc *tensors
                 segment_pieces(tensors[i], i, d, tp, tp_src, src_rank, b, here, p->pieces);
                 for (size_t k = first; k < p->pieces.size(); ++k) {
                     Piece &pc = p->pieces[k];
-                    int64_t nt = pc.len == 0 ? 1 : ((int64_t)pc.len + rose::kTile - 1) / rose::kTile;
+                    // (element numbers stay below 2^31 however far the last tile reaches past the piece)
+                    const bool lines = !(pc.flags & rose::kPieceStrided) ||
+                                       ((pc.flags & rose::kPieceLoad16) && pc.run % rose::kShiftElems == 0 &&
+                                        pc.stride % rose::kShiftElems == 0);
+                    if (lines && pc.len > rose::kTile && pc.len <= INT32_MAX - 2 * rose::kTile)
+                        pc.flags |= rose::kPieceShift;
+                    const int64_t reach = (int64_t)pc.len + ((pc.flags & rose::kPieceShift) ? rose::kShiftElems - 1 : 0);
+                    int64_t nt = pc.len == 0 ? 1 : (reach + rose::kTile - 1) / rose::kTile;
                     if (n_tiles + nt >= ((int64_t)1 << 31) - 1) {
                         delete p;
                         return ROSE_ERR_UNSUPPORTED;

@@ -25,6 +25,7 @@ constexpr int kVec = 8;
 constexpr int kIters = ROSE_ITERS;
 constexpr int kWaveSpan = 64 * kVec * kIters;      // elements one wave covers in a tile
 constexpr int kTile = kThreads * kVec * kIters;    // elements per tile
+constexpr int kShiftElems = 64;                     // 16-bit elements in a 128-byte line
 
 enum : int32_t {
     kPieceFirst = 1,    // first piece of its (tensor, shard) segment
@@ -33,6 +34,9 @@ enum : int32_t {
     kPieceLoad16 = 32,  // a vector of kVec elements is one 128-bit load of the source, at any alignment: the source is
                         // contiguous or its runs are at least kVec long (then two, see kPieceSplit)
     kPieceSplit = 64,   // with kPieceLoad16: source runs that are no multiple of kVec, a vector may straddle two
+    kPieceShift = 128,  // its tiles may be moved down to 128-byte lines of the source: several tiles, and the source is
+                        // contiguous or in runs and strides of whole lines.  There are tiles enough for the piece moved
+                        // as far as can be (one more where it fills its last one; that is empty if nothing is moved)
     kPieceDstStrided = 8 // runs of `run` elements every `lstride` LOCAL indices (the sender's slice
                         // covers only part of each row of the destination shard)
 };
