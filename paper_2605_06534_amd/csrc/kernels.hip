@@ -2507,9 +2507,11 @@ __global__ __launch_bounds__(WAVES * 64) void apply_object_kernel(const char *ob
 // of its loads in flight together, loads and stores non-temporal: what a plain copy does best with (2 GiB:
 // 5.0 - 5.4 TB/s from a grid of 2048 or 8192 workgroups, 5.9 from one workgroup per tile, 6.1 with both hints).
 // Loads take any alignment at little cost, stores do not (5.7 TB/s), so a tile's vectors are lined up with
-// the DESTINATION: they begin `head` elements into the piece, which the first tile copies one by one.
-// (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements, TP2: 4130 -> 1421 us; rows of
-// 765 elements a shard, 131 M weights: 248 -> 89 us.)
+// the DESTINATION: they begin `head` elements into the piece, which the first tile copies one by one.  Pieces of several
+// tiles are lined up with 128-byte lines, not with vectors only (packed, eight 7B-style layers, TP4: 1445 -> 1313 us, fp32
+// masters 2117 -> 1932).
+// (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements: 4130 -> 1421 us at TP2; rows of
+// 765 elements a shard, 131 M weights: 248 -> 89 us; figures before that.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kCopyAtOnce = 2112;       // workgroups (2048 of 256 threads, 8 waves per SIMD; a few find nothing to copy)
 template <int NEW_F32>
@@ -2522,7 +2524,8 @@ __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const uint32_t len = (uint32_t)pc.len;
     const uint32_t k_tile = (uint32_t)(tile - pc.first_tile) * (uint32_t)kTile;
     const bool dst_strided = (pc.flags & kPieceDstStrided) != 0;
-    const uint32_t head = dst_strided ? 0u : (0u - ((uint32_t)((uintptr_t)dst >> 1) + (uint32_t)pc.local_base)) & 7u;
+    const uint32_t line = len > (uint32_t)kTile ? (uint32_t)kShiftElems : (uint32_t)kVec;     // (a short piece: little to copy singly)
+    const uint32_t head = dst_strided ? 0u : (0u - ((uint32_t)((uintptr_t)dst >> 1) + (uint32_t)pc.local_base)) & (line - 1u);
     const uint32_t k0 = k_tile + head, k_lane = k0 + (uint32_t)wave * kWaveSpan + (uint32_t)lane * kVec;
     auto copy_one = [&](uint32_t k) {
         const int64_t s = src_index(pc, k, false);
