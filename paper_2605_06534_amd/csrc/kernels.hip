@@ -2343,9 +2343,27 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
     constexpr int kTileEntries = LOADS * 1024, kValLoads = LOADS > 1 ? LOADS / 2 : 1, kValLanes = LOADS > 1 ? 256 : 128;
     const int32_t *from_idx = b.idx + first;
     const uint16_t *from_val = b.val + first;
-    for (int64_t e0 = (int64_t)blockIdx.x * kTileEntries; e0 < n; e0 += (int64_t)gridDim.x * kTileEntries) {
+    // Large objects: each array's tiles begin at a 128-byte line of the object, the entries in front of it go singly (the
+    // same eight objects: 189.0 us with stores across lines, 186.3 this way; 400 M entries in one bucket 885 and 864).
+    int64_t n_idx = n, n_val = n;
+    if constexpr (LOADS > 1) {
+        const int64_t h_idx = ((0u - (uint32_t)reinterpret_cast<uintptr_t>(idx)) & 127u) / 4;
+        const int64_t h_val = ((0u - (uint32_t)reinterpret_cast<uintptr_t>(val)) & 127u) / 2;
+        n_idx = n > h_idx ? n - h_idx : 0;
+        n_val = n > h_val ? n - h_val : 0;
+        if (blockIdx.x == 0) {
+            if ((int64_t)threadIdx.x < n - n_idx) idx[threadIdx.x] = from_idx[threadIdx.x];
+            if ((int64_t)threadIdx.x < n - n_val) val[threadIdx.x] = from_val[threadIdx.x];
+        }
+        idx += n - n_idx;
+        from_idx += n - n_idx;
+        val += n - n_val;
+        from_val += n - n_val;
+    }
+    const int64_t n_least = n_idx < n_val ? n_idx : n_val, n_most = n_idx < n_val ? n_val : n_idx;
+    for (int64_t e0 = (int64_t)blockIdx.x * kTileEntries; e0 < n_most; e0 += (int64_t)gridDim.x * kTileEntries) {
         uint4 vi[LOADS], vv[kValLoads];
-        if (e0 + kTileEntries <= n) {
+        if (e0 + kTileEntries <= n_least) {
 #pragma unroll
             for (int j = 0; j < LOADS; ++j) vi[j] = gload16_stream(from_idx + e0 + (j * 256 + threadIdx.x) * 4);
             if (threadIdx.x < kValLanes) {
@@ -2359,7 +2377,8 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
                 for (int j = 0; j < kValLoads; ++j) gstore16_stream(val + e0 + (j * 256 + threadIdx.x) * 8, vv[j]);
             }
         } else {                                        // the last tile: whole vectors, then the few entries behind them
-            const int64_t left = n - e0, i_end = left & ~(int64_t)3, v_end = left & ~(int64_t)7;
+            const int64_t left_i = min(max(n_idx - e0, (int64_t)0), (int64_t)kTileEntries), i_end = left_i & ~(int64_t)3;
+            const int64_t left_v = min(max(n_val - e0, (int64_t)0), (int64_t)kTileEntries), v_end = left_v & ~(int64_t)7;
 #pragma unroll
             for (int j = 0; j < LOADS; ++j) {
                 const int64_t e = (j * 256 + threadIdx.x) * 4;
@@ -2380,8 +2399,8 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
                 const int64_t e = (j * 256 + threadIdx.x) * 8;
                 if (e < v_end) gstore16_stream(val + e0 + e, vv[j]);
             }
-            if (threadIdx.x < left - i_end) idx[e0 + i_end + threadIdx.x] = from_idx[e0 + i_end + threadIdx.x];
-            if (threadIdx.x < left - v_end) val[e0 + v_end + threadIdx.x] = from_val[e0 + v_end + threadIdx.x];
+            if (threadIdx.x < left_i - i_end) idx[e0 + i_end + threadIdx.x] = from_idx[e0 + i_end + threadIdx.x];
+            if (threadIdx.x < left_v - v_end) val[e0 + v_end + threadIdx.x] = from_val[e0 + v_end + threadIdx.x];
         }
     }
 }
