@@ -2542,6 +2542,7 @@ __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     uint16_t *dst = reinterpret_cast<uint16_t *>(cload64(a.dst_ptrs + pc.tensor));
     const uint32_t len = (uint32_t)pc.len;
     const uint32_t k_tile = (uint32_t)(tile - pc.first_tile) * (uint32_t)kTile;
+    if (k_tile >= len) return;                          // see kPieceShift: nothing is left for it
     const bool dst_strided = (pc.flags & kPieceDstStrided) != 0;
     const uint32_t line = len > (uint32_t)kTile ? (uint32_t)kShiftElems : (uint32_t)kVec;     // (a short piece: little to copy singly)
     const uint32_t head = dst_strided ? 0u : (0u - ((uint32_t)((uintptr_t)dst >> 1) + (uint32_t)pc.local_base)) & (line - 1u);
