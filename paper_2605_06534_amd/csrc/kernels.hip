@@ -2328,7 +2328,8 @@ __global__ __launch_bounds__(256) void pack_kernel(BucketDev b, int32_t shard, i
             int64_t v = b.seg_off[t] - first;
             seg[t] = v < 0 ? 0 : (v > n ? n : v);
         }
-        // the index and value arrays end on 16-byte boundaries: zero the slack
+        // the segment table and the index and value arrays end on 16-byte boundaries: zero the slack
+        if (threadIdx.x == 0 && n_tensors % 2 == 0) seg[n_tensors + 1] = 0;
         int32_t *idx = reinterpret_cast<int32_t *>(obj + a_off);
         uint16_t *val = reinterpret_cast<uint16_t *>(obj + b_off);
         if (threadIdx.x < 4 && n + threadIdx.x < (int64_t)(up16(4 * (size_t)n) / 4)) idx[n + threadIdx.x] = 0;
