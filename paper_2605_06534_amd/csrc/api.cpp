@@ -1,7 +1,6 @@
 // C ABI: argument checks, the plan's device tables, and hand-off to the kernel launchers.
 #include <hip/hip_runtime_api.h>
 
-#include <chrono>
 #include <cstring>
 
 #include "rose_internal.h"
@@ -21,7 +20,7 @@ public:
         std::lock_guard<std::mutex> lock(mu_);
         if (!words_) {
             void *p = nullptr;
-            if (hipHostMalloc(&p, kWords * sizeof(int64_t), hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+            if (hipHostMalloc(&p, kWords * sizeof(int64_t), hipHostMallocPortable) != hipSuccess) {
                 (void)hipGetLastError();
                 return false;
             }
@@ -57,8 +56,6 @@ private:
     int plans_ = 0;
 };
 Mail mail;
-constexpr int64_t kNoTotal = INT64_MIN;                 // no bucket's total
-constexpr int kLookFor = 40;                            // microseconds
 
 constexpr int32_t kNeighboursBelowPpm = 75000, kTimedBelowPpm = 40000;   // see encode_common
 
@@ -353,25 +350,14 @@ extern "C" rose_status rose_bucket_check(const rose_plan *p, const rose_bucket *
     int64_t total = 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
     int64_t *word = mail.take();
-    const int64_t *from = bucket->seg_off + p->n_tensors;
-    int dev = -1;
-    bool have = false;
-    // (a word that something may still write after an error stays taken)
-    if (word && hipGetDevice(&dev) == hipSuccess && dev == p->device) {
-        // A kernel writes the total into the word and the host looks at it for a while: what a caller waits for here is
-        // mostly the way there and back, and the runtime's copy and wait take longer ones (small updates, 12.2 us a check,
-        // this way 6 - 7).  Work in front of it that lasts longer is waited for by the runtime.
-        volatile int64_t *seen = word;
-        *seen = kNoTotal;
-        if (rose::launch_total(from, word, st) != 0) return ROSE_ERR_HIP;
-        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(kLookFor);
-        do {
-            for (int i = 0; i < 32 && !have; ++i) have = __atomic_load_n(word, __ATOMIC_ACQUIRE) != kNoTotal;
-        } while (!have && std::chrono::steady_clock::now() < until);
-    } else if (hipMemcpyAsync(word ? word : &total, from, sizeof total, hipMemcpyDeviceToHost, st) != hipSuccess) {
+    int64_t *to = word ? word : &total;
+    // (a word whose copy may still be on its way after an error stays taken)
+    // The runtime's copy and wait, not a kernel that writes the total for the host to look at: the stream is to be
+    // synchronised, with its errors, and seg_off may lie where only the runtime can read it.  (Such a kernel and its look took
+    // 14.0 us a check where this takes 19.7 as a caller in Python sees it; with the wait behind them 22.5.)
+    if (hipMemcpyAsync(to, bucket->seg_off + p->n_tensors, sizeof total, hipMemcpyDeviceToHost, st) != hipSuccess)
         return ROSE_ERR_HIP;
-    }
-    if (!have && hipStreamSynchronize(st) != hipSuccess) return ROSE_ERR_HIP;
+    if (hipStreamSynchronize(st) != hipSuccess) return ROSE_ERR_HIP;
     if (word) {
         total = *static_cast<volatile int64_t *>(word);
         mail.put(word);

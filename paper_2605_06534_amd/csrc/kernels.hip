@@ -2966,15 +2966,6 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
     return (int)hipGetLastError();
 }
 
-// One word into pinned host memory that the host is looking at.
-__global__ void total_kernel(const int64_t *from, int64_t *host_word) {
-    __hip_atomic_store(host_word, *from, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-int launch_total(const int64_t *from, int64_t *host_word, void *stream) {
-    void *args[] = {&from, &host_word};      // (this launch's own error, not one that an earlier call has left)
-    return (int)hipLaunchKernel(reinterpret_cast<const void *>(total_kernel), dim3(1), dim3(1), args, 0, static_cast<hipStream_t>(stream));
-}
-
 typedef void (*ApplyKernel)(BucketDev, int32_t, const int32_t *, void *const *, int, int64_t);
 int launch_apply(const BucketDev &b, int32_t n_tensors, const int32_t *local_numel, void *const *dst_ptrs,
                  int arith, int64_t shard_elems, void *stream) {

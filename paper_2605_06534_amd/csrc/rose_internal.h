@@ -142,7 +142,6 @@ inline uint32_t magic_div(uint32_t k, uint32_t magic, uint32_t shift) {
 }
 
 // kernel launchers (kernels.hip); all return a hipError_t as int
-int launch_total(const int64_t *from, int64_t *host_word, void *stream);
 // replicated tensors to copy new -> old after an encode with refresh (device arrays of n entries)
 struct RefreshArgs {
     const int32_t *list;

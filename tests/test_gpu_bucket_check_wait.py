@@ -1,5 +1,5 @@
-"""rose_bucket_check looks for the total in a pinned word for a while, then waits for the stream: the same answer at once,
-behind work that lasts longer than it looks, on other streams, from several threads and for a plan that is resident nowhere."""
+"""rose_bucket_check reads the total back into a pinned word and waits for the stream: the same answer at once, behind work
+that lasts, on other streams, from several threads and for a plan that is resident nowhere."""
 import threading
 
 import pytest
