@@ -1781,13 +1781,11 @@ __global__ __launch_bounds__(kThreads) void emit_tiles_kernel(EncodeArgs a, cons
         nullptr, s_before, s_cnt);
 }
 
-// Second launch, staged: a workgroup copies out 2^group_log2 neighbouring tiles of one chain.
-template <int NEW_F32, int REFRESH, int ARITH>
-__global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, const uint16_t *counts, const uint32_t *slots,
-                                                              int32_t slot_size, int32_t group_log2) {
-    __shared__ uint32_t s_entry[kTile / 2];
-    __shared__ uint16_t s_was[ARITH ? kTile / 2 : 1];
-    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+// A workgroup copies out 2^group_log2 neighbouring tiles of one chain, as far as they are in their slots.  Returns whether
+// the group is a single tile that is not; *tile and *excl are then its number and the entries in front of it.
+template <int ARITH>
+__device__ __forceinline__ bool copy_group(const EncodeArgs &a, const uint16_t *counts, const uint32_t *slots, int32_t slot_size,
+                                           int32_t group_log2, uint32_t *s_before, int32_t *tile, u64 *excl_out) {
     __shared__ EmitTile s_tile[kGroupMost + 1];
     __shared__ uint32_t s_over;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1797,7 +1795,7 @@ __global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, con
     while (blk >= a.block_first[shard + 1]) ++shard;
     const int32_t chain_begin = a.chain_first[shard], chain_end = a.chain_first[shard + 1];
     const int32_t t0 = chain_begin + first - a.block_first[shard] * kBlock;
-    if (t0 >= chain_end) return;
+    if (t0 >= chain_end) return false;
     const int32_t n = chain_end - t0 < group ? chain_end - t0 : group;
     const BucketDev b = a.bucket[shard];
 
@@ -1880,18 +1878,50 @@ __global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, con
             if (threadIdx.x < done) write(excl + threadIdx.x, early, s_tile[0].base, s_tile[0].piece);
         }
         if (all > done) copy(done, all);
-        return;
+        return false;
     }
+    *tile = t0;
+    *excl_out = excl;
+    if (group == 1) return true;
     for (int32_t i = 0; i < n; ++i) {
         const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tile[i].start);
         const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tile[i + 1].start);
-        if (end - begin > (uint32_t)slot_size) {
-            __syncthreads();                                   // s_before and the tile before's s_entry have been read
-            emit_read<NEW_F32, REFRESH, ARITH, 2, false>(a, t0 + i, excl + begin, [](const TileCtx &) { return 0u; }, s_entry,
-                                                         s_was, s_before, s_cnt);
-        } else if (end > begin) {
-            copy(begin, end);
-        }
+        if (end > begin && end - begin <= (uint32_t)slot_size) copy(begin, end);
+    }
+    return false;
+}
+
+// Second launch, staged: the first group_wgs workgroups copy out groups of tiles.  A tile past its slot is read again: by
+// its workgroup, if that has no other; else by one of those behind, to which such tiles are dealt so that neighbours go to
+// different ones.  Changes that lie close together had one workgroup read 2 to 16 tiles one behind the other: 2 % of
+// 192 MiB, all in neighbouring tiles, 117 us that way and 42 this way; of 480 MiB 238 and 88; of 1200 MiB 349 and 206;
+// all of 192 MiB at 30 % 109 and 84.  With 2048 workgroups for it, what the device holds at once, 384 MiB at 30 % take 176 us,
+// with kOverWgs 160.  Where no tile is past its slot they look at their counts and end (850 MiB 154 us with and without).
+constexpr int kOverWgs = 8192;
+static_assert((kStageMostTiles + kOverWgs - 1) / kOverWgs <= 64, "a wave looks at a workgroup's tiles");
+template <int NEW_F32, int REFRESH, int ARITH>
+__global__ __launch_bounds__(kThreads) void emit_staged_kernel(EncodeArgs a, const uint16_t *counts, const uint32_t *slots,
+                                                              int32_t slot_size, int32_t group_log2, int32_t group_wgs) {
+    __shared__ uint32_t s_entry[kTile / 2];
+    __shared__ uint16_t s_was[ARITH ? kTile / 2 : 1];
+    __shared__ uint32_t s_before[kWaves], s_cnt[kWaves];
+    const bool grouped = (int32_t)blockIdx.x < group_wgs;
+    int32_t mine = 0;                                          // a tile for each bit of `over`
+    u64 over = 1, excl = 0;
+    if (grouped) {
+        if (!copy_group<ARITH>(a, counts, slots, slot_size, group_log2, s_before, &mine, &excl)) return;
+    } else {
+        const int32_t wgs = (int32_t)gridDim.x - group_wgs;
+        mine = (int32_t)blockIdx.x - group_wgs + (int32_t)(threadIdx.x & 63) * wgs;
+        over = __ballot(mine < a.n_tiles && gload_u16(counts + (mine < a.n_tiles ? mine : 0)) > (uint32_t)slot_size);
+    }
+    for (; over; over &= over - 1) {
+        const int32_t tile = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)over) - 1);
+        __syncthreads();                                       // s_before and the tile before's s_entry have been read
+        emit_read<NEW_F32, REFRESH, ARITH, 2, false>(
+            a, tile, excl,
+            [&](const TileCtx &c) { return grouped ? 0u : wave_share_of_counts(counts, a.chain_first[c.pc.shard], tile); },
+            s_entry, s_was, s_before, s_cnt);
     }
 }
 
@@ -2748,7 +2778,7 @@ static EncodeKernel encode_variant(int new_is_f32, int refresh, int arith) {
 typedef void (*CountKernel)(EncodeArgs, uint16_t *);
 typedef void (*StageKernel)(EncodeArgs, uint16_t *, uint32_t *, int32_t, int32_t);
 typedef void (*EmitKernel)(EncodeArgs, const uint16_t *);
-typedef void (*EmitStagedKernel)(EncodeArgs, const uint16_t *, const uint32_t *, int32_t, int32_t);
+typedef void (*EmitStagedKernel)(EncodeArgs, const uint16_t *, const uint32_t *, int32_t, int32_t, int32_t);
 static StageKernel stage_variant(int new_is_f32, int refresh, int arith) {
     static const StageKernel table[8] = {stage_tiles_kernel<0, 0, 0>, stage_tiles_kernel<1, 0, 0>, stage_tiles_kernel<0, 1, 0>,
                                          stage_tiles_kernel<1, 1, 0>, stage_tiles_kernel<0, 0, 1>, stage_tiles_kernel<1, 0, 1>,
@@ -2920,8 +2950,10 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
             if (two.form == kStaged) {
                 hipLaunchKernelGGL(stage_variant(new_is_f32, r, arith), dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts, a.slots,
                                    a.slot_size, two.stream);
-                hipLaunchKernelGGL(emit_staged_variant(new_is_f32, r, arith), dim3(a.n_blocks * (kBlock >> two.group_log2)),
-                                   dim3(kThreads), 0, st, a, counts, a.slots, a.slot_size, two.group_log2);
+                const int32_t group_wgs = a.n_blocks * (kBlock >> two.group_log2);
+                const int32_t over_wgs = two.group_log2 == 0 ? 0 : a.n_tiles < kOverWgs ? a.n_tiles : kOverWgs;
+                hipLaunchKernelGGL(emit_staged_variant(new_is_f32, r, arith), dim3(group_wgs + over_wgs), dim3(kThreads), 0, st, a,
+                                   counts, a.slots, a.slot_size, two.group_log2, group_wgs);
             } else {
                 const CountKernel count = new_is_f32 ? count_tiles_kernel<1> : count_tiles_kernel<0>;
                 hipLaunchKernelGGL(count, dim3(a.n_tiles), dim3(kThreads), 0, st, a, counts);
