@@ -1545,12 +1545,11 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 //             them to the bucket.  A tile that holds more than its slot does parks nothing and is read again.
 //   read again   no slots: the second launch reads every tile a second time.
 // ---------------------------------------------------------------------------------------------
-// The header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one, and all tiles
-// were handed out (by the grid).
+// The header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one, no tickets.
 __device__ __forceinline__ void write_header(const EncodeArgs &a) {
     if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
     if (threadIdx.x == kWsTilesWord) a.abort_flag[kWsTilesWord] = (uint32_t)a.n_tiles;
-    if (threadIdx.x == kWsTilesWord + 1) *a.ticket = (uint32_t)a.n_tiles;
+    if (threadIdx.x == kWsTilesWord + 1) *a.ticket = 0;
 }
 
 constexpr int kGroupMost = 16;           // tiles a workgroup of the second launch copies out at most

@@ -34,12 +34,14 @@ def test_order_follows_the_density_read_back(p, want):
                                     (0.06, binding.TILE_ORDER_NEIGHBOURS), (0.12, binding.TILE_ORDER_SPREAD)])
 @pytest.mark.parametrize("arith", [False, True])
 def test_launches_in_the_order_picked(p, want, arith):
-    """An update too large for two launches: one launch before any density is known, one in the order picked from
-    the density read back, one after a wrong guess (a tenth of the density).  The workspace's ticket counter
-    (word 1024) shows that tickets were taken."""
+    """An update too large for reading it twice, in a workspace with no room to park entries: one launch before any
+    density is known, one in the order picked from the density read back, one after a wrong guess (a tenth of the
+    density).  The workspace's words 4 (tiles of an update without tickets) and 1024 (the ticket counter) show that
+    tickets were taken."""
     print("case: launch in the picked order p=%g arith=%s" % (p, arith), flush=True)
     ts = models.decoder(2, 1024, 16, 16, 64, 2816, 4096, fused=True)
     c = bern_case(ts, 4, p, seed=9)
+    c.ws = c.ws[:(c.plan.workspace_bytes() - c.plan.n_tiles() * 2016 * 4 + 7) // 8].clone()
     for what in ("unknown", "known", "guessed too low"):
         c.ws.fill_(0)
         for b in c.buckets:
@@ -53,4 +55,4 @@ def test_launches_in_the_order_picked(p, want, arith):
         elif what == "known":
             assert c.plan.pick_tile_order([b.capacity for b in c.buckets]) == want
         check_arith(c) if arith else full_parity(c, check_dense=False)
-        assert int(c.ws.view(torch.int32)[1024]) > 0, what
+        assert int(c.ws.view(torch.int32)[4]) == 0 and int(c.ws.view(torch.int32)[1024]) > 0, what
