@@ -123,6 +123,13 @@ def profile_traffic(name, density, kernel):
     return None, src
 
 
+def encode_kernels(form, f32, arith):
+    """The kernels of an encode of this form (32-bit word 5 of its workspace)."""
+    return {0: ["encode_kernel<%d, 0, %d>" % (f32, arith)],
+            1: ["stage_tiles_kernel<%d, 0, %d>" % (f32, arith), "emit_staged_kernel<%d, 0, %d>" % (f32, arith)],
+            2: ["count_tiles_kernel<%d>" % f32, "emit_tiles_kernel<%d, 0, %d>" % (f32, arith)]}[form]
+
+
 def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_host_sample):
     """Build the workload on the device, check one step, time `steps` steps.  -> dict of results."""
     from workloads import models, synth
@@ -209,9 +216,6 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
     torch.cuda.synchronize()
     nnz = [R.bucket_check(plan, buckets[d]) for d in range(n_b)]   # raises if a bucket overflowed
     nnz_total = sum(nnz)
-    # Updates that are not large go in two launches instead of tickets; the workspace's 32-bit word 4 (the tiles of such
-    # an update, 0 after one by tickets) says which way these went.
-    by_tickets = int(ws.view(torch.int32)[4]) == 0
 
     if arith:
         # an arithmetic bucket may be applied once only: start the receivers from W_{t-1} again and
@@ -262,6 +266,9 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
         ms_per_step = (time.perf_counter() - t0) * 1e3 / steps
     t_enc = sum(e[0].elapsed_time(e[1]) for e in events) / steps
     t_app = sum(e[1].elapsed_time(e[2]) for e in events) / steps
+    # Updates that are not large go in two launches instead of by tickets; the workspace's 32-bit word 5 says which way
+    # the timed ones went (0: tickets, 1: entries parked, 2: everything read again).
+    form = int(ws.view(torch.int32)[5])
 
     # dense path for comparison (Sec. 6.3 crossover): every shard's slice of the new weights copied
     ev_c = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
@@ -290,7 +297,7 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
         "nnz": nnz_total, "new_dtype": "fp32->bf16 RNE" if new_dtype == R.FP32_RNE else "bf16",
         "in_bytes_per_elem": in_bytes_per_elem, "ms_per_step": ms_per_step, "t_enc": t_enc, "t_app": t_app,
         "t_copy": t_copy, "scanned": scanned, "enc_bytes": enc_bytes, "app_bytes": app_bytes,
-        "app_line_bytes": app_line_bytes, "tiles": plan.n_tiles(), "by_tickets": by_tickets,
+        "app_line_bytes": app_line_bytes, "tiles": plan.n_tiles(), "form": form,
         "enc_frac": enc_bytes / 1e9 / (t_enc / 1e3) / HBM_PEAK_GBS,
         "both_frac": (enc_bytes + app_bytes) / 1e9 / ((t_enc + t_app) / 1e3) / HBM_PEAK_GBS,
         "app_line_frac": app_line_bytes / 1e9 / (t_app / 1e3) / HBM_PEAK_GBS if t_app > 0 else None,
@@ -427,8 +434,7 @@ def main():
                                       "dense_s": round(m["t_copy"] / 1e3 + 2 * m["n_elems"] / bps, 4)}
 
     f32, arith = 1 if recipe == "clustered_f32" else 0, 1 if args.payload == "arith" else 0
-    kernels = ["encode_kernel<%d, 0, %d>" % (f32, arith)] if m["by_tickets"] else \
-        ["stage_tiles_kernel<%d, 0, %d>" % (f32, arith), "emit_staged_kernel<%d, 0, %d>" % (f32, arith)]
+    kernels = encode_kernels(m["form"], f32, arith)
     kernel = " + ".join(kernels)
     traffic, traffic_src = None, {"note": "non-default run: no committed profile applies"}
     if args.traffic_bytes is not None:

@@ -1545,11 +1545,13 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 //             them to the bucket.  A tile that holds more than its slot does parks nothing and is read again.
 //   read again   no slots: the second launch reads every tile a second time.
 // ---------------------------------------------------------------------------------------------
+enum : int { kTickets = 0, kStaged = 1, kReadAgain = 2 };
 // The header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one, no tickets.
-__device__ __forceinline__ void write_header(const EncodeArgs &a) {
+__device__ __forceinline__ void write_header(const EncodeArgs &a, uint32_t form) {
     if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
     if (threadIdx.x == kWsTilesWord) a.abort_flag[kWsTilesWord] = (uint32_t)a.n_tiles;
-    if (threadIdx.x == kWsTilesWord + 1) *a.ticket = 0;
+    if (threadIdx.x == kWsFormWord) a.abort_flag[kWsFormWord] = form;
+    if (threadIdx.x == kWsFormWord + 1) *a.ticket = 0;
 }
 
 constexpr int kGroupMost = 16;           // tiles a workgroup of the second launch copies out at most
@@ -1616,7 +1618,7 @@ __global__ __launch_bounds__(kThreads) void stage_tiles_kernel(EncodeArgs a, uin
         total += s_cnt[w];
     }
     if (threadIdx.x == 0) counts[tile] = (uint16_t)total;
-    if (tile == 0) write_header(a);
+    if (tile == 0) write_header(a, kStaged);
     total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
     if (total == 0 || total > (uint32_t)slot_size) return;
 #pragma unroll
@@ -1657,7 +1659,7 @@ __global__ __launch_bounds__(kThreads) void count_tiles_kernel(EncodeArgs a, uin
         for (int w = 0; w < kWaves; ++w) total += s_cnt[w];
         counts[blockIdx.x] = (uint16_t)total;
     }
-    if (blockIdx.x == 0) write_header(a);
+    if (blockIdx.x == 0) write_header(a, kReadAgain);
 }
 
 // What the second launch needs of a tile besides its count.
@@ -2902,7 +2904,6 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
 // 1, 2, 4, 8, 16 tiles: 64 MiB 15.0 14.4 14.8 15.0 16.6 / 16.7 17.4 18.7 21.6 27.5; 512 MiB 114 103 98 96 96 / 130 120 112 114
 // 114).  stream: slots written non-temporal from 192 MiB on (512 MiB, 1 %: 95.7 / 102.4 without, 95.8 / 100.1 with; 1 GiB
 // 188.6 / 207.9 and 186.5 / 191.4; 64 MiB 14.9 / 19.4 and 15.3 / 19.8).
-enum : int { kTickets = 0, kStaged = 1, kReadAgain = 2 };
 struct TwoLaunches {
     int form, group_log2, stream;
 };

@@ -118,6 +118,7 @@ constexpr size_t kWsAbortOff = 0;
 constexpr int kWsCarefulWord = 2;      // 32-bit word 2 of the header counts same-group ticket pairs (diagnostic)
 constexpr int kWsAheadWord = 3;        // 32-bit word 3: how often tiles were counted ahead of a wait (diagnostic)
 constexpr int kWsTilesWord = 4;        // 32-bit word 4: tiles of a launch without tickets, else 0
+constexpr int kWsFormWord = 5;         // 32-bit word 5: 0 after tickets, 1 entries parked, 2 everything read again
 constexpr size_t kWsTicketOff = 4096;
 constexpr size_t kWsHeaderBytes = 8192;
 // Behind them (at a multiple of 256 bytes): room for compacted entries, a slot per tile, of the plans that may be encoded

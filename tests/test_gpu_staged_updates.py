@@ -1,7 +1,7 @@
 """Updates that go in two launches with their entries parked in slots of the workspace: slots that are too small for
 some tiles or for all, groups of tiles that end with a chain, odd widths and alignments, every payload and input type,
 and the lines up to which this form is taken.  Expected values come from the oracle, bit for bit; the workspace's 32-bit
-word 4 (the tiles of a launch without tickets, else 0) says which form ran."""
+words 4 (the tiles of a launch without tickets, else 0) and 5 (1: entries parked, 2: all read again) say which form ran."""
 import numpy as np
 import pytest
 import torch
