@@ -258,8 +258,9 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  *
  * Unless a tile order or a worker cap is set, an update that reads at most 80 MiB goes in two launches that wait
  * for nothing, and so does a larger one (300 MiB at 12 % up to 1.2 GiB at 1 % of changed elements; half as much again
- * with arithmetic payloads or refresh) once the density is known (rose_bucket_check has read a total back, or the
- * buckets bound it), as far as the workspace has room for the entries.  What follows is about the others.
+ * with arithmetic payloads or refresh) where the density is known, as far as the workspace has room for the entries: up to
+ * 300 MiB by the last total that rose_bucket_check has read back, above only if the buckets' capacities bound it too (buckets
+ * sized for what is expected, not for every element).  What follows is about the others.
  * The kernel's workgroups wait on each other's tile counts.  The wait is bounded: if a count does
  * not arrive within a few seconds the launch is marked as failed, every workgroup still exits,
  * seg_off[n_tensors] of every bucket is set to -1, rose_bucket_check returns ROSE_ERR_HIP and

@@ -170,17 +170,19 @@ extern "C" void rose_shard_plan_destroy(rose_plan *p) {
     delete p;
 }
 
-// Changed elements per million that a launch into these buckets is expected to find (-1: unknown).
+// Changed elements per million that these buckets could hold: no update of more of them is of use to anyone.
+static int32_t room_ppm(const rose_plan *p, const rose_bucket *buckets) {
+    double room = 0;
+    for (int32_t d = 0; d < p->n_buckets; ++d) room += (double)(buckets[d].capacity > 0 ? buckets[d].capacity : 0);
+    return p->capacity_sum > 0 && room < (double)p->capacity_sum ? (int32_t)(1e6 * room / (double)p->capacity_sum) : 1000000;
+}
+
+// Changed elements per million that a launch into these buckets is expected to find (-1: unknown): as many as the last time
+// something was read back, until then as many as the buckets could hold.
 static int32_t expected_ppm(const rose_plan *p, const rose_bucket *buckets) {
-    int32_t ppm = p->seen_density_ppm.load(std::memory_order_relaxed);
-    if (ppm < 0 && p->capacity_sum > 0) {
-        // nothing read back yet: the buckets cannot hold more than their capacities, which bounds the density
-        double room = 0;
-        for (int32_t d = 0; d < p->n_buckets; ++d) room += (double)(buckets[d].capacity > 0 ? buckets[d].capacity : 0);
-        const double bound = 1e6 * room / (double)p->capacity_sum;
-        ppm = bound >= 1e6 ? -1 : (int32_t)bound;
-    }
-    return ppm;
+    const int32_t seen = p->seen_density_ppm.load(std::memory_order_relaxed);
+    const int32_t room = seen < 0 ? room_ppm(p, buckets) : 0;
+    return seen >= 0 ? seen : room < 1000000 ? room : -1;
 }
 
 // The tile order a launch into these buckets uses: the caller's choice, else by density.
@@ -259,7 +261,7 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     const bool order_free = p->tile_order.load(std::memory_order_relaxed) == ROSE_TILE_ORDER_AUTO_PICK;
     return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, resident,
                                p->worker_cap.load(std::memory_order_relaxed), order, order_free, ppm,
-                               stream) == 0
+                               room_ppm(p, buckets), stream) == 0
                ? ROSE_OK
                : ROSE_ERR_HIP;
 }

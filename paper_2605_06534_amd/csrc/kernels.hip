@@ -2886,7 +2886,7 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
 //         16 MiB   7.9 / 12.2     7.4 / 11.3    33                             1 %
 //         64 MiB   21.9 / 28.2    14.3 / 18.9   40 / 41                        1 %
 //         64 MiB   26.0 / 34.5    18.9 / 26.7   42 / 43                        10 %
-//         64 MiB   33.1 / 41.9    38.6 / 46.3   48 / 48                        30 % (past the slots: read again)
+//         64 MiB   33.4 / 39.1    35.2 / 41.5   48 / 48                        30 % (past the slots: read again)
 //        192 MiB                  37 / 41       65 / 65                        1 %
 //        450 MiB                  84 / 91       113 / 112                      1 %
 //        450 MiB                  104 / 120     123 / 123                      5 %
@@ -2898,36 +2898,53 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
 //   refresh,    bf16 1000 MiB     277 / 314     322 / 319                      5 %
 // So: read again below 12 MiB, where the second reading comes out of the caches at once, and where the slots do not hold
 // the tiles; staged up to kStagedMib of the density, half as much again for arithmetic payloads and refresh; by tickets
-// above.  Without a density (no bucket checked yet, buckets with room for everything) 80 MiB are the line for all.
-// Slots have to hold twice what is expected of a tile (densities differ between the rows of a model), below 80 MiB 1.25
-// times.  group: a workgroup of the second launch takes more tiles the more there are and the less they hold (1 % / 5 %,
+// above.  Slots have to hold twice what is expected of a tile (densities differ between the rows of a model), below 80 MiB
+// 1.25 times.
+// The density is that of the last update looked at, and another may come.  What is past its slot is read again, so that the
+// staged form then takes (1 % seen, one matrix, bf16, us, in the caches; beside it reading again up to 80 MiB, tickets above):
+//   comes     64 MiB         192 MiB     300 MiB     384 MiB     850 MiB     1200 MiB
+//     1 %     14.7  22.2      37   64     57   84     73  101    154  183    219  244
+//    10 %     22.1  26.2      55   71     78   92    106  113    348  222    510  302
+//    13 %     24.4  27.6      60   74     83   94    156  119    354  224    527  303
+//    20 %     29.0  29.9      69   97    123  121    160  150    368  308    581  431
+//    30 %     35.2  33.4      88   98    129  133    168  158    422  333    613  448
+//   100 %     49.8  46.5     121  163    200  231    254  291    569  617    820  894
+// (the worst between these: 64 MiB at 25 % 35.6 and 31.5, with arithmetic payloads 42 and 33; 300 MiB at 17 % 121 and 112).
+// From 48 to 300 MiB a wrong guess costs little beside what a right one gains, and the last density is taken.  Elsewhere the
+// form goes by the most that the buckets could hold where that is more: above 300 MiB, as the table shows, and below 48 MiB,
+// where reading again is nearly as fast (32 MiB, 1 %: 11.7 and 9.7) and a wrong guess dear (25 % come: 15.7 and 21.7).  With no
+// density at all (no bucket checked yet, buckets with room for everything) updates are read again up to 80 MiB and go by
+// tickets above.
+// group: a workgroup of the second launch takes more tiles the more there are and the less they hold (1 % / 5 %,
 // 1, 2, 4, 8, 16 tiles: 64 MiB 15.0 14.4 14.8 15.0 16.6 / 16.7 17.4 18.7 21.6 27.5; 512 MiB 114 103 98 96 96 / 130 120 112 114
 // 114).  stream: slots written non-temporal from 192 MiB on (512 MiB, 1 %: 95.7 / 102.4 without, 95.8 / 100.1 with; 1 GiB
 // 188.6 / 207.9 and 186.5 / 191.4; 64 MiB 14.9 / 19.4 and 15.3 / 19.8).
 struct TwoLaunches {
     int form, group_log2, stream;
 };
-constexpr int64_t kReadAgainMib = 12, kUnknownMib = 80, kStreamMib = 192;
+constexpr int64_t kReadAgainMib = 12, kUnknownMib = 80, kStreamMib = 192, kGuessFromMib = 48, kGuessToMib = 300;
 constexpr struct {
     int32_t below_ppm;
     int64_t mib;
 } kStagedMib[] = {{12000, 1200}, {22000, 850}, {32000, 700}, {55000, 480}, {85000, 400}, {125000, 300}};
 static_assert((kUnknownMib << 20) / 4 < (int64_t)1 << 31 && kStageMostTiles * kTile < (int64_t)1 << 31,
               "the second launch adds up entries in 32 bits");
-static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh, int arith, int32_t ppm) {
+static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh, int arith, int32_t ppm, int32_t room_ppm) {
     const int64_t bytes = (int64_t)a.n_tiles * kTile * (new_is_f32 ? 6 : 4), mib = (bytes + (1 << 19)) >> 20;
-    const int64_t expected = ppm < 0 ? 0 : (int64_t)ppm * kTile / 1000000;
+    const bool guess = mib >= kGuessFromMib && mib <= kGuessToMib;
+    const int32_t by = ppm < 0 ? 1000000 : guess || room_ppm < ppm ? ppm : room_ppm;
+    const int64_t expected = (int64_t)by * kTile / 1000000;
     TwoLaunches t = {kTickets, 0, mib >= kStreamMib};
     if (mib <= kUnknownMib) {
         t.form = mib <= kReadAgainMib || a.slot_size < kThreads || expected * 5 / 4 + 64 > a.slot_size ? kReadAgain : kStaged;
-    } else if (ppm >= 0 && expected * 2 + 64 <= a.slot_size) {
+    } else if (expected * 2 + 64 <= a.slot_size) {
         for (const auto &line : kStagedMib)
-            if (ppm < line.below_ppm) {
+            if (by < line.below_ppm) {
                 if (mib <= (refresh || arith ? line.mib * 3 / 2 : line.mib)) t.form = kStaged;
                 break;
             }
     }
-    const int g = (mib >= 32) + (mib >= 96) + (mib >= 192) + (mib >= 384) - (ppm > 30000) - (ppm > 80000);
+    const int g = (mib >= 32) + (mib >= 96) + (mib >= 192) + (mib >= 384) - (by > 30000) - (by > 80000);
     t.group_log2 = g > 0 ? g : 0;
     return t;
 }
@@ -2939,12 +2956,12 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
 }
 
 int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
-                  int worker_cap, int order, bool order_free, int32_t ppm, void *stream) {
+                  int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
     if (order_free && worker_cap == 0) {
         const int r = refresh ? 1 : 0;
-        const TwoLaunches two = two_launches(a, new_is_f32, r, arith, ppm);
+        const TwoLaunches two = two_launches(a, new_is_f32, r, arith, ppm, room_ppm);
         if (two.form != kTickets) {
             uint16_t *counts = reinterpret_cast<uint16_t *>(a.tile_desc);
             if (two.form == kStaged) {

@@ -152,9 +152,9 @@ struct RefreshArgs {
 // resident: workgroups of this kernel variant that fit on the device at once (encode_resident_all);
 // worker_cap: 0, or the most workgroups that may walk tiles; order: ROSE_TILE_ORDER_SPREAD, _NEIGHBOURS or _TIMED;
 // order_free: nobody asked for that order, small updates may go without tickets; ppm: changed elements per
-// million as far as known or bounded, else -1
+// million as far as known or bounded, else -1; room_ppm: as many as the buckets could hold
 int launch_encode(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
-                  int worker_cap, int order, bool order_free, int32_t ppm, void *stream);
+                  int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream);
 // resident workgroups of each of the eight encode kernel variants on the current device
 // (index: fp32 input + 2 * refresh + 4 * arithmetic payload)
 int encode_resident_all(int resident[8]);

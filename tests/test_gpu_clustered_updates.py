@@ -5,20 +5,32 @@ import torch
 
 import paper_2605_06534_amd as R
 from test_gpu_parity import T
-from test_gpu_staged_updates import CHECKS, know_density, make, tiles_without_tickets
+from test_gpu_staged_updates import CHECKS, PARKED, form, know_density, make, tiles_without_tickets
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("what", sorted(CHECKS))
-@pytest.mark.parametrize("mib,tp,p,dense,fp32", [(14, 1, 0.001, 40, False), (60, 2, 0.002, 70, True), (70, 4, 0.002, 300, False),
+@pytest.mark.parametrize("mib,tp,p,dense,fp32", [(14, 1, 0.001, 20, False), (60, 2, 0.002, 70, True), (70, 4, 0.002, 300, False),
                                                  (290, 2, 0.001, 900, False)])
 def test_runs_of_dense_tiles(mib, tp, p, dense, fp32, what):
     print("case: %d dense tiles in %d MiB tp=%d %s fp32=%s" % (dense, mib, tp, what, fp32), flush=True)
     c = make(mib, tp, 513, p, mib + dense, fp32, dense)
     know_density(c)
     CHECKS[what](c)
-    assert tiles_without_tickets(c) == c.plan.n_tiles()
+    assert tiles_without_tickets(c) == c.plan.n_tiles() and form(c) == PARKED
+
+
+@pytest.mark.parametrize("what", sorted(CHECKS))
+@pytest.mark.parametrize("entries", [256, 300, 2016])
+def test_small_slots(entries, what):
+    """Room for so many entries a tile, tiles that hold nearly as many or 8192."""
+    print("case: slots of %d entries, %s" % (entries, what), flush=True)
+    c = make(34, 2, 8, 0.16 if entries == 2016 else 0.006, entries, dense=2)
+    base = c.plan.workspace_bytes() - c.plan.n_tiles() * 2016 * 4
+    c.ws = torch.full(((base + c.plan.n_tiles() * entries * 4) // 8 + 1,), -1, dtype=torch.int64, device="cuda")
+    CHECKS[what](c)
+    assert form(c) == PARKED
 
 
 def test_time_of_changes_that_lie_together():

@@ -30,8 +30,11 @@ def tensors(mib, tp, run, fp32):
 
 
 def make(mib, tp, run, p, seed, fp32=False, dense=0):
-    """dense: so many tiles' worth of neighbouring elements of the large tensor all change."""
+    """dense: so many tiles' worth of neighbouring elements of the large tensor all change.  The buckets have room for
+    little more than comes: the form goes by that where the density is not known, or not taken."""
     c = packed_case(tensors(mib, tp, run, fp32), tp, p, seed, 1, 3, fp32)
+    for b in c.buckets:
+        b.capacity = min(b.capacity, int(1.05 * p * b.capacity) + (dense + 2) * TILE)
     if dense:
         part = slice(TILE * 5 + 100, TILE * (5 + dense) + 100)
         was = c.old[-1][part].view(torch.int16)
@@ -52,6 +55,13 @@ def tiles_without_tickets(c):
     return int(c.ws.view(torch.int32)[4])
 
 
+PARKED, READ_AGAIN = 1, 2
+
+
+def form(c):
+    return int(c.ws.view(torch.int32)[5])
+
+
 @pytest.mark.parametrize("fp32", [False, True])
 @pytest.mark.parametrize("what", sorted(CHECKS))
 @pytest.mark.parametrize("run,tp,p,dense", [(765, 3, 0.01, 0), (8, 2, 0.2, 0), (7, 1, 0.05, 33)])
@@ -60,6 +70,7 @@ def test_small(run, tp, p, dense, what, fp32):
     c = make(13, tp, run, p, run, fp32, dense)
     CHECKS[what](c)
     assert tiles_without_tickets(c) == c.plan.n_tiles()
+    assert form(c) == (READ_AGAIN if p == 0.2 else PARKED)
 
 
 @pytest.mark.parametrize("mib,tp,p,what,fp32", [(34, 5, 0.04, "new", False), (81, 2, 0.01, "arith", False), (100, 8, 0.06, "new", True),
@@ -73,6 +84,7 @@ def test_groups_of_tiles(mib, tp, p, what, fp32):
     know_density(c)
     CHECKS[what](c)
     assert tiles_without_tickets(c) == c.plan.n_tiles()
+    assert form(c) == PARKED
 
 
 @pytest.mark.parametrize("entries", [0, 31, 255, 256, 300, 2016])

@@ -33,3 +33,29 @@ def test_kernels_of_an_update(mib, seen, order, form):
     words = ws.view(torch.int32)
     assert " ".join(k.split("<")[0] for k in bench.encode_kernels(int(words[5]), 0, 0)) == form
     assert int(words[4]) == (0 if form == TICKETS else plan.n_tiles()) and (int(words[1024]) > 0) == (form == TICKETS)
+
+
+@pytest.mark.parametrize("mib,seen,room,form", [
+    (13, None, 1.0, READ_AGAIN), (64, None, 1.0, READ_AGAIN), (90, None, 1.0, TICKETS),         # nothing known
+    (30, None, 0.02, PARKED), (64, None, 0.3, READ_AGAIN), (200, None, 0.02, PARKED),           # what the buckets hold
+    (30, 0.01, 1.0, READ_AGAIN), (30, 0.01, 0.02, PARKED), (30, 0.02, 0.01, PARKED),
+    (64, 0.01, 1.0, PARKED), (64, 0.3, 0.02, READ_AGAIN), (280, 0.01, 1.0, PARKED),             # the last density
+    (320, 0.01, 1.0, TICKETS), (320, 0.01, 0.02, PARKED), (800, 0.01, 1.0, TICKETS), (800, 0.01, 0.012, PARKED),
+    (800, 0.01, 0.1, TICKETS)])
+def test_a_wrong_guess(mib, seen, room, form):
+    """The form is chosen by a density that may be outdated only where that costs little if it is."""
+    print("case: form of %d MiB, seen %s, room for %g" % (mib, seen, room), flush=True)
+    n = (mib << 20) // 4
+    plan = R.shard_plan([T(n // 4096, 4096, R.SPLIT_ROWS)], 1)
+    weights = torch.zeros(n, dtype=torch.int16, device="cuda")
+    tab = R.ptr_table([weights])
+    b = R.Bucket(int(room * n), 1)
+    if seen is not None:
+        b.seg_off[-1], b.capacity = int(seen * n), 1 << 40
+        R.bucket_check(plan, b)
+        b.capacity = int(room * n)
+    ws = R.workspace(plan)
+    ws.fill_(-1)
+    R.delta_encode(plan, tab, tab, R.BF16, [b], ws)
+    assert R.bucket_check(plan, b) == 0
+    assert " ".join(k.split("<")[0] for k in bench.encode_kernels(int(ws.view(torch.int32)[5]), 0, 0)) == form
