@@ -2896,8 +2896,9 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
 //   arithmetic, bf16 1000 MiB     229 / 259     258 / 259                      5 %
 //               bf16 2000 MiB     365 / 399     430 / 432                      1 %
 //   refresh,    bf16 1000 MiB     277 / 314     322 / 319                      5 %
-// So: read again below 12 MiB, where the second reading comes out of the caches at once, and where the slots do not hold
-// the tiles; staged up to kStagedMib of the density, half as much again for arithmetic payloads and refresh; by tickets
+// So: read again below 12 MiB, where the second reading comes out of the caches at once, and below 24 MiB from 10 % on (16 MiB at
+// 5 / 10 / 15 %: read again 8.7 9.1 9.8, staged 8.5 9.1 10.4; 24 MiB: 10.2 10.6 11.3 and 9.6 10.5 11.7), and where the slots do
+// not hold the tiles; staged up to kStagedMib of the density, half as much again for arithmetic payloads and refresh; by tickets
 // above.  Slots have to hold twice what is expected of a tile (densities differ between the rows of a model), below 80 MiB
 // 1.25 times.
 // The density is that of the last update looked at, and another may come.  What is past its slot is read again, so that the
@@ -2922,7 +2923,8 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
 struct TwoLaunches {
     int form, group_log2, stream;
 };
-constexpr int64_t kReadAgainMib = 12, kUnknownMib = 80, kStreamMib = 192, kGuessFromMib = 48, kGuessToMib = 300;
+constexpr int64_t kReadAgainMib = 12, kReadAgainDenseMib = 24, kUnknownMib = 80, kStreamMib = 192, kGuessFromMib = 48, kGuessToMib = 300;
+constexpr int32_t kReadAgainDensePpm = 100000;
 constexpr struct {
     int32_t below_ppm;
     int64_t mib;
@@ -2936,7 +2938,8 @@ static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh
     const int64_t expected = (int64_t)by * kTile / 1000000;
     TwoLaunches t = {kTickets, 0, mib >= kStreamMib};
     if (mib <= kUnknownMib) {
-        t.form = mib <= kReadAgainMib || a.slot_size < kThreads || expected * 5 / 4 + 64 > a.slot_size ? kReadAgain : kStaged;
+        const bool read_again = mib <= kReadAgainMib || (mib <= kReadAgainDenseMib && by >= kReadAgainDensePpm);
+        t.form = read_again || a.slot_size < kThreads || expected * 5 / 4 + 64 > a.slot_size ? kReadAgain : kStaged;
     } else if (expected * 2 + 64 <= a.slot_size) {
         for (const auto &line : kStagedMib)
             if (by < line.below_ppm) {
