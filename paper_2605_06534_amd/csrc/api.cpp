@@ -97,20 +97,24 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
         }
     }
     rose::Piece *dp = nullptr;
-    int32_t *dt = nullptr, *dn = nullptr, *dr = nullptr;
+    int32_t *dt = nullptr, *dc = nullptr, *dn = nullptr, *dr = nullptr;
     int64_t *drn = nullptr;
     unsigned long long *dv = nullptr;
     int resident[8];
     void *sws = nullptr;
     size_t sws_bytes = 0;
     const size_t pb = p->pieces.size() * sizeof(rose::Piece), tb = p->tile_piece.size() * sizeof(int32_t);
+    const size_t cfb = p->copy_first.size() * sizeof(int32_t), cpb = p->copy_piece.size() * sizeof(int32_t);
     const size_t nb = numel.size() * sizeof(int32_t), vb = kVerdictSlots * sizeof(unsigned long long);
     bool ok = hipMalloc(reinterpret_cast<void **>(&dp), pb) == hipSuccess &&
               hipMalloc(reinterpret_cast<void **>(&dt), tb) == hipSuccess &&
+              hipMalloc(reinterpret_cast<void **>(&dc), cfb + cpb) == hipSuccess &&
               hipMalloc(reinterpret_cast<void **>(&dn), nb) == hipSuccess &&
               hipMalloc(reinterpret_cast<void **>(&dv), vb) == hipSuccess &&
               hipMemcpy(dp, p->pieces.data(), pb, hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(dt, p->tile_piece.data(), tb, hipMemcpyHostToDevice) == hipSuccess &&
+              hipMemcpy(dc, p->copy_first.data(), cfb, hipMemcpyHostToDevice) == hipSuccess &&
+              (cpb == 0 || hipMemcpy(dc + p->copy_first.size(), p->copy_piece.data(), cpb, hipMemcpyHostToDevice) == hipSuccess) &&
               hipMemcpy(dn, numel.data(), nb, hipMemcpyHostToDevice) == hipSuccess &&
               hipMemset(dv, 0, vb) == hipSuccess;
     if (ok && !repl.empty()) {
@@ -123,6 +127,7 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
     if (!ok) {
         if (dp) (void)hipFree(dp);
         if (dt) (void)hipFree(dt);
+        if (dc) (void)hipFree(dc);
         if (dn) (void)hipFree(dn);
         if (dv) (void)hipFree(dv);
         if (dr) (void)hipFree(dr);
@@ -131,6 +136,7 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
     }
     p->d_pieces = dp;
     p->d_tile_piece = dt;
+    p->d_copy = dc;
     p->d_local_numel = dn;
     p->d_verdict = dv;
     p->d_repl_list = dr;
@@ -162,6 +168,7 @@ extern "C" void rose_shard_plan_destroy(rose_plan *p) {
     if (!p) return;
     if (p->d_pieces) (void)hipFree(p->d_pieces);
     if (p->d_tile_piece) (void)hipFree(p->d_tile_piece);
+    if (p->d_copy) (void)hipFree(p->d_copy);
     if (p->d_local_numel) (void)hipFree(p->d_local_numel);
     if (p->d_verdict) (void)hipFree(p->d_verdict);
     if (p->d_repl_list) (void)hipFree(p->d_repl_list);
@@ -338,11 +345,12 @@ extern "C" rose_status rose_dense_copy(const rose_plan *p, int32_t d, const void
     rose_status s = device_tables(p);
     if (s != ROSE_OK) return s;
     a.pieces = p->d_pieces;
-    a.tile_piece = p->d_tile_piece;
+    a.tile_piece = p->copy_piece.empty() ? p->d_tile_piece : p->d_copy + p->copy_first.size();
+    a.first_tile = p->d_copy;
     a.new_ptrs = new_ptrs;
     a.dst_ptrs = dst_ptrs;
-    a.tile_begin = p->chain_first[d];
-    a.n_tiles = p->chain_first[d + 1] - p->chain_first[d];
+    a.tile_begin = p->copy_chain_first[d];
+    a.n_tiles = p->copy_chain_first[d + 1] - p->copy_chain_first[d];
     return rose::launch_dense_copy(a, new_dtype == ROSE_FP32_RNE, stream) == 0 ? ROSE_OK : ROSE_ERR_HIP;
 }
 

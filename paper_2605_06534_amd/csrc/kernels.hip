@@ -2564,17 +2564,18 @@ __global__ __launch_bounds__(WAVES * 64) void apply_object_kernel(const char *ob
 // (Eight 7B-style layers, TP4, four shards: 1416 -> 1287 us; packed at odd elements: 4130 -> 1421 us at TP2; rows of
 // 765 elements a shard, 131 M weights: 248 -> 89 us; figures before that.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCopyAtOnce = 2112;       // workgroups (2048 of 256 threads, 8 waves per SIMD; a few find nothing to copy)
+constexpr int kCopyAtOnce = 2048;       // workgroups (of 256 threads, 8 waves per SIMD)
 template <int NEW_F32>
 __global__ __launch_bounds__(kThreads) void dense_copy_kernel(CopyArgs a) {
     const int32_t tile = a.tile_begin + (int32_t)blockIdx.x;
-    const Piece pc = load_piece(a.pieces + cload32(a.tile_piece + tile));
+    const int32_t piece = cload32(a.tile_piece + tile);
+    const Piece pc = load_piece(a.pieces + piece);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const void *new_base = reinterpret_cast<const void *>(cload64(a.new_ptrs + pc.tensor));
     uint16_t *dst = reinterpret_cast<uint16_t *>(cload64(a.dst_ptrs + pc.tensor));
     const uint32_t len = (uint32_t)pc.len;
-    const uint32_t k_tile = (uint32_t)(tile - pc.first_tile) * (uint32_t)kTile;
-    if (k_tile >= len) return;                          // see kPieceShift: nothing is left for it
+    const uint32_t k_tile = (uint32_t)(tile - cload32(a.first_tile + piece)) * (uint32_t)kTile;
+    if (k_tile >= len) return;                          // a tile for being moved (kPieceShift), or an empty piece
     const bool dst_strided = (pc.flags & kPieceDstStrided) != 0;
     const uint32_t line = len > (uint32_t)kTile ? (uint32_t)kShiftElems : (uint32_t)kVec;     // (a short piece: little to copy singly)
     const uint32_t head = dst_strided ? 0u : (0u - ((uint32_t)((uintptr_t)dst >> 1) + (uint32_t)pc.local_base)) & (line - 1u);

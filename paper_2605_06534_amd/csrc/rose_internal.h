@@ -127,9 +127,13 @@ constexpr int64_t kStageMostTiles = 65536;               // 2 GiB read in bf16
 constexpr size_t kStageMostBytes = ROSE_STATIC_SCRATCH_BYTES;   // all of it together, so that the built-in scratch holds it
 constexpr int kStageSlot = 2016;                         // entries of a slot at most: 24 % of a tile, 8 KB of LDS a workgroup
 
+// Plans of at most so many tiles have a numbering of their own for the dense copy's (copy_tiles).
+constexpr int64_t kCopyOwnTiles = 65536;
+
 struct CopyArgs {
     const Piece *pieces;
-    const int32_t *tile_piece;
+    const int32_t *tile_piece;              // piece of each tile
+    const int32_t *first_tile;              // first tile of each piece
     const void *const *new_ptrs;
     void *const *dst_ptrs;
     int32_t tile_begin;
@@ -200,6 +204,9 @@ struct rose_plan {
     std::vector<int64_t> global_base;          // [n_tensors + 1]
     std::vector<rose::Piece> pieces;
     std::vector<int32_t> tile_piece;           // piece of each tile
+    std::vector<int32_t> copy_piece;           // the same for the dense copy (empty: the encode's tiles)
+    std::vector<int32_t> copy_first;           // first tile of each piece there
+    int32_t copy_chain_first[ROSE_MAX_TP + 1] = {0};
     int32_t chain_first[ROSE_MAX_TP + 1] = {0};
     int32_t block_first[ROSE_MAX_TP + 1] = {0};
     mutable std::atomic<int32_t> worker_cap{0};     // rose_plan_set_worker_cap
@@ -213,6 +220,7 @@ struct rose_plan {
     mutable int device = -1;
     mutable rose::Piece *d_pieces = nullptr;
     mutable int32_t *d_tile_piece = nullptr;
+    mutable int32_t *d_copy = nullptr;         // copy_first, then copy_piece
     mutable int32_t *d_local_numel = nullptr;  // [pp_dst][n_tensors] elements of a shard's copy of each tensor
                                                // (0 where the stage does not hold the tensor)
     mutable int32_t *d_repl_list = nullptr;    // replicated tensors this sender holds (ordinals) and their sizes

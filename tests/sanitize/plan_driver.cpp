@@ -26,6 +26,25 @@ static rose_tensor_desc desc(int64_t rows, int64_t cols, int32_t rule, std::vect
     return t;
 }
 
+static void copy_tiles(const rose_plan *p, int32_t tp) {
+    // the dense copy's tiles: each piece as many as it fills, one if it is empty, one piece behind the other; those of
+    // the encode for a plan of many
+    int64_t c = 0;
+    for (size_t k = 0; k < p->pieces.size(); ++k) {
+        const rose::Piece &pc = p->pieces[k];
+        const int32_t next = k + 1 < p->pieces.size() ? p->pieces[k + 1].first_tile : (int32_t)p->tile_piece.size();
+        const int64_t nt = p->copy_piece.empty() ? next - pc.first_tile : pc.len == 0 ? 1 : (pc.len + rose::kTile - 1) / rose::kTile;
+        if (p->copy_first[k] != c || c < p->copy_chain_first[pc.shard] || c + nt > p->copy_chain_first[pc.shard + 1])
+            fail("first tile of a copy", (int)k);
+        const std::vector<int32_t> &of = p->copy_piece.empty() ? p->tile_piece : p->copy_piece;
+        for (int64_t j = 0; j < nt; ++j, ++c)
+            if (c >= (int64_t)of.size() || of[c] != (int32_t)k) fail("piece of a copy's tile", (int)c);
+        if (p->copy_piece.empty() && pc.first_tile != p->copy_first[k]) fail("shared tiles", (int)k);
+    }
+    if (c != p->copy_chain_first[tp] || (!p->copy_piece.empty() && c != (int64_t)p->copy_piece.size())) fail("tiles of a copy", (int)c);
+    if (p->copy_piece.empty() != (p->tile_piece.size() > (size_t)rose::kCopyOwnTiles)) fail("whose tiles", (int)c);
+}
+
 static void walk(const std::vector<rose_tensor_desc> &ts, int32_t tp, int32_t tp_src, int32_t src_rank) {
     rose_plan *p = nullptr;
     rose_status s = rose_shard_plan_create_src(ts.data(), (int32_t)ts.size(), tp, tp_src, src_rank, &p);
@@ -59,6 +78,7 @@ static void walk(const std::vector<rose_tensor_desc> &ts, int32_t tp, int32_t tp
         const bool sends = ts[t].rule != ROSE_REPLICATED || t % tp_src == src_rank;
         if (sent != (sends ? n : 0)) fail("a sender sends its whole slice, or nothing of a replicated tensor", t);
     }
+    copy_tiles(p, tp);
     delete p;                                        // the plan owns no device memory before its first device call
 }
 
@@ -66,7 +86,7 @@ int main() {
     std::vector<rose_tensor_desc> ts = {
         desc(3, 41, ROSE_REPLICATED), desc(0, 16, ROSE_SPLIT_ROWS), desc(16, 37, ROSE_SPLIT_ROWS),
         desc(5, 64, ROSE_SPLIT_COLS), desc(64, 9, ROSE_FUSED_ROWS, {32, 16, 16}), desc(2, 20000, ROSE_SPLIT_COLS),
-        desc(1, 3 * 8192 + 5, ROSE_REPLICATED),
+        desc(1, 3 * 8192 + 5, ROSE_REPLICATED), desc(8, 2 * 8192 - 3, ROSE_SPLIT_ROWS), desc(1, 2 * 8192, ROSE_REPLICATED),
     };
     for (int32_t tp : {1, 2, 4, 8})
         for (int32_t tp_src : {1, 2, 4, 8})
@@ -75,6 +95,12 @@ int main() {
     for (int32_t tp : {1, 2, 4, 8})
         for (int32_t tp_src : {1, 2, 4, 8})
             for (int32_t s = 0; s < tp_src; ++s) walk(g, tp, tp_src, s);
+    std::vector<rose_tensor_desc> many = {desc(8, 7, ROSE_REPLICATED), desc(8, (int64_t)8192 * 8192, ROSE_SPLIT_ROWS), desc(8, 8192 * 2, ROSE_SPLIT_ROWS)};
+    rose_plan *large = nullptr;
+    if (rose_shard_plan_create(many.data(), 3, 4, &large) != ROSE_OK) fail("create", 0);
+    copy_tiles(large, 4);
+    if (!large->copy_piece.empty()) fail("a plan of many tiles shares them", 0);
+    delete large;
     // descriptors the planner must turn down without touching anything
     rose_plan *p = nullptr;
     std::vector<rose_tensor_desc> bad = {desc(6, 4, ROSE_SPLIT_ROWS)};
