@@ -127,7 +127,8 @@ def encode_kernels(form, f32, arith):
     """The kernels of an encode of this form (32-bit word 5 of its workspace)."""
     return {0: ["encode_kernel<%d, 0, %d>" % (f32, arith)],
             1: ["stage_tiles_kernel<%d, 0, %d>" % (f32, arith), "emit_staged_kernel<%d, 0, %d>" % (f32, arith)],
-            2: ["count_tiles_kernel<%d>" % f32, "emit_tiles_kernel<%d, 0, %d>" % (f32, arith)]}[form]
+            2: ["count_tiles_kernel<%d>" % f32, "emit_tiles_kernel<%d, 0, %d>" % (f32, arith)],
+            3: ["encode_elements_kernel"]}[form]
 
 
 def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_host_sample):
@@ -267,7 +268,7 @@ def measure(R, name, tensors, tp, recipe, p, args, steps, warmup, probes, keep_h
     t_enc = sum(e[0].elapsed_time(e[1]) for e in events) / steps
     t_app = sum(e[1].elapsed_time(e[2]) for e in events) / steps
     # Updates that are not large go in two launches instead of by tickets; the workspace's 32-bit word 5 says which way
-    # the timed ones went (0: tickets, 1: entries parked, 2: everything read again).
+    # the timed ones went (encode_kernels).
     form = int(ws.view(torch.int32)[5])
 
     # dense path for comparison (Sec. 6.3 crossover): every shard's slice of the new weights copied

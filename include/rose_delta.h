@@ -276,8 +276,9 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * and 3 of the workspace hold diagnostic counts (how often a workgroup received two tickets of one group of blocks in a row;
  * how often it counted a ticket's remaining tiles ahead of a wait, which happens where more than
  * about a third of the elements change; both are 0 after an update in two launches).  Word 4 is the number of tiles
- * of an update in two launches, and 0 after one by tickets.  Word 5 says how the update went: 0 by tickets, 1 in two launches
- * with the entries parked in the workspace, 2 in two launches that both read the tensors.
+ * of an update in two launches, and 0 after one by tickets.  Word 5 says how the update went: 0 by tickets (3 if
+ * arithmetic payloads were formed of every element, not of the entries), 1 in two launches with the entries parked in the
+ * workspace, 2 in two launches that both read the tensors.
  */
 rose_status rose_delta_encode(const rose_plan *plan, const void *const *old_ptrs,
                               const void *const *new_ptrs, int32_t new_dtype,

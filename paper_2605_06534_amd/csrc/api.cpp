@@ -100,7 +100,7 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
     int32_t *dt = nullptr, *dc = nullptr, *dn = nullptr, *dr = nullptr;
     int64_t *drn = nullptr;
     unsigned long long *dv = nullptr;
-    int resident[8];
+    int resident[rose::kEncodeKernels];
     void *sws = nullptr;
     size_t sws_bytes = 0;
     const size_t pb = p->pieces.size() * sizeof(rose::Piece), tb = p->tile_piece.size() * sizeof(int32_t);
@@ -258,7 +258,6 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     }
     rose::RefreshArgs r{p->d_repl_list, p->d_repl_numel, p->n_repl};
     const bool f32 = new_dtype == ROSE_FP32_RNE;
-    const int resident = p->resident[(f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     // Tile order: the caller's choice, else picked from the density the plan's last checked launch showed
     // (7B-style workload on the same buffers, ms: timed 4.66 / 4.74 at 3.5 / 4 % where neighbours takes 4.78 /
     // 4.77, which pays from 4.5 % on; neighbours 5.29 / 5.46 / 6.19 at 7 / 8 / 10 % where spread takes
@@ -266,7 +265,7 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     const int32_t ppm = expected_ppm(p, buckets);
     const int order = pick_tile_order(p, ppm);
     const bool order_free = p->tile_order.load(std::memory_order_relaxed) == ROSE_TILE_ORDER_AUTO_PICK;
-    return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, resident,
+    return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, p->resident,
                                p->worker_cap.load(std::memory_order_relaxed), order, order_free, ppm,
                                room_ppm(p, buckets), stream) == 0
                ? ROSE_OK

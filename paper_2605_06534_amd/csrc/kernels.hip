@@ -351,10 +351,11 @@ __device__ __forceinline__ u64 desc_load(u64 *p) {
 }
 
 // The workspace is one array of 64-bit words: header (abort flag, ticket counters), tile words,
-// block words.  All of it starts at zero.
-__global__ void reset_kernel(u64 *workspace, int64_t n_words) {
+// block words.  All of it starts at zero, but for the word that says how the update goes.
+__global__ void reset_kernel(u64 *workspace, int64_t n_words, uint32_t form) {
+    static_assert(kWsFormWord % 2 == 1, "an upper half");
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; i < n_words; i += (int64_t)gridDim.x * blockDim.x) workspace[i] = 0;
+    for (; i < n_words; i += (int64_t)gridDim.x * blockDim.x) workspace[i] = i == kWsFormWord / 2 ? (u64)form << 32 : 0;
 }
 
 // After encode: if any wave gave up waiting, mark every bucket as invalid (total = -1) so that
@@ -847,8 +848,12 @@ __device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, 
     return (entry & 0x7FFF0000u) | payload | (escapes ? 0x80000000u : 0u);
 }
 
-template <int NEW_F32, int REFRESH, int ARITH>
+// PAYLOAD = 1: arithmetic payloads formed of the compacted entries; 2: of every element, before they are compacted.
+template <int NEW_F32, int REFRESH, int PAYLOAD>
 __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
+    constexpr int ARITH = PAYLOAD == 1;                // entries carry the old pattern beside them
+    constexpr int FORMED = PAYLOAD == 2;               // entries are payloads from the start
+    static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
     __shared__ uint32_t s_ring[kRing];      // an entry: offset inside its tile (13 bits) << 16 | new pattern
@@ -978,13 +983,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 if (kk >= phase && pos < (u64)b.capacity) {
                     const uint32_t entry = parked<ARITH>((off + k) & (kRing - 1), s_ring, s_was);
                     const uint32_t base = k < c1 ? b0 : k < c2 ? b1 : k < c3 ? b2 : b3;
-                    uint32_t local = base + (ARITH ? (entry >> 16) & (uint32_t)(kTile - 1) : entry >> 16);
+                    uint32_t local = base + (PAYLOAD ? (entry >> 16) & (uint32_t)(kTile - 1) : entry >> 16);
                     if (piece >= 0) {                  // base is the tile's first element number here
                         // (runs of one element have no magic divisor: the quotient is the number itself)
                         const uint32_t q = l_run == 1u ? local : (__umulhi(local, l_magic) >> l_shift);
                         local = l_base + q * l_stride + (local - q * l_run);
                     }
-                    if constexpr (ARITH) local |= entry & 0x80000000u;
+                    if constexpr (PAYLOAD) local |= entry & 0x80000000u;
 #if ROSE_NT_STORES
                     __builtin_nontemporal_store((int32_t)local, b.idx + pos);
                     __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
@@ -1173,9 +1178,10 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         cur = loaded ? nxt : start_tile(tile);         // not loaded: the first tile, or one named late
         // ---- (a) change masks ----
         const uint32_t k_wave = cur.k_tile + (uint32_t)wave * kWaveSpan;
-        uint4 nv[kIters];                              // the new patterns
+        uint4 nv[kIters];                              // the new patterns (FORMED: the payloads)
         uint4 ov[ARITH ? kIters : 1];                  // the old ones
         uint32_t mask[kIters];
+        uint32_t escaped = 0;                          // FORMED: bit 8 j + e: element e of vector j escapes
         // Always taken from the load registers, also for a tile that has no 128-bit loads (its
         // result is replaced below): this way every path consumes what was loaded, and the
         // compiler never has to wait for memory before the registers are loaded again.
@@ -1184,6 +1190,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             nv[j] = raw_to_bf16(raw_new, j);
             mask[j] = nz16_mask(xor4(raw_old.v[j], nv[j]));
             if constexpr (ARITH) ov[j] = raw_old.v[j];
+            if constexpr (FORMED) {
+                uint32_t esc8;
+                nv[j] = arith_vec(raw_old.v[j], nv[j], &esc8);
+                escaped |= esc8 << (8 * j);
+            }
         }
         // pin the above here: the load registers are dead from this point on, whatever the
         // scheduler would prefer
@@ -1194,6 +1205,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 #pragma unroll
             for (int j = 0; j < kIters; ++j) asm volatile("" : "+v"(ov[j].x), "+v"(ov[j].y), "+v"(ov[j].z), "+v"(ov[j].w));
         }
+        if constexpr (FORMED) asm volatile("" : "+v"(escaped));
         // (the rare cases are marked as such: laid out in line they cost the fp32 kernels 2 % of an update of 67 M
         // elements)
         if (__builtin_expect((cur.vec & 1u) != 0, 1)) {
@@ -1206,6 +1218,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                         nv[j] = in_place(nv[j], moved);
                         if constexpr (ARITH) ov[j] = in_place(ov[j], moved);
                     }
+                    if constexpr (FORMED)
+                        escaped = (escaped & ~(0xFFu << (8 * j))) | (in_place((escaped >> (8 * j)) & 0xFFu, moved) << (8 * j));
                 }
             }
             // Runs that are no multiple of 8 elements: the vectors that straddle the end of a run hold
@@ -1230,9 +1244,14 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                     const uint32_t left = split_left(c.pc, k_wave + (js * 64 + (uint32_t)lane) * kVec, &q);
                     const int64_t e = split_tail_at(c.pc, q, left);
                     const uint4 o = gload16(c.old_base + e);
-                    const uint4 n = load_new_vec<NEW_F32>(c.new_base, e);
+                    uint4 n = load_new_vec<NEW_F32>(c.new_base, e);
                     const uint32_t tail = 0xFFu & ~((1u << left) - 1u);
                     masks = (masks & ~(tail << (8 * js))) | ((nz16_mask(xor4(o, n)) & tail) << (8 * js));
+                    if constexpr (FORMED) {
+                        uint32_t esc8;
+                        n = arith_vec(o, n, &esc8);
+                        escaped = (escaped & ~(tail << (8 * js))) | ((esc8 & tail) << (8 * js));
+                    }
 #pragma unroll
                     for (int jj = 0; jj < kIters; ++jj) {
                         // (a vector that is not meant keeps all its elements: no branch, hence no second set of registers)
@@ -1255,6 +1274,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 uint4 o = load_vec_general<0>(c.old_base, c.pc, k);
                 uint4 n = load_vec_general<NEW_F32>(c.new_base, c.pc, k);
                 uint32_t m = nz16_mask(xor4(o, n));
+                if constexpr (FORMED) {
+                    uint32_t esc8;
+                    n = arith_vec(o, n, &esc8);
+                    escaped = (escaped & ~(0xFFu << (8 * j))) | (esc8 << (8 * j));
+                }
 #pragma unroll
                 for (int jj = 0; jj < kIters; ++jj) {
                     if (jj == j) {
@@ -1389,7 +1413,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 while (m && !(ROSE_DIAG & 8)) {
                     const uint32_t e = __ffs(m) - 1;
                     m &= m - 1;
-                    s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu);
+                    s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu) |
+                                                 (FORMED ? (escaped >> (8 * j + e)) << 31 : 0u);
                     if constexpr (ARITH) s_was[slot & (kRing - 1)] = (uint16_t)pick16(ov[j], e);
                     ++slot;
                 }
@@ -1515,9 +1540,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 // kernels without spills; the fp32-master kernels hold twice the raw data, and those that form arithmetic
 // payloads keep old and new patterns side by side (and half as much LDS again): those get 3
 // (the one that does all three at once: 2).  Arithmetic payloads are formed of the compacted entries: formed of every
-// element, as this kernel did with 4 waves, they are 400 instructions a wave and tile for some 30 that are needed (eight
+// element, with 4 waves, they are 400 instructions a wave and tile for some 30 that are needed (eight
 // 7B-style layers, TP4, 1 / 5 / 10 %: 1428 / 1603 / 1822 us, this way 1311 / 1516 / 1733; with refresh 2 % 2050 and
 // 1996; two 32B-style layers of fp32 masters, 1.6 / 5 %: 2772 / 3059 and 2645 / 2972, with refresh 3939 and 3688).
+// Where much changes that turns for bf16 weights without refresh, whose payloads are then formed of every element
+// (encode_elements_kernel, see kElementsPpm).
 // REFRESH = 1 also writes the new bf16 values over the old ones; ARITH = 1 emits arithmetic payloads.
 template <int NEW_F32, int REFRESH, int ARITH> __global__ void encode_kernel(EncodeArgs a);
 #define ROSE_ENCODE_KERNEL(F32, REFRESH, ARITH, WAVES, VGPRS)                                                         \
@@ -1535,6 +1562,10 @@ ROSE_ENCODE_KERNEL(1, 1, 0, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 0, 1, 3, kNumVgpr1)
 ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 #undef ROSE_ENCODE_KERNEL
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4), amdgpu_num_vgpr(kNumVgpr0)))
+void encode_elements_kernel(EncodeArgs a) {
+    encode_body<0, 0, 2>(a);
+}
 
 // ---------------------------------------------------------------------------------------------
 // encode in two launches, without tickets (launch_encode says when).  Nothing waits for another workgroup, so there
@@ -1545,7 +1576,7 @@ ROSE_ENCODE_KERNEL(1, 1, 1, 2, kNumVgpr2)
 //             them to the bucket.  A tile that holds more than its slot does parks nothing and is read again.
 //   read again   no slots: the second launch reads every tile a second time.
 // ---------------------------------------------------------------------------------------------
-enum : int { kTickets = 0, kStaged = 1, kReadAgain = 2 };
+enum : int { kTickets = 0, kStaged = 1, kReadAgain = 2, kTicketsElements = 3 };
 // The header is this call's, whatever the workspace held: no wait gave up, no tile was counted ahead of one, no tickets.
 __device__ __forceinline__ void write_header(const EncodeArgs &a, uint32_t form) {
     if (threadIdx.x <= kWsAheadWord) a.abort_flag[threadIdx.x] = 0;
@@ -2770,6 +2801,13 @@ __global__ __launch_bounds__(256) void bw_lines_kernel(uint4 *dst, size_t n_line
 
 // the encode kernel variant for (fp32 master input, sender refresh, arithmetic payload)
 typedef void (*EncodeKernel)(EncodeArgs);
+// Arithmetic payloads of bf16 weights, without refresh: formed of every element from this density on, of the compacted
+// entries below.  One matrix, us, of elements / of entries, 1000 MiB: 10 % 288 / 268, 20 % 348 / 342, 25 % 411 / 405,
+// 30 % 430 / 432, 35 % 520 / 541, 60 % 640 / 721, 100 % 734 / 857; 400 MiB: 20 % 159 / 152, 25 % 174 / 174, 30 % 180 / 183,
+// 100 % 316 / 357.  Where more comes than the last time, entries lose more (1200 MiB, 1 % seen, 25 / 60 / 100 % come:
+// 936 / 843 / 976 and 1337 / 977 / 1202), so the line is for the most that the buckets could hold.
+constexpr int32_t kElementsPpm = 300000;
+constexpr int kElementsVariant = 8;
 static EncodeKernel encode_variant(int new_is_f32, int refresh, int arith) {
     static const EncodeKernel table[8] = {encode_kernel<0, 0, 0>, encode_kernel<1, 0, 0>, encode_kernel<0, 1, 0>,
                                           encode_kernel<1, 1, 0>, encode_kernel<0, 0, 1>, encode_kernel<1, 0, 1>,
@@ -2801,14 +2839,15 @@ static EmitKernel emit_variant(int new_is_f32, int refresh, int arith) {
 }
 
 // Number of workgroups of each encode kernel variant that fit on the current device at once.
-int encode_resident_all(int resident[8]) {
+int encode_resident_all(int resident[kEncodeKernels]) {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return (int)e;
-    for (int v = 0; v < 8; ++v) {
+    for (int v = 0; v < kEncodeKernels; ++v) {
         int per_cu = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, encode_variant(v & 1, v & 2, v & 4), kThreads, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, v == kElementsVariant ? encode_elements_kernel : encode_variant(v & 1, v & 2, v & 4), kThreads, 0);
         if (e != hipSuccess) return (int)e;
         if (per_cu < 1 || cus < 1) return (int)hipErrorInvalidValue;
         if (per_cu > ROSE_WGS_PER_CU) per_cu = ROSE_WGS_PER_CU;
@@ -2851,7 +2890,7 @@ int static_scratch(void **ptr, size_t *bytes) {
 // 41 us the bucket stores may go out (0: always).  ppm: changed elements per million, -1 unknown.
 //   timed       4 tiles, 10 us.  The entries of a period fit the ring up to about 4 %.
 //   neighbours  Denser: 3 tiles, whose prefixes are ready sooner and leave the ring room, and longer windows, so
-//               that less waits: up to 5 % 15 us, above 20 us.
+//               that less waits: up to 5 % 15 us, above, and where payloads are formed of every element, 20 us.
 // 7B-style workload, one process, same buffers, ms (always = neighbours with no windows, 3 tiles):
 //               4 %   4.5 %   5 %   5.5 %   6 %   7 %   8 %   10 %   30 %
 //   always      5.11  5.13    5.19  5.21    5.27  5.32  5.52  6.34   10.75
@@ -2865,7 +2904,7 @@ int static_scratch(void **ptr, size_t *bytes) {
 // lose far more: seen 4.5 %, 20 / 30 % came: 8.9 / 19.4 ms with 4 x 15 us, 7.8 / 10.0 with 3 x 15; fp32 masters, 15 %
 // came: 19.4 and 11.1 (always: 7.8 / 10.3 and 11.8).
 constexpr int32_t kNearBelowPpm = 50000;
-static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
+static void encode_walk(int order, int32_t ppm, bool of_elements, EncodeArgs *a) {
     a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
     a->batch = kBatch;
     a->window_open = 0;
@@ -2873,7 +2912,7 @@ static void encode_walk(int order, int32_t ppm, EncodeArgs *a) {
         a->batch = kBatchTimed;
         a->window_open = ROSE_WRITE_OPEN_TIMED;
     } else if (order == ROSE_TILE_ORDER_NEIGHBOURS) {
-        const bool near = ppm >= 0 && ppm < kNearBelowPpm;
+        const bool near = !of_elements && ppm >= 0 && ppm < kNearBelowPpm;
         a->window_open = near ? ROSE_WRITE_OPEN_NEAR : ROSE_WRITE_OPEN_WIDE;
     }
 }
@@ -2959,7 +2998,7 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
                            new_is_f32);
 }
 
-int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
+int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
@@ -2984,7 +3023,9 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
             return (int)hipGetLastError();
         }
     }
-    encode_walk(order, ppm, &a);
+    const bool of_elements = arith && !new_is_f32 && !refresh && (ppm < 0 || ppm >= kElementsPpm || room_ppm >= kElementsPpm);
+    const int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+    encode_walk(order, ppm, of_elements, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are
@@ -3011,9 +3052,10 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
     const int64_t n_words = (int64_t)(kWsHeaderBytes / sizeof(u64)) + a.n_tiles + a.n_blocks;
     int reset_blocks = (int)((n_words + 1023) / 1024);
     if (reset_blocks > 2048) reset_blocks = 2048;
-    hipLaunchKernelGGL(reset_kernel, dim3(reset_blocks), dim3(256), 0, st, reinterpret_cast<u64 *>(a.abort_flag), n_words);
+    hipLaunchKernelGGL(reset_kernel, dim3(reset_blocks), dim3(256), 0, st, reinterpret_cast<u64 *>(a.abort_flag), n_words,
+                       (uint32_t)(of_elements ? kTicketsElements : kTickets));
     const dim3 grid(workers + server_wgs), block(kThreads);
-    hipLaunchKernelGGL(encode_variant(new_is_f32, refresh ? 1 : 0, arith), grid, block, 0, st, a);
+    hipLaunchKernelGGL(of_elements ? encode_elements_kernel : encode_variant(new_is_f32, refresh ? 1 : 0, arith), grid, block, 0, st, a);
     launch_refresh_replicated(a, new_is_f32, refresh, st);
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64), 0, st, a);
     return (int)hipGetLastError();

@@ -118,7 +118,7 @@ constexpr size_t kWsAbortOff = 0;
 constexpr int kWsCarefulWord = 2;      // 32-bit word 2 of the header counts same-group ticket pairs (diagnostic)
 constexpr int kWsAheadWord = 3;        // 32-bit word 3: how often tiles were counted ahead of a wait (diagnostic)
 constexpr int kWsTilesWord = 4;        // 32-bit word 4: tiles of a launch without tickets, else 0
-constexpr int kWsFormWord = 5;         // 32-bit word 5: 0 after tickets, 1 entries parked, 2 everything read again
+constexpr int kWsFormWord = 5;         // 32-bit word 5: 0 after tickets (3: payloads formed of every element), 1 entries parked, 2 all read again
 constexpr size_t kWsTicketOff = 4096;
 constexpr size_t kWsHeaderBytes = 8192;
 // Behind them (at a multiple of 256 bytes): room for compacted entries, a slot per tile, of the plans that may be encoded
@@ -153,15 +153,16 @@ struct RefreshArgs {
     const int64_t *numel;
     int32_t n;
 };
-// resident: workgroups of this kernel variant that fit on the device at once (encode_resident_all);
+// resident: workgroups of each kernel variant that fit on the device at once (encode_resident_all);
 // worker_cap: 0, or the most workgroups that may walk tiles; order: ROSE_TILE_ORDER_SPREAD, _NEIGHBOURS or _TIMED;
 // order_free: nobody asked for that order, small updates may go without tickets; ppm: changed elements per
 // million as far as known or bounded, else -1; room_ppm: as many as the buckets could hold
-int launch_encode(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, int arith, int resident,
+int launch_encode(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream);
-// resident workgroups of each of the eight encode kernel variants on the current device
-// (index: fp32 input + 2 * refresh + 4 * arithmetic payload)
-int encode_resident_all(int resident[8]);
+// resident workgroups of each of the encode kernel variants on the current device
+// (index: fp32 input + 2 * refresh + 4 * arithmetic payload; 8: arithmetic payloads formed of every element)
+constexpr int kEncodeKernels = 9;
+int encode_resident_all(int resident[kEncodeKernels]);
 // Address and size of the library's built-in scratch array on the current device (one array per
 // device, found once per device with hipGetSymbolAddress and kept).
 int static_scratch(void **ptr, size_t *bytes);
@@ -227,7 +228,7 @@ struct rose_plan {
     mutable int64_t *d_repl_numel = nullptr;
     mutable int32_t n_repl = 0;
     mutable unsigned long long *d_verdict = nullptr;   // [kVerdictSlots]
-    mutable int resident[8] = {0};             // see encode_resident_all
+    mutable int resident[rose::kEncodeKernels] = {0};   // see encode_resident_all
     mutable bool uses_mail = false;            // holds a share of the pinned words of bucket checks (api.cpp)
     mutable void *static_ws = nullptr;         // the library's built-in scratch on `device`
     mutable size_t static_ws_bytes = 0;
