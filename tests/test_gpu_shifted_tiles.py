@@ -15,12 +15,13 @@ LENS = [TILE, TILE + 1, TILE + LINE - 1, 2 * TILE - LINE + 1, 2 * TILE - LINE + 
 
 def tensors(tp, mib):
     ts = [T(tp, n, R.SPLIT_ROWS) for n in LENS] + [T(1, 3 * TILE, R.REPLICATED), T(2 * tp, 2 * TILE + 9, R.FUSED_ROWS, [tp, tp]),
-                                                  T(TILE // 8 + 3, 24 * tp, R.SPLIT_COLS), T(301, 192 * tp, R.SPLIT_COLS)]
+                                                  T(TILE // 8 + 3, 24 * tp, R.SPLIT_COLS), T(301, 192 * tp, R.SPLIT_COLS),
+                                                  T(tp, 32 * TILE, R.SPLIT_ROWS), T(33 * TILE // 192, 192 * tp, R.SPLIT_COLS)]
     return ts + [T(tp * 2, (mib << 20) // 4 // tp // 2, R.SPLIT_ROWS)] if mib else ts
 
 
 def test_tiles_of_a_plan():
-    for n, tiles in zip(LENS, [1, 2, 2, 2, 3, 3, 3, 3, 4]):
+    for n, tiles in zip(LENS + [31 * TILE, 32 * TILE - LINE + 1, 32 * TILE - LINE + 2, 32 * TILE], [1, 2, 2, 2, 2, 2, 2, 3, 4, 31, 32, 33, 33]):
         assert R.shard_plan([T(1, n, R.SPLIT_ROWS)], 1).n_tiles() == tiles, n
     assert R.shard_plan([T(TILE, 4, R.SPLIT_COLS)], 2).n_tiles() == 4          # rows of no whole lines: not moved
     assert R.shard_plan([T(TILE, 128, R.SPLIT_COLS)], 2).n_tiles() == 2 * (64 + 1)
