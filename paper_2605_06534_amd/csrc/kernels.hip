@@ -2939,8 +2939,9 @@ static void encode_walk(int order, int32_t ppm, bool of_elements, EncodeArgs *a)
 // So: read again below 12 MiB, where the second reading comes out of the caches at once, and below 24 MiB from 10 % on (16 MiB at
 // 5 / 10 / 15 %: read again 8.7 9.1 9.8, staged 8.5 9.1 10.4; 24 MiB: 10.2 10.6 11.3 and 9.6 10.5 11.7), and where the slots do
 // not hold the tiles; staged up to kStagedMib of the density, half as much again for arithmetic payloads and refresh; by tickets
-// above.  Slots have to hold twice what is expected of a tile (densities differ between the rows of a model), below 80 MiB
-// 1.25 times.
+// above.  Slots have to hold twice what is expected of a tile, since densities differ between the rows of a model (31 MiB of
+// fp32 masters, 12 % with a rate of its own for each 4096 elements: parked 20.4 us, read again 16.4), from 48 to 80 MiB, where
+// parking gains more, 1.25 times (75 MiB of the same: 31.4 and 34.7).
 // The density is that of the last update looked at, and another may come.  What is past its slot is read again, so that the
 // staged form then takes (1 % seen, one matrix, bf16, us, in the caches; beside it reading again up to 80 MiB, tickets above):
 //   comes     64 MiB         192 MiB     300 MiB     384 MiB     850 MiB     1200 MiB
@@ -2979,7 +2980,8 @@ static TwoLaunches two_launches(const EncodeArgs &a, int new_is_f32, int refresh
     TwoLaunches t = {kTickets, 0, mib >= kStreamMib};
     if (mib <= kUnknownMib) {
         const bool read_again = mib <= kReadAgainMib || (mib <= kReadAgainDenseMib && by >= kReadAgainDensePpm);
-        t.form = read_again || a.slot_size < kThreads || expected * 5 / 4 + 64 > a.slot_size ? kReadAgain : kStaged;
+        const int64_t room = mib < kGuessFromMib ? expected * 2 + 64 : expected * 5 / 4 + 64;
+        t.form = read_again || a.slot_size < kThreads || room > a.slot_size ? kReadAgain : kStaged;
     } else if (expected * 2 + 64 <= a.slot_size) {
         for (const auto &line : kStagedMib)
             if (by < line.below_ppm) {

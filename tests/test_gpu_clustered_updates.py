@@ -26,7 +26,7 @@ def test_runs_of_dense_tiles(mib, tp, p, dense, fp32, what):
 def test_small_slots(entries, what):
     """Room for so many entries a tile, tiles that hold nearly as many or 8192."""
     print("case: slots of %d entries, %s" % (entries, what), flush=True)
-    c = make(34, 2, 8, 0.16 if entries == 2016 else 0.006, entries, dense=2)
+    c = make(50, 2, 8, 0.16 if entries == 2016 else 0.006, entries, dense=2)
     base = c.plan.workspace_bytes() - c.plan.n_tiles() * 2016 * 4
     c.ws = torch.full(((base + c.plan.n_tiles() * entries * 4) // 8 + 1,), -1, dtype=torch.int64, device="cuda")
     CHECKS[what](c)

@@ -37,7 +37,7 @@ def test_kernels_of_an_update(mib, seen, order, form):
 
 @pytest.mark.parametrize("mib,seen,room,form", [
     (13, None, 1.0, READ_AGAIN), (64, None, 1.0, READ_AGAIN), (90, None, 1.0, TICKETS),         # nothing known
-    (16, None, 0.05, PARKED), (16, None, 0.12, READ_AGAIN), (24, None, 0.12, READ_AGAIN), (25, None, 0.12, PARKED),
+    (16, None, 0.05, PARKED), (16, None, 0.12, READ_AGAIN), (24, None, 0.11, READ_AGAIN), (25, None, 0.11, PARKED), (47, None, 0.13, READ_AGAIN), (48, None, 0.13, PARKED),
     (30, None, 0.02, PARKED), (64, None, 0.3, READ_AGAIN), (200, None, 0.02, PARKED),           # what the buckets hold
     (30, 0.01, 1.0, READ_AGAIN), (30, 0.01, 0.02, PARKED), (30, 0.02, 0.01, PARKED),
     (64, 0.01, 1.0, PARKED), (64, 0.3, 0.02, READ_AGAIN), (280, 0.01, 1.0, PARKED),             # the last density
