@@ -275,9 +275,11 @@ extern "C" rose_status rose_shard_plan_create_pp(const rose_tensor_desc *tensors
                     // (26 layers, hidden 512, TP8, 15 %, refresh: 7512 tiles 106 us, with 8552 113; 28 layers of 320,
                     // TP2, 22 %, arithmetic: 85 and 95, this way 81; what that costs packed tensors, 24 layers of 512, TP8,
                     // 2 %: 102 us with all pieces moved, 107 this way, 138 with none).
+                    // Pieces of two or three tiles are not moved at all, since nearly each of those has an end whose vectors
+                    // have to be put in place (64 layers of 224, packed, TP4, 10 / 30 / 47 %: 62 72 126 us, moved 70 88 146).
                     const int64_t filled = ((int64_t)pc.len + rose::kTile - 1) / rose::kTile;
                     const int64_t reached = ((int64_t)pc.len + rose::kShiftElems - 1 + rose::kTile - 1) / rose::kTile;
-                    if (lines && pc.len > rose::kTile && pc.len <= INT32_MAX - 2 * rose::kTile &&
+                    if (lines && filled >= rose::kShiftFewestTiles && pc.len <= INT32_MAX - 2 * rose::kTile &&
                         (reached == filled || filled >= rose::kShiftLeastTiles))
                         pc.flags |= rose::kPieceShift;
                     int64_t nt = pc.len == 0 ? 1 : (pc.flags & rose::kPieceShift) ? reached : filled;

@@ -26,7 +26,8 @@ constexpr int kIters = ROSE_ITERS;
 constexpr int kWaveSpan = 64 * kVec * kIters;      // elements one wave covers in a tile
 constexpr int kTile = kThreads * kVec * kIters;    // elements per tile
 constexpr int kShiftElems = 64;                     // 16-bit elements in a 128-byte line
-constexpr int kShiftLeastTiles = 32;                // tiles of a piece that is moved (kPieceShift) at the price of one more
+constexpr int kShiftFewestTiles = 4;                // tiles of a piece that is moved (kPieceShift) ...
+constexpr int kShiftLeastTiles = 32;                // ... at the price of one more
 
 enum : int32_t {
     kPieceFirst = 1,    // first piece of its (tensor, shard) segment

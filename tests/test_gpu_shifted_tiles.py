@@ -11,10 +11,11 @@ from test_gpu_unaligned import packed_case
 
 TILE, LINE = 8192, 64
 LENS = [TILE, TILE + 1, TILE + LINE - 1, 2 * TILE - LINE + 1, 2 * TILE - LINE + 2, 2 * TILE - 1, 2 * TILE, 2 * TILE + 7, 3 * TILE + 5]
+MOVED = [4 * TILE - LINE + 1, 4 * TILE + 1, 5 * TILE + 7, 6 * TILE - LINE, 6 * TILE + LINE - 1, 7 * TILE - LINE + 1]
 
 
 def tensors(tp, mib):
-    ts = [T(tp, n, R.SPLIT_ROWS) for n in LENS] + [T(1, 3 * TILE, R.REPLICATED), T(2 * tp, 2 * TILE + 9, R.FUSED_ROWS, [tp, tp]),
+    ts = [T(tp, n, R.SPLIT_ROWS) for n in LENS + MOVED] + [T(1, 3 * TILE, R.REPLICATED), T(2 * tp, 2 * TILE + 9, R.FUSED_ROWS, [tp, tp]),
                                                   T(TILE // 8 + 3, 24 * tp, R.SPLIT_COLS), T(301, 192 * tp, R.SPLIT_COLS),
                                                   T(tp, 32 * TILE, R.SPLIT_ROWS), T(33 * TILE // 192, 192 * tp, R.SPLIT_COLS)]
     return ts + [T(tp * 2, (mib << 20) // 4 // tp // 2, R.SPLIT_ROWS)] if mib else ts
