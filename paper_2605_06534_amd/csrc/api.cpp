@@ -57,7 +57,7 @@ private:
 };
 Mail mail;
 
-constexpr int32_t kNeighboursBelowPpm = 75000, kTimedBelowPpm = 40000;   // see encode_common
+constexpr int32_t kNeighboursBelowPpm = rose::kSpreadFromPpm, kTimedBelowPpm = 40000;   // see encode_common
 
 // Copy the piece and tile tables to the current device once; later calls on the same device
 // reuse them.  A plan is bound to the first device it is used on.  `may_allocate` = false: only
@@ -96,14 +96,15 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
             repl_numel.push_back(t.rows * t.cols);
         }
     }
-    rose::Piece *dp = nullptr;
-    int32_t *dt = nullptr, *dc = nullptr, *dn = nullptr, *dr = nullptr;
+    rose::Piece *dp = nullptr, *dfp = nullptr;
+    int32_t *dt = nullptr, *dft = nullptr, *dc = nullptr, *dn = nullptr, *dr = nullptr;
     int64_t *drn = nullptr;
     unsigned long long *dv = nullptr;
     int resident[rose::kEncodeKernels];
     void *sws = nullptr;
     size_t sws_bytes = 0;
     const size_t pb = p->pieces.size() * sizeof(rose::Piece), tb = p->tile_piece.size() * sizeof(int32_t);
+    const size_t fpb = p->fewer.pieces.size() * sizeof(rose::Piece), ftb = p->fewer.tile_piece.size() * sizeof(int32_t);
     const size_t cfb = p->copy_first.size() * sizeof(int32_t), cpb = p->copy_piece.size() * sizeof(int32_t);
     const size_t nb = numel.size() * sizeof(int32_t), vb = kVerdictSlots * sizeof(unsigned long long);
     bool ok = hipMalloc(reinterpret_cast<void **>(&dp), pb) == hipSuccess &&
@@ -117,6 +118,12 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
               (cpb == 0 || hipMemcpy(dc + p->copy_first.size(), p->copy_piece.data(), cpb, hipMemcpyHostToDevice) == hipSuccess) &&
               hipMemcpy(dn, numel.data(), nb, hipMemcpyHostToDevice) == hipSuccess &&
               hipMemset(dv, 0, vb) == hipSuccess;
+    if (ok && fpb) {
+        ok = hipMalloc(reinterpret_cast<void **>(&dfp), fpb) == hipSuccess &&
+             hipMalloc(reinterpret_cast<void **>(&dft), ftb) == hipSuccess &&
+             hipMemcpy(dfp, p->fewer.pieces.data(), fpb, hipMemcpyHostToDevice) == hipSuccess &&
+             hipMemcpy(dft, p->fewer.tile_piece.data(), ftb, hipMemcpyHostToDevice) == hipSuccess;
+    }
     if (ok && !repl.empty()) {
         ok = hipMalloc(reinterpret_cast<void **>(&dr), repl.size() * sizeof(int32_t)) == hipSuccess &&
              hipMalloc(reinterpret_cast<void **>(&drn), repl.size() * sizeof(int64_t)) == hipSuccess &&
@@ -127,6 +134,8 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
     if (!ok) {
         if (dp) (void)hipFree(dp);
         if (dt) (void)hipFree(dt);
+        if (dfp) (void)hipFree(dfp);
+        if (dft) (void)hipFree(dft);
         if (dc) (void)hipFree(dc);
         if (dn) (void)hipFree(dn);
         if (dv) (void)hipFree(dv);
@@ -136,6 +145,8 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
     }
     p->d_pieces = dp;
     p->d_tile_piece = dt;
+    p->d_fewer_pieces = dfp;
+    p->d_fewer_tile_piece = dft;
     p->d_copy = dc;
     p->d_local_numel = dn;
     p->d_verdict = dv;
@@ -168,6 +179,8 @@ extern "C" void rose_shard_plan_destroy(rose_plan *p) {
     if (!p) return;
     if (p->d_pieces) (void)hipFree(p->d_pieces);
     if (p->d_tile_piece) (void)hipFree(p->d_tile_piece);
+    if (p->d_fewer_pieces) (void)hipFree(p->d_fewer_pieces);
+    if (p->d_fewer_tile_piece) (void)hipFree(p->d_fewer_tile_piece);
     if (p->d_copy) (void)hipFree(p->d_copy);
     if (p->d_local_numel) (void)hipFree(p->d_local_numel);
     if (p->d_verdict) (void)hipFree(p->d_verdict);
@@ -235,21 +248,27 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     }
     if (workspace_bytes < need) return ROSE_ERR_ARG;
     if (!aligned(workspace, 256)) return ROSE_ERR_ALIGN;
-    std::memcpy(a.chain_first, p->chain_first, sizeof a.chain_first);
-    std::memcpy(a.block_first, p->block_first, sizeof a.block_first);
-    a.pieces = p->d_pieces;
-    a.tile_piece = p->d_tile_piece;
     a.old_ptrs = old_ptrs;
     a.new_ptrs = new_ptrs;
     char *ws = static_cast<char *>(workspace);
     a.abort_flag = reinterpret_cast<unsigned int *>(ws + rose::kWsAbortOff);
     a.ticket = reinterpret_cast<unsigned int *>(ws + rose::kWsTicketOff);
     a.tile_desc = reinterpret_cast<unsigned long long *>(ws + rose::kWsHeaderBytes);
-    a.n_tiles = (int32_t)p->tile_piece.size();
-    a.n_blocks = p->block_first[p->n_buckets];
-    a.block_desc = a.tile_desc + a.n_tiles;
     a.tp = p->n_buckets;
     a.n_tensors = p->n_tensors;
+    rose::EncodeArgs fewer = a;
+    auto set_tiles = [&](rose::EncodeArgs *e, const rose::Tiles &t, const rose::Piece *pieces, const int32_t *tile_piece) {
+        std::memcpy(e->chain_first, t.chain_first, sizeof e->chain_first);
+        std::memcpy(e->block_first, t.block_first, sizeof e->block_first);
+        e->pieces = pieces;
+        e->tile_piece = tile_piece;
+        e->n_tiles = (int32_t)t.tile_piece.size();
+        e->n_blocks = t.block_first[p->n_buckets];
+        e->block_desc = e->tile_desc + e->n_tiles;
+    };
+    set_tiles(&a, *p, p->d_pieces, p->d_tile_piece);
+    if (p->d_fewer_pieces) set_tiles(&fewer, p->fewer, p->d_fewer_pieces, p->d_fewer_tile_piece);
+    else fewer = a;
     const size_t slots_at = (need + 255) / 256 * 256;
     if (a.n_tiles > 0 && a.n_tiles <= rose::kStageMostTiles && workspace_bytes > slots_at) {
         const size_t room = (workspace_bytes - slots_at) / sizeof(uint32_t) / (size_t)a.n_tiles / 32 * 32;   // whole lines
@@ -265,7 +284,7 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
     const int32_t ppm = expected_ppm(p, buckets);
     const int order = pick_tile_order(p, ppm);
     const bool order_free = p->tile_order.load(std::memory_order_relaxed) == ROSE_TILE_ORDER_AUTO_PICK;
-    return rose::launch_encode(a, f32, refresh ? &r : nullptr, arith ? 1 : 0, p->resident,
+    return rose::launch_encode(a, fewer, f32, refresh ? &r : nullptr, arith ? 1 : 0, p->resident,
                                p->worker_cap.load(std::memory_order_relaxed), order, order_free, ppm,
                                room_ppm(p, buckets), stream) == 0
                ? ROSE_OK

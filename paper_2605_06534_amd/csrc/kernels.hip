@@ -3000,7 +3000,7 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
                            new_is_f32);
 }
 
-int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
+int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     EncodeArgs a = args;
@@ -3027,6 +3027,7 @@ int launch_encode(const EncodeArgs &args, int new_is_f32, const RefreshArgs *ref
     }
     const bool of_elements = arith && !new_is_f32 && !refresh && (ppm < 0 || ppm >= kElementsPpm || room_ppm >= kElementsPpm);
     const int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+    if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
     encode_walk(order, ppm, of_elements, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than

@@ -194,6 +194,57 @@ static void segment_pieces(const rose_tensor_desc &t, int32_t ti, int32_t d, int
     out[first].flags |= rose::kPieceFirst;
 }
 
+// May the tiles of this piece be moved down to lines (kPieceShift)?  Every piece of several tiles may (`all`), but by tickets,
+// where much changes, a tile costs more than lines gain a short piece.  One that a piece only has for being moved (it fills
+// its last one) is empty if nothing is moved, and yet counted, served a prefix and part of a ticket, so short pieces are not
+// moved then if it takes one (26 layers, hidden 512, TP8, 15 %, refresh: 7512 tiles 106 us, 8552 113; 28 layers of 320, TP2,
+// 22 %, arithmetic: 81 and 95), and pieces of two or three tiles not at all, since nearly each of those has an end whose
+// vectors have to be put in place (64 layers of 224, packed, TP4, 10 / 30 / 47 %: 62 72 126 us, moved 70 88 146).  What moving
+// them all gains packed tensors elsewhere: in two launches 26 layers of 512, TP4, 0.1 % 23 -> 18 us, 35 of 640, TP8 105 -> 89;
+// by tickets 64 of 768, TP8, 1 % with refresh 701 -> 583.
+static bool moved(const Piece &pc, bool all) {
+    // (element numbers stay below 2^31 however far the last tile reaches past the piece)
+    const bool lines = !(pc.flags & rose::kPieceStrided) ||
+                       ((pc.flags & rose::kPieceLoad16) && pc.run % rose::kShiftElems == 0 && pc.stride % rose::kShiftElems == 0);
+    if (!lines || pc.len <= rose::kTile || pc.len > INT32_MAX - 2 * rose::kTile) return false;
+    const int64_t filled = ((int64_t)pc.len + rose::kTile - 1) / rose::kTile;
+    const int64_t reached = ((int64_t)pc.len + rose::kShiftElems - 1 + rose::kTile - 1) / rose::kTile;
+    return all || filled >= (reached == filled ? rose::kShiftFewestTiles : rose::kShiftLeastTiles);
+}
+static int64_t tiles_of(const Piece &pc, bool moved) {
+    return pc.len == 0 ? 1 : ((int64_t)pc.len + (moved ? rose::kShiftElems - 1 : 0) + rose::kTile - 1) / rose::kTile;
+}
+static int64_t count_tiles(const rose::Tiles &t, bool all) {
+    int64_t n = 0;
+    for (const Piece &pc : t.pieces) n += tiles_of(pc, moved(pc, all));
+    return n;
+}
+static int64_t count_moved(const rose::Tiles &t, bool all) {
+    int64_t n = 0;
+    for (const Piece &pc : t.pieces) n += moved(pc, all);
+    return n;
+}
+// Number the tiles of all pieces (which are in the order of their shards).
+static void cut_tiles(rose::Tiles *t, int32_t n_chains, bool all) {
+    int32_t n = 0, chain = 0;
+    t->tile_piece.reserve((size_t)count_tiles(*t, all));
+    for (size_t k = 0; k < t->pieces.size(); ++k) {
+        Piece &pc = t->pieces[k];
+        while (chain <= pc.shard) t->chain_first[chain++] = n;
+        if (moved(pc, all)) pc.flags |= rose::kPieceShift;
+        const int32_t nt = (int32_t)tiles_of(pc, (pc.flags & rose::kPieceShift) != 0);
+        pc.first_tile = n;
+        n += nt;
+        t->tile_piece.insert(t->tile_piece.end(), (size_t)nt, (int32_t)k);
+    }
+    while (chain <= ROSE_MAX_TP) t->chain_first[chain++] = n;
+    int32_t n_blocks = 0;
+    for (int32_t b = 0; b <= ROSE_MAX_TP; ++b) {
+        t->block_first[b] = n_blocks;
+        if (b < n_chains) n_blocks += (t->chain_first[b + 1] - t->chain_first[b] + rose::kBlock - 1) / rose::kBlock;
+    }
+}
+
 // The dense copy's tiles.  They are lined up with the destination and begin where the piece does, so it has nothing to do in
 // the tile that a piece may have for being moved; for workgroups that find nothing two short layers took 20.4 us in four
 // shards, without 19.8; four layers 52.8 and 51.5.  From kCopyOwnTiles on that does not show (58 k tiles 311.9 and 311.7),
@@ -256,51 +307,24 @@ extern "C" rose_status rose_shard_plan_create_pp(const rose_tensor_desc *tensors
             p->stage_src_of[i] = stage_of(tensors[i].layer, n_layers, pp_src);
             p->stage_dst_of[i] = stage_of(tensors[i].layer, n_layers, pp_dst);
         }
-        int64_t n_tiles = 0;
         for (int32_t b = 0; b < p->n_buckets; ++b) {
             const int32_t stage_dst = b / tp, d = b % tp;
-            p->chain_first[b] = (int32_t)n_tiles;
             for (int32_t i = 0; i < n_tensors; ++i) {
-                size_t first = p->pieces.size();
                 const bool here = p->stage_src_of[i] == stage_src && p->stage_dst_of[i] == stage_dst;
                 segment_pieces(tensors[i], i, d, tp, tp_src, src_rank, b, here, p->pieces);
-                for (size_t k = first; k < p->pieces.size(); ++k) {
-                    Piece &pc = p->pieces[k];
-                    // (element numbers stay below 2^31 however far the last tile reaches past the piece)
-                    const bool lines = !(pc.flags & rose::kPieceStrided) ||
-                                       ((pc.flags & rose::kPieceLoad16) && pc.run % rose::kShiftElems == 0 &&
-                                        pc.stride % rose::kShiftElems == 0);
-                    // The tile more that a piece needs for it where it fills its last one is empty if nothing is moved,
-                    // and yet counted, served a prefix and part of a ticket: short pieces are not moved if it takes one
-                    // (26 layers, hidden 512, TP8, 15 %, refresh: 7512 tiles 106 us, with 8552 113; 28 layers of 320,
-                    // TP2, 22 %, arithmetic: 85 and 95, this way 81; what that costs packed tensors, 24 layers of 512, TP8,
-                    // 2 %: 102 us with all pieces moved, 107 this way, 138 with none).
-                    // Pieces of two or three tiles are not moved at all, since nearly each of those has an end whose vectors
-                    // have to be put in place (64 layers of 224, packed, TP4, 10 / 30 / 47 %: 62 72 126 us, moved 70 88 146).
-                    const int64_t filled = ((int64_t)pc.len + rose::kTile - 1) / rose::kTile;
-                    const int64_t reached = ((int64_t)pc.len + rose::kShiftElems - 1 + rose::kTile - 1) / rose::kTile;
-                    if (lines && filled >= rose::kShiftFewestTiles && pc.len <= INT32_MAX - 2 * rose::kTile &&
-                        (reached == filled || filled >= rose::kShiftLeastTiles))
-                        pc.flags |= rose::kPieceShift;
-                    int64_t nt = pc.len == 0 ? 1 : (pc.flags & rose::kPieceShift) ? reached : filled;
-                    if (n_tiles + nt >= ((int64_t)1 << 31) - 1) {
-                        delete p;
-                        return ROSE_ERR_UNSUPPORTED;
-                    }
-                    pc.first_tile = (int32_t)n_tiles;
-                    n_tiles += nt;
-                    p->tile_piece.insert(p->tile_piece.end(), (size_t)nt, (int32_t)k);
-                }
             }
         }
-        for (int32_t b = p->n_buckets; b <= ROSE_MAX_TP; ++b) p->chain_first[b] = (int32_t)n_tiles;
+        if (count_tiles(*p, true) >= ((int64_t)1 << 31) - 1) {
+            delete p;
+            return ROSE_ERR_UNSUPPORTED;
+        }
+        if (count_moved(*p, true) != count_moved(*p, false)) {
+            p->fewer = *p;
+            cut_tiles(&p->fewer, p->n_buckets, false);
+        }
+        cut_tiles(p, p->n_buckets, true);
         copy_tiles(p);
         for (const Piece &pc : p->pieces) p->capacity_sum += pc.len;
-        int32_t n_blocks = 0;
-        for (int32_t b = 0; b <= ROSE_MAX_TP; ++b) {
-            p->block_first[b] = n_blocks;
-            if (b < p->n_buckets) n_blocks += (p->chain_first[b + 1] - p->chain_first[b] + rose::kBlock - 1) / rose::kBlock;
-        }
     } catch (...) {
         delete p;
         return ROSE_ERR_ARG;

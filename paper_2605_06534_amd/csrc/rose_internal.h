@@ -66,6 +66,14 @@ struct Piece {
 };
 static_assert(sizeof(Piece) == 56, "Piece layout is shared with device code");
 
+// Pieces, shard by shard, and the tiles they are cut into: one prefix chain of tiles per shard, in blocks of kBlock.
+struct Tiles {
+    std::vector<Piece> pieces;
+    std::vector<int32_t> tile_piece;           // piece of each tile
+    int32_t chain_first[ROSE_MAX_TP + 1] = {0};
+    int32_t block_first[ROSE_MAX_TP + 1] = {0};
+};
+
 struct BucketDev {
     int32_t *idx;
     uint16_t *val;
@@ -148,6 +156,8 @@ inline uint32_t magic_div(uint32_t k, uint32_t magic, uint32_t shift) {
     return (uint32_t)(((uint64_t)k * magic) >> 32) >> shift;
 }
 
+constexpr int32_t kSpreadFromPpm = 75000;  // changed elements per million from which tiles are taken in the spread order
+
 // kernel launchers (kernels.hip); all return a hipError_t as int
 // replicated tensors to copy new -> old after an encode with refresh (device arrays of n entries)
 struct RefreshArgs {
@@ -159,7 +169,8 @@ struct RefreshArgs {
 // worker_cap: 0, or the most workgroups that may walk tiles; order: ROSE_TILE_ORDER_SPREAD, _NEIGHBOURS or _TIMED;
 // order_free: nobody asked for that order, small updates may go without tickets; ppm: changed elements per
 // million as far as known or bounded, else -1; room_ppm: as many as the buckets could hold
-int launch_encode(const EncodeArgs &a, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident,
+// a, fewer: with the plan's tiles and with those where only the longer pieces are moved (everything else is alike)
+int launch_encode(const EncodeArgs &a, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream);
 // resident workgroups of each of the encode kernel variants on the current device
 // (index: fp32 input + 2 * refresh + 4 * arithmetic payload; 8: arithmetic payloads formed of every element)
@@ -193,7 +204,7 @@ int launch_bw_probe_mixed(const void *a, const void *b, void *dst, size_t n_chun
 // words of device memory that object applies use to hand the validation pass's verdict to the apply pass
 constexpr int kVerdictSlots = 4096;
 
-struct rose_plan {
+struct rose_plan : rose::Tiles {               // (its tiles with all pieces moved that may be)
     int32_t tp_src = 1, src_rank = 0;          // the sender holds shard src_rank of tp_src of every tensor
     int32_t tp = 0;
     // pipeline stages (Sec. 4.2: TP and PP on both sides): the sender is stage stage_src of pp_src and holds
@@ -205,13 +216,10 @@ struct rose_plan {
     std::vector<rose_tensor_desc> tensors;
     std::vector<int32_t> stage_src_of, stage_dst_of;   // [n_tensors] stage that holds each tensor on either side
     std::vector<int64_t> global_base;          // [n_tensors + 1]
-    std::vector<rose::Piece> pieces;
-    std::vector<int32_t> tile_piece;           // piece of each tile
+    rose::Tiles fewer;                         // tiles with only the longer pieces moved (no pieces: the plan's own)
     std::vector<int32_t> copy_piece;           // the same for the dense copy (empty: the encode's tiles)
     std::vector<int32_t> copy_first;           // first tile of each piece there
     int32_t copy_chain_first[ROSE_MAX_TP + 1] = {0};
-    int32_t chain_first[ROSE_MAX_TP + 1] = {0};
-    int32_t block_first[ROSE_MAX_TP + 1] = {0};
     mutable std::atomic<int32_t> worker_cap{0};     // rose_plan_set_worker_cap
     mutable std::atomic<int32_t> tile_order{0};     // rose_plan_set_tile_order
     mutable std::atomic<int32_t> seen_density_ppm{-1};   // changed elements per million as estimated from the last
@@ -223,6 +231,8 @@ struct rose_plan {
     mutable int device = -1;
     mutable rose::Piece *d_pieces = nullptr;
     mutable int32_t *d_tile_piece = nullptr;
+    mutable rose::Piece *d_fewer_pieces = nullptr;     // the same of `fewer`, if there are
+    mutable int32_t *d_fewer_tile_piece = nullptr;
     mutable int32_t *d_copy = nullptr;         // copy_first, then copy_piece
     mutable int32_t *d_local_numel = nullptr;  // [pp_dst][n_tensors] elements of a shard's copy of each tensor
                                                // (0 where the stage does not hold the tensor)

@@ -45,6 +45,35 @@ static void copy_tiles(const rose_plan *p, int32_t tp) {
     if (p->copy_piece.empty() != (p->tile_piece.size() > (size_t)rose::kCopyOwnTiles)) fail("whose tiles", (int)c);
 }
 
+// the tiles of one numbering: every piece's in order, as many as its elements need, chains and blocks as they follow
+static void tiles(const rose::Tiles &t, int32_t n_chains, bool all) {
+    int64_t n = 0;
+    int32_t blocks = 0;
+    for (size_t k = 0; k < t.pieces.size(); ++k) {
+        const rose::Piece &pc = t.pieces[k];
+        const bool shift = (pc.flags & rose::kPieceShift) != 0;
+        const int64_t filled = (pc.len + rose::kTile - 1) / rose::kTile, reached = (pc.len + rose::kShiftElems - 1 + rose::kTile - 1) / rose::kTile;
+        if (pc.first_tile != n || n < t.chain_first[pc.shard] || n >= t.chain_first[pc.shard + 1]) fail("first tile", (int)k);
+        if (shift && (pc.len <= rose::kTile || (!all && filled < (reached == filled ? rose::kShiftFewestTiles : rose::kShiftLeastTiles)))) fail("moved", (int)k);
+        const int64_t nt = pc.len == 0 ? 1 : shift ? reached : filled;
+        for (int64_t j = 0; j < nt; ++j, ++n)
+            if (n >= (int64_t)t.tile_piece.size() || t.tile_piece[n] != (int32_t)k) fail("piece of a tile", (int)n);
+    }
+    if (n != (int64_t)t.tile_piece.size() || t.chain_first[n_chains] != n) fail("tiles", (int)n);
+    for (int32_t b = 0; b < n_chains; ++b) {
+        if (t.block_first[b] != blocks) fail("blocks", b);
+        blocks += (t.chain_first[b + 1] - t.chain_first[b] + rose::kBlock - 1) / rose::kBlock;
+    }
+    if (t.block_first[n_chains] != blocks) fail("blocks", n_chains);
+}
+
+static void both_tiles(const rose_plan *p, int32_t n_chains) {
+    tiles(*p, n_chains, true);
+    if (p->fewer.pieces.empty()) return;
+    tiles(p->fewer, n_chains, false);
+    if (p->fewer.pieces.size() != p->pieces.size() || p->fewer.tile_piece.size() > p->tile_piece.size()) fail("two numberings", 0);
+}
+
 static void walk(const std::vector<rose_tensor_desc> &ts, int32_t tp, int32_t tp_src, int32_t src_rank) {
     rose_plan *p = nullptr;
     rose_status s = rose_shard_plan_create_src(ts.data(), (int32_t)ts.size(), tp, tp_src, src_rank, &p);
@@ -79,6 +108,7 @@ static void walk(const std::vector<rose_tensor_desc> &ts, int32_t tp, int32_t tp
         if (sent != (sends ? n : 0)) fail("a sender sends its whole slice, or nothing of a replicated tensor", t);
     }
     copy_tiles(p, tp);
+    both_tiles(p, tp);
     delete p;                                        // the plan owns no device memory before its first device call
 }
 
@@ -99,6 +129,7 @@ int main() {
     rose_plan *large = nullptr;
     if (rose_shard_plan_create(many.data(), 3, 4, &large) != ROSE_OK) fail("create", 0);
     copy_tiles(large, 4);
+    both_tiles(large, 4);
     if (!large->copy_piece.empty()) fail("a plan of many tiles shares them", 0);
     delete large;
     // descriptors the planner must turn down without touching anything

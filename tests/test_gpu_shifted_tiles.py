@@ -22,7 +22,7 @@ def tensors(tp, mib):
 
 
 def test_tiles_of_a_plan():
-    for n, tiles in zip(LENS + [31 * TILE, 32 * TILE - LINE + 1, 32 * TILE - LINE + 2, 32 * TILE], [1, 2, 2, 2, 2, 2, 2, 3, 4, 31, 32, 33, 33]):
+    for n, tiles in zip(LENS + [31 * TILE, 32 * TILE - LINE + 1, 32 * TILE - LINE + 2, 32 * TILE], [1, 2, 2, 2, 3, 3, 3, 3, 4, 32, 32, 33, 33]):
         assert R.shard_plan([T(1, n, R.SPLIT_ROWS)], 1).n_tiles() == tiles, n
     assert R.shard_plan([T(TILE, 4, R.SPLIT_COLS)], 2).n_tiles() == 4          # rows of no whole lines: not moved
     assert R.shard_plan([T(TILE, 128, R.SPLIT_COLS)], 2).n_tiles() == 2 * (64 + 1)
