@@ -233,11 +233,14 @@ rose_status rose_plan_map_index(const rose_plan *plan, int32_t t, int64_t g, int
                                 int32_t *n_dest, int32_t *local);
 /* worst-case number of entries this sender produces for bucket d (every element changed) */
 rose_status rose_plan_bucket_capacity(const rose_plan *plan, int32_t d, int64_t *max_entries);
-/* bytes of device scratch for rose_delta_encode (256-byte aligned buffer).  For plans of up to 65536 tiles this
- * includes room to park entries in (at most 8064 bytes a tile, and 48 MiB together), which lets updates that are not
+/* bytes of device scratch for rose_delta_encode (256-byte aligned buffer).  What a launch cannot do without are 8 KB, 8
+ * bytes a tile and 8 a block of 64 tiles (of one destination each); for plans of up to 65536 tiles the answer includes
+ * room to park entries in as well (at most 8064 bytes a tile, and 48 MiB together), which lets updates that are not
  * large go without tickets. */
 rose_status rose_plan_workspace_bytes(const rose_plan *plan, size_t *bytes);
-/* number of tiles the encode kernel walks (for reporting) */
+/* number of tiles the plan is cut into (for reporting).  Pieces of several tiles whose tensors may begin anywhere have room
+ * for one tile more where they fill their last; a launch by tickets that expects many changes, and a dense copy, may walk
+ * fewer tiles than this. */
 rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
 
 /*
@@ -250,7 +253,9 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  *                       read element by element, which is slow.  Both are only read.
  *   buckets             HOST array of rose_plan_n_buckets bucket structs (tp of them; tp * pp_dst for a
  *                       pipeline plan); their device arrays are written.
- *   workspace           DEVICE scratch of at least rose_plan_workspace_bytes, 256-byte aligned;
+ *   workspace           DEVICE scratch of rose_plan_workspace_bytes, 256-byte aligned (less, or none,
+ *                       of the room to park entries in is accepted: the update then goes another way
+ *                       and the buckets are the same; below the rest ROSE_ERR_ARG);
  *                       contents before the call do not matter; calls that share a workspace
  *                       must be ordered on one stream.
  * Returns ROSE_ERR_ARG / ROSE_ERR_ALIGN / ROSE_ERR_HIP without queuing anything.  A bucket
@@ -259,8 +264,8 @@ rose_status rose_plan_n_tiles(const rose_plan *plan, int64_t *n_tiles);
  * Unless a tile order or a worker cap is set, an update that reads at most 80 MiB goes in two launches that wait
  * for nothing, and so does a larger one (300 MiB at 12 % up to 1.2 GiB at 1 % of changed elements; half as much again
  * with arithmetic payloads or refresh) where the density is known, as far as the workspace has room for the entries: up to
- * 300 MiB by the last total that rose_bucket_check has read back, above only if the buckets' capacities bound it too (buckets
- * sized for what is expected, not for every element).  What follows is about the others.
+ * 300 MiB by the last total that rose_bucket_check has read back, above (and, for parking, below 48 MiB) only if the buckets'
+ * capacities bound it too (buckets sized for what is expected, not for every element).  What follows is about the others.
  * The kernel's workgroups wait on each other's tile counts.  The wait is bounded: if a count does
  * not arrive within a few seconds the launch is marked as failed, every workgroup still exits,
  * seg_off[n_tensors] of every bucket is set to -1, rose_bucket_check returns ROSE_ERR_HIP and
@@ -346,10 +351,11 @@ rose_status rose_delta_apply_ex(const rose_plan *plan, int32_t d, const rose_buc
  * the buckets come out identical.
  *   - the plan must be resident on the current device already (rose_plan_upload, or any earlier
  *     device call on it): otherwise ROSE_ERR_SCRATCH, nothing queued;
- *   - rose_plan_workspace_bytes(plan) must not exceed ROSE_STATIC_SCRATCH_BYTES (about 6 million
- *     tiles, i.e. 50 G elements): otherwise ROSE_ERR_SCRATCH, nothing queued;
+ *   - what a launch cannot do without (see rose_plan_workspace_bytes) must not exceed
+ *     ROSE_STATIC_SCRATCH_BYTES (about 6 million tiles, i.e. 50 G elements): otherwise
+ *     ROSE_ERR_SCRATCH, nothing queued; what the array holds beyond it is room to park entries in;
  *   - every call on a device shares that device's array, which keeps the previous call's contents
- *     (the launch clears what it uses first): calls that overlap in time on one device race, whatever
+ *     (a launch clears or writes what it reads): calls that overlap in time on one device race, whatever
  *     their streams or plans.  Order them on one stream.
  */
 #define ROSE_STATIC_SCRATCH_BYTES (48u << 20)
