@@ -56,6 +56,7 @@ private:
     int plans_ = 0;
 };
 Mail mail;
+constexpr size_t kOneCopyBytes = (size_t)1 << 20;       // tables gathered on the host; larger ones go there one by one
 
 constexpr int32_t kNeighboursBelowPpm = rose::kSpreadFromPpm, kTimedBelowPpm = 40000;   // see encode_common
 
@@ -96,62 +97,60 @@ rose_status device_tables_locked(const rose_plan *p, bool may_allocate) {
             repl_numel.push_back(t.rows * t.cols);
         }
     }
-    rose::Piece *dp = nullptr, *dfp = nullptr;
-    int32_t *dt = nullptr, *dft = nullptr, *dc = nullptr, *dn = nullptr, *dr = nullptr;
-    int64_t *drn = nullptr;
-    unsigned long long *dv = nullptr;
+    // All tables lie in one allocation, and small ones go there in one copy: with an allocation and a copy for each a plan of
+    // one matrix took 85 us (and that was before the dense copy had tables of its own), this way 64; one of 32 layers of
+    // hidden 4096, TP4, 270 either way.
+    struct Part {
+        const void *from;                               // nullptr: zeros
+        size_t bytes, at;
+    };
+    std::vector<Part> parts;
+    size_t total = 0;
+    auto add = [&](const void *from, size_t bytes) {
+        parts.push_back({from, bytes, total});
+        total += (bytes + 255) / 256 * 256;
+        return parts.back().at;
+    };
+    auto add_table = [&](const auto &t) { return add(t.data(), t.size() * sizeof t[0]); };
+    const size_t verdict_at = add(nullptr, kVerdictSlots * sizeof(unsigned long long));
+    const size_t pieces_at = add_table(p->pieces), tile_piece_at = add_table(p->tile_piece);
+    const size_t fewer_pieces_at = add_table(p->fewer.pieces), fewer_tile_piece_at = add_table(p->fewer.tile_piece);
+    std::vector<int32_t> copy_table(p->copy_first);
+    copy_table.insert(copy_table.end(), p->copy_piece.begin(), p->copy_piece.end());
+    const size_t copy_at = add_table(copy_table), numel_at = add_table(numel);
+    const size_t repl_at = add_table(repl), repl_numel_at = add_table(repl_numel);
+    std::vector<char> all(total <= kOneCopyBytes ? total : 0);
+    for (const Part &t : parts)
+        if (!all.empty() && t.from && t.bytes) std::memcpy(all.data() + t.at, t.from, t.bytes);
+
     int resident[rose::kEncodeKernels];
     void *sws = nullptr;
     size_t sws_bytes = 0;
-    const size_t pb = p->pieces.size() * sizeof(rose::Piece), tb = p->tile_piece.size() * sizeof(int32_t);
-    const size_t fpb = p->fewer.pieces.size() * sizeof(rose::Piece), ftb = p->fewer.tile_piece.size() * sizeof(int32_t);
-    const size_t cfb = p->copy_first.size() * sizeof(int32_t), cpb = p->copy_piece.size() * sizeof(int32_t);
-    const size_t nb = numel.size() * sizeof(int32_t), vb = kVerdictSlots * sizeof(unsigned long long);
-    bool ok = hipMalloc(reinterpret_cast<void **>(&dp), pb) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&dt), tb) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&dc), cfb + cpb) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&dn), nb) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&dv), vb) == hipSuccess &&
-              hipMemcpy(dp, p->pieces.data(), pb, hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemcpy(dt, p->tile_piece.data(), tb, hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemcpy(dc, p->copy_first.data(), cfb, hipMemcpyHostToDevice) == hipSuccess &&
-              (cpb == 0 || hipMemcpy(dc + p->copy_first.size(), p->copy_piece.data(), cpb, hipMemcpyHostToDevice) == hipSuccess) &&
-              hipMemcpy(dn, numel.data(), nb, hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemset(dv, 0, vb) == hipSuccess;
-    if (ok && fpb) {
-        ok = hipMalloc(reinterpret_cast<void **>(&dfp), fpb) == hipSuccess &&
-             hipMalloc(reinterpret_cast<void **>(&dft), ftb) == hipSuccess &&
-             hipMemcpy(dfp, p->fewer.pieces.data(), fpb, hipMemcpyHostToDevice) == hipSuccess &&
-             hipMemcpy(dft, p->fewer.tile_piece.data(), ftb, hipMemcpyHostToDevice) == hipSuccess;
-    }
-    if (ok && !repl.empty()) {
-        ok = hipMalloc(reinterpret_cast<void **>(&dr), repl.size() * sizeof(int32_t)) == hipSuccess &&
-             hipMalloc(reinterpret_cast<void **>(&drn), repl.size() * sizeof(int64_t)) == hipSuccess &&
-             hipMemcpy(dr, repl.data(), repl.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess &&
-             hipMemcpy(drn, repl_numel.data(), repl.size() * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess;
+    char *base = nullptr;
+    bool ok = hipMalloc(reinterpret_cast<void **>(&base), total) == hipSuccess;
+    if (ok && !all.empty()) ok = hipMemcpy(base, all.data(), total, hipMemcpyHostToDevice) == hipSuccess;
+    for (size_t i = 0; ok && all.empty() && i < parts.size(); ++i) {
+        const Part &t = parts[i];
+        if (!t.bytes) continue;
+        ok = (t.from ? hipMemcpy(base + t.at, t.from, t.bytes, hipMemcpyHostToDevice) : hipMemset(base + t.at, 0, t.bytes)) == hipSuccess;
     }
     ok = ok && rose::encode_resident_all(resident) == 0 && rose::static_scratch(&sws, &sws_bytes) == 0;
     if (!ok) {
-        if (dp) (void)hipFree(dp);
-        if (dt) (void)hipFree(dt);
-        if (dfp) (void)hipFree(dfp);
-        if (dft) (void)hipFree(dft);
-        if (dc) (void)hipFree(dc);
-        if (dn) (void)hipFree(dn);
-        if (dv) (void)hipFree(dv);
-        if (dr) (void)hipFree(dr);
-        if (drn) (void)hipFree(drn);
+        if (base) (void)hipFree(base);
         return ROSE_ERR_HIP;
     }
-    p->d_pieces = dp;
-    p->d_tile_piece = dt;
-    p->d_fewer_pieces = dfp;
-    p->d_fewer_tile_piece = dft;
-    p->d_copy = dc;
-    p->d_local_numel = dn;
-    p->d_verdict = dv;
-    p->d_repl_list = dr;
-    p->d_repl_numel = drn;
+    p->d_tables = base;
+    p->d_verdict = reinterpret_cast<unsigned long long *>(base + verdict_at);
+    p->d_pieces = reinterpret_cast<rose::Piece *>(base + pieces_at);
+    p->d_tile_piece = reinterpret_cast<int32_t *>(base + tile_piece_at);
+    if (!p->fewer.pieces.empty()) {
+        p->d_fewer_pieces = reinterpret_cast<rose::Piece *>(base + fewer_pieces_at);
+        p->d_fewer_tile_piece = reinterpret_cast<int32_t *>(base + fewer_tile_piece_at);
+    }
+    p->d_copy = reinterpret_cast<int32_t *>(base + copy_at);
+    p->d_local_numel = reinterpret_cast<int32_t *>(base + numel_at);
+    p->d_repl_list = reinterpret_cast<int32_t *>(base + repl_at);
+    p->d_repl_numel = reinterpret_cast<int64_t *>(base + repl_numel_at);
     p->n_repl = (int32_t)repl.size();
     std::memcpy(p->resident, resident, sizeof resident);
     if (!p->uses_mail) p->uses_mail = mail.share();
@@ -177,15 +176,7 @@ extern "C" rose_status rose_plan_upload(const rose_plan *p) {
 
 extern "C" void rose_shard_plan_destroy(rose_plan *p) {
     if (!p) return;
-    if (p->d_pieces) (void)hipFree(p->d_pieces);
-    if (p->d_tile_piece) (void)hipFree(p->d_tile_piece);
-    if (p->d_fewer_pieces) (void)hipFree(p->d_fewer_pieces);
-    if (p->d_fewer_tile_piece) (void)hipFree(p->d_fewer_tile_piece);
-    if (p->d_copy) (void)hipFree(p->d_copy);
-    if (p->d_local_numel) (void)hipFree(p->d_local_numel);
-    if (p->d_verdict) (void)hipFree(p->d_verdict);
-    if (p->d_repl_list) (void)hipFree(p->d_repl_list);
-    if (p->d_repl_numel) (void)hipFree(p->d_repl_numel);
+    if (p->d_tables) (void)hipFree(p->d_tables);
     if (p->uses_mail) mail.give_back();
     delete p;
 }

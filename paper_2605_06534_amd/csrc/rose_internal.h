@@ -217,8 +217,8 @@ struct rose_plan : rose::Tiles {               // (its tiles with all pieces mov
     std::vector<int32_t> stage_src_of, stage_dst_of;   // [n_tensors] stage that holds each tensor on either side
     std::vector<int64_t> global_base;          // [n_tensors + 1]
     rose::Tiles fewer;                         // tiles with only the longer pieces moved (no pieces: the plan's own)
-    std::vector<int32_t> copy_piece;           // the same for the dense copy (empty: the encode's tiles)
-    std::vector<int32_t> copy_first;           // first tile of each piece there
+    std::vector<int32_t> copy_piece;           // piece of each of the dense copy's tiles (empty: it has the encode's)
+    std::vector<int32_t> copy_first;           // first of its tiles of each piece
     int32_t copy_chain_first[ROSE_MAX_TP + 1] = {0};
     mutable std::atomic<int32_t> worker_cap{0};     // rose_plan_set_worker_cap
     mutable std::atomic<int32_t> tile_order{0};     // rose_plan_set_tile_order
@@ -229,6 +229,7 @@ struct rose_plan : rose::Tiles {               // (its tiles with all pieces mov
     // device copies of pieces / tile_piece, made on first use on a device (the only device the plan is used on)
     mutable std::mutex mu;
     mutable int device = -1;
+    mutable void *d_tables = nullptr;          // the allocation that holds all of these
     mutable rose::Piece *d_pieces = nullptr;
     mutable int32_t *d_tile_piece = nullptr;
     mutable rose::Piece *d_fewer_pieces = nullptr;     // the same of `fewer`, if there are
