@@ -319,10 +319,6 @@ constexpr u64 kStatusPrefix = 2;      // tile word: the tile's exclusive prefix;
                                       // this block and all earlier blocks of the chain
 constexpr u64 kValueMask = (1ull << kStatusShift) - 1;
 
-#ifndef ROSE_DIAG
-#define ROSE_DIAG 0           // timing experiments only: 1 no waiting for prefixes, 2 no bucket writes,
-                              // 4 no publishing, 8 no parking in LDS
-#endif
 #ifndef ROSE_WRITE_PERIOD_LOG2
 #define ROSE_WRITE_PERIOD_LOG2 12     // ticks of the 100 MHz clock between windows (2^12: 41 us)
 #endif
@@ -915,7 +911,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             // everything about the tiles is uniform: kept in scalar registers, the bucket's
             // pointers come through scalar loads
             const uint32_t cnt0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_count[slot]);
-            if (!ok || (ROSE_DIAG & 2)) {
+            if (!ok) {
                 freed += cnt0;
                 ++i;
                 continue;
@@ -1021,7 +1017,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         if (wave == 0) {
             bool ok = true;
             int n_ready = q_len;
-#if !(ROSE_DIAG & 1)
             unsigned int spins = 0;
             for (;;) {
                 if (lane < q_len && !has_prefix(wq_w)) wq_w = desc_load(a.tile_desc + wq_tile);
@@ -1034,9 +1029,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                     break;
                 }
             }
-#else
-            wq_w = kStatusPrefix << kStatusShift;
-#endif
             if (lane < n_ready) s_excl_sync[lane] = wq_w & kValueMask;
             if (lane == 0) {
                 s_ok = ok ? 1 : 0;
@@ -1120,7 +1112,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         if (threadIdx.x == 0) {
             uint32_t total = 0;
             for (int w = 0; w < kWaves; ++w) total += s_count_only[w];
-            if (!(ROSE_DIAG & 4)) desc_store(a.tile_desc + t, (kStatusAggregate << kStatusShift) | total);
+            desc_store(a.tile_desc + t, (kStatusAggregate << kStatusShift) | total);
         }
     };
     int32_t tile = -1;
@@ -1295,9 +1287,6 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         }
         ticket_out = false;
         if (wave == 0 && lane < n_polled && !has_prefix(wq_w)) wq_w = polled;
-#if ROSE_DIAG & 1
-        wq_w = kStatusPrefix << kStatusShift;
-#endif
         if (n_announced > 0) {
             ring_used -= copy_out(n_announced, s_excl[parity ^ 1], true);
             pop(n_announced);
@@ -1360,7 +1349,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         parity ^= 1;
 
         // publish the count: a serving wave turns it into this tile's prefix
-        if (threadIdx.x == 0 && !cur_redo && !(ROSE_DIAG & 4))
+        if (threadIdx.x == 0 && !cur_redo)
             desc_store(a.tile_desc + tile, (kStatusAggregate << kStatusShift) | tile_total);
 
         // Room to park?  Making room may wait, and nothing may wait while a ticket is on its way
@@ -1408,7 +1397,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 uint32_t m = mask[j];
                 uint32_t slot = base + rank[j];
                 const uint32_t in_tile0 = t_off + (uint32_t)(j * 64) * kVec;
-                while (m && !(ROSE_DIAG & 8)) {
+                while (m) {
                     const uint32_t e = __ffs(m) - 1;
                     m &= m - 1;
                     s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu) |
