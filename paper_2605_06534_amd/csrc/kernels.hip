@@ -147,9 +147,6 @@ __device__ __forceinline__ uint32_t or_of_four(uint32_t x) {
 #define ROSE_NT_LOADS 1
 #endif
 constexpr int kRefreshWide = 200;      // entries per tile up to which a refresh writes 128-byte lines, see encode_body
-#ifndef ROSE_NT_STORES
-#define ROSE_NT_STORES 1
-#endif
 // 128-bit load / store through the global address space (pointers fetched from a table would
 // otherwise be treated as generic and use the slower flat instructions).  The address needs no more
 // than the alignment of a 16-bit element: the compiler emits the same instruction, and the memory
@@ -175,6 +172,14 @@ __device__ __forceinline__ uint4 gload16_stream(const void *p) {
 __device__ __forceinline__ void gstore16_stream(void *p, uint4 v) {
     u32x4 w = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(w, reinterpret_cast<global_u32x4 *>(reinterpret_cast<uintptr_t>(p)));
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef __attribute__((address_space(1))) u32x2_any global_u32x2;
+__device__ __forceinline__ void gstore8_stream(void *p, uint32_t x, uint32_t y) {
+    u32x2 w = {x, y};
+    __builtin_nontemporal_store(w, reinterpret_cast<global_u32x2 *>(reinterpret_cast<uintptr_t>(p)));
 }
 
 // Single elements the same way.  (Flat accesses may come back out of turn: where one can be on its way, the compiler
@@ -490,9 +495,9 @@ __device__ __forceinline__ void serve_blocks(const EncodeArgs &a, int32_t server
 // others are workers that walk the tiles their tickets name (see ticket_tile and struct Walk).
 //
 // Worker, per tile: (1) the tile's 128-bit loads were issued one tile earlier; XOR old and new
-// into an 8-bit change mask per vector, (2) copy out parked tiles whose prefixes have arrived,
+// into an 8-bit change mask per vector, (2) see which parked tiles' prefixes have arrived,
 // poll for the others, ask for a ticket, (3) issue the NEXT tile's loads, (4) wave prefix sums of
-// the popcounts, wave totals through LDS, (5) publish the tile's count, (6) park the tile's
+// the popcounts, wave totals through LDS, (5) publish the tile's count, copy out parked tiles, (6) park the tile's
 // entries, compacted, in an LDS ring and go on (the order of the memory operations matters: see
 // the comment in encode_body).  The wait for a tile's prefix is deferred: parked tiles are polled
 // one lane per tile, every iteration, without waiting; only when the ring (kRing entries) or the
@@ -516,9 +521,6 @@ static_assert((kRing & (kRing - 1)) == 0 && (kQueue & (kQueue - 1)) == 0 && kQue
 
 enum : int { kLoadVec = 0, kLoadGeneral = 1 };
 enum : int { kDrainOldest = 0, kDrainAll = 1, kDrainReady = 2 };
-#ifndef ROSE_ALIGN_STORES
-#define ROSE_ALIGN_STORES 1
-#endif
 
 
 struct TileCtx {
@@ -842,6 +844,86 @@ __device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, 
     return (entry & 0x7FFF0000u) | payload | (escapes ? 0x80000000u : 0u);
 }
 
+// Local index of a parked entry of a run whose elements are numbered from `base` on: an entry keeps the low 15 bits of its
+// element's number (bit 31 is the escape's), and a run spans less than 2^15 elements.
+constexpr int kRunTiles = 4;
+static_assert(kRunTiles * kTile <= 1 << 15, "15 bits tell the elements of a run apart");
+__device__ __forceinline__ uint32_t run_local(uint32_t entry, uint32_t base) {
+    return base + (((entry - (base << 16)) >> 16) & 0x7FFFu);
+}
+
+// The cnt entries that lie in the ring from `off` on go to positions excl .. of a bucket.  All threads of the workgroup.
+// A wave's stores begin at multiples of 32 entries of the BUCKET, not of the run, so that every store but the first and last
+// of a run fills whole 64-byte lines (otherwise each wave's store starts and ends inside a line and the line's 32-byte halves
+// are written twice: 1.20 x the bytes at the memory).
+// A thread takes four entries, whose places are found together and which leave as one 128-bit and one 64-bit store.  All
+// workgroups copy out in the same windows of time, the memory then waits for them, and a load is away for less time than an
+// entry after the other takes (without its stores, an entry a lane, copying out cost 8.6 GB read 0.18 ms of 1.53 at 5 %).
+template <int ARITH, bool ESCAPES>
+__device__ __forceinline__ void write_run(const EncodeArgs &a, int32_t shard, int32_t piece, uint32_t base, uint32_t off, u64 excl,
+                                          uint32_t cnt, const uint32_t *s_ring, const uint16_t *s_was) {
+    const BucketDev b = a.bucket[shard];
+    if (!ARITH && piece < 0 && excl + cnt <= (u64)b.capacity) {
+        int32_t *const idx = b.idx + excl;
+        uint16_t *const val = b.val + excl;
+        const int32_t n = (int32_t)cnt, first = (int32_t)(threadIdx.x * 4) - (int32_t)((uint32_t)excl & 31u);
+        // places of the ring are read whether they are the run's or not: no lane waits for LDS twice
+        auto four = [&](int32_t k, uint32_t (&e)[4]) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = s_ring[(off + (uint32_t)(k + i)) & (uint32_t)(kRing - 1)];
+        };
+        auto put = [&](int32_t k, const uint32_t (&e)[4]) {
+            uint32_t local[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) local[i] = run_local(e[i], base) | (ESCAPES ? e[i] & 0x80000000u : 0u);
+            if (k >= 0 && k + 4 <= n) {
+                gstore16_stream(idx + k, make_uint4(local[0], local[1], local[2], local[3]));
+                gstore8_stream(val + k, __builtin_amdgcn_perm(e[1], e[0], 0x05040100u), __builtin_amdgcn_perm(e[3], e[2], 0x05040100u));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k + i >= 0 && k + i < n) {
+                        __builtin_nontemporal_store((int32_t)local[i], idx + k + i);
+                        __builtin_nontemporal_store((uint16_t)e[i], val + k + i);
+                    }
+            }
+        };
+        for (int32_t k = first; k < n; k += kThreads * 4) {
+            uint32_t e[4];
+            four(k, e);
+            put(k, e);
+        }
+        return;
+    }
+    // a run that ends behind the bucket's end, or whose local indices come in strided runs
+    uint32_t l_base = 0, l_run = 0, l_magic = 0, l_shift = 0, l_stride = 0;
+    if (piece >= 0) {
+        const Piece pc = load_piece(a.pieces + piece);
+        l_base = (uint32_t)pc.local_base;
+        l_run = (uint32_t)pc.run;
+        l_magic = pc.magic;
+        l_shift = pc.shift;
+        l_stride = (uint32_t)pc.lstride;
+    }
+    const uint32_t phase = (uint32_t)excl & 31u;
+    for (uint32_t kk = threadIdx.x; kk < cnt + phase; kk += kThreads) {
+        const uint32_t k = kk - phase;                 // (wraps below phase: caught by the first test)
+        const u64 pos = excl + k;
+        if (kk >= phase && pos < (u64)b.capacity) {
+            const uint32_t entry = parked<ARITH>((off + k) & (kRing - 1), s_ring, s_was);
+            uint32_t local = run_local(entry, base);
+            if (piece >= 0) {                          // it is the element's number inside the piece here
+                // (runs of one element have no magic divisor: the quotient is the number itself)
+                const uint32_t q = l_run == 1u ? local : (__umulhi(local, l_magic) >> l_shift);
+                local = l_base + q * l_stride + (local - q * l_run);
+            }
+            if constexpr (ESCAPES) local |= entry & 0x80000000u;
+            __builtin_nontemporal_store((int32_t)local, b.idx + pos);
+            __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
+        }
+    }
+}
+
 // PAYLOAD = 1: arithmetic payloads formed of the compacted entries; 2: of every element, before they are compacted.
 template <int NEW_F32, int REFRESH, int PAYLOAD>
 __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
@@ -850,7 +932,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
-    __shared__ uint32_t s_ring[kRing];      // an entry: offset inside its tile (13 bits) << 16 | new pattern
+    __shared__ uint32_t s_ring[kRing];      // an entry: low 15 bits of its element's number (TileMeta::out_base) << 16 | new pattern
     __shared__ uint16_t s_was[ARITH ? kRing : 1];    // arithmetic payload: the old patterns, from which it is formed
     __shared__ uint32_t s_wave_total[2][kWaves];
     __shared__ u64 s_excl[2][kQueue];       // prefixes of the tiles an iteration copies out, oldest first
@@ -884,16 +966,17 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     // iteration's other memory operations (bucket stores, the poll, the ticket request):
     //   top   the tile's data has landed; so have last iteration's poll answers and ticket
     //   (a)   change masks of this tile (frees the load registers)
-    //   (b)   copy out the parked tiles announced at the last barrier; wave 0 takes in the poll
-    //         answers and announces (through LDS, valid after this iteration's barrier) which
-    //         parked tiles can be copied out next time
+    //   (b)   wave 0 takes in the poll answers and announces (through LDS, valid after this
+    //         iteration's barrier) which parked tiles can be copied out
     //   (c)   wave 0 polls the parked tiles without a prefix; thread 0 asks for a ticket
     //   (d)   the NEXT tile's loads are issued
-    //   (e)   scan, barrier, publish this tile's count, park its entries (LDS only)
+    //   (e)   scan, barrier, publish this tile's count, copy out the announced tiles, park this tile's entries
+    // (Copied out in (b), in front of the loads, 8.6 GB read take 1.419 ms at 1 %, this way 1.411.  Nothing waits for the
+    // stores by themselves.)
     int q_head = 0, q_len = 0;
     uint32_t ring_used = 0, ring_head = 0;
     int parity = 0;
-    int n_announced = 0;        // oldest parked tiles whose prefixes lie in s_excl[parity ^ 1]
+    int n_gone = 0;             // tiles copied out since wave 0's lanes were last moved down
     // wave 0 only: lane i tracks the i-th oldest parked tile
     int32_t wq_tile = 0;
     u64 wq_w = 0;               // the newest copy of its descriptor word: the prefix once the status says so
@@ -902,108 +985,64 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     bool ticket_out = false;    // a ticket has been asked for and not yet taken in
 
     // copy the n oldest parked tiles to the buckets (prefixes in excl[0..n)); returns ring entries freed.
-    // Tiles that follow each other in the bucket (up to four: same shard, each starting where the one
+    // Tiles that follow each other in the bucket and in their piece (up to four: each starting where the one
     // before ends; their entries follow each other in the ring as well) are written as one run.
     auto copy_out = [&](int n, const u64 *excl_by_age, bool ok) -> uint32_t {
-        uint32_t freed = 0;
+        // lane i looks at the i-th oldest tile, so that the waves wait for LDS once and not tile by tile
+        const bool mine = lane < n;
+        const int slot = (q_head + lane) & (kQueue - 1);
+        const uint32_t count = mine ? s_q_count[slot] : 0u, off = s_q_off[slot], base = s_q_base[slot];
+        const int32_t piece = s_q_piece[slot], shard = s_q_shard[slot];
+        const u64 excl = mine ? excl_by_age[lane] : 0;
+        const uint32_t excl_lo = (uint32_t)excl, excl_hi = (uint32_t)(excl >> 32);
+        const uint32_t freed = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(count), 63);
+        if (!ok) return freed;
+        auto of = [](uint32_t x, int t) { return (uint32_t)__builtin_amdgcn_readlane((int)x, t); };
+        if (wave == 0) {                               // segment ends (few tiles have one)
+            const int32_t seg = s_q_seg[slot], last = s_q_last[slot];
+            for (u64 ends = __ballot(mine & ((seg >= 0) | (last != 0))); ends; ends &= ends - 1) {
+                const int i = __ffsll((long long)ends) - 1;
+                int64_t *const seg_off = a.bucket[of((uint32_t)shard, i)].seg_off;
+                const u64 at = (u64)of(excl_hi, i) << 32 | of(excl_lo, i);
+                if (lane == 0) {
+                    if ((int32_t)of((uint32_t)seg, i) >= 0) seg_off[of((uint32_t)seg, i)] = (int64_t)at;
+                    if (of((uint32_t)last, i)) seg_off[a.n_tensors] = (int64_t)(at + of(count, i));
+                }
+            }
+        }
+        // (positions that continue each other agree in their low halves; all lanes take part in the moves)
+        auto below = [](uint32_t x) {                  // the lane below's
+            return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xf, 0xf, false);     // wave_shr:1
+        };
+        const uint32_t shard_b = below((uint32_t)shard), piece_b = below((uint32_t)piece), base_b = below(base), end_b = below(excl_lo + count);
+        const bool next = (lane > 0) & ((uint32_t)shard == shard_b) & ((int32_t)((uint32_t)piece & piece_b) < 0) &
+                          (base == base_b + (uint32_t)kTile) & (excl_lo == end_b);
+        const u64 starts = __ballot(mine & !next);
         for (int i = 0; i < n;) {
-            const int slot = (q_head + i) & (kQueue - 1);
-            // everything about the tiles is uniform: kept in scalar registers, the bucket's
-            // pointers come through scalar loads
-            const uint32_t cnt0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_count[slot]);
-            if (!ok) {
-                freed += cnt0;
-                ++i;
-                continue;
-            }
-            const u64 excl = ((u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(excl_by_age[i] >> 32)) << 32) |
-                             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)excl_by_age[i]);
-            const uint32_t off = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_off[slot]);
-            const int32_t shard = __builtin_amdgcn_readfirstlane(s_q_shard[slot]);
-            const BucketDev b = a.bucket[shard];
-            const int32_t piece = __builtin_amdgcn_readfirstlane(s_q_piece[slot]);
-            // the run: this tile and the parked tiles behind it that continue it (c1..c3: where the
-            // second to fourth tile's entries start inside the run; b0..b3: see TileMeta::out_base)
-            uint32_t cnt = cnt0, c1 = 0xFFFFFFFFu, c2 = 0xFFFFFFFFu, c3 = 0xFFFFFFFFu;
-            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_base[slot]);
-            uint32_t b1 = 0, b2 = 0, b3 = 0;
-            int g = 1;
-            if (threadIdx.x == 0) {
-                const int32_t seg = s_q_seg[slot];
-                if (seg >= 0) b.seg_off[seg] = (int64_t)excl;
-                if (s_q_last[slot]) b.seg_off[a.n_tensors] = (int64_t)(excl + cnt0);
-            }
-            while (piece < 0 && g < 4 && i + g < n) {
-                const int s2 = (q_head + i + g) & (kQueue - 1);
-                const u64 e2 = ((u64)(uint32_t)__builtin_amdgcn_readfirstlane((int)(excl_by_age[i + g] >> 32)) << 32) |
-                               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)excl_by_age[i + g]);
-                if (__builtin_amdgcn_readfirstlane(s_q_shard[s2]) != shard || e2 != excl + cnt ||
-                    __builtin_amdgcn_readfirstlane(s_q_piece[s2]) >= 0)
-                    break;
-                const uint32_t cg = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_count[s2]);
-                const uint32_t bg = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_q_base[s2]);
-                if (threadIdx.x == 0) {
-                    const int32_t seg = s_q_seg[s2];
-                    if (seg >= 0) b.seg_off[seg] = (int64_t)e2;
-                    if (s_q_last[s2]) b.seg_off[a.n_tensors] = (int64_t)(e2 + cg);
-                }
-                if (g == 1) { c1 = cnt; b1 = bg; }
-                else if (g == 2) { c2 = cnt; b2 = bg; }
-                else { c3 = cnt; b3 = bg; }
-                cnt += cg;
-                ++g;
-            }
-            freed += cnt;
-            // local index of the element at offset o of the tile
-            uint32_t l_base = b0, l_run = 0, l_magic = 0, l_shift = 0, l_stride = 0;
-            if (piece >= 0) {                          // the piece's local indices come in strided runs
-                const Piece pc = load_piece(a.pieces + piece);
-                l_base = (uint32_t)pc.local_base;
-                l_run = (uint32_t)pc.run;
-                l_magic = pc.magic;
-                l_shift = pc.shift;
-                l_stride = (uint32_t)pc.lstride;
-            }
-            // A wave's store covers 64 entries = 256 bytes of indices, 128 of values.  The run starts at an
-            // arbitrary entry of the bucket, so the threads are lined up with the BUCKET, not with the run:
-            // thread t of a round handles the entry whose position is t more than a multiple of 32
-            // entries.  Every store but the first and last of a run then fills whole 64-byte lines
-            // (otherwise each wave's store starts and ends inside a line and the line's 32-byte halves
-            // are written twice: 1.20 x the bytes at the memory).
-            const uint32_t phase = ROSE_ALIGN_STORES ? (uint32_t)excl & 31u : 0u;
-            for (uint32_t kk = threadIdx.x; kk < cnt + phase; kk += kThreads) {
-                const uint32_t k = kk - phase;         // (wraps below phase: caught by the first test)
-                const u64 pos = excl + k;
-                if (kk >= phase && pos < (u64)b.capacity) {
-                    const uint32_t entry = parked<ARITH>((off + k) & (kRing - 1), s_ring, s_was);
-                    const uint32_t base = k < c1 ? b0 : k < c2 ? b1 : k < c3 ? b2 : b3;
-                    uint32_t local = base + (PAYLOAD ? (entry >> 16) & (uint32_t)(kTile - 1) : entry >> 16);
-                    if (piece >= 0) {                  // base is the tile's first element number here
-                        // (runs of one element have no magic divisor: the quotient is the number itself)
-                        const uint32_t q = l_run == 1u ? local : (__umulhi(local, l_magic) >> l_shift);
-                        local = l_base + q * l_stride + (local - q * l_run);
-                    }
-                    if constexpr (PAYLOAD) local |= entry & 0x80000000u;
-#if ROSE_NT_STORES
-                    __builtin_nontemporal_store((int32_t)local, b.idx + pos);
-                    __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
-#else
-                    b.idx[pos] = (int32_t)local;
-                    b.val[pos] = (uint16_t)entry;
-#endif
-                }
-            }
+            // everything about the run is uniform: scalar registers, the bucket's pointers come through scalar loads
+            const u64 behind = starts >> i >> 1;
+            int g = behind ? __ffsll((long long)behind) : n - i;
+            g = g < kRunTiles ? g : kRunTiles;
+            const u64 first = (u64)of(excl_hi, i) << 32 | of(excl_lo, i);
+            const uint32_t cnt = of(excl_lo, i + g - 1) + of(count, i + g - 1) - (uint32_t)first;
+            write_run<ARITH, PAYLOAD != 0>(a, (int32_t)of((uint32_t)shard, i), (int32_t)of((uint32_t)piece, i), of(base, i), of(off, i), first,
+                                           cnt, s_ring, s_was);
             i += g;
         }
         return freed;
     };
-    auto pop = [&](int n) {      // forget the n oldest tiles (wave 0 shifts its lanes down)
+    auto pop = [&](int n, uint32_t freed) {      // forget the n oldest tiles
         q_head = (q_head + n) & (kQueue - 1);
         q_len -= n;
-        if (wave == 0) {
-            wq_tile = __shfl(wq_tile, lane + n, 64);
-            wq_w = __shfl(wq_w, lane + n, 64);
+        ring_used -= freed;
+        n_gone += n;
+    };
+    auto move_lanes = [&]() {    // wave 0 moves its lanes down by the tiles that are gone (the poll has been taken in or is forgotten)
+        if (wave == 0 && n_gone > 0) {
+            wq_tile = __shfl(wq_tile, lane + n_gone, 64);
+            wq_w = __shfl(wq_w, lane + n_gone, 64);
         }
+        n_gone = 0;
     };
 
     // Blocking drain, for when there is no room to park (or at the end): waits until the oldest
@@ -1013,6 +1052,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     // copies out what has its prefix by now.
     auto drain = [&](int mode) {
         const bool all = mode == kDrainAll;
+        move_lanes();                                  // (a poll in flight is forgotten: its tiles are polled again)
+        n_polled = 0;
         __syncthreads();                               // parked entries visible; earlier copies done
         if (wave == 0) {
             bool ok = true;
@@ -1039,10 +1080,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         const int n_ready = __builtin_amdgcn_readfirstlane(s_ready);
         const uint32_t freed = copy_out(n_ready, s_excl_sync, s_ok != 0);
         __syncthreads();                               // ring and queue slots may be reused
-        pop(n_ready);
-        ring_used -= freed;
-        n_announced = 0;
-        n_polled = 0;                                  // the lanes of wave 0 have moved
+        pop(n_ready, freed);
+        move_lanes();
     };
 
     // Tiles come from tickets (dynamic, so that faster workgroups take more): thread 0 asks for a
@@ -1147,7 +1186,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         ring_used = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring_used);
         ring_head = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring_head);
         parity = __builtin_amdgcn_readfirstlane(parity);
-        n_announced = __builtin_amdgcn_readfirstlane(n_announced);
+        n_gone = __builtin_amdgcn_readfirstlane(n_gone);
         n_polled = __builtin_amdgcn_readfirstlane(n_polled);
         walk.ticket = __builtin_amdgcn_readfirstlane(walk.ticket);
         walk.j = __builtin_amdgcn_readfirstlane(walk.j);
@@ -1280,18 +1319,14 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             }
         }
 
-        // ---- (b) poll answers and ticket of the previous iteration; copy out what was announced ----
+        // ---- (b) poll answers and ticket of the previous iteration ----
         const bool accept_now = ticket_out;
         if (accept_now && threadIdx.x == 0) {
             s_ticket[parity] = (int32_t)ticket_take<WIDE>();   // nothing else is in flight here
         }
         ticket_out = false;
         if (wave == 0 && lane < n_polled && !has_prefix(wq_w)) wq_w = polled;
-        if (n_announced > 0) {
-            ring_used -= copy_out(n_announced, s_excl[parity ^ 1], true);
-            pop(n_announced);
-            n_announced = 0;
-        }
+        move_lanes();
         if (wave == 0) {
             const u64 unknown = __ballot(lane < q_len && !has_prefix(wq_w));
             int n_ready = unknown ? __ffsll((long long)unknown) - 1 : q_len;
@@ -1337,7 +1372,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         if (lane == 0) s_wave_total[parity][wave] = wave_total;
         __syncthreads();
         if (accept_now) walk_accept(a, walk, (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket[parity]));
-        n_announced = __builtin_amdgcn_readfirstlane(s_nready[parity]);
+        const int n_announced = __builtin_amdgcn_readfirstlane(s_nready[parity]);
         uint32_t wave_excl = 0, tile_total = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
@@ -1351,6 +1386,18 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         // publish the count: a serving wave turns it into this tile's prefix
         if (threadIdx.x == 0 && !cur_redo)
             desc_store(a.tile_desc + tile, (kStatusAggregate << kStatusShift) | tile_total);
+
+        // copy out what was announced, while the next tile's loads are on their way
+        if (n_announced > 0) {
+            const bool crowded = q_len == kQueue || ring_used + tile_total > (uint32_t)kRing;
+            const uint32_t freed = copy_out(n_announced, s_excl[parity ^ 1], true);
+            pop(n_announced, freed);
+            if (crowded) {                             // what is parked next may take the places of what is being copied
+                move_lanes();                          // (and the last lane; the poll in flight is forgotten)
+                n_polled = 0;
+                __syncthreads();
+            }
+        }
 
         // Room to park?  Making room may wait, and nothing may wait while a ticket is on its way
         // (it could be of the current ticket's group): take it in first.
@@ -1396,12 +1443,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             for (int j = 0; j < kIters; ++j) {
                 uint32_t m = mask[j];
                 uint32_t slot = base + rank[j];
-                const uint32_t in_tile0 = t_off + (uint32_t)(j * 64) * kVec;
+                const uint32_t number0 = cur.out_base + t_off + (uint32_t)(j * 64) * kVec;
                 while (m) {
                     const uint32_t e = __ffs(m) - 1;
                     m &= m - 1;
-                    s_ring[slot & (kRing - 1)] = ((in_tile0 + e) << 16) | (pick16(nv[j], e) & 0xFFFFu) |
-                                                 (FORMED ? (escaped >> (8 * j + e)) << 31 : 0u);
+                    uint32_t number = (number0 + e) << 16;         // (bit 31 counts only where it is an escape)
+                    if constexpr (FORMED) number = (number & 0x7FFF0000u) | (escaped >> (8 * j + e)) << 31;
+                    s_ring[slot & (kRing - 1)] = number | (pick16(nv[j], e) & 0xFFFFu);
                     if constexpr (ARITH) s_was[slot & (kRing - 1)] = (uint16_t)pick16(ov[j], e);
                     ++slot;
                 }
@@ -1416,7 +1464,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 s_q_seg[slot] = seg;
                 s_q_last[slot] = tile == chain_last;
             }
-            if (wave == 0 && lane == q_len) {
+            if (wave == 0 && lane == q_len + n_gone) {
                 wq_tile = tile;
                 wq_w = 0;
             }
