@@ -325,7 +325,7 @@ constexpr u64 kStatusPrefix = 2;      // tile word: the tile's exclusive prefix;
 constexpr u64 kValueMask = (1ull << kStatusShift) - 1;
 
 #ifndef ROSE_WRITE_PERIOD_LOG2
-#define ROSE_WRITE_PERIOD_LOG2 12     // ticks of the 100 MHz clock between windows (2^12: 41 us)
+#define ROSE_WRITE_PERIOD_LOG2 12     // ticks of the 100 MHz clock between windows (2^12: 41 us; encode_walk doubles it)
 #endif
 // Ticks a window is open, for the tile order and density a launch runs with (rule: encode_walk).
 #ifndef ROSE_WRITE_OPEN_TIMED
@@ -1205,6 +1205,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             walk.redo = flags & 64;
         }
         cur = loaded ? nxt : start_tile(tile);         // not loaded: the first tile, or one named late
+        // From here until the next tile's loads are issued this workgroup asks nothing of the memory, so its waves go first.
+        // (Among equals the oldest wave of a SIMD goes first, always: of four workgroups on a CU one then walked 160 tiles
+        // where another walked 360, all others' entries waited in their rings for its counts, and at 5 % two of five tiles
+        // left outside the windows because a ring was full.  This way they walk 200 to 320.)
+        __builtin_amdgcn_s_setprio(3);
         // ---- (a) change masks ----
         const uint32_t k_wave = cur.k_tile + (uint32_t)wave * kWaveSpan;
         uint4 nv[kIters];                              // the new patterns (FORMED: the payloads)
@@ -1341,7 +1346,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             // entries outside the windows (7B-style workload at 4 %: 5.04 ms; 4.74 ms this way).
             if (a.window_open) {
                 const uint32_t now = (uint32_t)__builtin_amdgcn_s_memrealtime();
-                const bool open = (now & ((1u << ROSE_WRITE_PERIOD_LOG2) - 1u)) < a.window_open;
+                const bool open = (now & a.window_mask) < a.window_open;
                 if (!open && q_len <= kQueue * 3 / 4) n_ready = 0;
             }
             if (lane < n_ready) s_excl[parity][lane] = wq_w & kValueMask;
@@ -1366,6 +1371,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         loaded = next_state == kWalkTile;
         if (loaded) nxt = start_tile(next);
 
+        __builtin_amdgcn_s_setprio(0);
         // ---- (e) ranks of the entries ----
         uint32_t rank[kIters];
         const uint32_t wave_total = vector_ranks(mask, rank);
@@ -2925,31 +2931,32 @@ int static_scratch(void **ptr, size_t *bytes) {
 #define ROSE_SERVER_WGS 16          // workgroups of the grid that serve prefixes (kWaves servers each)
 #endif
 
-// How a launch in this tile order walks its tiles: tiles per ticket, and how long of each period of
-// 41 us the bucket stores may go out (0: always).  ppm: changed elements per million, -1 unknown.
-//   timed       4 tiles, 10 us.  The entries of a period fit the ring up to about 4 %.
-//   neighbours  Denser: 3 tiles, whose prefixes are ready sooner and leave the ring room, and longer windows, so
-//               that less waits: up to 5 % 15 us, above, and where payloads are formed of every element, 20 us.
-// 7B-style workload, one process, same buffers, ms (always = neighbours with no windows, 3 tiles):
-//               4 %   4.5 %   5 %   5.5 %   6 %   7 %   8 %   10 %   30 %
-//   always      5.11  5.13    5.19  5.21    5.27  5.32  5.52  6.34   10.75
-//   4 x 10 us   4.74  4.90    5.10  5.26    5.33  5.55  6.02  6.49   19.5
-//   4 x 15 us   4.77  4.83    4.96  5.12    5.24  5.48  6.03  6.49   19.5
-//   3 x 20 us   4.96  4.98    5.03  5.06    5.14  5.29  5.46  6.19   10.30
-// (fp32 masters, two 32B-style layers: 3.16 / 3.06 / 2.98 / 2.95 ms at 5 %, 3.17 / 3.24 / 3.19 / 3.04 at 6 %;
-// arithmetic payloads, 15 / 20 us: eight 7B-style layers 1.477 / 1.491 ms at 4.5 %, 1.489 / 1.515 at 4.8 %, fp32 masters
-// 2.83 / 2.89 at 4.5 %)
-// Four tiles would gain up to 3 % between 4 and 5 %, but the density is the last launch's, and where more comes they
-// lose far more: seen 4.5 %, 20 / 30 % came: 8.9 / 19.4 ms with 4 x 15 us, 7.8 / 10.0 with 3 x 15; fp32 masters, 15 %
-// came: 19.4 and 11.1 (always: 7.8 / 10.3 and 11.8).
-constexpr int32_t kNearBelowPpm = 50000;
-static void encode_walk(int order, int32_t ppm, bool of_elements, EncodeArgs *a) {
+// How a launch in this tile order walks its tiles: tiles per ticket, and how long of each period the bucket stores may go out
+// (0: always).  ppm: changed elements per million, -1 unknown; room_ppm: as many as the buckets could hold.
+//   timed       4 tiles, 10 us of each 82; from kLongBelowPpm on of each 41: the entries of a period have to fit the ring.
+//   neighbours  4 tiles and 10 us of 41 as well, as long as it is known that no more comes (the buckets hold no more than
+//               kNearRoomPpm) and the ring holds it; else 3 tiles, whose prefixes are ready sooner and leave the ring room,
+//               and longer windows, so that less waits: up to 5 % 15 us, above, and where payloads are formed of every element, 20 us.
+// Eight 7B-style layers, TP4, one process, same buffers, ms (bf16 / fp32 masters / arithmetic payloads):
+//                 1 %                  3 %                  4 %                  5 %                  6 %                  7 %
+//   4 x 10 of 82  1.057 1.594 1.064    1.102 1.641 1.115    1.159 1.711 1.184    1.223 1.837 1.236    1.269 1.954 1.291    1.342 2.015 1.356
+//   4 x 10 of 41  1.075 1.658 1.080    1.115 1.700 1.138    1.131 1.716 1.173    1.158 1.747 1.210    1.214 1.821 1.266    1.311 1.936 1.320
+//   3 x 15        1.156 1.702 1.158    1.190 1.744 1.209    1.204 1.765 1.231    1.226 1.779 1.256    1.241 1.801 1.280    1.291 1.853 1.318
+//   3 x 20        1.160 1.742 1.157    1.190 1.797 1.212    1.206 1.813 1.238    1.223 1.824 1.261    1.237 1.841 1.285    1.284 1.866 1.330
+// Where the density is the last launch's and more comes, 4 tiles lose far more than 3 (4 / 3 tiles: 12 % 1.61 / 1.38, 20 % 2.03 / 1.80,
+// 30 % 4.12 / 2.31).
+constexpr int32_t kLongBelowPpm = 33000, kNearBelowPpm = 50000;
+constexpr int32_t kNearFourPpm = 65000, kNearFourPpmF32 = 57000, kNearRoomPpm = 80000;
+static void encode_walk(int order, int32_t ppm, int32_t room_ppm, int new_is_f32, bool of_elements, EncodeArgs *a) {
     a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
     a->batch = kBatch;
     a->window_open = 0;
-    if (order == ROSE_TILE_ORDER_TIMED) {
+    a->window_mask = (1u << ROSE_WRITE_PERIOD_LOG2) - 1u;
+    const bool four = !of_elements && ppm >= 0 && ppm < (new_is_f32 ? kNearFourPpmF32 : kNearFourPpm) && room_ppm < kNearRoomPpm;
+    if (order == ROSE_TILE_ORDER_TIMED || (order == ROSE_TILE_ORDER_NEIGHBOURS && four)) {
         a->batch = kBatchTimed;
         a->window_open = ROSE_WRITE_OPEN_TIMED;
+        if (order == ROSE_TILE_ORDER_TIMED && ppm >= 0 && ppm < kLongBelowPpm) a->window_mask = 2 * a->window_mask + 1;
     } else if (order == ROSE_TILE_ORDER_NEIGHBOURS) {
         const bool near = !of_elements && ppm >= 0 && ppm < kNearBelowPpm;
         a->window_open = near ? ROSE_WRITE_OPEN_NEAR : ROSE_WRITE_OPEN_WIDE;
@@ -3067,7 +3074,7 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     const bool of_elements = arith && !new_is_f32 && !refresh && (ppm < 0 || ppm >= kElementsPpm || room_ppm >= kElementsPpm);
     const int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
-    encode_walk(order, ppm, of_elements, &a);
+    encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are
