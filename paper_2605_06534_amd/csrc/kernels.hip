@@ -453,11 +453,25 @@ __device__ __forceinline__ bool block_look_back(u64 *block_desc, unsigned int *a
     return true;
 }
 
-// A serving wave: blocks server, server + n_servers, ... in increasing order.
+// The n-th block in the order in which a launch walks them, see Turns.  A refresh writes lines of what it reads all the
+// time, and the memory takes that better where they lie in several places (eight 7B-style layers, TP4, at 1 / 5 / 15 %: chain by chain
+// 1813 / 2190 / 2428 us, in turns 1750 / 2109 / 2397; arithmetic payloads at 2 % 1978 and 1899, fp32 masters 2695 and
+// 2653; but arithmetic payloads of fp32 masters, with half the waves, 2624 and 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns 1349 / 1599.
+template <int TURNS>
+__device__ __forceinline__ WalkedBlock nth_block(const EncodeArgs &a, int32_t n, int32_t shard) {
+    if constexpr (TURNS) return walked_block(a.turns, a.block_first, n);
+    while (n >= a.block_first[shard + 1]) ++shard;     // (blocks are numbered chain by chain; shard: that of an earlier one)
+    return {shard, n};
+}
+
+// A serving wave: blocks server, server + n_servers, ... of those that are walked, in their order.
+template <int TURNS>
 __device__ __forceinline__ void serve_blocks(const EncodeArgs &a, int32_t server, int lane) {
     int32_t shard = 0;
-    for (int32_t blk = server; blk < a.n_blocks; blk += a.n_servers) {
-        while (blk >= a.block_first[shard + 1]) ++shard;          // blocks are numbered chain by chain
+    for (int32_t at = server; at < a.n_blocks; at += a.n_servers) {
+        const WalkedBlock walked = nth_block<TURNS>(a, at, shard);
+        const int32_t blk = walked.blk;
+        shard = walked.shard;
         const int32_t blk_first = a.block_first[shard];
         const int32_t first_tile = a.chain_first[shard] + (blk - blk_first) * kBlock;
         const int32_t n = min(kBlock, a.chain_first[shard + 1] - first_tile);   // tiles in this block
@@ -733,6 +747,7 @@ __device__ __forceinline__ void tile_masks(const TileCtx &c, uint32_t t_off, uin
 // whole lines, which is what no shared lines at all would give: 3 % faster at 1 - 5 %, 7 % at 10 %.)
 // The price: a block's prefixes are ready kBatch tile-times later, so more entries wait in the ring,
 // which pays while the ring holds them (see launch_encode for who picks the order).  Uniform.
+template <int TURNS>
 __device__ __forceinline__ int32_t ticket_tile(const EncodeArgs &a, int32_t ticket, int32_t j) {
     ticket = __builtin_amdgcn_readfirstlane(ticket);    // uniform anyway: keeps the table look-ups scalar
     j = __builtin_amdgcn_readfirstlane(j);
@@ -743,16 +758,15 @@ __device__ __forceinline__ int32_t ticket_tile(const EncodeArgs &a, int32_t tick
         pos = slot & (kBlock - 1);
     }
     if (blk >= a.n_blocks) return -1;
-    int32_t shard = 0;
-    while (blk >= a.block_first[shard + 1]) ++shard;
-    const int32_t t = a.chain_first[shard] + (blk - a.block_first[shard]) * kBlock + pos;
-    return t < a.chain_first[shard + 1] ? t : -1;
+    const WalkedBlock b = nth_block<TURNS>(a, blk, 0);
+    const int32_t t = a.chain_first[b.shard] + (b.blk - a.block_first[b.shard]) * kBlock + pos;
+    return t < a.chain_first[b.shard + 1] ? t : -1;
 }
 
 // A worker's position in the tile order it is given by its tickets (uniform state).
 //
 // Waiting and tickets.  A worker may wait for the prefix of a parked tile X only while every tile
-// it holds a ticket for and has not published lies in a later block than X: then the earliest
+// it holds a ticket for and has not published lies in a block walked later than X's (see Turns): then the earliest
 // block that is not fully published never depends on a waiting worker, and all waits end.  Tickets
 // are taken in order, so the tiles of a worker's tickets lie in later and later groups, except
 // when two tickets in a row fall into the SAME group (few workers are taking tickets, e.g. while
@@ -795,11 +809,12 @@ __device__ __forceinline__ void walk_accept(const EncodeArgs &a, Walk &w, uint32
 
 // Advance to the next tile.  kWalkNeedTicket: the current ticket is used up and no further one
 // is at hand (ask the counter, then call again); kWalkDone: no tiles are left.
+template <int TURNS>
 __device__ __forceinline__ int walk_step(const EncodeArgs &a, Walk &w, int32_t *tile) {
     for (;;) {
         while (w.j + 1 < a.batch) {
             ++w.j;
-            const int32_t t = ticket_tile(a, w.ticket, w.j);
+            const int32_t t = ticket_tile<TURNS>(a, w.ticket, w.j);
             if (t >= 0) {
                 *tile = t;
                 return kWalkTile;
@@ -930,6 +945,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     constexpr int ARITH = PAYLOAD == 1;                // entries carry the old pattern beside them
     constexpr int FORMED = PAYLOAD == 2;               // entries are payloads from the start
     static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
+    constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);     // see nth_block
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
     __shared__ uint32_t s_ring[kRing];      // an entry: low 15 bits of its element's number (TileMeta::out_base) << 16 | new pattern
@@ -951,7 +967,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if ((int32_t)blockIdx.x < a.n_server_wgs) {
-        serve_blocks(a, (int32_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave), lane);
+        serve_blocks<TURNS>(a, (int32_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave), lane);
         return;
     }
 
@@ -1156,7 +1172,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     };
     int32_t tile = -1;
     for (;;) {
-        const int st = walk_step(a, walk, &tile);
+        const int st = walk_step<TURNS>(a, walk, &tile);
         if (st == kWalkTile) break;
         if (st == kWalkDone) return;
         settle_ticket();
@@ -1364,7 +1380,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         // ---- (d) the next tile's loads go out now and stay in flight during everything below ----
         int32_t next = -1;
         const int32_t ticket_before = walk.ticket;
-        int next_state = walk_step(a, walk, &next);     // kWalkNeedTicket: decided after the barrier
+        int next_state = walk_step<TURNS>(a, walk, &next);     // kWalkNeedTicket: decided after the barrier
         next_state = __builtin_amdgcn_readfirstlane(next_state);   // uniform anyway: scalar branches below
         next = __builtin_amdgcn_readfirstlane(next);
         bool nxt_redo = walk.redo;
@@ -1541,13 +1557,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 int32_t j_from = a.batch;               // first slot of tA to walk again
                 if (redo_cur)
                     for (int32_t j = 0; j < a.batch; ++j)
-                        if (ticket_tile(a, tA, j) == tile) j_from = j;
+                        if (ticket_tile<TURNS>(a, tA, j) == tile) j_from = j;
                 redo_cur = false;
                 // slot j_from itself is published (it is this iteration's tile); when tA is used up
                 // (j_from = kBatch) every slot of tB is still to be counted
 #pragma unroll 1
                 for (int32_t j = j_from < a.batch ? j_from + 1 : a.batch; j < j_end; ++j) {
-                    const int32_t t = j < a.batch ? ticket_tile(a, tA, j) : ticket_tile(a, tB, j - a.batch);
+                    const int32_t t = j < a.batch ? ticket_tile<TURNS>(a, tA, j) : ticket_tile<TURNS>(a, tB, j - a.batch);
                     if (t >= 0) publish_count(t);
                 }
                 __syncthreads();
@@ -1559,7 +1575,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 walk.redo = true;
                 walk.redo_through = pair ? tB : tA;
                 walk.j = j_from - 1;
-                next_state = walk_step(a, walk, &next);
+                next_state = walk_step<TURNS>(a, walk, &next);
                 late = true;
             }
             if (next_state != kWalkNeedTicket) break;
@@ -1567,7 +1583,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 settle_ticket();
                 if (walk.careful) continue;
             }
-            next_state = walk_step(a, walk, &next);
+            next_state = walk_step<TURNS>(a, walk, &next);
             late = true;
         }
         if (late) {
@@ -3046,6 +3062,13 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
                            new_is_f32);
 }
 
+// The refresh of bf16 weights does better with three workgroups on a CU than with the four that fit, but where it writes next to
+// nothing: fewer lines are on their way back among fewer reads (eight 7B-style layers, TP4, in turns, four and three: 0.1 %
+// 1459 / 1518 us, 0.5 % 1657 / 1690, 1 % 1773 / 1743, 5 % 2160 / 2107, 15 % 2430 / 2391; TP1 at 2 % 1921 / 1872).  Without
+// refresh that holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 / 1401) nor for a sender's share of a
+// 32B style (1385 / 1393).
+constexpr int32_t kRefreshFewerPpm = 9000;
+
 int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -3072,9 +3095,11 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
         }
     }
     const bool of_elements = arith && !new_is_f32 && !refresh && (ppm < 0 || ppm >= kElementsPpm || room_ppm >= kElementsPpm);
-    const int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
+    int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
     encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
+    if (refresh) a.turns = turns_of(a.block_first, a.tp);
+    if (refresh && !new_is_f32 && !arith && (ppm < 0 || ppm >= kRefreshFewerPpm)) resident -= resident / 4;
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are

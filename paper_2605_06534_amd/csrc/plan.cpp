@@ -25,6 +25,22 @@ void make_magic(uint32_t divisor, uint32_t *magic, uint32_t *shift) {
     *shift = l - 1;     // after taking the high 32 bits of the product
 }
 
+// The chains that follow each other and have at least half as many blocks as the longest take turns: the shards of a model
+// all do; a sender that holds part of one shard has one long chain, and short ones for what it sends to every shard.
+Turns turns_of(const int32_t *block_first, int32_t n_chains) {
+    const auto blocks = [&](int32_t d) { return block_first[d + 1] - block_first[d]; };
+    int32_t longest = 0;
+    for (int32_t d = 0; d < n_chains; ++d) longest = blocks(d) > longest ? blocks(d) : longest;
+    const auto is_long = [&](int32_t d) { return blocks(d) >= (longest + 1) / 2; };
+    Turns t = {0, 0, longest, 0, 0};
+    while (t.chain < n_chains && !is_long(t.chain)) ++t.chain;
+    for (; t.chain + t.chains < n_chains && is_long(t.chain + t.chains); ++t.chains)
+        t.each = blocks(t.chain + t.chains) < t.each ? blocks(t.chain + t.chains) : t.each;
+    if (t.chains < 2) t.chains = t.each = 0;
+    else make_magic((uint32_t)t.chains, &t.magic, &t.shift);
+    return t;
+}
+
 static bool magic_ok(uint32_t divisor, uint32_t magic, uint32_t shift, uint32_t limit) {
     // exhaustive over the quotient boundaries inside [0, limit)
     for (uint64_t q = 0; q * divisor < limit; ++q) {

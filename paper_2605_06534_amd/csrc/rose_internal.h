@@ -74,6 +74,53 @@ struct Tiles {
     int32_t block_first[ROSE_MAX_TP + 1] = {0};
 };
 
+#ifdef __HIP__
+#define ROSE_BOTH __host__ __device__
+#else
+#define ROSE_BOTH
+#endif
+
+// host side of the magic-number division used for strided pieces
+void make_magic(uint32_t divisor, uint32_t *magic, uint32_t *shift);
+ROSE_BOTH inline uint32_t magic_div(uint32_t k, uint32_t magic, uint32_t shift) {
+    return (uint32_t)(((uint64_t)k * magic) >> 32) >> shift;
+}
+
+// Blocks are numbered chain by chain, and walked in that order, or (where a launch walks in turns) those of the chains
+// chain .. chain + chains - 1 in turn, a block of each, `each` times; what the longer ones have besides comes behind.  The
+// blocks of one chain are walked in their order in any case, which is all that the waits for prefixes rest on.
+struct Turns {
+    int32_t chain, chains, each;
+    uint32_t magic, shift;                  // k / chains
+};
+Turns turns_of(const int32_t *block_first, int32_t n_chains);
+struct WalkedBlock {
+    int32_t shard, blk;
+};
+// the n-th block that is walked in turns
+ROSE_BOTH inline WalkedBlock walked_block(const Turns &t, const int32_t *block_first, int32_t n) {
+    WalkedBlock b;
+    int32_t x = n - block_first[t.chain];
+    const int32_t in_turn = t.chains * t.each;
+    if (x >= 0 && x < in_turn) {
+        const int32_t q = (int32_t)magic_div((uint32_t)x, t.magic, t.shift);
+        b.shard = t.chain + (x - q * t.chains);
+        b.blk = block_first[b.shard] + q;
+        return b;
+    }
+    if (x >= in_turn && n < block_first[t.chain + t.chains]) {
+        b.shard = t.chain;
+        x -= in_turn;
+        for (int32_t rest; x >= (rest = block_first[b.shard + 1] - block_first[b.shard] - t.each); ++b.shard) x -= rest;
+        b.blk = block_first[b.shard] + t.each + x;
+        return b;
+    }
+    b.shard = 0;
+    b.blk = n;
+    while (n >= block_first[b.shard + 1]) ++b.shard;
+    return b;
+}
+
 struct BucketDev {
     int32_t *idx;
     uint16_t *val;
@@ -103,6 +150,7 @@ struct EncodeArgs {
     int32_t batch;                          // tiles per ticket
     uint32_t window_open;                   // clock ticks of a period in which bucket stores go out (0: always)
     uint32_t window_mask;                   // ticks of a period (a power of two) less one
+    Turns turns;                            // in which a refresh walks its blocks
     unsigned int *ticket;                   // workspace header: the ticket counter
     uint32_t *slots;                        // one slot of slot_size entries per tile (see stage_tiles_kernel)
     int32_t slot_size;                      // 0: the workspace has no room for slots
@@ -150,12 +198,6 @@ struct CopyArgs {
     int32_t tile_begin;
     int32_t n_tiles;
 };
-
-// host side of the magic-number division used for strided pieces
-void make_magic(uint32_t divisor, uint32_t *magic, uint32_t *shift);
-inline uint32_t magic_div(uint32_t k, uint32_t magic, uint32_t shift) {
-    return (uint32_t)(((uint64_t)k * magic) >> 32) >> shift;
-}
 
 constexpr int32_t kSpreadFromPpm = 75000;  // changed elements per million from which tiles are taken in the spread order
 
