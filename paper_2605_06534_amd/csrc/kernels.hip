@@ -337,6 +337,7 @@ constexpr u64 kValueMask = (1ull << kStatusShift) - 1;
 #ifndef ROSE_WRITE_OPEN_WIDE
 #define ROSE_WRITE_OPEN_WIDE 2048     // 20 us
 #endif
+constexpr uint32_t kPollLead = 800;   // ticks before a window from which on prefixes are asked for
 #ifndef ROSE_COUNT_AHEAD
 #define ROSE_COUNT_AHEAD 1    // count the rest of a ticket's tiles before waiting for room (dense inputs)
 #endif
@@ -514,7 +515,7 @@ __device__ __forceinline__ void serve_blocks(const EncodeArgs &a, int32_t server
 // the popcounts, wave totals through LDS, (5) publish the tile's count, copy out parked tiles, (6) park the tile's
 // entries, compacted, in an LDS ring and go on (the order of the memory operations matters: see
 // the comment in encode_body).  The wait for a tile's prefix is deferred: parked tiles are polled
-// one lane per tile, every iteration, without waiting; only when the ring (kRing entries) or the
+// one lane per tile, in iterations near a window, without waiting; only when the ring (kRing entries) or the
 // queue of parked tiles (kQueue) is full, and at the end, does a workgroup wait.  This keeps
 // loads in flight while counts travel between workgroups.  The ring holds any tile, all of whose elements may have changed.
 // Inside a tile wave w covers a contiguous part and walks it in kIters steps of 512 elements,
@@ -1348,6 +1349,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         ticket_out = false;
         if (wave == 0 && lane < n_polled && !has_prefix(wq_w)) wq_w = polled;
         move_lanes();
+        bool poll = true;
         if (wave == 0) {
             const u64 unknown = __ballot(lane < q_len && !has_prefix(wq_w));
             int n_ready = unknown ? __ffsll((long long)unknown) - 1 : q_len;
@@ -1364,13 +1366,18 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 const uint32_t now = (uint32_t)__builtin_amdgcn_s_memrealtime();
                 const bool open = (now & a.window_mask) < a.window_open;
                 if (!open && q_len <= kQueue * 3 / 4) n_ready = 0;
+                // Prefixes are asked for from 8 us before a window on: what has none by then has had time to get one, and asked
+                // for in every iteration they cost the reads (two 32B-style layers of fp32 masters, 1.6 %: 2547 us, this way 2527;
+                // 1.9 G weights hardly changed, bf16 1191 and 1187, fp32 masters 1841 and 1829; asked for from 16 us before,
+                // the same and at 5 % 0.5 % more).
+                poll = open || ((now + kPollLead) & a.window_mask) < a.window_open || q_len > kQueue / 2;
             }
             if (lane < n_ready) s_excl[parity][lane] = wq_w & kValueMask;
             if (lane == 0) s_nready[parity] = n_ready;
             // ---- (c) poll: one lane per parked tile that has no prefix yet ----
-            if (lane < q_len && !has_prefix(wq_w)) polled = desc_load(a.tile_desc + wq_tile);
+            if (poll && lane < q_len && !has_prefix(wq_w)) polled = desc_load(a.tile_desc + wq_tile);
         }
-        n_polled = q_len;
+        n_polled = poll ? q_len : 0;                   // (counts in wave 0 only)
         // ask for the next ticket as soon as the one fetched ahead has been taken into use
         if (!walk.have_next && !accept_now && !walk.exhausted && !walk.redo) {
             if (threadIdx.x == 0) ticket_request<WIDE>(a.ticket);
