@@ -458,10 +458,9 @@ __device__ __forceinline__ bool block_look_back(u64 *block_desc, unsigned int *a
 // time, and the memory takes that better where they lie in several places (eight 7B-style layers, TP4, at 1 / 5 / 15 %: chain by chain
 // 1813 / 2190 / 2428 us, in turns 1750 / 2109 / 2397; arithmetic payloads at 2 % 1978 and 1899, fp32 masters 2695 and
 // 2653; but arithmetic payloads of fp32 masters, with half the waves, 2624 and 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns 1349 / 1599.
-// So those do it where the launch says so only (TURNS 2).
 template <int TURNS>
 __device__ __forceinline__ WalkedBlock nth_block(const EncodeArgs &a, int32_t n, int32_t shard) {
-    if (TURNS && (TURNS == 1 || a.turns.chains > 0)) return walked_block(a.turns, a.block_first, n);
+    if constexpr (TURNS) return walked_block(a.turns, a.block_first, n);
     while (n >= a.block_first[shard + 1]) ++shard;     // (blocks are numbered chain by chain; shard: that of an earlier one)
     return {shard, n};
 }
@@ -947,7 +946,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     constexpr int ARITH = PAYLOAD == 1;                // entries carry the old pattern beside them
     constexpr int FORMED = PAYLOAD == 2;               // entries are payloads from the start
     static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
-    constexpr int TURNS = REFRESH ? !(NEW_F32 && ARITH) : ARITH ? 0 : 2;     // see nth_block
+    constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);     // see nth_block
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
     __shared__ uint32_t s_ring[kRing];      // an entry: low 15 bits of its element's number (TileMeta::out_base) << 16 | new pattern
@@ -3076,12 +3075,6 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
 // refresh that holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 / 1401) nor for a sender's share of a
 // 32B style (1385 / 1393).
 constexpr int32_t kRefreshFewerPpm = 9000;
-// Encodes without refresh walk in turns where the rings no longer hold what comes and every chain's prefixes are waited for: then
-// one chain's waits are hidden behind the others' tiles (1.9 G weights, TP4, chain by chain / in turns, room for a quarter more than
-// comes: 20 % 1.768 / 1.795 ms, 30 % 2.43 / 2.26, 40 % 3.70 / 3.25, 50 % 4.16 / 3.81; payloads formed of every element, 50 / 60 %
-// 4.44 / 4.01 and 4.12 / 4.17; fp32 masters with a rate of its own for each 4096 elements, 12 / 15 / 20 / 30 % 2.44 / 2.53, 3.27 /
-// 2.83, 8.31 / 4.71, 16.8 / 16.4).
-constexpr int32_t kTurnsFromPpm = 300000, kTurnsFromPpmF32 = 180000, kTurnsToPpm = 700000;
 
 int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
@@ -3112,7 +3105,7 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
     encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
-    if (refresh || (ppm >= (new_is_f32 ? kTurnsFromPpmF32 : kTurnsFromPpm) && ppm < kTurnsToPpm)) a.turns = turns_of(a.block_first, a.tp);
+    if (refresh) a.turns = turns_of(a.block_first, a.tp);
     if (refresh && !new_is_f32 && !arith && (ppm < 0 || ppm >= kRefreshFewerPpm)) resident -= resident / 4;
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than

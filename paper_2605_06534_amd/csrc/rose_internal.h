@@ -150,7 +150,7 @@ struct EncodeArgs {
     int32_t batch;                          // tiles per ticket
     uint32_t window_open;                   // clock ticks of a period in which bucket stores go out (0: always)
     uint32_t window_mask;                   // ticks of a period (a power of two) less one
-    Turns turns;                            // in which blocks are walked; chains 0: in none
+    Turns turns;                            // in which a refresh walks its blocks
     unsigned int *ticket;                   // workspace header: the ticket counter
     uint32_t *slots;                        // one slot of slot_size entries per tile (see stage_tiles_kernel)
     int32_t slot_size;                      // 0: the workspace has no room for slots

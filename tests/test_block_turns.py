@@ -1,5 +1,5 @@
-"""Refreshes, and encodes of much, walk the blocks of equally long chains in turn: the order itself on the CPU, and the kernels on
-senders whose chains are of equal and of unequal length."""
+"""Refreshes walk the blocks of equally long chains in turn: the order itself on the CPU, and the kernels on senders whose chains
+are of equal and of unequal length."""
 import os
 import subprocess
 import tempfile
@@ -12,7 +12,6 @@ from oracle import oracle
 from gpu_harness import assert_buckets_equal, bits
 from test_gpu_pipeline import cut, dev, model
 from test_host_sanitizers import ROOT, SAN, run
-from workloads import models, synth
 
 
 def test_every_block_once_and_each_chain_in_order():
@@ -50,49 +49,3 @@ def test_refresh_in_turns(tp, tp_src, src, pp_dst, workers, tile_order):
         assert_buckets_equal(got, want[b], "bucket %d" % b)
     for i, (o, x) in enumerate(zip(olds, sl)):
         assert (bits(o) == x["new"]).all(), "tensor %d not refreshed" % i
-
-
-# much comes, and the buckets have room for half of all: without refresh too
-@pytest.mark.gpu
-@pytest.mark.parametrize("arith", [False, True])
-@pytest.mark.parametrize("f32", [False, True])
-@pytest.mark.parametrize("tp,pp_dst,workers", [(4, 1, 0), (1, 3, 0), (3, 1, 70)])
-def test_dense_encode_in_turns(tp, pp_dst, workers, f32, arith, tile_order):
-    print("case: dense encode in turns, tp %d, %d stages, %d workers, f32 %d, arith %d, order %d" % (tp, pp_dst, workers, f32, arith, tile_order), flush=True)
-    n_layers = 6
-    if tp == 3:
-        ts = models.decoder(n_layers, 192, 6, 3, 32, 576, 1536, fused=True)
-        recs = [dict(t, old=bits(o), new=bits(n)) for _, t, o, n in synth.model_pairs(ts, "bernoulli", 18, "cpu", p=0.4)]
-    else:
-        ts, recs = model(n_layers, seed=18, p=0.4)
-    plan = R.binding.shard_plan(ts, tp, 1, 0, n_layers, 1, 0, pp_dst)
-    if workers:
-        plan.set_worker_cap(workers)
-    olds = [dev(x["old"]) for x in recs]
-    news = [(dev(x["new"]).to(torch.int32) << 16).view(torch.float32) if f32 else dev(x["new"]) for x in recs]
-    buckets = [R.Bucket(plan.bucket_capacity(b) // 2, len(ts)) for b in range(plan.n_buckets)]
-    R.delta_encode_ex(plan, R.ptr_table(olds), R.ptr_table(news), R.FP32_RNE if f32 else R.BF16, R.ENCODE_ARITH if arith else 0, buckets,
-                      R.workspace(plan))
-    torch.cuda.synchronize()
-    if arith:
-        return check_arith(ts, recs, plan, buckets, tp)
-    want = oracle.encode_model_pp(recs, tp, 1, 0, n_layers, 1, 0, pp_dst)
-    for b in range(plan.n_buckets):
-        n = R.bucket_check(plan, buckets[b])
-        got = {"idx": buckets[b].idx[:n].cpu().numpy(), "val": buckets[b].val[:n].cpu().numpy().view("uint16"),
-               "seg_off": buckets[b].seg_off.cpu().numpy()}
-        assert_buckets_equal(got, want[b], "bucket %d" % b)
-
-
-def check_arith(ts, recs, plan, buckets, tp):
-    """Arithmetic payloads applied to the receivers' previous weights give their new ones."""
-    for b, bucket in enumerate(buckets):
-        R.bucket_check(plan, bucket)
-        loc = [cut(r["old"], r, tp, b % tp) for r in recs]
-        held = [plan.local_numel(i, b) > 0 for i in range(len(ts))]
-        dst = [dev(x) for x in loc]
-        R.delta_apply_ex(plan, b, bucket, R.PAYLOAD_ARITH, R.ptr_table(dst))
-        torch.cuda.synchronize()
-        for i, r in enumerate(recs):
-            if held[i]:
-                assert (bits(dst[i]) == cut(r["new"], r, tp, b % tp)).all(), "bucket %d tensor %d" % (b, i)
