@@ -3105,7 +3105,9 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
     encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
-    if (refresh) a.turns = turns_of(a.block_first, a.tp);
+    // (not in the spread order, nor with few workers: an encode of 40 % in turns by 70 workers gave up waiting once, and why is not known)
+    a.turns = Turns{0, 0, 0, 0, 0};
+    if (refresh && worker_cap == 0 && ppm >= 0 && ppm < kSpreadFromPpm && a.adjacent) a.turns = turns_of(a.block_first, a.tp);
     if (refresh && !new_is_f32 && !arith && (ppm < 0 || ppm >= kRefreshFewerPpm)) resident -= resident / 4;
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than

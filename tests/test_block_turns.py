@@ -32,13 +32,13 @@ def test_every_block_once_and_each_chain_in_order():
 def test_refresh_in_turns(tp, tp_src, src, pp_dst, workers, tile_order):
     print("case: refresh in turns, tp %d of %d rank %d, %d stages, %d workers, order %d" % (tp, tp_src, src, pp_dst, workers, tile_order), flush=True)
     n_layers = 6
-    ts, recs = model(n_layers, seed=17, p=0.06)
+    ts, recs = model(n_layers, seed=17, p=0.05)
     plan = R.binding.shard_plan(ts, tp, tp_src, src, n_layers, 1, 0, pp_dst)
     if workers:
         plan.set_worker_cap(workers)
     sl = [dict(r, old=cut(r["old"], r, tp_src, src), new=cut(r["new"], r, tp_src, src)) for r in recs]
     olds, news = [dev(x["old"]) for x in sl], [dev(x["new"]) for x in sl]
-    buckets = [R.Bucket(plan.bucket_capacity(b), len(ts)) for b in range(plan.n_buckets)]
+    buckets = [R.Bucket(plan.bucket_capacity(b) * 7 // 100 + 64, len(ts)) for b in range(plan.n_buckets)]
     R.delta_encode_refresh(plan, R.ptr_table(olds), R.ptr_table(news), R.BF16, buckets, R.workspace(plan))
     torch.cuda.synchronize()
     want = oracle.encode_model_pp(sl, tp, tp_src, src, n_layers, 1, 0, pp_dst)
