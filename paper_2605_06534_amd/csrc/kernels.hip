@@ -454,17 +454,6 @@ __device__ __forceinline__ bool block_look_back(u64 *block_desc, unsigned int *a
     return true;
 }
 
-// The n-th block in the order in which a launch walks them, see Turns.  A refresh writes lines of what it reads all the
-// time, and the memory takes that better where they lie in several places (eight 7B-style layers, TP4, at 1 / 5 / 15 %: chain by chain
-// 1813 / 2190 / 2428 us, in turns 1750 / 2109 / 2397; arithmetic payloads at 2 % 1978 and 1899, fp32 masters 2695 and
-// 2653; but arithmetic payloads of fp32 masters, with half the waves, 2624 and 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns 1349 / 1599.
-template <int TURNS>
-__device__ __forceinline__ WalkedBlock nth_block(const EncodeArgs &a, int32_t n, int32_t shard) {
-    if constexpr (TURNS) return walked_block(a.turns, a.block_first, n);
-    while (n >= a.block_first[shard + 1]) ++shard;     // (blocks are numbered chain by chain; shard: that of an earlier one)
-    return {shard, n};
-}
-
 // A serving wave: blocks server, server + n_servers, ... of those that are walked, in their order.
 template <int TURNS>
 __device__ __forceinline__ void serve_blocks(const EncodeArgs &a, int32_t server, int lane) {
@@ -734,100 +723,19 @@ __device__ __forceinline__ void tile_masks(const TileCtx &c, uint32_t t_off, uin
     }
 }
 
-// The j-th tile of a ticket, or -1 if there is none.  A ticket stands for a.batch tiles (kBatch below; the
-// launcher picks it).  A group of kBatch consecutive blocks has
-// kBatch * kBlock tile positions ("slots", block after block) and kBlock tickets.  Two orders:
-// spread (a.adjacent = 0): ticket n of the group stands for position n of each of the group's blocks, so
-// that a block's 64 tiles are walked by 64 workers at once and its prefixes are ready one tile-time
-// later; neighbours (a.adjacent = 1): ticket n stands for the kBatch NEIGHBOURING slots
-// n * kBatch .. n * kBatch + kBatch - 1.  Neighbouring slots are
-// neighbouring tiles of one chain (except where a chain ends inside the group: a chain's short last
-// block has no tile for its last positions), so the entries of a ticket's tiles follow each other in
-// the bucket and are written as one run: only the two ends of a ticket's run share 64-byte lines of
-// the bucket with another workgroup's.  (Measured on the 7B-style workload with every run padded to
-// whole lines, which is what no shared lines at all would give: 3 % faster at 1 - 5 %, 7 % at 10 %.)
-// The price: a block's prefixes are ready kBatch tile-times later, so more entries wait in the ring,
-// which pays while the ring holds them (see launch_encode for who picks the order).  Uniform.
+// (uniform anyway: said here, the table look-ups stay scalar)
 template <int TURNS>
 __device__ __forceinline__ int32_t ticket_tile(const EncodeArgs &a, int32_t ticket, int32_t j) {
-    ticket = __builtin_amdgcn_readfirstlane(ticket);    // uniform anyway: keeps the table look-ups scalar
-    j = __builtin_amdgcn_readfirstlane(j);
-    int32_t blk = (ticket / kBlock) * a.batch + j, pos = ticket & (kBlock - 1);
-    if (a.adjacent) {
-        const int32_t slot = (ticket & (kBlock - 1)) * a.batch + j;
-        blk = (ticket / kBlock) * a.batch + slot / kBlock;
-        pos = slot & (kBlock - 1);
-    }
-    if (blk >= a.n_blocks) return -1;
-    const WalkedBlock b = nth_block<TURNS>(a, blk, 0);
-    const int32_t t = a.chain_first[b.shard] + (b.blk - a.block_first[b.shard]) * kBlock + pos;
-    return t < a.chain_first[b.shard + 1] ? t : -1;
+    return tile_of_ticket<TURNS>(a, __builtin_amdgcn_readfirstlane(ticket), __builtin_amdgcn_readfirstlane(j));
 }
-
-// A worker's position in the tile order it is given by its tickets (uniform state).
-//
-// Waiting and tickets.  A worker may wait for the prefix of a parked tile X only while every tile
-// it holds a ticket for and has not published lies in a block walked later than X's (see Turns): then the earliest
-// block that is not fully published never depends on a waiting worker, and all waits end.  Tickets
-// are taken in order, so the tiles of a worker's tickets lie in later and later groups, except
-// when two tickets in a row fall into the SAME group (few workers are taking tickets, e.g. while
-// most of them wait).  Such a pair is handled with care: from the moment the second ticket is
-// accepted nothing waits until the counts of all tiles of both tickets are published by a
-// count-only pass; then those tiles are walked again ("redo", without publishing) in the normal
-// way.  While redoing, no further ticket is asked for.
-// The same machinery serves tiles so dense that the ring does not hold a ticket's worth of them: a
-// worker that would have to wait for room with fewer tiles parked than a ticket has, and with tiles
-// of the current ticket still uncounted, counts those first and walks the ticket again from the
-// current tile on.  (Waiting there is allowed by the rule above, but every later group of workers
-// would wait for those counts in turn, and the groups would run one after the other.)
-struct Walk {
-    int32_t ticket, j;          // ticket in use (-1: none yet) and its batch slot
-    int32_t next_ticket;        // ticket fetched ahead of time
-    int32_t redo_through;       // last ticket of a redo
-    bool have_next;
-    bool exhausted;             // the counter has run out
-    bool careful;               // a same-group ticket was accepted; its counts are not published yet
-    bool redo;                  // tiles up to the end of ticket redo_through are published already
-};
-enum : int { kWalkTile = 0, kWalkNeedTicket = 1, kWalkDone = 2 };
-
-// take in the counter's answer n
-__device__ __forceinline__ void walk_accept(const EncodeArgs &a, Walk &w, uint32_t n) {
-    if (n >= (uint32_t)a.n_tickets) {
-        w.exhausted = true;
-    } else if ((int32_t)n <= w.ticket) {
-        // One counter hands the tickets out in order, so a worker's tickets increase.  A value that
-        // does not is not a ticket (the register it arrives in is only reserved by asking the
-        // compiler, see ticket_request): walk no further and mark the launch as failed.
-        __hip_atomic_store(a.abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        w.exhausted = true;
-    } else {
-        w.next_ticket = (int32_t)n;
-        w.have_next = true;
-        if (w.ticket >= 0 && (int32_t)n / kBlock == w.ticket / kBlock) w.careful = true;
-    }
-}
-
-// Advance to the next tile.  kWalkNeedTicket: the current ticket is used up and no further one
-// is at hand (ask the counter, then call again); kWalkDone: no tiles are left.
 template <int TURNS>
 __device__ __forceinline__ int walk_step(const EncodeArgs &a, Walk &w, int32_t *tile) {
-    for (;;) {
-        while (w.j + 1 < a.batch) {
-            ++w.j;
-            const int32_t t = ticket_tile<TURNS>(a, w.ticket, w.j);
-            if (t >= 0) {
-                *tile = t;
-                return kWalkTile;
-            }
-        }
-        w.j = a.batch;
-        if (w.redo && w.ticket == w.redo_through) w.redo = false;
-        if (!w.have_next) return w.exhausted ? kWalkDone : kWalkNeedTicket;
-        w.ticket = w.next_ticket;
-        w.have_next = false;
-        w.j = -1;
-    }
+    return walk_step(a.batch, w, tile, [&](int32_t ticket, int32_t j) { return ticket_tile<TURNS>(a, ticket, j); });
+}
+// A value that is no ticket marks the launch as failed: the register it arrives in is only reserved by asking the compiler, see
+// ticket_request.
+__device__ __forceinline__ void walk_accept(const EncodeArgs &a, Walk &w, uint32_t n) {
+    if (!walk_accept(a.n_tickets, w, n)) __hip_atomic_store(a.abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Exclusive rank of each of this lane's vectors inside the wave's span; returns the wave's total.  The
@@ -946,7 +854,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     constexpr int ARITH = PAYLOAD == 1;                // entries carry the old pattern beside them
     constexpr int FORMED = PAYLOAD == 2;               // entries are payloads from the start
     static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
-    constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);     // see nth_block
+    // Blocks in turns: a refresh writes lines of what it reads all the time, and the memory takes that better where they lie in several
+    // places (eight 7B-style layers, TP4, at 1 / 5 / 15 %: chain by chain 1813 / 2190 / 2428 us, in turns 1750 / 2109 / 2397; arithmetic
+    // payloads at 2 % 1978 and 1899, fp32 masters 2695 and 2653; but arithmetic payloads of fp32 masters, with half the waves, 2624 and
+    // 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns
+    // 1349 / 1599.
+    constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
     __shared__ uint32_t s_ring[kRing];      // an entry: low 15 bits of its element's number (TileMeta::out_base) << 16 | new pattern
@@ -1418,7 +1331,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
 
         // copy out what was announced, while the next tile's loads are on their way
         const bool no_slot = q_len == kQueue, no_place = ring_used + tile_total > (uint32_t)kRing, crowded = no_slot || no_place;
-        const bool few = q_len < a.batch;
+        const bool ahead = ROSE_COUNT_AHEAD && !a.adjacent && no_place && q_len < a.batch;      // see below
         if (n_announced > 0) {
             const uint32_t freed = copy_out(n_announced, s_excl[parity ^ 1], true);
             pop(n_announced, freed);
@@ -1429,10 +1342,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             }
         }
 
-        // Room to park?  Making room may wait, and nothing may wait while a ticket is on its way
-        // (it could be of the current ticket's group): take it in first.
-        if (ticket_out && !walk.careful && (q_len == kQueue || ring_used + tile_total > (uint32_t)kRing))
-            settle_ticket();
+        // Room to park?  Making room may wait, and nothing may wait, or be walked again, while a ticket is on its way.
+        if (ticket_first(walk, ticket_out, q_len == kQueue || ring_used + tile_total > (uint32_t)kRing, ahead)) settle_ticket();
         // A same-group ticket has just been accepted: nothing may wait now.  This tile is not
         // parked; it is walked again after the count-only pass at the end of the iteration.
         // Tiles so dense that the ring does not hold a ticket's worth (fewer tiles are parked than a
@@ -1455,7 +1366,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 if (q_len > 0) drain(kDrainReady);
                 dense = q_len == kQueue || ring_used + tile_total > (uint32_t)kRing;
             }
-        } else if (__builtin_expect(no_place && few, 0)) {
+        } else if (__builtin_expect(ahead, 0)) {
             // (also where the announced tiles have just made room: their neighbours will not have left in time for this
             // ticket's next tiles, whose wait would then hold up all others.  40 / 50 %, eight 7B-style layers: 2.94 / 3.24 ms,
             // with a look at the room that is left 3.59 / 4.90)
@@ -3105,7 +3016,9 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
     encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
-    // (not in the spread order, nor with few workers: an encode of 40 % in turns by 70 workers gave up waiting once, and why is not known)
+    // In turns: refreshes of little, by all workers.  (Of more, they were faster in turns as well: at 15 % 2428 and 2397 us, fp32 masters
+    // at 20 % 6.6 and 4.5 ms.  They have been walked chain by chain since an encode of 40 % in turns by 70 workers gave up waiting; that
+    // was no fault of the turns but a ticket on its way while tiles were counted ahead, see ticket_first.)
     a.turns = Turns{0, 0, 0, 0, 0};
     if (refresh && worker_cap == 0 && ppm >= 0 && ppm < kSpreadFromPpm && a.adjacent) a.turns = turns_of(a.block_first, a.tp);
     if (refresh && !new_is_f32 && !arith && (ppm < 0 || ppm >= kRefreshFewerPpm)) resident -= resident / 4;

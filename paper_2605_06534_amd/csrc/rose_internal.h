@@ -79,6 +79,7 @@ struct Tiles {
 #else
 #define ROSE_BOTH
 #endif
+#define ROSE_INLINE ROSE_BOTH inline __attribute__((always_inline))
 
 // host side of the magic-number division used for strided pieces
 void make_magic(uint32_t divisor, uint32_t *magic, uint32_t *shift);
@@ -160,7 +161,6 @@ struct EncodeArgs {
 // and hands every tile of the block its prefix.
 constexpr int kBlock = 64;
 
-// workspace layout (bytes): header, tile descriptors, block descriptors
 // A ticket hands a worker a batch of tiles: the tiles at one position of as many consecutive blocks
 // (a "group" of blocks has kBlock tickets).  All tickets come from one counter, in order.  The
 // counter serves one ticket in about 14 ns, whoever asks: with 3 tiles (96 KB of input) per ticket it
@@ -173,6 +173,118 @@ constexpr int kBlock = 64;
 #endif
 constexpr int kBatch = ROSE_BATCH, kBatchTimed = ROSE_BATCH_TIMED;
 
+// The n-th block in the order in which a launch walks them.
+template <int TURNS>
+ROSE_INLINE WalkedBlock nth_block(const EncodeArgs &a, int32_t n, int32_t shard) {
+    if constexpr (TURNS) return walked_block(a.turns, a.block_first, n);
+    while (n >= a.block_first[shard + 1]) ++shard;     // (blocks are numbered chain by chain; shard: that of an earlier one)
+    return {shard, n};
+}
+
+// The j-th tile of a ticket, or -1 if there is none.  A ticket stands for a.batch tiles (kBatch below; the
+// launcher picks it).  A group of kBatch consecutive blocks has
+// kBatch * kBlock tile positions ("slots", block after block) and kBlock tickets.  Two orders:
+// spread (a.adjacent = 0): ticket n of the group stands for position n of each of the group's blocks, so
+// that a block's 64 tiles are walked by 64 workers at once and its prefixes are ready one tile-time
+// later; neighbours (a.adjacent = 1): ticket n stands for the kBatch NEIGHBOURING slots
+// n * kBatch .. n * kBatch + kBatch - 1.  Neighbouring slots are
+// neighbouring tiles of one chain (except where a chain ends inside the group: a chain's short last
+// block has no tile for its last positions), so the entries of a ticket's tiles follow each other in
+// the bucket and are written as one run: only the two ends of a ticket's run share 64-byte lines of
+// the bucket with another workgroup's.  (Measured on the 7B-style workload with every run padded to
+// whole lines, which is what no shared lines at all would give: 3 % faster at 1 - 5 %, 7 % at 10 %.)
+// The price: a block's prefixes are ready kBatch tile-times later, so more entries wait in the ring,
+// which pays while the ring holds them (see launch_encode for who picks the order).  Uniform.
+template <int TURNS>
+ROSE_INLINE int32_t tile_of_ticket(const EncodeArgs &a, int32_t ticket, int32_t j) {
+    int32_t blk = (ticket / kBlock) * a.batch + j, pos = ticket & (kBlock - 1);
+    if (a.adjacent) {
+        const int32_t slot = (ticket & (kBlock - 1)) * a.batch + j;
+        blk = (ticket / kBlock) * a.batch + slot / kBlock;
+        pos = slot & (kBlock - 1);
+    }
+    if (blk >= a.n_blocks) return -1;
+    const WalkedBlock b = nth_block<TURNS>(a, blk, 0);
+    const int32_t t = a.chain_first[b.shard] + (b.blk - a.block_first[b.shard]) * kBlock + pos;
+    return t < a.chain_first[b.shard + 1] ? t : -1;
+}
+
+// A worker's position in the tile order it is given by its tickets (uniform state).
+//
+// Waiting and tickets.  A worker may wait for the prefix of a parked tile X only while every tile
+// it holds a ticket for and has not published lies in a block walked later than X's (see Turns): then the earliest
+// block that is not fully published never depends on a waiting worker, and all waits end.  Tickets
+// are taken in order, so the tiles of a worker's tickets lie in later and later groups, except
+// when two tickets in a row fall into the SAME group (few workers are taking tickets, e.g. while
+// most of them wait).  Such a pair is handled with care: from the moment the second ticket is
+// accepted nothing waits until the counts of all tiles of both tickets are published by a
+// count-only pass; then those tiles are walked again ("redo", without publishing) in the normal
+// way.  While redoing, no further ticket is asked for, nor is one on its way when a redo begins (see ticket_first): one of
+// the same group, accepted in the middle of a redo, would have tiles counted that are published already, and a count stored
+// over a prefix is a prefix that nobody stores again.
+// The same machinery serves tiles so dense that the ring does not hold a ticket's worth of them: a
+// worker that would have to wait for room with fewer tiles parked than a ticket has, and with tiles
+// of the current ticket still uncounted, counts those first and walks the ticket again from the
+// current tile on.  (Waiting there is allowed by the rule above, but every later group of workers
+// would wait for those counts in turn, and the groups would run one after the other.)
+struct Walk {
+    int32_t ticket, j;          // ticket in use (-1: none yet) and its batch slot
+    int32_t next_ticket;        // ticket fetched ahead of time
+    int32_t redo_through;       // last ticket of a redo
+    bool have_next;
+    bool exhausted;             // the counter has run out
+    bool careful;               // a same-group ticket was accepted; its counts are not published yet
+    bool redo;                  // tiles up to the end of ticket redo_through are published already
+};
+enum : int { kWalkTile = 0, kWalkNeedTicket = 1, kWalkDone = 2 };
+
+// Whether a ticket that is on its way is taken in before the tile at hand is dealt with: where the worker may come to wait
+// for room (full), since the ticket could be of the current one's group, and where it will count the rest of the current ticket
+// and walk it again (ahead).
+ROSE_INLINE bool ticket_first(const Walk &w, bool ticket_out, bool full, bool ahead) {
+    return ticket_out && !w.careful && (full || ahead);
+}
+
+// take in the counter's answer n; false if it is none
+ROSE_INLINE bool walk_accept(int32_t n_tickets, Walk &w, uint32_t n) {
+    if (n >= (uint32_t)n_tickets) {
+        w.exhausted = true;
+    } else if ((int32_t)n <= w.ticket) {
+        // One counter hands the tickets out in order, so a worker's tickets increase.  A value that
+        // does not is not a ticket: walk no further.
+        w.exhausted = true;
+        return false;
+    } else {
+        w.next_ticket = (int32_t)n;
+        w.have_next = true;
+        if (w.ticket >= 0 && (int32_t)n / kBlock == w.ticket / kBlock) w.careful = true;
+    }
+    return true;
+}
+
+// Advance to the next tile; tile_of(ticket, j): see tile_of_ticket.  kWalkNeedTicket: the current ticket is used up and no
+// further one is at hand (ask the counter, then call again); kWalkDone: no tiles are left.
+template <typename TILE_OF>
+ROSE_INLINE int walk_step(int32_t batch, Walk &w, int32_t *tile, const TILE_OF &tile_of) {
+    for (;;) {
+        while (w.j + 1 < batch) {
+            ++w.j;
+            const int32_t t = tile_of(w.ticket, w.j);
+            if (t >= 0) {
+                *tile = t;
+                return kWalkTile;
+            }
+        }
+        w.j = batch;
+        if (w.redo && w.ticket == w.redo_through) w.redo = false;
+        if (!w.have_next) return w.exhausted ? kWalkDone : kWalkNeedTicket;
+        w.ticket = w.next_ticket;
+        w.have_next = false;
+        w.j = -1;
+    }
+}
+
+// workspace layout (bytes): header, tile descriptors, block descriptors
 constexpr size_t kWsAbortOff = 0;
 constexpr int kWsCarefulWord = 2;      // 32-bit word 2 of the header counts same-group ticket pairs (diagnostic)
 constexpr int kWsAheadWord = 3;        // 32-bit word 3: how often tiles were counted ahead of a wait (diagnostic)
