@@ -1329,10 +1329,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         if (threadIdx.x == 0 && !cur_redo)
             desc_store(a.tile_desc + tile, (kStatusAggregate << kStatusShift) | tile_total);
 
-        // copy out what was announced, while the next tile's loads are on their way
+        // copy out what was announced, while the next tile's loads are on their way; not before tiles are counted ahead, since
+        // others wait for those counts
         const bool no_slot = q_len == kQueue, no_place = ring_used + tile_total > (uint32_t)kRing, crowded = no_slot || no_place;
         const bool ahead = ROSE_COUNT_AHEAD && !a.adjacent && no_place && q_len < a.batch;      // see below
-        if (n_announced > 0) {
+        if (n_announced > 0 && !ahead) {
             const uint32_t freed = copy_out(n_announced, s_excl[parity ^ 1], true);
             pop(n_announced, freed);
             if (crowded) __syncthreads();              // what is parked next may take the places of what is being copied
@@ -1367,9 +1368,10 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 dense = q_len == kQueue || ring_used + tile_total > (uint32_t)kRing;
             }
         } else if (__builtin_expect(ahead, 0)) {
-            // (also where the announced tiles have just made room: their neighbours will not have left in time for this
-            // ticket's next tiles, whose wait would then hold up all others.  40 / 50 %, eight 7B-style layers: 2.94 / 3.24 ms,
-            // with a look at the room that is left 3.59 / 4.90)
+            // (also where the announced tiles would make room: their neighbours will not have left in time for this
+            // ticket's next tiles, whose wait would then hold up all others.  And they stay where they are: their stores would
+            // hold up the counts.  Eight 7B-style layers, TP4, 40 / 50 %, ms: by the room they leave 4.60 / 6.06, by the room
+            // there was and copied out first 3.54 / 4.25, this way 3.38 / 3.86; 60 / 80 % 3.82 / 4.17 either way)
             dense = mid_ticket;
         }
 #endif

@@ -16,8 +16,10 @@ using namespace rose;
 constexpr int kRing = 8192, kQueue = 64;
 enum : int { kEmpty = 0, kCount = 1, kPrefix = 2 };
 
-struct Rules {                  // the rule under test, and a wrong one that the simulation has to find
-    bool settle_ahead;
+// The rules under test, or a mistake that the simulation has to find: announced tiles leave although the rest of the ticket
+// is to be counted ahead, and only the room that is left then decides whether the ticket on its way is taken in first.
+struct Rules {
+    bool right;
 };
 
 struct Outcome {
@@ -140,10 +142,11 @@ struct Worker {
             if (!cur_redo) s.publish(tile);
             const bool no_place = ring + s.count[tile] > kRing;
             const bool ahead = !s.a.adjacent && no_place && (int)parked.size() < s.a.batch;
+            if (ahead && s.rules.right) n_announced = 0;
             leave(n_announced);
             n_polled = n_polled > n_announced ? n_polled - n_announced : 0;
             for (int i = 0; i < n_announced && !polled.empty(); ++i) polled.pop_front();
-            if (ticket_first(w, ticket_out, full(), ahead && s.rules.settle_ahead)) settle();
+            if (ticket_first(w, ticket_out, full(), ahead && s.rules.right)) settle();
             const bool mid_ticket = !w.careful && !cur_redo && !w.redo && next_state == kWalkTile && w.ticket == ticket_before;
             dense = false;
             if (s.a.adjacent) {
