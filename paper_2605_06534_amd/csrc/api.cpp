@@ -254,6 +254,7 @@ static rose_status encode_common(const rose_plan *p, const void *const *old_ptrs
         e->pieces = pieces;
         e->tile_piece = tile_piece;
         e->n_tiles = (int32_t)t.tile_piece.size();
+        e->n_pieces = (int32_t)t.pieces.size();
         e->n_blocks = t.block_first[p->n_buckets];
         e->block_desc = e->tile_desc + e->n_tiles;
     };

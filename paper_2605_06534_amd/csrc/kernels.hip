@@ -2983,11 +2983,15 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
 }
 
 // The refresh of bf16 weights does better with three workgroups on a CU than with the four that fit, but where it writes next to
-// nothing: fewer lines are on their way back among fewer reads (eight 7B-style layers, TP4, in turns, four and three: 0.1 %
-// 1459 / 1518 us, 0.5 % 1657 / 1690, 1 % 1773 / 1743, 5 % 2160 / 2107, 15 % 2430 / 2391; TP1 at 2 % 1921 / 1872).  Without
-// refresh that holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 / 1401) nor for a sender's share of a
-// 32B style (1385 / 1393).
-constexpr int32_t kRefreshFewerPpm = 9000;
+// nothing: fewer lines are on their way back among fewer reads (eight 7B-style layers, TP4, four and three, us: in turns, 0.1 % 1459 /
+// 1518, 0.5 % 1657 / 1690, 1 % 1773 / 1743, 5 % 2160 / 2107, TP1 at 2 % 1921 / 1872; chain by chain, 10 % 2370 / 2316, 20 % 2604 / 2564,
+// 30 % 3134 / 2897).  Not from a third on, where tickets are counted ahead (35 % 3964 / 4111, 40 % 4065 / 4196, 60 % 4620 / 4789, TP1 at
+// 40 % 3493 / 3831), nor where pieces are short and every tile begins with a walk through tables (500 M weights, pieces of half a tile,
+// 1 % 806 / 963; of 2 / 4 / 6 / 8 / 12 tiles, 1 % 534 / 601, 493 / 521, 493 / 499, 538 / 527, 491 / 487, 2 % 557 / 616, 533 / 541, 535 / 527,
+// 594 / 578, 535 / 521).  Packed tensors and a sender's share of a 32B style gain less, and nothing where buffers lie well (packed at
+// 1 / 5 / 20 % 1754 / 1763, 2107 / 2071, 2361 / 2403; a share 1890 / 1905, 2365 / 2314, 2466 / 2541).
+// Without refresh it holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 / 1401) nor for such a share (1385 / 1393).
+constexpr int32_t kRefreshFewerPpm = 9000, kRefreshFewerToPpm = 333000, kRefreshFewerTiles = 6;
 
 int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
                   int worker_cap, int order, bool order_free, int32_t ppm, int32_t room_ppm, void *stream) {
@@ -3023,7 +3027,9 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     // was no fault of the turns but a ticket on its way while tiles were counted ahead, see ticket_first.)
     a.turns = Turns{0, 0, 0, 0, 0};
     if (refresh && worker_cap == 0 && ppm >= 0 && ppm < kSpreadFromPpm && a.adjacent) a.turns = turns_of(a.block_first, a.tp);
-    if (refresh && !new_is_f32 && !arith && (ppm < 0 || ppm >= kRefreshFewerPpm)) resident -= resident / 4;
+    if (refresh && !new_is_f32 && !arith && (ppm < 0 || (ppm >= kRefreshFewerPpm && ppm < kRefreshFewerToPpm)) &&
+        a.n_tiles / kRefreshFewerTiles >= a.n_pieces)
+        resident -= resident / 4;
     if (resident < 1) return (int)hipErrorInvalidValue;
     // servers: one wave per block at most, ROSE_SERVER_WGS workgroups at most, and never more than
     // a quarter of what is resident.  They are the first workgroups of the grid, so they are

@@ -141,6 +141,7 @@ struct EncodeArgs {
     unsigned long long *block_desc;         // one descriptor per block of kBlock tiles of a chain
     unsigned int *abort_flag;               // workspace header: set when a wait gave up
     int32_t n_tiles;
+    int32_t n_pieces;
     int32_t n_blocks;
     int32_t n_tensors;
     int32_t tp;
