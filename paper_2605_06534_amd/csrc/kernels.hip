@@ -771,6 +771,7 @@ __device__ __forceinline__ uint32_t parked(uint32_t k, const uint32_t *s_entry, 
 // Local index of a parked entry of a run whose elements are numbered from `base` on: an entry keeps the low 15 bits of its
 // element's number (bit 31 is the escape's), and a run spans less than 2^15 elements.
 constexpr int kRunTiles = 4;
+static_assert(kRunTiles <= kWaves, "a wave takes a tile of a run");
 static_assert(kRunTiles * kTile <= 1 << 15, "15 bits tell the elements of a run apart");
 __device__ __forceinline__ uint32_t run_local(uint32_t entry, uint32_t base) {
     return base + (((entry - (base << 16)) >> 16) & 0x7FFFu);
@@ -848,6 +849,27 @@ __device__ __forceinline__ void write_run(const EncodeArgs &a, int32_t shard, in
     }
 }
 
+// The same for a run of tiles of several pieces (tensors of a tile or two): its tiles are numbered each by itself, and a wave
+// takes one of them.  (Each as a run of its own / this way, us at 1 %: tensors of half a tile a shard 653 / 588, fp32 masters 796 / 733;
+// of one tile 744 / 697; of two 868 / 845.  An entry's tile found by compares in write_run instead, real models are 1 % slower.)
+template <int ARITH, bool ESCAPES>
+__device__ __forceinline__ void write_tile(const BucketDev &b, uint32_t base, uint32_t off, u64 excl, uint32_t cnt, int lane,
+                                           const uint32_t *s_ring, const uint16_t *s_was) {
+    const uint32_t phase = (uint32_t)excl & 31u;
+#pragma unroll 1
+    for (uint32_t kk = (uint32_t)lane; kk < cnt + phase; kk += 64) {
+        const uint32_t k = kk - phase;                 // (wraps below phase: caught by the first test)
+        const u64 pos = excl + k;
+        if (kk >= phase && pos < (u64)b.capacity) {
+            const uint32_t entry = parked<ARITH>((off + k) & (kRing - 1), s_ring, s_was);
+            uint32_t local = run_local(entry, base);
+            if constexpr (ESCAPES) local |= entry & 0x80000000u;
+            __builtin_nontemporal_store((int32_t)local, b.idx + pos);
+            __builtin_nontemporal_store((uint16_t)entry, b.val + pos);
+        }
+    }
+}
+
 // PAYLOAD = 1: arithmetic payloads formed of the compacted entries; 2: of every element, before they are compacted.
 template <int NEW_F32, int REFRESH, int PAYLOAD>
 __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
@@ -860,6 +882,10 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     // 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns
     // 1349 / 1599.
     constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);
+    // Runs of tiles of one piece only, see write_tile: with that beside it this kernel's ordinary runs take 1.2 % longer (eight
+    // 7B-style layers at 5 %: 1379 and 1399 us), which is more than small tensors gain where there are few (all of half a tile: 757 and
+    // 724 us, of one 752 and 720, of two 991 and 998).
+    constexpr bool STRAIGHT = !NEW_F32 && !REFRESH && ARITH;
     // register class, see ticket_request
     constexpr int WIDE = (NEW_F32 && REFRESH && ARITH) ? 2 : (NEW_F32 || ARITH) ? 1 : 0;
     __shared__ uint32_t s_ring[kRing];      // an entry: low 15 bits of its element's number (TileMeta::out_base) << 16 | new pattern
@@ -915,7 +941,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     bool ticket_out = false;    // a ticket has been asked for and not yet taken in
 
     // copy the n oldest parked tiles to the buckets (prefixes in excl[0..n)); returns ring entries freed.
-    // Tiles that follow each other in the bucket and in their piece (up to four: each starting where the one
+    // Tiles that follow each other in the bucket (up to four: same shard, each starting where the one
     // before ends; their entries follow each other in the ring as well) are written as one run.
     auto copy_out = [&](int n, const u64 *excl_by_age, bool ok) -> uint32_t {
         // lane i looks at the i-th oldest tile, so that the waves wait for LDS once and not tile by tile
@@ -945,18 +971,25 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xf, 0xf, false);     // wave_shr:1
         };
         const uint32_t shard_b = below((uint32_t)shard), piece_b = below((uint32_t)piece), base_b = below(base), end_b = below(excl_lo + count);
-        const bool next = (lane > 0) & ((uint32_t)shard == shard_b) & ((int32_t)((uint32_t)piece & piece_b) < 0) &
-                          (base == base_b + (uint32_t)kTile) & (excl_lo == end_b);
-        const u64 starts = __ballot(mine & !next);
+        const bool next = (lane > 0) & ((uint32_t)shard == shard_b) & ((int32_t)((uint32_t)piece & piece_b) < 0) & (excl_lo == end_b) &
+                          (!STRAIGHT | (base == base_b + (uint32_t)kTile));
+        const u64 starts = __ballot(mine & !next), apart = __ballot(base != base_b + (uint32_t)kTile);   // (of another piece)
         for (int i = 0; i < n;) {
             // everything about the run is uniform: scalar registers, the bucket's pointers come through scalar loads
             const u64 behind = starts >> i >> 1;
             int g = behind ? __ffsll((long long)behind) : n - i;
             g = g < kRunTiles ? g : kRunTiles;
-            const u64 first = (u64)of(excl_hi, i) << 32 | of(excl_lo, i);
-            const uint32_t cnt = of(excl_lo, i + g - 1) + of(count, i + g - 1) - (uint32_t)first;
-            write_run<ARITH, PAYLOAD != 0>(a, (int32_t)of((uint32_t)shard, i), (int32_t)of((uint32_t)piece, i), of(base, i), of(off, i), first,
-                                           cnt, s_ring, s_was);
+            if (!STRAIGHT && __builtin_expect((apart >> i >> 1 & ((1u << (g - 1)) - 1u)) != 0, 0)) {
+                const int t = i + __builtin_amdgcn_readfirstlane(wave);
+                if (t < i + g)
+                    write_tile<ARITH, PAYLOAD != 0>(a.bucket[of((uint32_t)shard, t)], of(base, t), of(off, t), (u64)of(excl_hi, t) << 32 | of(excl_lo, t),
+                                                    of(count, t), lane, s_ring, s_was);
+            } else {
+                const u64 first = (u64)of(excl_hi, i) << 32 | of(excl_lo, i);
+                const uint32_t cnt = of(excl_lo, i + g - 1) + of(count, i + g - 1) - (uint32_t)first;
+                write_run<ARITH, PAYLOAD != 0>(a, (int32_t)of((uint32_t)shard, i), (int32_t)of((uint32_t)piece, i), of(base, i), of(off, i),
+                                               first, cnt, s_ring, s_was);
+            }
             i += g;
         }
         return freed;
