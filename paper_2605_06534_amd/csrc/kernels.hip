@@ -353,11 +353,11 @@ __device__ __forceinline__ u64 desc_load(u64 *p) {
 }
 
 // The workspace is one array of 64-bit words: header (abort flag, ticket counters), tile words,
-// block words.  All of it starts at zero, but for the word that says how the update goes.
-__global__ void reset_kernel(u64 *workspace, int64_t n_words, uint32_t form) {
-    static_assert(kWsFormWord % 2 == 1, "an upper half");
+// block words.  All of it starts at zero, but for the words that say how the update goes.
+__global__ void reset_kernel(u64 *workspace, int64_t n_words, uint32_t form, uint32_t walk) {
+    static_assert(kWsFormWord % 2 == 1 && kWsWalkWord == kWsFormWord + 1, "an upper half and the lower half behind it");
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; i < n_words; i += (int64_t)gridDim.x * blockDim.x) workspace[i] = i == kWsFormWord / 2 ? (u64)form << 32 : 0;
+    for (; i < n_words; i += (int64_t)gridDim.x * blockDim.x) workspace[i] = i == kWsFormWord / 2 ? (u64)form << 32 : i == kWsWalkWord / 2 ? (u64)walk : 0;
 }
 
 // After encode: if any wave gave up waiting, mark every bucket as invalid (total = -1) so that
@@ -2903,8 +2903,8 @@ int static_scratch(void **ptr, size_t *bytes) {
 // How a launch in this tile order walks its tiles: tiles per ticket, and how long of each period the bucket stores may go out
 // (0: always).  ppm: changed elements per million, -1 unknown; room_ppm: as many as the buckets could hold.
 //   timed       4 tiles, 10 us of each 82; from kLongBelowPpm on of each 41: the entries of a period have to fit the ring.
-//   neighbours  4 tiles and 10 us of 41 as well, as long as it is known that no more comes (the buckets hold no more than
-//               kNearRoomPpm) and the ring holds it; else 3 tiles, whose prefixes are ready sooner and leave the ring room,
+//   neighbours  4 tiles and 10 us of 41 as well, as long as the ring holds them and no more is expected (the buckets hold no more
+//               than kNearRoomPpm; an update that overflows them may be slow), without refresh; else 3 tiles, whose prefixes are ready sooner and leave the ring room,
 //               and longer windows, so that less waits: up to 5 % 15 us, above, and where payloads are formed of every element, 20 us.
 // Eight 7B-style layers, TP4, one process, same buffers, ms (bf16 / fp32 masters / arithmetic payloads):
 //                 1 %                  3 %                  4 %                  5 %                  6 %                  7 %
@@ -2913,15 +2913,17 @@ int static_scratch(void **ptr, size_t *bytes) {
 //   3 x 15        1.156 1.702 1.158    1.190 1.744 1.209    1.204 1.765 1.231    1.226 1.779 1.256    1.241 1.801 1.280    1.291 1.853 1.318
 //   3 x 20        1.160 1.742 1.157    1.190 1.797 1.212    1.206 1.813 1.238    1.223 1.824 1.261    1.237 1.841 1.285    1.284 1.866 1.330
 // Where the density is the last launch's and more comes, 4 tiles lose far more than 3 (4 / 3 tiles: 12 % 1.61 / 1.38, 20 % 2.03 / 1.80,
-// 30 % 4.12 / 2.31).
+// 30 % 4.12 / 2.31).  With refresh, in turns, 4 tiles lose from 4 % on too (room for 5.6 / 6.3 %, 4 and 3 tiles: eight 7B-style layers
+// 2.09 / 2.06, 2.12 / 2.09; six 8B-style ones 2.67 / 2.62, 2.67 / 2.63; a sender's share of a 32B style 2.27 / 2.23, 2.31 / 2.27; packed 2.09 /
+// 2.07, 2.11 / 2.09; arithmetic payloads 2.09 / 2.06, 2.04 / 2.00; fp32 masters 2.64 / 2.61), below the periods of 82 us do no harm.
 constexpr int32_t kLongBelowPpm = 33000, kNearBelowPpm = 50000;
 constexpr int32_t kNearFourPpm = 65000, kNearFourPpmF32 = 57000, kNearRoomPpm = 80000;
-static void encode_walk(int order, int32_t ppm, int32_t room_ppm, int new_is_f32, bool of_elements, EncodeArgs *a) {
+static void encode_walk(int order, int32_t ppm, int32_t room_ppm, int new_is_f32, bool of_elements, bool refresh, EncodeArgs *a) {
     a->adjacent = order == ROSE_TILE_ORDER_SPREAD ? 0 : 1;
     a->batch = kBatch;
     a->window_open = 0;
     a->window_mask = (1u << ROSE_WRITE_PERIOD_LOG2) - 1u;
-    const bool four = !of_elements && ppm >= 0 && ppm < (new_is_f32 ? kNearFourPpmF32 : kNearFourPpm) && room_ppm < kNearRoomPpm;
+    const bool four = !of_elements && !refresh && ppm >= 0 && ppm < (new_is_f32 ? kNearFourPpmF32 : kNearFourPpm) && room_ppm < kNearRoomPpm;
     if (order == ROSE_TILE_ORDER_TIMED || (order == ROSE_TILE_ORDER_NEIGHBOURS && four)) {
         a->batch = kBatchTimed;
         a->window_open = ROSE_WRITE_OPEN_TIMED;
@@ -3054,7 +3056,7 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     const bool of_elements = arith && !new_is_f32 && !refresh && (ppm < 0 || ppm >= kElementsPpm || room_ppm >= kElementsPpm);
     int resident = resident_of[of_elements ? kElementsVariant : (new_is_f32 ? 1 : 0) + (refresh ? 2 : 0) + (arith ? 4 : 0)];
     if (ppm < 0 || ppm >= kSpreadFromPpm) a = fewer;           // see `moved` in plan.cpp
-    encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, &a);
+    encode_walk(order, ppm, room_ppm, new_is_f32, of_elements, refresh != nullptr, &a);
     // In turns: refreshes of little, by all workers.  (Of more, they were faster in turns as well: at 15 % 2428 and 2397 us, fp32 masters
     // at 20 % 6.6 and 4.5 ms.  They have been walked chain by chain since an encode of 40 % in turns by 70 workers gave up waiting; that
     // was no fault of the turns but a ticket on its way while tiles were counted ahead, see ticket_first.)
@@ -3090,7 +3092,7 @@ int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f3
     int reset_blocks = (int)((n_words + 1023) / 1024);
     if (reset_blocks > 2048) reset_blocks = 2048;
     hipLaunchKernelGGL(reset_kernel, dim3(reset_blocks), dim3(256), 0, st, reinterpret_cast<u64 *>(a.abort_flag), n_words,
-                       (uint32_t)(of_elements ? kTicketsElements : kTickets));
+                       (uint32_t)(of_elements ? kTicketsElements : kTickets), (uint32_t)(a.batch | a.turns.chains << 8));
     const dim3 grid(workers + server_wgs), block(kThreads);
     hipLaunchKernelGGL(of_elements ? encode_elements_kernel : encode_variant(new_is_f32, refresh ? 1 : 0, arith), grid, block, 0, st, a);
     launch_refresh_replicated(a, new_is_f32, refresh, st);

@@ -291,6 +291,7 @@ constexpr int kWsCarefulWord = 2;      // 32-bit word 2 of the header counts sam
 constexpr int kWsAheadWord = 3;        // 32-bit word 3: how often tiles were counted ahead of a wait (diagnostic)
 constexpr int kWsTilesWord = 4;        // 32-bit word 4: tiles of a launch without tickets, else 0
 constexpr int kWsFormWord = 5;         // 32-bit word 5: 0 after tickets (3: payloads formed of every element), 1 entries parked, 2 all read again
+constexpr int kWsWalkWord = 6;         // 32-bit word 6, after tickets: tiles a ticket, and from bit 8 on how many chains took turns
 constexpr size_t kWsTicketOff = 4096;
 constexpr size_t kWsHeaderBytes = 8192;
 // Behind them (at a multiple of 256 bytes): room for compacted entries, a slot per tile, of the plans that may be encoded

@@ -10,6 +10,7 @@ from workloads import models
 from gpu_harness import full_parity
 from test_gpu_arith import check_arith
 from test_gpu_parity import bern_case
+from test_gpu_refresh import check_refresh
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,23 @@ def test_launches_in_the_order_picked(p, want, arith):
             assert c.plan.pick_tile_order([b.capacity for b in c.buckets]) == want
         check_arith(c) if arith else full_parity(c, check_dense=False)
         assert int(c.ws.view(torch.int32)[4]) == 0 and int(c.ws.view(torch.int32)[1024]) > 0, what
+
+
+@pytest.mark.parametrize("refresh", [False, True])
+@pytest.mark.parametrize("fp32,few,more", [(False, 0.06, 0.07), (True, 0.052, 0.062)])
+def test_four_neighbours_a_ticket(fp32, few, more, refresh):
+    """The neighbours order takes four tiles a ticket where the buckets have room for little more than its line, three where
+    they have for more, and three with refresh; the workspace's word 6 says how many a launch took."""
+    print("case: neighbours, room for %g and %g, fp32 %d, refresh %d" % (few, more, fp32, refresh), flush=True)
+    ts = models.decoder(2, 1024, 16, 16, 64, 2816, 4096, fused=True)
+    for room in (few, more):
+        c = bern_case(ts, 4, 0.045, seed=11)
+        if fp32:
+            c.new = [n.float() for n in c.new]
+            c.new_tab, c.new_dtype = R.ptr_table(c.new), R.FP32_RNE
+        c.plan.set_tile_order(binding.TILE_ORDER_NEIGHBOURS)
+        for b in c.buckets:
+            b.capacity = int(room * b.capacity)
+        c.ws.fill_(-1)
+        check_refresh(c) if refresh else full_parity(c, check_dense=False)
+        assert int(c.ws.view(torch.int32)[6]) & 255 == (4 if room == few and not refresh else 3), room
