@@ -876,11 +876,11 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     constexpr int ARITH = PAYLOAD == 1;                // entries carry the old pattern beside them
     constexpr int FORMED = PAYLOAD == 2;               // entries are payloads from the start
     static_assert(!(FORMED && REFRESH), "a refresh needs the new patterns");
-    // Blocks in turns: a refresh writes lines of what it reads all the time, and the memory takes that better where they lie in several
-    // places (eight 7B-style layers, TP4, at 1 / 5 / 15 %: chain by chain 1813 / 2190 / 2428 us, in turns 1750 / 2109 / 2397; arithmetic
-    // payloads at 2 % 1978 and 1899, fp32 masters 2695 and 2653; but arithmetic payloads of fp32 masters, with half the waves, 2624 and
-    // 2652: not those).  Others write to the buckets only, which then are several at a time too: at 5 / 10 % 1334 / 1546 us, in turns
-    // 1349 / 1599.
+    // Blocks in turns: a refresh writes lines of what it reads all the time, and the memory takes that better where they lie in
+    // several places (eight 7B-style layers with embedding and head, TP4, at 1 / 5 / 15 %: chain by chain 1813 / 2190 / 2428 us, in
+    // turns 1750 / 2109 / 2397; arithmetic payloads at 2 % 1978 and 1899, fp32 masters 2695 and 2653; but arithmetic payloads of
+    // fp32 masters, with half the waves, 2624 and 2652: not those).  Others write to the buckets only, which then are several at a
+    // time too: at 5 / 10 % 1334 / 1546 us, in turns 1349 / 1599.
     constexpr int TURNS = REFRESH && !(NEW_F32 && ARITH);
     // Runs of tiles of one piece only, see write_tile: with that beside it this kernel's ordinary runs take 1.2 % longer (eight
     // 7B-style layers at 5 %: 1379 and 1399 us), which is more than small tensors gain where there are few (all of half a tile: 757 and
@@ -918,8 +918,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     // memory operations in issue order, and the compiler can only wait for "all but the newest
     // n" with an n it can count at compile time; behind loops and branches it has to wait for
     // everything.  So results are taken in only at the top of an iteration, where everything in
-    // flight is wanted anyway, and the long-latency loads of the next tile are issued after the
-    // iteration's other memory operations (bucket stores, the poll, the ticket request):
+    // flight is wanted anyway, and the long-latency loads of the next tile are issued after all that
+    // is asked for (the poll, the ticket request) and before the bucket stores, which nothing waits for by themselves:
     //   top   the tile's data has landed; so have last iteration's poll answers and ticket
     //   (a)   change masks of this tile (frees the load registers)
     //   (b)   wave 0 takes in the poll answers and announces (through LDS, valid after this
@@ -927,8 +927,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     //   (c)   wave 0 polls the parked tiles without a prefix; thread 0 asks for a ticket
     //   (d)   the NEXT tile's loads are issued
     //   (e)   scan, barrier, publish this tile's count, copy out the announced tiles, park this tile's entries
-    // (Copied out in (b), in front of the loads, 8.6 GB read take 1.419 ms at 1 %, this way 1.411.  Nothing waits for the
-    // stores by themselves.)
+    // (Copied out in (b), in front of the loads, 8.6 GB read take 1.419 ms at 1 %, this way 1.411.)
     int q_head = 0, q_len = 0;
     uint32_t ring_used = 0, ring_head = 0;
     int parity = 0;
@@ -1168,7 +1167,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             walk.redo = flags & 64;
         }
         cur = loaded ? nxt : start_tile(tile);         // not loaded: the first tile, or one named late
-        // From here until the next tile's loads are issued this workgroup asks nothing of the memory, so its waves go first.
+        // From here until the next tile's loads are issued this workgroup has no tile on its way (only now and then a vector's tail,
+        // a poll and a ticket), so its waves go first.
         // (Among equals the oldest wave of a SIMD goes first, always: of four workgroups on a CU one then walked 160 tiles
         // where another walked 360, all others' entries waited in their rings for its counts, and at 5 % two of five tiles
         // left outside the windows because a ring was full.  This way they walk 200 to 320.)
@@ -1403,8 +1403,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
         } else if (__builtin_expect(ahead, 0)) {
             // (also where the announced tiles would make room: their neighbours will not have left in time for this
             // ticket's next tiles, whose wait would then hold up all others.  And they stay where they are: their stores would
-            // hold up the counts.  Eight 7B-style layers, TP4, 40 / 50 %, ms: by the room they leave 4.60 / 6.06, by the room
-            // there was and copied out first 3.54 / 4.25, this way 3.38 / 3.86; 60 / 80 % 3.82 / 4.17 either way)
+            // hold up the counts.  Eight 7B-style layers with embedding and head, TP4, 40 / 50 %, ms: by the room they leave 4.60 /
+            // 6.06, by the room there was and copied out first 3.54 / 4.25, this way 3.38 / 3.86; 60 / 80 % 3.82 / 4.17 either way)
             dense = mid_ticket;
         }
 #endif
@@ -2904,18 +2904,20 @@ int static_scratch(void **ptr, size_t *bytes) {
 // (0: always).  ppm: changed elements per million, -1 unknown; room_ppm: as many as the buckets could hold.
 //   timed       4 tiles, 10 us of each 82; from kLongBelowPpm on of each 41: the entries of a period have to fit the ring.
 //   neighbours  4 tiles and 10 us of 41 as well, as long as the ring holds them and no more is expected (the buckets hold no more
-//               than kNearRoomPpm; an update that overflows them may be slow), without refresh; else 3 tiles, whose prefixes are ready sooner and leave the ring room,
-//               and longer windows, so that less waits: up to 5 % 15 us, above, and where payloads are formed of every element, 20 us.
-// Eight 7B-style layers, TP4, one process, same buffers, ms (bf16 / fp32 masters / arithmetic payloads):
+//               than kNearRoomPpm; an update that overflows them may be slow), without refresh; else 3 tiles, whose prefixes are
+//               ready sooner and leave the ring room, and longer windows, so that less waits: up to 5 % 15 us, above, and where
+//               payloads are formed of every element, 20 us.
+// Eight 7B-style layers without embedding and head, TP4, one process, same buffers, ms (bf16 / fp32 masters / arithmetic payloads):
 //                 1 %                  3 %                  4 %                  5 %                  6 %                  7 %
 //   4 x 10 of 82  1.057 1.594 1.064    1.102 1.641 1.115    1.159 1.711 1.184    1.223 1.837 1.236    1.269 1.954 1.291    1.342 2.015 1.356
 //   4 x 10 of 41  1.075 1.658 1.080    1.115 1.700 1.138    1.131 1.716 1.173    1.158 1.747 1.210    1.214 1.821 1.266    1.311 1.936 1.320
 //   3 x 15        1.156 1.702 1.158    1.190 1.744 1.209    1.204 1.765 1.231    1.226 1.779 1.256    1.241 1.801 1.280    1.291 1.853 1.318
 //   3 x 20        1.160 1.742 1.157    1.190 1.797 1.212    1.206 1.813 1.238    1.223 1.824 1.261    1.237 1.841 1.285    1.284 1.866 1.330
-// Where the density is the last launch's and more comes, 4 tiles lose far more than 3 (4 / 3 tiles: 12 % 1.61 / 1.38, 20 % 2.03 / 1.80,
-// 30 % 4.12 / 2.31).  With refresh, in turns, 4 tiles lose from 4 % on too (room for 5.6 / 6.3 %, 4 and 3 tiles: eight 7B-style layers
-// 2.09 / 2.06, 2.12 / 2.09; six 8B-style ones 2.67 / 2.62, 2.67 / 2.63; a sender's share of a 32B style 2.27 / 2.23, 2.31 / 2.27; packed 2.09 /
-// 2.07, 2.11 / 2.09; arithmetic payloads 2.09 / 2.06, 2.04 / 2.00; fp32 masters 2.64 / 2.61), below the periods of 82 us do no harm.
+// Where the density is the last launch's and more comes, 4 tiles lose far more than 3 (4 / 3 tiles: 12 % 1.61 / 1.38, 20 % 2.03 /
+// 1.80, 30 % 4.12 / 2.31).  With refresh, in turns, 4 tiles lose from 4 % on too (room for 5.6 / 6.3 %, 4 and 3 tiles: eight such
+// layers with embedding and head 2.09 / 2.06, 2.12 / 2.09; six 8B-style ones 2.67 / 2.62, 2.67 / 2.63; a sender's share of a 32B
+// style 2.27 / 2.23, 2.31 / 2.27; packed 2.09 / 2.07, 2.11 / 2.09; arithmetic payloads 2.09 / 2.06, 2.04 / 2.00; fp32 masters 2.64
+// / 2.61); the timed order's 4 tiles and periods of 82 us, below that, do refreshes no harm.
 constexpr int32_t kLongBelowPpm = 33000, kNearBelowPpm = 50000;
 constexpr int32_t kNearFourPpm = 65000, kNearFourPpmF32 = 57000, kNearRoomPpm = 80000;
 static void encode_walk(int order, int32_t ppm, int32_t room_ppm, int new_is_f32, bool of_elements, bool refresh, EncodeArgs *a) {
@@ -3018,14 +3020,16 @@ static void launch_refresh_replicated(const EncodeArgs &a, int new_is_f32, const
 }
 
 // The refresh of bf16 weights does better with three workgroups on a CU than with the four that fit, but where it writes next to
-// nothing: fewer lines are on their way back among fewer reads (eight 7B-style layers, TP4, four and three, us: in turns, 0.1 % 1459 /
-// 1518, 0.5 % 1657 / 1690, 1 % 1773 / 1743, 5 % 2160 / 2107, TP1 at 2 % 1921 / 1872; chain by chain, 10 % 2370 / 2316, 20 % 2604 / 2564,
-// 30 % 3134 / 2897).  Not from a third on, where tickets are counted ahead (35 % 3964 / 4111, 40 % 4065 / 4196, 60 % 4620 / 4789, TP1 at
-// 40 % 3493 / 3831), nor where pieces are short and every tile begins with a walk through tables (500 M weights, pieces of half a tile,
-// 1 % 806 / 963; of 2 / 4 / 6 / 8 / 12 tiles, 1 % 534 / 601, 493 / 521, 493 / 499, 538 / 527, 491 / 487, 2 % 557 / 616, 533 / 541, 535 / 527,
-// 594 / 578, 535 / 521).  Packed tensors and a sender's share of a 32B style gain less, and nothing where buffers lie well (packed at
-// 1 / 5 / 20 % 1754 / 1763, 2107 / 2071, 2361 / 2403; a share 1890 / 1905, 2365 / 2314, 2466 / 2541).
-// Without refresh it holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 / 1401) nor for such a share (1385 / 1393).
+// nothing: fewer lines are on their way back among fewer reads (eight 7B-style layers with embedding and head, TP4, four and three,
+// us: in turns, 0.1 % 1459 / 1518, 0.5 % 1657 / 1690, 1 % 1773 / 1743, 5 % 2160 / 2107, TP1 at 2 % 1921 / 1872; chain by chain, 10
+// % 2370 / 2316, 20 % 2604 / 2564, 30 % 3134 / 2897).  Not from a third on, where tickets are counted ahead (35 % 3964 / 4111, 40 %
+// 4065 / 4196, 60 % 4620 / 4789, TP1 at 40 % 3493 / 3831), nor where pieces are short and every tile begins with a walk through
+// tables (500 M weights, pieces of half a tile, 1 % 806 / 963; of 2 / 4 / 6 / 8 / 12 tiles, 1 % 534 / 601, 493 / 521, 493 / 499,
+// 538 / 527, 491 / 487, 2 % 557 / 616, 533 / 541, 535 / 527, 594 / 578, 535 / 521).  Packed tensors and a sender's share of a 32B
+// style gain less, and lose where little changes (1 / 5 / 20 %, packed 1760 / 1789, 2140 / 2118, 2639 / 2616, a share 1941 / 1939,
+// 2317 / 2263, 2771 / 2737, aligned weights beside them 1757 / 1741, 2120 / 2075, 2604 / 2571; at 20 % with other buffers packed
+// 2361 / 2403, a share 2466 / 2541). Without refresh it holds for aligned weights (5 % 1352 / 1334), not for packed ones (1382 /
+// 1401) nor for such a share (1385 / 1393).
 constexpr int32_t kRefreshFewerPpm = 9000, kRefreshFewerToPpm = 333000, kRefreshFewerTiles = 6;
 
 int launch_encode(const EncodeArgs &args, const EncodeArgs &fewer, int new_is_f32, const RefreshArgs *refresh, int arith, const int *resident_of,
