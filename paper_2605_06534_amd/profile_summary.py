@@ -38,24 +38,32 @@ def short(name):
     return m.group(1).replace(" ", "") if m else None
 
 
+def rows_of_one_run(directory, name):
+    """The rows of the one CSV file of this name below the directory.  Each profiled process writes files of its own beside
+    those of earlier runs, whose figures are of another build perhaps."""
+    found = sorted(glob.glob(os.path.join(directory, "**", "*" + name), recursive=True))
+    if len(found) != 1:
+        sys.exit("%s holds the results of %d runs (*%s): empty it before a profiled run" % (directory, len(found), name))
+    with open(found[0]) as f:
+        return list(csv.DictReader(f))
+
+
 def counters(directory):
     """-> {kernel: {counter: (mean per dispatch, dispatches)}} for the library's kernels"""
     per = collections.defaultdict(lambda: collections.defaultdict(lambda: collections.defaultdict(float)))
-    for f in glob.glob(os.path.join(directory, "**", "*counter_collection.csv"), recursive=True):
-        for r in csv.DictReader(open(f)):
-            k = short(r["Kernel_Name"])
-            if k:
-                per[k][r["Counter_Name"]][r["Dispatch_Id"]] += float(r["Counter_Value"])
+    for r in rows_of_one_run(directory, "counter_collection.csv"):
+        k = short(r["Kernel_Name"])
+        if k:
+            per[k][r["Counter_Name"]][r["Dispatch_Id"]] += float(r["Counter_Value"])
     return {k: {c: (sum(d.values()) / len(d), len(d)) for c, d in cs.items()} for k, cs in per.items()}
 
 
 def stats(directory):
     rows = []
-    for f in glob.glob(os.path.join(directory, "**", "*kernel_stats.csv"), recursive=True):
-        for r in csv.DictReader(open(f)):
-            k = short(r["Name"])
-            if k:
-                rows.append((k, int(r["Calls"]), float(r["AverageNs"]), float(r["MinNs"]), float(r["MaxNs"])))
+    for r in rows_of_one_run(directory, "kernel_stats.csv"):
+        k = short(r["Name"])
+        if k:
+            rows.append((k, int(r["Calls"]), float(r["AverageNs"]), float(r["MinNs"]), float(r["MaxNs"])))
     return rows
 
 
